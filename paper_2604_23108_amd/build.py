@@ -15,7 +15,7 @@ LIB = os.path.join(HERE, "libmohge.so")
 BENCH_LIB = os.path.join(HERE, "libmohge_bench.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_tiled.hip", "ffn_skinny.hip",
+SOURCES = ["api.hip", "route.hip", "permute.hip", "ffn.hip", "ffn_f32.hip", "ffn_tiled.hip", "ffn_skinny.hip",
            "combine.hip", "aux_loss.hip", "ffn_bwd.hip", "route_bwd.hip", "decode_layer.hip"]
 BENCH_SOURCES = ["bench_api.hip", "box_probe.hip"]
 
