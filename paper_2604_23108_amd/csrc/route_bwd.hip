@@ -14,7 +14,7 @@
 //
 // Kernels: (1) one wave per token for the scalar chain above; (2) the two weight gradients as a
 // reduction over tokens, split over the grid with partial sums added in a fixed order (no
-// atomics: bit-identical from run to run); (3) the input gradient, 8 tokens per workgroup so
+// atomics: bit-identical from run to run); (3) the input gradient, up to 8 tokens per thread so
 // that every router weight is fetched once per 8 tokens.
 #include "common.h"
 
@@ -136,69 +136,87 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
 }
 
 // partial sums of dW[z, c] = sum_t dz[t, z] x[t, c] on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32: C[32x32] += A[32x2] B[2x32]): grid (ceil(d/1024), S), a wave owns 256
-// columns and a pass of 32 rows z, and takes the tokens of its split two at a time.  Lane
+// (v_mfma_f32_32x32x2_f32: C[32x32] += A[32x2] B[2x32]): grid (ceil(d/256), ceil(Z/32), S).  A
+// workgroup owns 256 columns and 32 rows z for the tokens of one split; its four waves take four
+// neighbouring stretches of them and their sums meet in LDS, added in wave order.  Lane
 // (j = lane%32, k = lane/32) loads dz[t+k, z0+j] (the A operand as it is) and the 8 columns
 // c0 + 8j .. +7 of x[t+k] (one 16-byte load); MFMA m takes element m of every lane's eight, so
 // its 32 B-columns are the tile columns {8j + m}.  A lane ends up with 8 consecutive columns of
-// 16 rows.  Loads run one group of 4 steps ahead of the arithmetic; nothing crosses waves.
+// 16 rows.  Loads run one group of 4 steps ahead of the arithmetic.
+// What bounds it is the chain of 64-clock MFMAs of a wave (8 per two tokens): the work has to be
+// spread.  With a wave per 256 columns that walked all row passes and all tokens of a split alone,
+// 777 tokens of a d = 1024 layer made 13 workgroups and took 43 us (8192 tokens at d = 2048: 36 us).
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-constexpr int kZC = 32, kTU = 4;
+constexpr int kZC = 32, kTU = 4, kWGradWaves = 4;
 
-__global__ void __launch_bounds__(256) route_bwd_wgrad_kernel(const RouteBwdArgs a) {
+__global__ void __launch_bounds__(64 * kWGradWaves) route_bwd_wgrad_kernel(const RouteBwdArgs a) {
+  __shared__ float4 red[(kWGradWaves - 1) * 16 * 64];        // 48 KB: half a wave's sums (4 columns) at a time
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int j = lane & 31, k = lane >> 5;
-  const int c0 = (blockIdx.x * 4 + w) * 256;
-  if (c0 >= a.d) return;                       // wave-uniform; the kernel has no barriers
-  const int c = c0 + 8 * j;
+  const int c = blockIdx.x * 256 + 8 * j;
   const bool col_ok = c < a.d;
   const int cc = col_ok ? c : 0;
-  const int t0 = blockIdx.y * a.tok_per_split;
-  const int t1 = min(a.T, t0 + a.tok_per_split);
-  for (int z0 = 0; z0 < a.Z; z0 += kZC) {
-    const int zl = z0 + j;
-    // step at token t: this lane's token is t + k (dz = 0 past the split or past Z)
-    auto load = [&](int t, uint4& xv, float& dzv) {
-      const int tok = t + k, tt = min(tok, a.T - 1);
-      xv = *reinterpret_cast<const uint4*>(a.x + (size_t)tt * a.d + cc);
-      const float v = a.dz[(size_t)tt * a.Z + min(zl, a.Z - 1)];
-      dzv = (tok < t1 && zl < a.Z) ? v : 0.f;
-    };
-    f32x16_t acc[8];
+  const int s0 = blockIdx.z * a.tok_per_split;
+  const int s1 = min(a.T, s0 + a.tok_per_split);
+  // (an even number of tokens per wave; a wave past the end adds zeros)
+  const int per_wave = ((s1 - s0 + 2 * kWGradWaves - 1) / (2 * kWGradWaves)) * 2;
+  const int t0 = min(s1, s0 + w * per_wave), t1 = min(s1, t0 + per_wave);
+  const int z0 = blockIdx.y * kZC, zl = z0 + j;
+  // step at token t: this lane's token is t + k (dz = 0 past the stretch or past Z)
+  auto load = [&](int t, uint4& xv, float& dzv) {
+    const int tok = t + k, tt = min(tok, a.T - 1);
+    xv = *reinterpret_cast<const uint4*>(a.x + (size_t)tt * a.d + cc);
+    const float v = a.dz[(size_t)tt * a.Z + min(zl, a.Z - 1)];
+    dzv = (tok < t1 && zl < a.Z) ? v : 0.f;
+  };
+  f32x16_t acc[8];
 #pragma unroll
-    for (int m = 0; m < 8; ++m)
+  for (int m = 0; m < 8; ++m)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
-    uint4 xc[kTU];
-    float dc[kTU];
+    for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+  uint4 xc[kTU];
+  float dc[kTU];
 #pragma unroll
-    for (int i = 0; i < kTU; ++i) load(t0 + 2 * i, xc[i], dc[i]);
-    for (int t = t0; t < t1; t += 2 * kTU) {
-      uint4 xn[kTU];
-      float dn[kTU];
+  for (int i = 0; i < kTU; ++i) load(t0 + 2 * i, xc[i], dc[i]);
+  for (int t = t0; t < t1; t += 2 * kTU) {
+    uint4 xn[kTU];
+    float dn[kTU];
 #pragma unroll
-      for (int i = 0; i < kTU; ++i) load(t + 2 * kTU + 2 * i, xn[i], dn[i]);
+    for (int i = 0; i < kTU; ++i) load(t + 2 * kTU + 2 * i, xn[i], dn[i]);
 #pragma unroll
-      for (int i = 0; i < kTU; ++i) {
-        const uint32_t u[4] = {xc[i].x, xc[i].y, xc[i].z, xc[i].w};
+    for (int i = 0; i < kTU; ++i) {
+      const uint32_t u[4] = {xc[i].x, xc[i].y, xc[i].z, xc[i].w};
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-          const float xf = __uint_as_float((m & 1) ? (u[m >> 1] & 0xffff0000u) : (u[m >> 1] << 16));
-          acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(dc[i], xf, acc[m], 0, 0, 0);
-        }
+      for (int m = 0; m < 8; ++m) {
+        const float xf = __uint_as_float((m & 1) ? (u[m >> 1] & 0xffff0000u) : (u[m >> 1] << 16));
+        acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(dc[i], xf, acc[m], 0, 0, 0);
       }
-#pragma unroll
-      for (int i = 0; i < kTU; ++i) { xc[i] = xn[i]; dc[i] = dn[i]; }
     }
-    // accumulator r of a lane: row 8*(r/4) + 4*k + r%4 of the pass, B-column j
-    if (col_ok) {
+#pragma unroll
+    for (int i = 0; i < kTU; ++i) { xc[i] = xn[i]; dc[i] = dn[i]; }
+  }
+  // accumulator r of a lane: row 8*(r/4) + 4*k + r%4 of the 32, B-column j.  Columns 0..3 of every
+  // lane's eight meet first, then columns 4..7.
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();                                          // (the first half has been read)
+    if (w > 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        red[((w - 1) * 16 + r) * 64 + lane] = make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
+    __syncthreads();
+    if (w == 0 && col_ok) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int z = z0 + 8 * (r / 4) + 4 * k + (r % 4);
         if (z < a.Z) {
-          float4* dst = reinterpret_cast<float4*>(a.part + ((size_t)blockIdx.y * a.Z + z) * a.d + c);
-          dst[0] = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
-          dst[1] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+          float4 s = make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
+#pragma unroll
+          for (int ww = 0; ww < kWGradWaves - 1; ++ww) {
+            const float4 v = red[(ww * 16 + r) * 64 + lane];
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+          }
+          *reinterpret_cast<float4*>(a.part + ((size_t)blockIdx.z * a.Z + z) * a.d + c + 4 * h) = s;
         }
       }
     }
@@ -232,62 +250,107 @@ __global__ void __launch_bounds__(256) route_bwd_wsum_kernel(const RouteBwdArgs 
   }
 }
 
-// dx: grid (ceil(T/8), ceil(d/2048)); a thread owns 8 columns of 8 tokens
-__global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a) {
-  constexpr int TB = 8;
-  const int c = (blockIdx.y * 256 + threadIdx.x) * 8;      // c >= d: helps staging dz only
-  const int t0 = blockIdx.x * TB;
-  float acc[TB][8];
-#pragma unroll
-  for (int k = 0; k < TB; ++k) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[k][i] = 0.f;
-    const int t = t0 + k;
-    if (t < a.T && a.dx_perm && c < a.d) {
-      // four slots at a time: the row loads are issued together, then added in slot order
-      for (int s0 = 0; s0 < a.Ke; s0 += 4) {
-        uint4 u[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int r = a.inv_perm[(size_t)t * a.Ke + min(s0 + i, a.Ke - 1)];
-          u[i] = *reinterpret_cast<const uint4*>(a.dx_perm + (size_t)r * a.d + c);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (s0 + i < a.Ke) {
-            acc[k][0] += __uint_as_float(u[i].x << 16); acc[k][1] += __uint_as_float(u[i].x & 0xffff0000u);
-            acc[k][2] += __uint_as_float(u[i].y << 16); acc[k][3] += __uint_as_float(u[i].y & 0xffff0000u);
-            acc[k][4] += __uint_as_float(u[i].z << 16); acc[k][5] += __uint_as_float(u[i].z & 0xffff0000u);
-            acc[k][6] += __uint_as_float(u[i].w << 16); acc[k][7] += __uint_as_float(u[i].w & 0xffff0000u);
-          }
-        }
-      }
-    }
-  }
-  // dz of the workgroup's 8 tokens: one contiguous block of dz[T, Z], staged in LDS and read
-  // back as broadcasts
-  __shared__ float dzs[TB * (kMaxGroups + kMaxExperts)];
+// dx: a thread owns 8 columns of TB tokens, a workgroup as many such token blocks as its 256 threads
+// cover (rows of d <= 1024 leave room for two or more); grid (token blocks, ceil(d/2048)).
+// Bound by the gathered rows of dx_perm, K_e of them per token: the rows of a token block are named
+// in LDS before the first one is requested, and the rows of two tokens are in flight together.  The
+// router weights come from L2 once per TB tokens, two rows ahead of their use; TB = 8 where that still
+// gives every compute unit two workgroups, fewer tokens otherwise.
+template <int TB>
+__global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a, int tpr) {
+  extern __shared__ __align__(16) unsigned char dx_smem[];
+  // tpr threads per row of this column block (a power of two up to 256), 256 / tpr token blocks
+  const int sub = threadIdx.x / tpr, nsub = 256 / tpr;
+  const int c = (blockIdx.y * 256 + (int)(threadIdx.x % tpr)) * 8;     // c >= d: helps staging only
+  const int b0 = blockIdx.x * nsub * TB;                               // first token of the workgroup
+  const int t0 = b0 + sub * TB;
+  float* dzs = reinterpret_cast<float*>(dx_smem);                      // [nsub * TB][Z]
+  int* rows = reinterpret_cast<int*>(dzs + nsub * TB * a.Z);           // [nsub * TB][Ke]
   {
-    const int n = TB * a.Z;
-    const size_t base = (size_t)t0 * a.Z, lim = (size_t)a.T * a.Z;
+    const int n = nsub * TB * a.Z;
+    const size_t base = (size_t)b0 * a.Z, lim = (size_t)a.T * a.Z;
     for (int i = threadIdx.x; i < n; i += 256) dzs[i] = base + i < lim ? a.dz[base + i] : 0.f;
+    if (a.dx_perm) {
+      const int m = nsub * TB * a.Ke;
+      const size_t rb = (size_t)b0 * a.Ke, rl = (size_t)a.T * a.Ke;
+      for (int i = threadIdx.x; i < m; i += 256) rows[i] = rb + i < rl ? a.inv_perm[rb + i] : 0;
+    }
   }
   __syncthreads();
-  if (c < a.d) {
-    for (int z = 0; z < a.Z; ++z) {
-      const float* wr = z < a.Ng ? a.w_group + (size_t)z * a.d + c : a.w_expert + (size_t)(z - a.Ng) * a.d + c;
-      const float4 w0 = *reinterpret_cast<const float4*>(wr), w1 = *reinterpret_cast<const float4*>(wr + 4);
+  if (c >= a.d) return;
+  const float* dzr = dzs + sub * TB * a.Z;
+  const int* rw = rows + sub * TB * a.Ke;
+  float acc[TB][8];
 #pragma unroll
-      for (int k = 0; k < TB; ++k) {
-        const float dzv = dzs[k * a.Z + z];
-        acc[k][0] = fmaf(dzv, w0.x, acc[k][0]); acc[k][1] = fmaf(dzv, w0.y, acc[k][1]);
-        acc[k][2] = fmaf(dzv, w0.z, acc[k][2]); acc[k][3] = fmaf(dzv, w0.w, acc[k][3]);
-        acc[k][4] = fmaf(dzv, w1.x, acc[k][4]); acc[k][5] = fmaf(dzv, w1.y, acc[k][5]);
-        acc[k][6] = fmaf(dzv, w1.z, acc[k][6]); acc[k][7] = fmaf(dzv, w1.w, acc[k][7]);
+  for (int k = 0; k < TB; ++k)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[k][i] = 0.f;
+  if (a.dx_perm) {
+    constexpr int TP = TB >= 2 ? 2 : 1;
+#pragma unroll
+    for (int k0 = 0; k0 < TB; k0 += TP) {
+      // four slots of TP tokens at a time: the row loads are issued together, then added in slot order
+      // (tokens past the end name row 0 and are not stored)
+      for (int s0 = 0; s0 < a.Ke; s0 += 4) {
+        uint4 u[TP][4];
+#pragma unroll
+        for (int p = 0; p < TP; ++p)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (s0 + i < a.Ke)
+              u[p][i] = *reinterpret_cast<const uint4*>(a.dx_perm + (size_t)rw[(k0 + p) * a.Ke + s0 + i] * a.d + c);
+#pragma unroll
+        for (int p = 0; p < TP; ++p)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (s0 + i < a.Ke) {
+              float (&ac)[8] = acc[k0 + p];
+              const uint4 v = u[p][i];
+              ac[0] += __uint_as_float(v.x << 16); ac[1] += __uint_as_float(v.x & 0xffff0000u);
+              ac[2] += __uint_as_float(v.y << 16); ac[3] += __uint_as_float(v.y & 0xffff0000u);
+              ac[4] += __uint_as_float(v.z << 16); ac[5] += __uint_as_float(v.z & 0xffff0000u);
+              ac[6] += __uint_as_float(v.w << 16); ac[7] += __uint_as_float(v.w & 0xffff0000u);
+            }
       }
     }
   }
-  if (c >= a.d) return;
+  // router rows: four at a time, the next four requested before the present ones are used
+  auto wrow = [&](int z) {
+    return z < a.Ng ? a.w_group + (size_t)z * a.d + c : a.w_expert + (size_t)(z - a.Ng) * a.d + c;
+  };
+  constexpr int ZU = 4;
+  float4 wc[ZU][2];
+#pragma unroll
+  for (int i = 0; i < ZU; ++i) {
+    const float* p = wrow(min(i, a.Z - 1));
+    wc[i][0] = *reinterpret_cast<const float4*>(p);
+    wc[i][1] = *reinterpret_cast<const float4*>(p + 4);
+  }
+  for (int z0 = 0; z0 < a.Z; z0 += ZU) {
+    float4 wn[ZU][2];
+#pragma unroll
+    for (int i = 0; i < ZU; ++i) {
+      const float* p = wrow(min(z0 + ZU + i, a.Z - 1));
+      wn[i][0] = *reinterpret_cast<const float4*>(p);
+      wn[i][1] = *reinterpret_cast<const float4*>(p + 4);
+    }
+#pragma unroll
+    for (int i = 0; i < ZU; ++i) {
+      if (z0 + i < a.Z) {
+        const float4 w0 = wc[i][0], w1 = wc[i][1];
+#pragma unroll
+        for (int k = 0; k < TB; ++k) {
+          const float dzv = dzr[k * a.Z + z0 + i];
+          acc[k][0] = fmaf(dzv, w0.x, acc[k][0]); acc[k][1] = fmaf(dzv, w0.y, acc[k][1]);
+          acc[k][2] = fmaf(dzv, w0.z, acc[k][2]); acc[k][3] = fmaf(dzv, w0.w, acc[k][3]);
+          acc[k][4] = fmaf(dzv, w1.x, acc[k][4]); acc[k][5] = fmaf(dzv, w1.y, acc[k][5]);
+          acc[k][6] = fmaf(dzv, w1.z, acc[k][6]); acc[k][7] = fmaf(dzv, w1.w, acc[k][7]);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < ZU; ++i) { wc[i][0] = wn[i][0]; wc[i][1] = wn[i][1]; }
+  }
 #pragma unroll
   for (int k = 0; k < TB; ++k) {
     const int t = t0 + k;
@@ -300,10 +363,13 @@ __global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a)
   }
 }
 
-// token splits of the weight-gradient reduction: about 64 tokens each, at most 256 splits and at
-// most 64 MB of partial sums
+// token splits of the weight-gradient reduction: enough for two workgroups per compute unit, at least
+// 32 tokens each (8 per wave: shorter stretches cost more in partial sums than they save in MFMAs), at
+// most 256 splits and at most 64 MB of partial sums
 static int wgrad_splits(const LayerDesc& L) {
-  long long s = (L.T + 63) / 64;
+  const long long per_split = (long long)((L.d + 255) / 256) * ((L.Ng + L.Ne + kZC - 1) / kZC);
+  long long s = (512 + per_split - 1) / per_split;
+  if (s > (L.T + 31) / 32) s = (L.T + 31) / 32;
   const long long cap = (64ll << 20) / ((long long)(L.Ng + L.Ne) * L.d * 4);
   if (s > cap) s = cap;
   if (s > 256) s = 256;
@@ -316,6 +382,25 @@ static size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 size_t route_bwd_workspace_bytes(const LayerDesc& L) {
   const size_t Z = L.Ng + L.Ne, T = L.T > 0 ? L.T : 1;
   return up256(T * Z * 4) + up256((size_t)wgrad_splits(L) * Z * L.d * 4);
+}
+
+static void launch_dx(const RouteBwdArgs& a, hipStream_t s) {
+  // threads per row: a power of two that covers a row of up to 2048 columns; the staged dz and row
+  // numbers of the workgroup's tokens stay below 32 KB
+  int tpr = 8;
+  while (tpr < 256 && tpr * 8 < a.d) tpr *= 2;
+  const unsigned cb = (unsigned)((a.d + 2047) / 2048);
+  for (int TB = 8; TB >= 2; TB /= 2) {
+    auto lds = [&](int t) { return (size_t)(256 / t) * TB * (a.Z + a.Ke) * 4; };
+    int t = tpr;
+    while (t < 256 && lds(t) > 32 * 1024) t *= 2;
+    const int per_wg = 256 / t * TB;
+    const unsigned tb = (unsigned)((a.T + per_wg - 1) / per_wg);
+    if (TB > 2 && (long long)tb * cb < 512) continue;
+    auto kern = TB == 8 ? route_bwd_dx_kernel<8> : TB == 4 ? route_bwd_dx_kernel<4> : route_bwd_dx_kernel<2>;
+    hipLaunchKernelGGL(kern, dim3(tb, cb), dim3(256), lds(t), s, a, t);
+    return;
+  }
 }
 
 hipError_t launch_route_bwd(const LayerDesc& L, const mohge_config& cfg, const void* x,
@@ -341,10 +426,11 @@ hipError_t launch_route_bwd(const LayerDesc& L, const mohge_config& cfg, const v
   a.dz = dz_out ? dz_out : reinterpret_cast<float*>(base);
   a.part = reinterpret_cast<float*>(base + dz_bytes);
   hipLaunchKernelGGL(route_bwd_token_kernel, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(route_bwd_wgrad_kernel, dim3((unsigned)((L.d + 1023) / 1024), (unsigned)a.S), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(route_bwd_wgrad_kernel,
+                     dim3((unsigned)((L.d + 255) / 256), (unsigned)((a.Z + kZC - 1) / kZC), (unsigned)a.S),
+                     dim3(64 * kWGradWaves), 0, s, a);
   hipLaunchKernelGGL(route_bwd_wsum_kernel, dim3((unsigned)(((size_t)a.Z * L.d / 4 + 31) / 32)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(route_bwd_dx_kernel, dim3((unsigned)((L.T + 7) / 8), (unsigned)((L.d + 2047) / 2048)),
-                     dim3(256), 0, s, a);
+  launch_dx(a, s);
   return hipGetLastError();
 }
 
