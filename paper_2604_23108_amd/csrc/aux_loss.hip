@@ -25,33 +25,56 @@ struct AuxArgs {
   float ratio[kMaxGroups];   // F_g / max F
 };
 
+// A workgroup takes its tokens 16 at a time: their rows of GS, ES' and the kept ids are contiguous in
+// memory and are staged in LDS with whole-workgroup loads, so that a batch costs one memory latency
+// (read where they are needed, every sum over a row was its own chain of loads: 12-14 us per call).
+constexpr int kAuxTok = 16;
+
 __global__ void __launch_bounds__(256) aux_partial_kernel(const AuxArgs a) {
+  extern __shared__ __align__(16) unsigned char aux_smem[];
   __shared__ double red[4][2 * (kMaxGroups + kMaxExperts)];
+  float* const s_gs = reinterpret_cast<float*>(aux_smem);               // [kAuxTok][Ng]
+  float* const s_es = s_gs + kAuxTok * a.Ng;                            // [kAuxTok][Ne]
+  int* const s_gi = reinterpret_cast<int*>(s_es + kAuxTok * a.Ne);      // [kAuxTok][Kg]
+  int* const s_ei = s_gi + kAuxTok * a.Kg;                              // [kAuxTok][Ke]
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int ncol = a.Ng + a.Ne;
   const int tbeg = blockIdx.x * a.tok_per_blk;
   const int tend = min(a.T, tbeg + a.tok_per_blk);
   double pG = 0.0, cG = 0.0, pE[4] = {0.0, 0.0, 0.0, 0.0}, cE[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int t = tbeg + w; t < tend; t += 4) {
-    if (lane < a.Ng) {
-      // s'_{g,t} = GS_{g,t} / sum_j GS_{j,t}
-      const float* row = a.gs + (size_t)t * a.Ng;
-      float sum = 0.f;
-      for (int j = 0; j < a.Ng; ++j) sum += row[j];
-      pG += (double)(row[lane] / sum);
-      for (int s = 0; s < a.Kg; ++s) cG += (a.gidx[(size_t)t * a.Kg + s] == lane) ? 1.0 : 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int e = lane + 64 * j;
-      if (e < a.Ne) {
-        // S^E_{g,i,t} = ES'_{g,i,t} / (sum_j ES'_{g,j,t} + eps)
-        const float* row = a.es1 + (size_t)t * a.Ne;
-        const int g0 = (e / a.N) * a.N;
+  for (int tb = tbeg; tb < tend; tb += kAuxTok) {
+    const int nt = min(kAuxTok, tend - tb);
+    __syncthreads();                         // the previous batch has been read
+    for (int i = threadIdx.x; i < nt * a.Ne; i += 256) s_es[i] = a.es1[(size_t)tb * a.Ne + i];
+    for (int i = threadIdx.x; i < nt * a.Ng; i += 256) s_gs[i] = a.gs[(size_t)tb * a.Ng + i];
+    for (int i = threadIdx.x; i < nt * a.Kg; i += 256) s_gi[i] = a.gidx[(size_t)tb * a.Kg + i];
+    for (int i = threadIdx.x; i < nt * a.Ke; i += 256) s_ei[i] = a.eidx[(size_t)tb * a.Ke + i];
+    __syncthreads();
+    for (int t = w; t < nt; t += 4) {
+      if (lane < a.Ng) {
+        // s'_{g,t} = GS_{g,t} / sum_j GS_{j,t}
+        const float* row = s_gs + t * a.Ng;
         float sum = 0.f;
-        for (int i = 0; i < a.N; ++i) sum += row[g0 + i];
-        pE[j] += (double)(row[e] / (sum + a.eps));
-        for (int s = 0; s < a.Ke; ++s) cE[j] += (a.eidx[(size_t)t * a.Ke + s] == e) ? 1.0 : 0.0;
+        for (int j = 0; j < a.Ng; ++j) sum += row[j];
+        pG += (double)(row[lane] / sum);
+        int n = 0;
+        for (int s = 0; s < a.Kg; ++s) n += s_gi[t * a.Kg + s] == lane;
+        cG += (double)n;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int e = lane + 64 * j;
+        if (e < a.Ne) {
+          // S^E_{g,i,t} = ES'_{g,i,t} / (sum_j ES'_{g,j,t} + eps)
+          const float* row = s_es + t * a.Ne;
+          const int g0 = (e / a.N) * a.N;
+          float sum = 0.f;
+          for (int i = 0; i < a.N; ++i) sum += row[g0 + i];
+          pE[j] += (double)(row[e] / (sum + a.eps));
+          int n = 0;
+          for (int s = 0; s < a.Ke; ++s) n += s_ei[t * a.Ke + s] == e;
+          cE[j] += (double)n;
+        }
       }
     }
   }
@@ -137,7 +160,8 @@ hipError_t launch_aux_loss(const LayerDesc& L, const mohge_config& cfg, const fl
   a.tok_per_blk = (L.T + a.nblk - 1) / a.nblk;
   a.alpha_g = cfg.alpha_g; a.alpha_e = cfg.alpha_e; a.eps = cfg.eps; a.freq_norm = cfg.aux_freq_norm;
   for (int g = 0; g < kMaxGroups; ++g) a.ratio[g] = g < L.Ng ? (float)L.F[g] / (float)L.Fmax : 0.f;
-  hipLaunchKernelGGL(aux_partial_kernel, dim3(a.nblk), dim3(256), 0, s, a);
+  const size_t smem = (size_t)kAuxTok * (a.Ng + a.Ne + a.Kg + a.Ke) * 4;      // at most 34 KB
+  hipLaunchKernelGGL(aux_partial_kernel, dim3(a.nblk), dim3(256), smem, s, a);
   hipLaunchKernelGGL(aux_final_kernel, dim3(1), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
