@@ -1,13 +1,13 @@
 // Expert feed-forward networks for decode-sized token counts on gfx950 (a handful of
 // tokens per expert): bandwidth-bound, every touched expert's weights are streamed once.
 //
-// A wave owns 2 x 16 weight rows (up: 16 W_gate rows and the matching 16 W_up rows;
-// down: 32 consecutive W_down rows) and runs over the whole reduction dimension with
+// A workgroup owns 2 x 16 weight rows (up: 16 W_gate rows and the matching 16 W_up rows;
+// down: 32 consecutive W_down rows); its four waves share the reduction and run
 // v_mfma_f32_16x16x32_bf16, the weight rows as the first operand and up to 32 of the
 // expert's tokens as the second.  Lanes load 16 contiguous bytes of "their" weight row,
 // which is the operand layout, so weights go global -> registers -> matrix core with no
 // LDS traffic; token rows come through L1/L2 (lanes past the token count load nothing).
-// Experts without tokens are skipped on the device: their workgroups exit at once.
+// Experts without tokens get no workgroups.
 //
 // Quantised weights (ffn_skinny_q_kernel): FP8 E4M3 codes with one fp32 scale per weight row, or
 // MXFP4 (E2M1 codes, two to a byte, an E8M0 scale per block of 32 elements of the reduction
@@ -24,9 +24,35 @@
 
 namespace mohge {
 
+// The grid numbers the experts that have rows (slot = blockIdx.x / ncb), so that a call of a few tokens does
+// not start a workgroup per column block of every idle expert; slots past the last such expert, and
+// columns past a narrower group's, exit.
 template <bool UP>
-__global__ void __launch_bounds__(256) ffn_skinny_kernel(const SkinnyArgs a) {
-  skinny_unit<UP, false>(a, (int)blockIdx.x);
+__global__ void __launch_bounds__(256, 3) ffn_skinny_kernel(const SkinnyArgs a, const int ncb) {
+  __shared__ f32x4 red[kSplitLdsBytes / 16];
+  const int lane = threadIdx.x & 63;
+  const int slot = blockIdx.x / ncb, c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
+  const int Ne = a.Ng * a.N;
+  int before = 0, e = -1, row0 = 0, cnt = 0;
+  for (int e0 = 0; e0 < Ne; e0 += 64) {
+    const int ee = e0 + lane < Ne ? e0 + lane : Ne - 1;
+    const int lo = a.offsets[ee], n = e0 + lane < Ne ? a.offsets[ee + 1] - lo : 0;
+    const unsigned long long has = __ballot(n > 0);
+    const int rank = before + __popcll(has & ((1ull << lane) - 1ull));
+    const unsigned long long hit = __ballot(n > 0 && rank == slot);
+    if (hit) {
+      const int l = (int)__builtin_ctzll(hit);
+      e = e0 + l;
+      row0 = __builtin_amdgcn_readlane(lo, l);
+      cnt = __builtin_amdgcn_readlane(n, l);
+      break;
+    }
+    before += __popcll(has);
+  }
+  if (e < 0) return;
+  const int g = e / a.N;
+  if (c0 >= (UP ? a.F[g] : a.d)) return;
+  skinny_unit<UP, false>(a, g, e - g * a.N, c0, row0, cnt, red);
 }
 
 // 16 E4M3 codes -> two operand fragments of 8 bf16 (codes 0..7 and 8..15)
@@ -63,8 +89,8 @@ __device__ __forceinline__ void fp4x8_to_bf16(const uint32_t c, const float scal
   o.u = make_uint4(p0.u, p1.u, p2.u, p3.u);
 }
 
-// Quantised-weight variant of ffn_skinny_kernel (BITS = 8: FP8 E4M3, BITS = 4: MXFP4): same split
-// of the weight rows over workgroups and waves.  A unit of the reduction is 64 bytes of a weight
+// Quantised-weight variant (BITS = 8: FP8 E4M3, BITS = 4: MXFP4): a workgroup has 128 weight rows, a wave
+// 2 x 16 of them and the whole reduction.  A unit of the reduction is 64 bytes of a weight
 // row: lane (r, q) holds 16 bytes of its row, 16 (FP8) or 32 (MXFP4) consecutive indices, used as
 // two or four MFMA steps.  With fewer bytes per weight, keeping the memory system busy takes more
 // loads in flight per wave than token fragments held in registers leave room for, so here
@@ -483,8 +509,10 @@ hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* p
     if (stages & 2) hipLaunchKernelGGL((ffn_skinny_q_kernel<false, 8>), dim3(nd), dim3(256), 0, s, dn);
     return hipGetLastError();
   }
-  if (stages & 1) hipLaunchKernelGGL((ffn_skinny_kernel<true>), dim3(nu), dim3(256), 0, s, up);
-  if (stages & 2) hipLaunchKernelGGL((ffn_skinny_kernel<false>), dim3(nd), dim3(256), 0, s, dn);
+  const int slots = L.P < L.Ne ? L.P : L.Ne;
+  const int cu = L.Fmax / 16, cd = (L.d + 31) / 32;
+  if (stages & 1) hipLaunchKernelGGL((ffn_skinny_kernel<true>), dim3(slots * cu), dim3(256), 0, s, up, cu);
+  if (stages & 2) hipLaunchKernelGGL((ffn_skinny_kernel<false>), dim3(slots * cd), dim3(256), 0, s, dn, cd);
   return hipGetLastError();
 }
 

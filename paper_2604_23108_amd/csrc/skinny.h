@@ -43,30 +43,31 @@ __device__ __forceinline__ void store8_device_scope(void* p, const uint2 v) {
   asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(q) : "memory");
 }
 
-// One unit of the bf16 decode kernels: workgroup `blk` of the launch that has one workgroup of 4
-// waves per (expert, 64 hidden units) [UP] or (expert, 128 output features) [down].  COHERENT:
-// the output rows are stored at device scope (for a consumer in the same launch).
+// One unit of the bf16 decode kernels: 16 hidden units [UP: 16 W_gate rows and the matching 16 W_up rows] or
+// 32 output features [down] of one expert, all its rows, 32 at a time.  The four waves of the workgroup take
+// the same weight rows and a quarter of the reduction indices each; their partial sums meet in LDS and are
+// added in wave order.  Bound by the weight stream, i.e. by the loads in flight: a wave has the weights
+// and token rows of 128 (64 with more than 16 rows) reduction indices on the way while it multiplies the
+// previous ones, and requests its first weights before it looks up the expert's rows.  The quarters
+// also start a quarter of a row apart, which spreads the waves over the memory channels (rows begin at
+// multiples of the row size, a power of two at the usual hidden sizes).
+// Measured against a wave per 32 weight rows that walked the whole reduction, up + down of d = 4096, 64
+// experts (widths 768..2048): 88 -> 33 us with one token (352 waves, not two per compute unit, each with 16
+// steps of memory latency), 194 -> 170 at 8 tokens, 357 -> 328 (5.9 TB/s) at 32; d = 1024, 32 experts:
+// 36 -> 29 at 32 tokens.
+constexpr int kSplitWaves = 4;
+constexpr int kSplitLdsBytes = (kSplitWaves - 1) * 4 * 64 * 16;
+
+// expert e = group g, index i inside it; c0: first of 16 hidden units [UP] or 32 output features [down].
+// red: LDS, kSplitLdsBytes.  Called by the whole workgroup of 4 waves, the same arguments in all of them.
 template <bool UP, bool COHERENT>
-__device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int blk) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, const int i, const int c0,
+                                                  const int row0, const int cnt, f32x4* const red) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, q = lane >> 4;
-  int g = 0;
-  while (g + 1 < a.Ng && blk >= a.blk_prefix[g + 1]) ++g;
   const int F = a.F[g];
   const int K = UP ? a.d : F;
   const int ncols = UP ? F : a.d;
-  // workgroup = 4 waves; up: 64 hidden units; down: 128 output features
-  constexpr int COLS_PER_BLOCK = UP ? 64 : 128;
-  const int blocks_per_expert = (ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  const int local = blk - a.blk_prefix[g];
-  const int i = local / blocks_per_expert, cb = local % blocks_per_expert;
-  const int e = g * a.N + i;
-  const int row0 = a.offsets[e], cnt = a.offsets[e + 1] - row0;
-  if (cnt <= 0) return;
-  const int c0 = cb * COLS_PER_BLOCK + w * (UP ? 16 : 32);
-  if (c0 >= ncols) return;
-
-  // the two weight-row sets of this wave
   const uint16_t* wp[2];
   if constexpr (UP) {
     const uint16_t* base = a.W[g] + (long long)i * 2 * F * K;
@@ -79,15 +80,27 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int blk) 
     wp[0] = base + (long long)(c0 + r) * K + 8 * q;
     wp[1] = base + (long long)n1 * K + 8 * q;
   }
-
+  // this wave's indices: whole blocks of 64 (none where the reduction is shorter than 256)
+  const int nb = K / 64;
+  const int kb = nb * w / kSplitWaves * 64, ke = nb * (w + 1) / kSplitWaves * 64;
   for (int tb0 = 0; tb0 < cnt; tb0 += 32) {
-    // NTB = token blocks of 16 in flight: decode mostly has a handful of tokens per expert, and
-    // the second block would cost its operand loads and matrix-core steps for nothing
     auto pass = [&](auto NTBC) {
-      constexpr int NTB = decltype(NTBC)::value;
-      const uint16_t* xp[2];
-      bool xv[2];
-  #pragma unroll
+      constexpr int NTB = decltype(NTBC)::value;             // token blocks of 16
+      constexpr int U = NTB == 1 ? 4 : 2;                    // 32-deep matrix-core steps per request
+      Frag wc[2][U], xc[NTB][U];
+      auto load_w = [&](Frag (&wf)[2][U], int k0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int f = 0; f < 2; ++f) {
+            wf[f][u].u = make_uint4(0u, 0u, 0u, 0u);
+            if (k0 + 32 * u < ke) wf[f][u].u = *reinterpret_cast<const uint4*>(wp[f] + k0 + 32 * u);
+          }
+      };
+      load_w(wc, kb);
+      const uint16_t* xp[NTB];
+      bool xv[NTB];
+#pragma unroll
       for (int tb = 0; tb < NTB; ++tb) {
         const int tt = tb0 + 16 * tb + r;
         xv[tb] = tt < cnt;
@@ -97,88 +110,108 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int blk) 
         else src = pos;
         xp[tb] = a.A + src * a.lda + 8 * q;
       }
-      f32x4 acc[2][2];
-  #pragma unroll
-      for (int f = 0; f < 2; ++f)
-  #pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) acc[f][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-      auto step = [&](int k0, auto UC) {
-        constexpr int U = decltype(UC)::value;
-        Frag wf[2][U], xf[2][U];
-  #pragma unroll
-        for (int u = 0; u < U; ++u) {
-  #pragma unroll
-          for (int f = 0; f < 2; ++f) wf[f][u].u = *reinterpret_cast<const uint4*>(wp[f] + k0 + 32 * u);
-  #pragma unroll
+      auto load_x = [&](Frag (&xf)[NTB][U], int k0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
           for (int tb = 0; tb < NTB; ++tb) {
             xf[tb][u].u = make_uint4(0u, 0u, 0u, 0u);
-            if (xv[tb]) xf[tb][u].u = *reinterpret_cast<const uint4*>(xp[tb] + k0 + 32 * u);
+            if (k0 + 32 * u < ke && xv[tb]) xf[tb][u].u = *reinterpret_cast<const uint4*>(xp[tb] + k0 + 32 * u);
           }
-        }
-  #pragma unroll
-        for (int u = 0; u < U; ++u)
-  #pragma unroll
-          for (int f = 0; f < 2; ++f)
-  #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb)
-              acc[f][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[f][u].v, xf[tb][u].v, acc[f][tb], 0, 0, 0);
       };
-      // The deepest unrolling only with one token block: the registers of the rarer two-block pass
-      // would otherwise set the kernel's occupancy.
-      // Every wave starts its walk along the rows at a different main step and wraps around.  All
-      // weight rows begin at multiples of the row size, a power of two at the usual hidden sizes,
-      // so waves that walk in step ask the same few memory channels at any one time; staggered
-      // they spread over all of them (a pure-read kernel with this access pattern: 5.2-5.6 TB/s in
-      // step, 6.2 TB/s staggered, at a row of 8 KB; this kernel, which also loads tokens and feeds
-      // the matrix cores, gains 1.5 %).  The order of the fp32 additions then depends on the wave,
-      // which is fixed by the launch: results stay bit-identical from run to run.
-      constexpr int MAIN = NTB == 1 ? 256 : 128;
-      const int nmain = K / MAIN;
-      int st = nmain > 0 ? (int)(((long long)blk * 4 + w) * 5 % nmain) : 0;
-      for (int sidx = 0; sidx < nmain; ++sidx) {
-        step(st * MAIN, std::integral_constant<int, MAIN / 32>{});
-        if (++st == nmain) st = 0;
+      load_x(xc, kb);
+      f32x4 acc[2][NTB];
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) acc[f][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int k0 = kb; k0 < ke; k0 += 32 * U) {
+        Frag wn[2][U], xn[NTB][U];
+        load_w(wn, k0 + 32 * U);
+        load_x(xn, k0 + 32 * U);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb)
+              acc[f][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wc[f][u].v, xc[tb][u].v, acc[f][tb], 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+          for (int f = 0; f < 2; ++f) wc[f][u] = wn[f][u];
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) xc[tb][u] = xn[tb][u];
+        }
       }
-      int k0 = nmain * MAIN;
-      for (; k0 + 128 <= K; k0 += 128) step(k0, std::integral_constant<int, 4>{});
-      for (; k0 < K; k0 += 64) step(k0, std::integral_constant<int, 2>{});
-
-      // lane holds token r of each token block, weight rows 4q..4q+3 of each row set
-  #pragma unroll
-      for (int tb = 0; tb < NTB; ++tb) {
-        const int tt = tb0 + 16 * tb + r;
-        if (tt >= cnt) continue;
-        uint16_t* crow = a.C + (long long)(row0 + tt) * a.ldc;
-        if constexpr (UP) {
-          float v[4];
-  #pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const float gt = acc[0][tb][b], up = acc[1][tb][b];
-            v[b] = gt / (1.f + __expf(-gt)) * up;
-          }
-          uint2 o;
-          o.x = pack_bf16x2(v[0], v[1]);
-          o.y = pack_bf16x2(v[2], v[3]);
-          if constexpr (COHERENT) store8_device_scope(crow + c0 + 4 * q, o);
-          else *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
-        } else {
-  #pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            const int col = c0 + 16 * f + 4 * q;
-            if (col < ncols) {
-              uint2 o;
-              o.x = pack_bf16x2(acc[f][tb][0], acc[f][tb][1]);
-              o.y = pack_bf16x2(acc[f][tb][2], acc[f][tb][3]);
-              if constexpr (COHERENT) store8_device_scope(crow + col, o);
-              else *reinterpret_cast<uint2*>(crow + col) = o;
+      if (w > 0)
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) red[((w - 1) * 4 + 2 * f + tb) * 64 + lane] = acc[f][tb];
+      __syncthreads();
+      if (w == 0) {
+        // lane holds token r of each token block, weight rows 4q..4q+3 of each row set
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int ww = 0; ww < kSplitWaves - 1; ++ww) acc[f][tb] += red[(ww * 4 + 2 * f + tb) * 64 + lane];
+          const int tt = tb0 + 16 * tb + r;
+          if (tt >= cnt) continue;
+          uint16_t* crow = a.C + (long long)(row0 + tt) * a.ldc;
+          if constexpr (UP) {
+            float v[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+              const float gt = acc[0][tb][b], up = acc[1][tb][b];
+              v[b] = gt / (1.f + __expf(-gt)) * up;
+            }
+            uint2 o;
+            o.x = pack_bf16x2(v[0], v[1]);
+            o.y = pack_bf16x2(v[2], v[3]);
+            if constexpr (COHERENT) store8_device_scope(crow + c0 + 4 * q, o);
+            else *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
+          } else {
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              const int col = c0 + 16 * f + 4 * q;
+              if (col < ncols) {
+                uint2 o;
+                o.x = pack_bf16x2(acc[f][tb][0], acc[f][tb][1]);
+                o.y = pack_bf16x2(acc[f][tb][2], acc[f][tb][3]);
+                if constexpr (COHERENT) store8_device_scope(crow + col, o);
+                else *reinterpret_cast<uint2*>(crow + col) = o;
+              }
             }
           }
         }
       }
+      __syncthreads();                                       // the sums have been read
     };
     if (cnt - tb0 > 16) pass(std::integral_constant<int, 2>{});
     else pass(std::integral_constant<int, 1>{});
+  }
+}
+
+// Workgroup `blk` of the numbering that has one unit per (expert, 64 hidden units) [UP] or (expert, 128
+// output features) [down]: four of the units above one after the other (the single-launch decode layer's
+// pieces of work).
+template <bool UP, bool COHERENT>
+__device__ __forceinline__ void skinny_block(const SkinnyArgs& a, const int blk, f32x4* const red) {
+  int g = 0;
+  while (g + 1 < a.Ng && blk >= a.blk_prefix[g + 1]) ++g;
+  const int ncols = UP ? a.F[g] : a.d;
+  constexpr int COLS_PER_BLOCK = UP ? 64 : 128;
+  const int blocks_per_expert = (ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
+  const int local = blk - a.blk_prefix[g];
+  const int i = local / blocks_per_expert, cb = local % blocks_per_expert;
+  const int e = g * a.N + i;
+  const int row0 = a.offsets[e], cnt = a.offsets[e + 1] - row0;
+  for (int sub = 0; sub < 4; ++sub) {
+    const int c0 = cb * COLS_PER_BLOCK + sub * (COLS_PER_BLOCK / 4);
+    if (c0 < ncols) skinny_unit<UP, COHERENT>(a, g, i, c0, row0, cnt, red);
   }
 }
 
