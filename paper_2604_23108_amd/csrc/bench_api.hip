@@ -18,6 +18,7 @@ using namespace mohge;
 #define OPT(p) do { int rc_ = need((p), #p, false); if (rc_) return rc_; } while (0)
 
 static int to_options(const mohge_ffn_options* in, const LayerDesc& L, FfnOptions* o) {
+  o->small = 0;       // this library's options describe the schedule-driven 256 x 256 form
   if (!in) return MOHGE_OK;
   for (int i = 0; i < 2; ++i) {
     const int v = i == 0 ? in->tile_rows_up : in->tile_rows_down;

@@ -8,7 +8,7 @@
 //     dx_r = W_gate^T da + W_up^T db
 //     dW_down[e] = sum_r dy_r h_r^T,   dW_gate[e] = sum_r da_r x_r^T,   dW_up[e] = sum_r db_r x_r^T
 //
-// All of it runs as four launches of the ragged grouped GEMM tile kernel of the forward pass:
+// All of it runs as four products of the ragged grouped GEMM tile kernel of the forward pass:
 //   dH   = dY . W_down        reduction over d        (SwiGLU derivative fused: writes [dA|dB])
 //   dX   = [dA|dB] . W13      reduction over 2 F_g
 //   dW2  = dY^T . H           reduction over the expert's routed rows
@@ -18,7 +18,7 @@
 // the weights are used as the forward pass stores them and no activation is transposed in
 // memory.  The only helper pass gathers the rows of x into sorted order for the last product
 // (the other three activations already are in sorted order); it shares a launch with the tile
-// schedules.
+// schedules, in the 128 x 128 form with the dH tiles.
 #include "common.h"
 #include "tiled.h"
 
@@ -129,6 +129,10 @@ hipError_t launch_expert_ffn_bwd(const LayerDesc& L, const void* x, const int32_
   GatherArgs ga;
   ga.x = static_cast<const uint4*>(x); ga.perm = perm; ga.xs = reinterpret_cast<uint4*>(xs);
   ga.zero_row = reinterpret_cast<uint4*>(zero_row); ga.P = L.P; ga.Ke = L.Ke; ga.chunks = L.d / 8;
+  if (use_small_tiles(L, o, true)) {
+    dh.coherent_out = 0;
+    return launch_small_bwd(L, dh, dxa, w2a, w13a, ga, s);
+  }
   hipError_t e = launch_bwd_schedules(dh, dxa, w2a, w13a, ga, fused, s);
   if (e != hipSuccess) return e;
   if (fused) {

@@ -76,6 +76,12 @@ constexpr bool tr_b(int mode) { return mode == kWgrad || mode == kDgradH || mode
 // reduction over d, F_g output columns
 constexpr bool red_d(int mode) { return is_up(mode) || mode == kDgradH; }
 
+// Tile geometry.  Big: 256 x 256 tiles, 8 waves, all 160 KB of LDS, one persistent workgroup per
+// compute unit.  Small: 128 x 128 tiles, 4 waves, half the LDS, two workgroups per compute unit (the
+// launches that would leave compute units idle with big tiles, see use_small_tiles).
+struct BigTile { static constexpr int BM = kBM, BN = kBN, WGM = kWGM, WGN = kWGN; };
+struct SmallTile { static constexpr int BM = 128, BN = 128, WGM = 2, WGN = 2; };
+
 template <int MODE>
 struct Shape {
   static constexpr int NCOLS_PER_TILE = is_up(MODE) ? kBN / 2 : kBN;
@@ -484,7 +490,7 @@ __device__ __forceinline__ void swiglu_bwd8(const uint4 dh, const uint4 pv, cons
 // phase clocks for the optional counters of the benchmark library (a.cycles)
 #define PROBE_T(i) do { if (a.cycles) ts[i] = __builtin_amdgcn_s_memtime(); } while (0)
 
-template <int MODE, int NACT>
+template <int MODE, int NACT, typename GEO>
 __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, unsigned char* lds,
                                          int lane, int w, int* signal = nullptr) {
   constexpr bool UP = is_up(MODE);
@@ -493,19 +499,20 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr bool DH = MODE == kDgradH;
   long long ts[6] = {0, 0, 0, 0, 0, 0};
   PROBE_T(0);
-  constexpr int BM = kBM, BN = kBN, BK = kBK;
-  constexpr int WGM = Shape<MODE>::WGM, WGN = Shape<MODE>::WGN, NWAVES = WGM * WGN, NT = 64 * NWAVES;
+  constexpr int BM = GEO::BM, BN = GEO::BN, BK = kBK;
+  static_assert(BM == BN, "one part size for both operands");
+  constexpr int WGM = GEO::WGM, WGN = GEO::WGN, NWAVES = WGM * WGN, NT = 64 * NWAVES;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int MF = WTM / 32, NF = WTN / 32;
   constexpr int CH = BK / 8, ROWB = BK * 2, RPL = 64 / CH, SH = 1;   // 8 chunks, 128-byte rows
   constexpr int KK = BK / 16;                                        // MFMA k-steps per stage
   constexpr int B_LOADS = BN * CH / NT;
   // wave-wide load j of the token part fills tile rows [64j, 64j+64): only NACT of them matter
-  // (token-major operands: a part is 64 tokens x 256 features, all of it is loaded)
+  // (token-major operands: a part is 64 tokens x BM features, all of it is loaded)
   // (NACT active fragments per wave cover the tile rows [0, NACT * 32 * WGM))
   constexpr int A_LOADS = TRA ? BM * CH / NT : NACT * (32 * WGM / (NWAVES * RPL));
   static_assert((32 * WGM) % (NWAVES * RPL) == 0 && B_LOADS * NWAVES * RPL == BN, "whole wave-wide loads");
-  constexpr int PART = BM * ROWB;                 // 32 KB: one token part or one weight part
+  constexpr int PART = BM * ROWB;                 // 32 (16) KB: one token part or one weight part
   constexpr int NM = NACT * NF;     // MFMAs per k-step
   constexpr int NR = NACT + NF;     // fragment reads per k-step
   static_assert(NACT >= 1 && NACT <= MF, "active fragments");
@@ -534,13 +541,14 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   const uint16_t* src_a[TRA ? 1 : A_LOADS];
   const uint16_t* src_b[TRB ? 1 : B_LOADS];
   // Operands stored reduction-index major (rows = reduction index, features contiguous): a part
-  // holds 64 reduction rows x 256 features, 512 bytes a row.  Wave-wide load j fills rows
-  // 2*(j*NWAVES + w) and the next one; lane l fills physical chunk l%32 of row t = that + l/32,
-  // which holds logical chunk (l%32) ^ (4*(t&3)): the four rows a transposing read touches at
-  // once then sit in different banks.
-  static_assert(!(TRA || TRB) || (NWAVES % 2 == 0 && B_LOADS == BM * CH / NT), "part layout");
-  const int trow0 = 2 * w + (lane >> 5);          // row of load 0; load j: + 2*NWAVES*j
-  const int tr_lc = (lane & 31) ^ (4 * (trow0 & 3));
+  // holds 64 reduction rows x BN features, TRB_ROW = 512 (256) bytes a row.  Wave-wide load j fills
+  // the TPL = 2 (4) rows from TPL*(j*NWAVES + w); lane l fills physical chunk l%TCH of row t = that +
+  // l/TCH, which holds logical chunk (l%TCH) ^ (4*(t&3)): the four rows a transposing read touches
+  // at once then sit in different banks.
+  constexpr int TRB_ROW = BN * 2, TCH = BN / 8, TPL = 1024 / TRB_ROW;
+  static_assert(!(TRA || TRB) || (NWAVES * TPL % 4 == 0 && B_LOADS == BM * CH / NT), "part layout");
+  const int trow0 = TPL * w + lane / TCH;         // row of load 0; load j: + TPL*NWAVES*j
+  const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3));
   const uint16_t* zsrc = nullptr;
   unsigned tr_ldb = 0;                            // row pitch of the B operand in elements
   if constexpr (TRA) {
@@ -553,7 +561,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     int nb = rec.n0 + tr_lc * 8;
     if constexpr (WG) {
       if (nb > a.Ncols[g] - 8) nb = a.Ncols[g] - 8;
-      zsrc = a.zero_row + (lane & 31) * 8;
+      zsrc = a.zero_row + (lane % TCH) * 8;
       tr_ldb = a.ldb;
       src_b[0] = a.B2 + (long long)(tok0 + trow0) * a.ldb + nb;
     } else if constexpr (DH) {
@@ -610,7 +618,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
                                   // unless the two operands differ)
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    foff_t[kk] = (16 * kk + 8 * (tq >> 1) + ta) * 512 + (2 * (tq & 1) + (tb >> 1)) * 16 + (tb & 1) * 8;
+    foff_t[kk] = (16 * kk + 8 * (tq >> 1) + ta) * TRB_ROW + (2 * (tq & 1) + (tb >> 1)) * 16 + (tb & 1) * 8;
     foff[kk] = frow * ROWB + (((2 * kk + fh) ^ ((frow >> SH) & (CH - 1))) << 4);
   }
   // first feature of a fragment -> its 16-byte chunk, swizzled like the loads wrote it
@@ -649,18 +657,18 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       typedef short s16x8 __attribute__((ext_vector_type(8)));
       typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * 512));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * TRB_ROW));
       const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
       return __builtin_bit_cast(bf16x8, v);
     } else {
       return *reinterpret_cast<const bf16x8*>(p);
     }
   };
-  // reduction-major operands: load j of a stage starts 2*NWAVES*j rows further down; in
+  // reduction-major operands: load j of a stage starts TPL*NWAVES*j rows further down; in
   // kWgrad the rows are routed tokens, and those at or past the expert's count read the zero
   // row instead
   auto tr_src = [&](const uint16_t* base, unsigned ld, int stage, int j) {
-    const int t = stage * BK + 2 * NWAVES * j;      // row of this load, less trow0
+    const int t = stage * BK + TPL * NWAVES * j;    // row of this load, less trow0
     // wave-uniform 32 x 32 -> 64 bit product: stays in scalar registers
     const uint16_t* p = base + (unsigned long long)(unsigned)t * ld;
     if constexpr (WG) return t + trow0 < ntok ? p : zsrc;
@@ -917,18 +925,18 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
 
 // The instantiation of run_tile for the tile's row count: a wave's k-th fragment serves the tile
 // rows [32 * WGM * k, 32 * WGM * (k + 1)) together with the other wave rows.
-template <int MODE>
+template <int MODE, typename GEO = BigTile>
 __device__ __forceinline__ void run_tile_rows(const TileArgs& a, const TileRec& rec, unsigned char* lds, int lane,
                                               int w, int* signal) {
-  constexpr int UNIT = 32 * Shape<MODE>::WGM, MF = kBM / UNIT;
+  constexpr int UNIT = 32 * GEO::WGM, MF = GEO::BM / UNIT;
   static_assert(MF == 2 || MF == 4, "two or four token fragments per wave");
   const int nact = (rec.rows + UNIT - 1) / UNIT;
   if constexpr (MF == 4) {
-    if (nact == 4) { run_tile<MODE, 4>(a, rec, lds, lane, w, signal); return; }
-    if (nact == 3) { run_tile<MODE, 3>(a, rec, lds, lane, w, signal); return; }
+    if (nact == 4) { run_tile<MODE, 4, GEO>(a, rec, lds, lane, w, signal); return; }
+    if (nact == 3) { run_tile<MODE, 3, GEO>(a, rec, lds, lane, w, signal); return; }
   }
-  if (nact >= 2) run_tile<MODE, 2>(a, rec, lds, lane, w, signal);
-  else run_tile<MODE, 1>(a, rec, lds, lane, w, signal);
+  if (nact >= 2) run_tile<MODE, 2, GEO>(a, rec, lds, lane, w, signal);
+  else run_tile<MODE, 1, GEO>(a, rec, lds, lane, w, signal);
 }
 
 // Persistent tile kernel: workgroup b serves XCD b % 8.  Its first tile is fixed (range start
@@ -1181,8 +1189,213 @@ __global__ void __launch_bounds__(Shape<M0>::THREADS) ffn_fused_kernel(const Til
 }
 
 // ---------------------------------------------------------------------------------------
+// small tiles: launches that would leave compute units idle with 256 x 256 tiles
+// ---------------------------------------------------------------------------------------
+// Bound by the latency of its operand loads (a workgroup has one token stage and two weight stages on the
+// way, about 1.1 us per stage with the weights coming from HBM), which two workgroups per compute unit and
+// a whole grid of them overlap; a big tile alone on its compute unit cannot.
+// Same tile code, 128 x 128, two workgroups per compute unit, one tile per workgroup; no schedule:
+// a workgroup finds its tile from `offsets` with wave-wide scans, the grid covers the largest possible number
+// of tiles and the workgroups past the last one exit.  The two projections are two launches (the
+// second has nothing to wait for tile by tile, and no counters have to be cleared first); so are the
+// two steps of the backward pass, each with everything that is independent in it.
+// Consecutive workgroups go to the 8 XCDs in turn; eight neighbouring tiles of the list (a few row
+// tiles x a few column tiles of one expert) go to one XCD, where they meet in its L2 (stretches of 32
+// measured the same on many tiles and up to 10 % slower on few).
+constexpr int kSmallChunk = 8;
+__device__ __forceinline__ int small_tile_index(int b) {
+  const int xcd = b % kXcds, q = b / kXcds;
+  return ((q / kSmallChunk) * kXcds + xcd) * kSmallChunk + q % kSmallChunk;
+}
+
+// tile t of the list of a token mode; false if there is none.  The same in every lane; called by whole waves.
+template <int MODE>
+__device__ __forceinline__ bool small_token_tile(const TileArgs& a, int t, int lane, TileRec& rec) {
+  constexpr int BM = SmallTile::BM, NCPT = is_up(MODE) ? SmallTile::BN / 2 : SmallTile::BN;
+  int before = 0;
+  for (int v0 = 0; v0 < a.Ne; v0 += 64) {
+    const int v = v0 + lane;                       // groups by decreasing width: the longest tiles start first
+    const int g = a.order[(v < a.Ne ? v : 0) / a.N], e = g * a.N + (v < a.Ne ? v : 0) % a.N;
+    const int lo = a.offsets[e], cnt = v < a.Ne ? a.offsets[e + 1] - lo : 0;
+    const int nt = ((red_d(MODE) ? a.F[g] : a.d) + NCPT - 1) / NCPT;
+    const int n = (cnt + BM - 1) / BM * nt;
+    int incl = n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int up = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += up;
+    }
+    const int first = before + incl - n;
+    const unsigned long long hit = __ballot(t >= first && t < first + n);
+    if (hit) {
+      const int l = (int)__builtin_ctzll(hit);
+      const int rel = t - __builtin_amdgcn_readlane(first, l), ntv = __builtin_amdgcn_readlane(nt, l);
+      const int c = __builtin_amdgcn_readlane(cnt, l), mt = (c + BM - 1) / BM;
+      // bands of four row tiles; inside a band column tile major, row tile minor
+      constexpr int RB = 4;
+      const int bnd = rel / (RB * ntv), rel2 = rel - bnd * RB * ntv, rb = min(RB, mt - bnd * RB);
+      const int ni = rel2 / rb, mi = bnd * RB + rel2 % rb;
+      rec.e = __builtin_amdgcn_readlane(e, l);
+      rec.row_start = __builtin_amdgcn_readlane(lo, l) + mi * BM;
+      rec.rows = min(BM, c - mi * BM);
+      rec.n0 = ni * NCPT;
+      rec.fam = 0;
+      rec.need = 0;
+      return rec.row_start >= 0 && rec.rows >= 1 && rec.row_start + rec.rows <= a.P;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return false;
+}
+
+// tile t of a weight gradient (the list depends on the layer's shape only)
+__device__ __forceinline__ bool small_wgrad_tile(const TileArgs& a, int t, TileRec& rec) {
+  for (int gi = 0; gi < a.Ng; ++gi) {
+    const int g = a.order[gi];
+    const int mt = (a.Mrows[g] + SmallTile::BM - 1) / SmallTile::BM, nt = (a.Ncols[g] + SmallTile::BN - 1) / SmallTile::BN;
+    if (t < a.N * mt * nt) {
+      const int i = t / (mt * nt), rel = t - i * mt * nt;
+      rec.e = g * a.N + i;
+      rec.row_start = rel / nt * SmallTile::BM;
+      rec.rows = min(SmallTile::BM, a.Mrows[g] - rec.row_start);
+      rec.n0 = rel % nt * SmallTile::BN;
+      rec.fam = 0;
+      rec.need = 0;
+      return a.offsets[rec.e] >= 0 && a.offsets[rec.e + 1] <= a.P && a.offsets[rec.e] <= a.offsets[rec.e + 1];
+    }
+    t -= a.N * mt * nt;
+  }
+  return false;
+}
+
+constexpr int kSmallThreads = 64 * SmallTile::WGM * SmallTile::WGN;
+constexpr int kSmallLds = (kStagesA * SmallTile::BM + kStagesB * SmallTile::BN) * kBK * 2;
+
+template <int MODE>
+__device__ __forceinline__ void small_tile(const TileArgs& a, int b, unsigned char* lds) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  TileRec rec;
+  bool ok;
+  if constexpr (MODE == kWgrad) ok = small_wgrad_tile(a, small_tile_index(b), rec);
+  else ok = small_token_tile<MODE>(a, small_tile_index(b), lane, rec);
+  if (ok) run_tile_rows<MODE, SmallTile>(a, rec, lds, lane, w, nullptr);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_kernel(const TileArgs a) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  // (nothing waits here: the flag that mohge_fused_status reads stays clear)
+  if (MODE == kDown && blockIdx.x == 0 && threadIdx.x == 0) a.hdr->pad[0] = 0;
+  small_tile<MODE>(a, blockIdx.x, lds);
+}
+
+// Backward, first launch: dH, and on the workgroups past its n_dh the rows of x in sorted order and the
+// row of zeros (kSmallGatherRows rows per workgroup, all loads of a wave's rows before the first store).
+constexpr int kSmallGatherRows = 16;
+
+__global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd1_kernel(const TileArgs dh, const GatherArgs ga, int n_dh) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  if ((int)blockIdx.x < n_dh) {
+    small_tile<kDgradH>(dh, blockIdx.x, lds);
+    return;
+  }
+  const int b = blockIdx.x - n_dh, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (b == 0 && threadIdx.x < 32) ga.zero_row[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+  if (ga.perm == nullptr) return;
+  constexpr int R = kSmallGatherRows / 4;
+  const int p0 = b * kSmallGatherRows + w * R;
+  long long src[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) src[i] = (long long)(ga.perm[min(p0 + i, ga.P - 1)] / ga.Ke) * ga.chunks;
+  for (int c = lane; c < ga.chunks; c += 64) {
+    uint4 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = ga.x[src[i] + c];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+      if (p0 + i < ga.P) ga.xs[(long long)(p0 + i) * ga.chunks + c] = v[i];
+  }
+}
+
+// Backward, second launch: dX (the longest reductions first), then both weight gradients
+__global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd2_kernel(const TileArgs dx, const TileArgs w2,
+                                                                          const TileArgs w13, int n_dx, int n_w2) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  const int b = blockIdx.x;
+  if (b == 0 && threadIdx.x == 0) dx.hdr->pad[0] = 0;
+  if (b < n_dx) small_tile<kDgradX>(dx, b, lds);
+  else if (b < n_dx + n_w2) small_tile<kWgrad>(w2, b - n_dx, lds);
+  else small_tile<kWgrad>(w13, b - n_dx - n_w2, lds);
+}
+
+// ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
+// Workgroups of a small-tile list, a multiple of 64 (small_tile_index).  Token modes: the counts are not
+// known here; full row tiles of the widest group plus a partial one per expert that can have rows.
+static int small_grid(const LayerDesc& L, int mode) {
+  const int cp = is_up(mode) ? SmallTile::BN / 2 : SmallTile::BN;
+  long long n = 0, widest = 0;
+  for (int g = 0; g < L.Ng; ++g) {
+    const long long nt = ((red_d(mode) ? L.F[g] : L.d) + cp - 1) / cp;
+    n += nt * L.N;
+    widest = nt > widest ? nt : widest;
+  }
+  if (L.P * widest < n) n = L.P * widest;
+  n += (long long)(L.P / SmallTile::BM) * widest;
+  return (int)((n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk));
+}
+
+static int small_wgrad_grid(const TileArgs& a) {
+  long long n = 0;
+  for (int g = 0; g < a.Ng; ++g)
+    n += (long long)a.N * ((a.Mrows[g] + SmallTile::BM - 1) / SmallTile::BM) * ((a.Ncols[g] + SmallTile::BN - 1) / SmallTile::BN);
+  return (int)((n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk));
+}
+
+template <typename K, typename... Args>
+static hipError_t launch_small(K kern, bool& attr_done, int grid, hipStream_t s, const Args&... args) {
+  if (!attr_done) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSmallThreads), kSmallLds, s, args...);
+  return hipGetLastError();
+}
+
+// Which geometry a bf16 call past decode size takes.  Measured (expert-network calls, schedule included, one
+// MI355X; big -> small, us): below 1.7 big up tiles per compute unit the small form wins because it fills the
+// chip and needs no schedule (1024 wide, 32 experts: 47 -> 30 at 256 tokens, 62 -> 50 at 777, 103 -> 71 at
+// 2048; backward 196 -> 106 at 777, 300 -> 234 at 2500; 2048 wide, 24 experts: 139 -> 103 at 1024), around 1.7
+// the two are even (119 -> 126 at 1.73; 150 -> 146 with 370 -> 368 backward at 2.3), above the big tile's
+// reuse of its operands wins (228 -> 279 at 2.25, backward 698 -> 779 at 3.0).  A forward call of a few rows
+// per expert streams weights either way; there the small form is ahead however many tiles there are
+// (192 -> 176 at 47 rows, 180 -> 165 at 15 rows, 128 experts; 264 -> 252 at 6 rows, d = 2560) except with
+// the longest reductions, where the big tile's deeper prefetch counts (d = 4096: 359 -> 410 at 3 rows,
+// 427 -> 439 at 10).
+bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
+  if (o.small >= 0) return o.small != 0;
+  const int rows = L.P > L.Ne ? L.P / L.Ne : 1;           // per expert if they were spread evenly
+  long long tiles = 0;                                     // big up tiles then
+  for (int g = 0; g < L.Ng; ++g)
+    tiles += (long long)L.N * ((rows + kBM - 1) / kBM) * ((L.F[g] + kBN / 2 - 1) / (kBN / 2));
+  if (10 * tiles < 17 * (long long)tile_num_cus()) return true;
+  return !backward && rows <= 64 && L.d <= 2560;
+}
+
+hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
+                            const TileArgs& w13, const GatherArgs& ga, hipStream_t s) {
+  static bool attr1 = false, attr2 = false;
+  const int n_dh = small_grid(L, kDgradH);
+  const int gather = ga.perm ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
+  hipError_t e = launch_small(ffn_small_bwd1_kernel, attr1, n_dh + gather, s, dh, ga, n_dh);
+  if (e != hipSuccess) return e;
+  const int n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
+  return launch_small(ffn_small_bwd2_kernel, attr2, n_dx + n_w2 + n_w13, s, dx, w2, w13, n_dx, n_w2);
+}
+
 void apply_options(TileArgs& t, const FfnOptions& o) {
   t.band = o.band > 0 ? o.band : 1;
   t.group_major = o.group_major != 0;
@@ -1373,6 +1586,15 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
     t.force_rows = o.tile_rows[st];
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
+  if (parts == 3 && use_small_tiles(L, o, false)) {
+    static bool attr_up = false, attr_save = false, attr_dn = false;
+    hipError_t e = hipSuccess;
+    if (stages & 1)
+      e = pre ? launch_small(ffn_small_kernel<kUpSave>, attr_save, small_grid(L, kUp), s, up)
+              : launch_small(ffn_small_kernel<kUp>, attr_up, small_grid(L, kUp), s, up);
+    if (e == hipSuccess && (stages & 2)) e = launch_small(ffn_small_kernel<kDown>, attr_dn, small_grid(L, kDown), s, dn);
+    return e;
+  }
   // the whole forward in one launch: up and down tiles share the persistent workgroups
   if (stages == 3 && o.fused) {
     up.coherent_out = 1;

@@ -100,6 +100,10 @@ hipError_t launch_tiles(int mode, const TileArgs& a, hipStream_t s);
 // launch.  The schedules must have been built in the same form (`fused`).
 void apply_options(TileArgs& t, const FfnOptions& o);
 size_t tiled_waiting_header_offset(const LayerDesc& L);
+// The 128 x 128 form: whether a call takes it, and the backward products in two launches
+bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward);
+hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
+                            const TileArgs& w13, const GatherArgs& ga, hipStream_t s);
 hipError_t launch_dgrad_pair(const TileArgs& dh, const TileArgs& dx, hipStream_t s);
 hipError_t launch_wgrad_pair(const TileArgs& w2, const TileArgs& w13, hipStream_t s);
 // Largest number of tiles a schedule of `mode` can hold for layer L (sizes the record area).

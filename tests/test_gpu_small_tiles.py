@@ -1,0 +1,59 @@
+"""The 128 x 128 tile form of the bf16 expert networks at the edges of its tiles, forward and backward,
+bit by bit against the 256 x 256 form (both add the products of an output in the same order) and, forward,
+against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from synth import Workload, generate
+
+pytestmark = pytest.mark.gpu
+
+# rows per expert: none, one, around one fragment, one tile, several tiles and one band of four
+COUNTS = [0, 1, 31, 64, 65, 127, 128, 129, 0, 257, 513, 640]
+
+
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448))])
+def test_small_tiles_equal_big_tiles(d, d_ff):
+    import paper_2604_23108_amd as M
+    from paper_2604_23108_amd import bench_binding as BB
+    from gpu_harness import DeviceLayer, to_dev
+    T = sum(COUNTS)                                     # one pair per token: any assignment is possible
+    w = Workload("small_tiles", T=T, d=d, n_groups=2, experts_per_group=6, d_ff=d_ff, k_groups=1, k_experts=1,
+                 seed=43, training=True)
+    inp = generate(w)
+    dl = DeviceLayer(w, inp, backward=True, guard=True)
+    L = dl.layer
+    eidx = np.random.default_rng(5).permutation(np.repeat(np.arange(12), COUNTS)).astype(np.int32).reshape(T, 1)
+    M.mohge_permute(dl.cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None,
+                    L.ws_permute)
+    L.dy_perm.copy_(to_dev(inp.dy, True)[L.perm.long()])
+    outs = []
+    for small in (True, False):
+        for t in [L.y_perm, L.dx_perm, *L.dw13, *L.dw2]:
+            t.fill_(float("nan"))
+        print(f"[small tiles] d={d} d_ff={d_ff} small={small}", flush=True)
+        args = (dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2)
+        if small:
+            M.mohge_expert_ffn(*args, L.y_perm, L.ws_ffn)
+            y = L.y_perm.clone()
+            M.mohge_expert_ffn_train(*args, L.y_perm, L.saved)
+            M.mohge_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd)
+            for call, ws in ((M.CALL_EXPERT_FFN, L.ws_ffn), (M.CALL_FFN_SAVED, L.saved), (M.CALL_EXPERT_FFN_BWD, L.ws_ffn_bwd)):
+                assert M.mohge_fused_status(dl.cfg, call, ws) == 0
+        else:
+            BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn)
+            y = L.y_perm.clone()
+            BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved)
+            BB.mohge_bench_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd)
+        torch.cuda.synchronize()
+        dl.check_guards()
+        outs.append([t.clone().view(torch.int16) for t in [y, L.y_perm, L.dx_perm, *L.dw13, *L.dw2]])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    want = oracle.expert_ffn(w, inp.x.f32, [t.f32 for t in inp.w_gate], [t.f32 for t in inp.w_up],
+                             [t.f32 for t in inp.w_down], np.arange(T, dtype=np.int32), eidx.reshape(-1))
+    got, want = L.y_perm.float().cpu().numpy(), want[L.perm.cpu().numpy()]
+    # h and y are rounded to bf16 once each: 2^-9 of the value and of a sum of such terms
+    assert np.abs(got - want).max() <= 8e-3 * np.abs(want).max()
