@@ -48,10 +48,11 @@ static hipError_t static_scratch(void** out) {
 __global__ void __launch_bounds__(256) permute_hist_kernel(const PermArgs a) {
   __shared__ int hist[kWavesPerBlock][kMaxExperts];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int seg = blockIdx.x * kWavesPerBlock + w;
+  const SegIds ids = load_segment(a, seg, lane);
   for (int e = threadIdx.x; e < kWavesPerBlock * kMaxExperts; e += blockDim.x) (&hist[0][0])[e] = 0;
   __syncthreads();
-  const int seg = blockIdx.x * kWavesPerBlock + w;
-  if (seg < a.nseg) wave_histogram(a, seg, lane, hist[w]);
+  wave_histogram(ids, hist[w]);
   __syncthreads();
   if (seg < a.nseg)
     for (int e = lane; e < a.Ne; e += 64) a.seg_hist[(size_t)seg * a.Ne + e] = hist[w][e];
@@ -100,17 +101,20 @@ __global__ void __launch_bounds__(256) permute_scatter_kernel(const PermArgs a) 
   __shared__ int wtot[4];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int seg = blockIdx.x * kWavesPerBlock + w;
+  const SegIds ids = load_segment(a, seg, lane);
   if constexpr (FUSED) {
     // stage the whole [segment][expert] count matrix in LDS with independent, coalesced
     // loads (one memory round trip), then walk it per expert
     __shared__ int hist[kFusedMaxCells];
     const int cells = a.nseg * a.Ne;
-    for (int i = threadIdx.x; i < cells; i += blockDim.x) hist[i] = a.seg_hist[i];
+#pragma unroll 8
+    for (int i = threadIdx.x; i < cells; i += 256) hist[i] = a.seg_hist[i];
     __syncthreads();
     const int e = threadIdx.x;                      // one expert per thread (Ne <= 256)
     const int seg0 = blockIdx.x * kWavesPerBlock;
     int run = 0, pre[kWavesPerBlock] = {0, 0, 0, 0};
     if (e < a.Ne) {
+#pragma unroll 8
       for (int s = 0; s < a.nseg; ++s) {
 #pragma unroll
         for (int k = 0; k < kWavesPerBlock; ++k)
@@ -143,10 +147,7 @@ __global__ void __launch_bounds__(256) permute_scatter_kernel(const PermArgs a) 
     for (int e = lane; e < a.Ne; e += 64) base[w][e] = a.seg_hist[(size_t)segc * a.Ne + e] + a.offsets[e];
   }
   __syncthreads();
-  // every wave runs the same number of rounds (pairs past P are inactive)
-  PermArgs b = a;
-  if (seg >= a.nseg) b.P = 0;
-  wave_scatter(b, seg, lane, base[w]);
+  wave_scatter(a, ids, seg, lane, base[w]);
 }
 
 __global__ void __launch_bounds__(256) permute_small_kernel(const PermArgs a) {

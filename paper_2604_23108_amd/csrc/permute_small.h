@@ -38,21 +38,34 @@ __device__ __forceinline__ int load_expert(const PermArgs& a, int p) {
   return e < 0 ? 0 : (e >= a.Ne ? a.Ne - 1 : e);
 }
 
-__device__ __forceinline__ void wave_histogram(const PermArgs& a, int seg, int lane, int* hist) {
-  const int p0 = seg * kSegPairs;
-  for (int i = 0; i < kSegPairs; i += 64) {
-    const int p = p0 + i + lane;
-    if (p < a.P) atomicAdd(&hist[load_expert(a, p)], 1);
+// The expert ids of a segment, lane l of register i holds pair seg * kSegPairs + 64 i + l (-1 past
+// the end): all loads in flight at once (a load per step made a walk of eight memory latencies).
+struct SegIds { int e[kSegPairs / 64]; };
+
+__device__ __forceinline__ SegIds load_segment(const PermArgs& a, int seg, int lane) {
+  SegIds s;
+#pragma unroll
+  for (int i = 0; i < kSegPairs / 64; ++i) {
+    const int p = seg * kSegPairs + 64 * i + lane;
+    s.e[i] = (unsigned)p < (unsigned)a.P ? load_expert(a, p) : -1;      // (unsigned: P may be close to 2^31)
   }
+  return s;
+}
+
+__device__ __forceinline__ void wave_histogram(const SegIds& s, int* hist) {
+#pragma unroll
+  for (int i = 0; i < kSegPairs / 64; ++i)
+    if (s.e[i] >= 0) atomicAdd(&hist[s.e[i]], 1);
 }
 
 // base[e] = first free output position for expert e in this segment (LDS, wave private)
-__device__ __forceinline__ void wave_scatter(const PermArgs& a, int seg, int lane, int* base) {
-  const int p0 = seg * kSegPairs;
-  for (int i = 0; i < kSegPairs; i += 64) {
-    const int p = p0 + i + lane;
-    const bool active = p < a.P;
-    const int e = active ? load_expert(a, p) : 0;
+__device__ __forceinline__ void wave_scatter(const PermArgs& a, const SegIds& s, int seg, int lane, int* base) {
+#pragma unroll
+  for (int i = 0; i < kSegPairs / 64; ++i) {
+    const int p = seg * kSegPairs + 64 * i + lane;
+    if ((unsigned)(seg * kSegPairs + 64 * i) >= (unsigned)a.P) break;      // (wave-uniform)
+    const bool active = s.e[i] >= 0;
+    const int e = active ? s.e[i] : 0;
     const unsigned long long m = match_mask(e, a.nbits, active);
     const unsigned long long lt = (1ull << lane) - 1ull;
     int r = 0;
@@ -79,9 +92,10 @@ __device__ __forceinline__ void wave_scatter(const PermArgs& a, int seg, int lan
 // hist: LDS, [kWavesPerBlock][kMaxExperts]; wtot: LDS, [kWavesPerBlock].  Called by all 256 threads.
 __device__ __forceinline__ void permute_small_body(const PermArgs& a, int (*hist)[kMaxExperts], int* wtot) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const SegIds ids = load_segment(a, w, lane);
   for (int e = threadIdx.x; e < kWavesPerBlock * kMaxExperts; e += blockDim.x) (&hist[0][0])[e] = 0;
   __syncthreads();
-  wave_histogram(a, w, lane, hist[w]);
+  wave_histogram(ids, hist[w]);
   __syncthreads();
   // one expert per thread (Ne <= 256): its count over the four segments, then an exclusive scan
   // over the experts (inside the waves by shuffles, across them through LDS)
@@ -114,7 +128,7 @@ __device__ __forceinline__ void permute_small_body(const PermArgs& a, int (*hist
     if (e == a.Ne - 1) a.offsets[a.Ne] = off_e + c;
   }
   __syncthreads();
-  wave_scatter(a, w, lane, hist[w]);
+  wave_scatter(a, ids, w, lane, hist[w]);
 }
 
 }  // namespace mohge

@@ -355,21 +355,31 @@ static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* plan
   return hipGetLastError();
 }
 
-// Second kernel of the split form: a workgroup takes as many tokens as it has waves (phase 2 is
-// one wave per token, and with few tokens its latency is the cost), adds the dsplit partial logit
-// sums of its tokens in index order and runs phase 2.
+// Second kernel of the split form: a workgroup takes four tokens (phase 2 is one wave per token, and with few
+// tokens its latency is the cost), adds the dsplit partial logit sums of its tokens in index order and
+// runs phase 2.  All partial sums of a logit are requested before the first is added: one after the other
+// they were a chain of up to 16 memory latencies, most of the 9 to 14 us this kernel took.
+constexpr int kSplitMax = 16;            // the most partial sums of a logit
+constexpr int kFinishTokens = 4;
+
 __global__ void __launch_bounds__(512) route_finish_kernel(const RouteArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int NW = blockDim.x >> 6;
-  const int BT = NW;
+  constexpr int BT = kFinishTokens;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t0 = blockIdx.x * BT;
   float* lg = reinterpret_cast<float*>(smem + a.region0);         // [BT][NOpad]
   for (int idx = threadIdx.x; idx < BT * a.NO; idx += blockDim.x) {
     const int tl = idx / a.NO, o = idx % a.NO;
     double sum = 0.0;
-    if (t0 + tl < a.T)
-      for (int sp = 0; sp < a.dsplit; ++sp) sum += a.gpart[((size_t)sp * a.T + t0 + tl) * a.NO + o];
+    if (t0 + tl < a.T) {
+      const double* p = a.gpart + (size_t)(t0 + tl) * a.NO + o;
+      double v[kSplitMax];
+#pragma unroll
+      for (int sp = 0; sp < kSplitMax; ++sp) v[sp] = sp < a.dsplit ? p[(size_t)sp * a.T * a.NO] : 0.0;
+#pragma unroll
+      for (int sp = 0; sp < kSplitMax; ++sp) sum += v[sp];
+    }
     lg[tl * a.NOpad + o] = (float)sum;
   }
   __syncthreads();
@@ -403,7 +413,7 @@ static hipError_t launch_tn(const RouteArgs& a, int TN, dim3 grid, dim3 block, s
 
 // Split form: used for at most kSplitMaxT tokens; the workspace holds up to kSplitMax partial
 // sums of every logit.
-constexpr int kSplitMaxT = 256, kSplitMax = 16;
+constexpr int kSplitMaxT = 256;
 constexpr int kPrefillMinT = 8192;       // from here on the bf16 matrix-core form (measured: 96 against
                                          // 190 us at 16384 tokens, even at 8192, slower below)
 
@@ -525,7 +535,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  hipLaunchKernelGGL(route_finish_kernel, dim3((L.T + NW - 1) / NW), block, smem, s, a);
+  hipLaunchKernelGGL(route_finish_kernel, dim3((L.T + kFinishTokens - 1) / kFinishTokens), block, smem, s, a);
   return hipGetLastError();
 }
 
