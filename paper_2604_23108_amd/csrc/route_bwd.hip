@@ -136,24 +136,27 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
 }
 
 // partial sums of dW[z, c] = sum_t dz[t, z] x[t, c] on the fp32 matrix cores
-// (v_mfma_f32_32x32x2_f32: C[32x32] += A[32x2] B[2x32]): grid (ceil(d/256), ceil(Z/32), S).  A
-// workgroup owns 256 columns and 32 rows z for the tokens of one split; its four waves take four
+// (v_mfma_f32_32x32x2_f32: C[32x32] += A[32x2] B[2x32]): grid (ceil(d/128), ceil(Z/32), S).  A
+// workgroup owns 128 columns and 32 rows z for the tokens of one split; its four waves take four
 // neighbouring stretches of them and their sums meet in LDS, added in wave order.  Lane
-// (j = lane%32, k = lane/32) loads dz[t+k, z0+j] (the A operand as it is) and the 8 columns
-// c0 + 8j .. +7 of x[t+k] (one 16-byte load); MFMA m takes element m of every lane's eight, so
-// its 32 B-columns are the tile columns {8j + m}.  A lane ends up with 8 consecutive columns of
-// 16 rows.  Loads run one group of 4 steps ahead of the arithmetic.
-// What bounds it is the chain of 64-clock MFMAs of a wave (8 per two tokens): the work has to be
-// spread.  With a wave per 256 columns that walked all row passes and all tokens of a split alone,
-// 777 tokens of a d = 1024 layer made 13 workgroups and took 43 us (8192 tokens at d = 2048: 36 us).
+// (j = lane%32, k = lane/32) loads dz[t+k, z0+j] (the A operand as it is) and the 4 columns
+// c0 + 4j .. +3 of x[t+k] (one 8-byte load); MFMA m takes element m of every lane's four, so
+// its 32 B-columns are the tile columns {4j + m}.  A lane ends up with 4 consecutive columns of
+// 16 rows.  Loads run one group of 8 steps ahead of the arithmetic.
+// What bounds it is the chain of 64-clock MFMAs of a wave (4 per two tokens) and, over short stretches,
+// memory latency: the work has to be spread, with several waves per SIMD.  With a wave per 256 columns
+// that walked all row passes and all tokens of a split alone, 777 tokens of a d = 1024 layer made 13
+// workgroups and took 43 us; 256 columns per wave also need 280 registers, one wave per SIMD (8192
+// tokens at d = 2048: 36 to 40 us with either split of the tokens).   With 128 columns, 120
+// registers: 9 us and 28 us.
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-constexpr int kZC = 32, kTU = 4, kWGradWaves = 4;
+constexpr int kZC = 32, kTU = 8, kWGradWaves = 4;
 
-__global__ void __launch_bounds__(64 * kWGradWaves) route_bwd_wgrad_kernel(const RouteBwdArgs a) {
-  __shared__ float4 red[(kWGradWaves - 1) * 16 * 64];        // 48 KB: half a wave's sums (4 columns) at a time
+__global__ void __launch_bounds__(64 * kWGradWaves, 3) route_bwd_wgrad_kernel(const RouteBwdArgs a) {
+  __shared__ float4 red[(kWGradWaves - 1) * 16 * 64];        // 48 KB: three workgroups per compute unit
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int j = lane & 31, k = lane >> 5;
-  const int c = blockIdx.x * 256 + 8 * j;
+  const int c = blockIdx.x * 128 + 4 * j;
   const bool col_ok = c < a.d;
   const int cc = col_ok ? c : 0;
   const int s0 = blockIdx.z * a.tok_per_split;
@@ -163,31 +166,31 @@ __global__ void __launch_bounds__(64 * kWGradWaves) route_bwd_wgrad_kernel(const
   const int t0 = min(s1, s0 + w * per_wave), t1 = min(s1, t0 + per_wave);
   const int z0 = blockIdx.y * kZC, zl = z0 + j;
   // step at token t: this lane's token is t + k (dz = 0 past the stretch or past Z)
-  auto load = [&](int t, uint4& xv, float& dzv) {
+  auto load = [&](int t, uint2& xv, float& dzv) {
     const int tok = t + k, tt = min(tok, a.T - 1);
-    xv = *reinterpret_cast<const uint4*>(a.x + (size_t)tt * a.d + cc);
+    xv = *reinterpret_cast<const uint2*>(a.x + (size_t)tt * a.d + cc);
     const float v = a.dz[(size_t)tt * a.Z + min(zl, a.Z - 1)];
     dzv = (tok < t1 && zl < a.Z) ? v : 0.f;
   };
-  f32x16_t acc[8];
+  f32x16_t acc[4];
 #pragma unroll
-  for (int m = 0; m < 8; ++m)
+  for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
-  uint4 xc[kTU];
+  uint2 xc[kTU];
   float dc[kTU];
 #pragma unroll
   for (int i = 0; i < kTU; ++i) load(t0 + 2 * i, xc[i], dc[i]);
   for (int t = t0; t < t1; t += 2 * kTU) {
-    uint4 xn[kTU];
+    uint2 xn[kTU];
     float dn[kTU];
 #pragma unroll
     for (int i = 0; i < kTU; ++i) load(t + 2 * kTU + 2 * i, xn[i], dn[i]);
 #pragma unroll
     for (int i = 0; i < kTU; ++i) {
-      const uint32_t u[4] = {xc[i].x, xc[i].y, xc[i].z, xc[i].w};
+      const uint32_t u[2] = {xc[i].x, xc[i].y};
 #pragma unroll
-      for (int m = 0; m < 8; ++m) {
+      for (int m = 0; m < 4; ++m) {
         const float xf = __uint_as_float((m & 1) ? (u[m >> 1] & 0xffff0000u) : (u[m >> 1] << 16));
         acc[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(dc[i], xf, acc[m], 0, 0, 0);
       }
@@ -195,29 +198,24 @@ __global__ void __launch_bounds__(64 * kWGradWaves) route_bwd_wgrad_kernel(const
 #pragma unroll
     for (int i = 0; i < kTU; ++i) { xc[i] = xn[i]; dc[i] = dn[i]; }
   }
-  // accumulator r of a lane: row 8*(r/4) + 4*k + r%4 of the 32, B-column j.  Columns 0..3 of every
-  // lane's eight meet first, then columns 4..7.
+  // accumulator r of a lane: row 8*(r/4) + 4*k + r%4 of the 32, B-column j
+  if (w > 0)
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    __syncthreads();                                          // (the first half has been read)
-    if (w > 0)
+    for (int r = 0; r < 16; ++r)
+      red[((w - 1) * 16 + r) * 64 + lane] = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+  __syncthreads();
+  if (w == 0 && col_ok) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        red[((w - 1) * 16 + r) * 64 + lane] = make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
-    __syncthreads();
-    if (w == 0 && col_ok) {
+    for (int r = 0; r < 16; ++r) {
+      const int z = z0 + 8 * (r / 4) + 4 * k + (r % 4);
+      if (z < a.Z) {
+        float4 s = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int z = z0 + 8 * (r / 4) + 4 * k + (r % 4);
-        if (z < a.Z) {
-          float4 s = make_float4(acc[4 * h][r], acc[4 * h + 1][r], acc[4 * h + 2][r], acc[4 * h + 3][r]);
-#pragma unroll
-          for (int ww = 0; ww < kWGradWaves - 1; ++ww) {
-            const float4 v = red[(ww * 16 + r) * 64 + lane];
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-          }
-          *reinterpret_cast<float4*>(a.part + ((size_t)blockIdx.z * a.Z + z) * a.d + c + 4 * h) = s;
+        for (int ww = 0; ww < kWGradWaves - 1; ++ww) {
+          const float4 v = red[(ww * 16 + r) * 64 + lane];
+          s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
         }
+        *reinterpret_cast<float4*>(a.part + ((size_t)blockIdx.z * a.Z + z) * a.d + c) = s;
       }
     }
   }
@@ -363,12 +361,12 @@ __global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a,
   }
 }
 
-// token splits of the weight-gradient reduction: enough for two workgroups per compute unit, at least
+// token splits of the weight-gradient reduction: enough for three workgroups per compute unit, at least
 // 32 tokens each (8 per wave: shorter stretches cost more in partial sums than they save in MFMAs), at
 // most 256 splits and at most 64 MB of partial sums
 static int wgrad_splits(const LayerDesc& L) {
-  const long long per_split = (long long)((L.d + 255) / 256) * ((L.Ng + L.Ne + kZC - 1) / kZC);
-  long long s = (512 + per_split - 1) / per_split;
+  const long long per_split = (long long)((L.d + 127) / 128) * ((L.Ng + L.Ne + kZC - 1) / kZC);
+  long long s = (768 + per_split - 1) / per_split;
   if (s > (L.T + 31) / 32) s = (L.T + 31) / 32;
   const long long cap = (64ll << 20) / ((long long)(L.Ng + L.Ne) * L.d * 4);
   if (s > cap) s = cap;
@@ -427,7 +425,7 @@ hipError_t launch_route_bwd(const LayerDesc& L, const mohge_config& cfg, const v
   a.part = reinterpret_cast<float*>(base + dz_bytes);
   hipLaunchKernelGGL(route_bwd_token_kernel, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s, a);
   hipLaunchKernelGGL(route_bwd_wgrad_kernel,
-                     dim3((unsigned)((L.d + 255) / 256), (unsigned)((a.Z + kZC - 1) / kZC), (unsigned)a.S),
+                     dim3((unsigned)((L.d + 127) / 128), (unsigned)((a.Z + kZC - 1) / kZC), (unsigned)a.S),
                      dim3(64 * kWGradWaves), 0, s, a);
   hipLaunchKernelGGL(route_bwd_wsum_kernel, dim3((unsigned)(((size_t)a.Z * L.d / 4 + 31) / 32)), dim3(256), 0, s, a);
   launch_dx(a, s);
