@@ -24,16 +24,10 @@
 
 namespace mohge {
 
-// The grid numbers the experts that have rows (slot = blockIdx.x / ncb), so that a call of a few tokens does
-// not start a workgroup per column block of every idle expert; slots past the last such expert, and
-// columns past a narrower group's, exit.
-template <bool UP>
-__global__ void __launch_bounds__(256, 3) ffn_skinny_kernel(const SkinnyArgs a, const int ncb) {
-  __shared__ f32x4 red[kSplitLdsBytes / 16];
-  const int lane = threadIdx.x & 63;
-  const int slot = blockIdx.x / ncb, c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
-  const int Ne = a.Ng * a.N;
-  int before = 0, e = -1, row0 = 0, cnt = 0;
+// The slot-th expert that has rows; false if there are fewer.  The same in every lane; called by whole waves.
+__device__ __forceinline__ bool expert_of_slot(const SkinnyArgs& a, int slot, int& e, int& row0, int& cnt) {
+  const int lane = threadIdx.x & 63, Ne = a.Ng * a.N;
+  int before = 0;
   for (int e0 = 0; e0 < Ne; e0 += 64) {
     const int ee = e0 + lane < Ne ? e0 + lane : Ne - 1;
     const int lo = a.offsets[ee], n = e0 + lane < Ne ? a.offsets[ee + 1] - lo : 0;
@@ -45,11 +39,22 @@ __global__ void __launch_bounds__(256, 3) ffn_skinny_kernel(const SkinnyArgs a, 
       e = e0 + l;
       row0 = __builtin_amdgcn_readlane(lo, l);
       cnt = __builtin_amdgcn_readlane(n, l);
-      break;
+      return true;
     }
     before += __popcll(has);
   }
-  if (e < 0) return;
+  return false;
+}
+
+// The grid numbers the experts that have rows (slot = blockIdx.x / ncb), so that a call of a few tokens does
+// not start a workgroup per column block of every idle expert; slots past the last such expert, and
+// columns past a narrower group's, exit.
+template <bool UP>
+__global__ void __launch_bounds__(256, 3) ffn_skinny_kernel(const SkinnyArgs a, const int ncb) {
+  __shared__ f32x4 red[kSplitLdsBytes / 16];
+  const int c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
+  int e, row0, cnt;
+  if (!expert_of_slot(a, blockIdx.x / ncb, e, row0, cnt)) return;
   const int g = e / a.N;
   if (c0 >= (UP ? a.F[g] : a.d)) return;
   skinny_unit<UP, false>(a, g, e - g * a.N, c0, row0, cnt, red);
@@ -87,6 +92,166 @@ __device__ __forceinline__ void fp4x8_to_bf16(const uint32_t c, const float scal
   p2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, scale, 2);
   p3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(c, scale, 3);
   o.u = make_uint4(p0.u, p1.u, p2.u, p3.u);
+}
+
+// FP8 weights with the reduction split over the four waves, like the bf16 kernel: a unit of the reduction is
+// 64 bytes of a weight row, lane (r, q) holds 16 codes of its row (two MFMA steps) and reads its token's
+// matching indices straight from L1/L2; weights run one step of four units ahead, tokens 128 indices.
+// Taken where few experts have rows (fp8_split): the staged kernel below then leaves compute units
+// idle or pays its staging for too few rows.  Up + down, staged -> split, us: d = 4096, 64 experts: 53 -> 25 at 1
+// token, 88 -> 72 at 4; d = 1024, 32 experts: 25.8 -> 23.4 at 7, 26.5 -> 24.6 at 32; 128 experts: 38 -> 28 at 4.
+// With many rows the token loads cost more than the staging (d = 4096: 187 -> 204 at 32 tokens), and so they do
+// for MXFP4 weights, whose 16-byte load needs four of them and a byte of scales (55 -> 107 at 7 tokens).
+template <bool UP>
+__global__ void __launch_bounds__(256, 3) ffn_skinny_fp8_split_kernel(const SkinnyArgs a, const int ncb) {
+  constexpr int UK = 64;                      // reduction indices per unit: 64 bytes of a weight row
+  constexpr int LK = UK / 4;                  // ... per lane
+  constexpr int NJ = LK / 8;                  // MFMA steps per unit
+  constexpr int U = 4;                        // units per step
+  constexpr int XG = 128 / UK;                // units whose token fragments are requested together
+  __shared__ f32x4 red[(kSplitWaves - 1) * 2 * 64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, q = lane >> 4;
+  const int c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
+  int e, row0, cnt;
+  if (!expert_of_slot(a, blockIdx.x / ncb, e, row0, cnt)) return;
+  const int g = e / a.N, i = e - g * a.N, F = a.F[g];
+  const int K = UP ? a.d : F;
+  const int ncols = UP ? F : a.d;
+  if (c0 >= ncols) return;
+  long long wrow[2];
+  if constexpr (UP) {
+    wrow[0] = (long long)i * 2 * F + c0 + r;
+    wrow[1] = (long long)i * 2 * F + F + c0 + r;
+  } else {
+    int n1 = c0 + 16 + r;
+    if (n1 > a.d - 1) n1 = a.d - 1;
+    wrow[0] = (long long)i * a.d + c0 + r;
+    wrow[1] = (long long)i * a.d + n1;
+  }
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.W[g]);
+  const uint8_t* wp[2] = {wbase + wrow[0] * K + 16 * q, wbase + wrow[1] * K + 16 * q};
+  const int nu = K / UK;                      // (K is a multiple of 64)
+  const int ub = nu * w / kSplitWaves, ue = nu * (w + 1) / kSplitWaves;
+  auto load_w = [&](uint4 (&wq)[2][U], int u0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        wq[f][u] = make_uint4(0u, 0u, 0u, 0u);
+        if (u0 + u < ue)
+          wq[f][u] = *reinterpret_cast<const uint4*>(wp[f] + (long long)(u0 + u) * 64);
+      }
+  };
+
+  for (int tb0 = 0; tb0 < cnt; tb0 += 16) {
+    uint4 wc[2][U];
+    load_w(wc, ub);
+    const int tt = tb0 + r;
+    const bool xv = tt < cnt;
+    const int pos = row0 + (xv ? tt : 0);
+    long long src;
+    if constexpr (UP) src = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
+    else src = pos;
+    const uint16_t* const xp = a.A + src * a.lda + LK * q;
+    auto load_x = [&](Frag (&xf)[XG][NJ], int u0) {
+#pragma unroll
+      for (int u = 0; u < XG; ++u)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          xf[u][j].u = make_uint4(0u, 0u, 0u, 0u);
+          if (xv && u0 + u < ue)
+            xf[u][j].u = *reinterpret_cast<const uint4*>(xp + (u0 + u) * UK + 8 * j);
+        }
+    };
+    Frag xc[XG][NJ];
+    load_x(xc, ub);
+    f32x4 acc[2];
+    acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int u0 = ub; u0 < ue; u0 += U) {
+      uint4 wn[2][U];
+      load_w(wn, u0 + U);
+#pragma unroll
+      for (int ug = 0; ug < U; ug += XG) {
+        Frag xn[XG][NJ];
+        load_x(xn, u0 + ug + XG);
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+          const int u = ug + x;
+          if (u0 + u < ue) {                  // wave-uniform
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              Frag wlo, whi;
+              fp8x16_to_bf16(wc[f][u], wlo, whi);
+              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, xc[x][0].v, acc[f], 0, 0, 0);
+              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, xc[x][1].v, acc[f], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) xc[x][j] = xn[x][j];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) wc[f][u] = wn[f][u];
+    }
+    if (w > 0)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) red[((w - 1) * 2 + f) * 64 + lane] = acc[f];
+    __syncthreads();
+    if (w == 0) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int ww = 0; ww < kSplitWaves - 1; ++ww) acc[f] += red[(ww * 2 + f) * 64 + lane];
+      // lane holds token r of the pass, weight rows 4q..4q+3 of each row set
+      // FP8: the scale of the weight row of accumulator element b multiplies the sum
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          long long row;
+          if constexpr (UP) row = (long long)i * 2 * F + (long long)f * F + c0 + 4 * q + b;
+          else {
+            int n = c0 + 16 * f + 4 * q + b;
+            if (n > a.d - 1) n = a.d - 1;
+            row = (long long)i * a.d + n;
+          }
+          acc[f][b] *= a.S[g][row];
+        }
+      if (xv) {
+        uint16_t* crow = a.C + (long long)(row0 + tt) * a.ldc;
+        if constexpr (UP) {
+          float v[4];
+#pragma unroll
+          for (int b = 0; b < 4; ++b) {
+            const float gt = acc[0][b], up = acc[1][b];
+            v[b] = gt / (1.f + __expf(-gt)) * up;
+          }
+          uint2 o;
+          o.x = pack_bf16x2(v[0], v[1]);
+          o.y = pack_bf16x2(v[2], v[3]);
+          *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
+        } else {
+#pragma unroll
+          for (int f = 0; f < 2; ++f) {
+            const int col = c0 + 16 * f + 4 * q;
+            if (col < ncols) {
+              uint2 o;
+              o.x = pack_bf16x2(acc[f][0], acc[f][1]);
+              o.y = pack_bf16x2(acc[f][2], acc[f][3]);
+              *reinterpret_cast<uint2*>(crow + col) = o;
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();                          // the sums have been read
+  }
 }
 
 // Quantised-weight variant (BITS = 8: FP8 E4M3, BITS = 4: MXFP4): a workgroup has 128 weight rows, a wave
@@ -491,6 +656,15 @@ void skinny_args(const LayerDesc& L, const void* x, const int32_t* perm, const i
   dn.blk_prefix[kMaxGroups] = nd;
 }
 
+// FP8 weights: the split kernel while a wave per 32 weight rows of the experts that can have rows would be
+// fewer than 1200 waves (not five per compute unit), or fewer than 2500 with at most two rows per expert.
+static bool fp8_split(const LayerDesc& L) {
+  long long f = 0;
+  for (int g = 0; g < L.Ng; ++g) f += L.F[g];
+  const long long waves = (L.P < L.Ne ? L.P : L.Ne) * (f / L.Ng) / 16;
+  return waves < 1200 || (waves < 2500 && L.P <= 2 * L.Ne);
+}
+
 hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* perm,
                              const int32_t* offsets, const GroupPtrs& W, void* y_perm, void* ws,
                              hipStream_t s, int stages, const float* const* s13, const float* const* s2,
@@ -499,20 +673,20 @@ hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* p
   SkinnyArgs up, dn;
   int nu = 0, nd = 0;
   skinny_args(L, x, perm, offsets, W, y_perm, ws, s13, s2, b13, b2, up, dn, nu, nd);
-  if (w4) {
-    if (stages & 1) hipLaunchKernelGGL((ffn_skinny_q_kernel<true, 4>), dim3(nu), dim3(256), 0, s, up);
-    if (stages & 2) hipLaunchKernelGGL((ffn_skinny_q_kernel<false, 4>), dim3(nd), dim3(256), 0, s, dn);
-    return hipGetLastError();
-  }
-  if (w8) {
-    if (stages & 1) hipLaunchKernelGGL((ffn_skinny_q_kernel<true, 8>), dim3(nu), dim3(256), 0, s, up);
-    if (stages & 2) hipLaunchKernelGGL((ffn_skinny_q_kernel<false, 8>), dim3(nd), dim3(256), 0, s, dn);
-    return hipGetLastError();
-  }
   const int slots = L.P < L.Ne ? L.P : L.Ne;
   const int cu = L.Fmax / 16, cd = (L.d + 31) / 32;
-  if (stages & 1) hipLaunchKernelGGL((ffn_skinny_kernel<true>), dim3(slots * cu), dim3(256), 0, s, up, cu);
-  if (stages & 2) hipLaunchKernelGGL((ffn_skinny_kernel<false>), dim3(slots * cd), dim3(256), 0, s, dn, cd);
+  auto launch = [&](auto ku, auto kd) {
+    if (stages & 1) hipLaunchKernelGGL(ku, dim3(slots * cu), dim3(256), 0, s, up, cu);
+    if (stages & 2) hipLaunchKernelGGL(kd, dim3(slots * cd), dim3(256), 0, s, dn, cd);
+  };
+  auto launch_staged = [&](auto ku, auto kd) {
+    if (stages & 1) hipLaunchKernelGGL(ku, dim3(nu), dim3(256), 0, s, up);
+    if (stages & 2) hipLaunchKernelGGL(kd, dim3(nd), dim3(256), 0, s, dn);
+  };
+  if (w4) launch_staged(ffn_skinny_q_kernel<true, 4>, ffn_skinny_q_kernel<false, 4>);
+  else if (w8 && fp8_split(L)) launch(ffn_skinny_fp8_split_kernel<true>, ffn_skinny_fp8_split_kernel<false>);
+  else if (w8) launch_staged(ffn_skinny_q_kernel<true, 8>, ffn_skinny_q_kernel<false, 8>);
+  else launch(ffn_skinny_kernel<true>, ffn_skinny_kernel<false>);
   return hipGetLastError();
 }
 
