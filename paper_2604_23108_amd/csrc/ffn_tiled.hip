@@ -97,13 +97,26 @@ struct Shape {
 // schedule: one workgroup of 256 threads per projection; thread v <-> expert at visiting
 // position v for the per-expert quantities, then threads stride over the tiles
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ long long wave_incl_scan64(long long v, int lane) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const long long up = __shfl_up(v, off, 64);
-    if (lane >= off) v += up;
-  }
+// Inclusive sums over the lanes of a wave in six register steps (row shifts, then the two broadcasts across
+// rows): a shuffle through LDS per step made the scans half of the schedule's arithmetic time.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);      // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);      // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);      // row_shr:8
+  v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
   return v;
+}
+
+// the same for 64-bit values (not negative): three parts of 24 bits, each summed by itself (64 x 2^24 fits an int)
+__device__ __forceinline__ long long wave_incl_scan64(long long v) {
+  const int lo = wave_incl_scan((int)(v & 0xffffff)), mid = wave_incl_scan((int)((v >> 24) & 0xffffff));
+  const int hi = wave_incl_scan((int)(v >> 48));
+  return ((long long)hi << 48) + ((long long)mid << 24) + lo;
 }
 
 struct SchedShared {
@@ -163,13 +176,10 @@ __device__ __forceinline__ int choose_tile_rows(const TileArgs& a, SchedShared& 
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const int h = 256 - 64 * c;
-    long long x = (long long)((cnt + h - 1) / h) * nt * kc;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-    cand[c] = x;
+    cand[c] = wave_incl_scan64((long long)((cnt + h - 1) / h) * nt * kc);      // lane 63: the wave's sum
   }
   __syncthreads();
-  if (lane == 0) { sh.wsum[w][0] = cand[0]; sh.wsum[w][1] = cand[1]; sh.wsum[w][2] = cand[2]; }
+  if (lane == 63) { sh.wsum[w][0] = cand[0]; sh.wsum[w][1] = cand[1]; sh.wsum[w][2] = cand[2]; }
   __syncthreads();
   if (v == 0) {
     long long kmax = 1;
@@ -179,12 +189,12 @@ __device__ __forceinline__ int choose_tile_rows(const TileArgs& a, SchedShared& 
     int best_rows = 256;
     for (int c = 0; c < 3; ++c) {
       const long long tot = sh.wsum[0][c] + sh.wsum[1][c] + sh.wsum[2][c] + sh.wsum[3][c];
-      const long long rounds = (tot + (long long)a.ncu * kmax - 1) / ((long long)a.ncu * kmax);
       // measured: a stage of a tile costs about 1850 + 100 * (rows / 64) clocks (operand traffic
       // and LDS work do not shrink with the tile height), so rounds count more than height
       // (fused launch: the down tiles fill the last round of up tiles, so the up tiles are
       // costed by their total work rather than by whole rounds)
-      const float units = fused ? (float)tot / (float)((long long)a.ncu * kmax) : (float)rounds;
+      const float units = fused ? (float)tot / (float)((long long)a.ncu * kmax)
+                                : (float)((tot + (long long)a.ncu * kmax - 1) / ((long long)a.ncu * kmax));
       const float est = units * ((float)(4 - c) + 18.5f);
       if (c == 0 || est < best) { best = est; best_rows = 256 - 64 * c; }
     }
@@ -215,11 +225,11 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
   }
   sh.e[v] = e; sh.cnt[v] = cnt; sh.nt[v] = nt; sh.kc[v] = kc; sh.row0[v] = row0;
   // exclusive prefix sums of tiles, cost and row blocks over the experts
-  const long long my_t = (long long)((cnt + h - 1) / h) * nt;
+  const int my_t = (cnt + h - 1) / h * nt;
   // cost of a tile = reduction stages x (kTileCost + its 64-row units): measured, a stage of a tile
   // costs about 1850 + 100 * units clocks, so a short tile is almost as expensive as a full one
   const long long my_c = ((long long)kTileCost * ((cnt + h - 1) / h) + (cnt + 63) / 64) * nt * kc;
-  const long long my_f = MODE == kWgrad ? 0 : (cnt + h - 1) / h;
+  const int my_f = MODE == kWgrad ? 0 : (cnt + h - 1) / h;
   // Second list of a fused launch (its tiles wait for tiles of the first): inside every XCD range
   // the tiles of the groups with the shortest reduction go last, everything else keeps its order.
   // The end of a range is then handed out in its smallest pieces (the launch ends when the slowest
@@ -232,9 +242,9 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
     kmax = max(kmax, k);
   }
   const bool short_last = fused && a.short_last && (MODE == kDown || MODE == kDgradX) && kmin < kmax;
-  const long long my_s = (short_last && v < a.Ne && kc == kmin) ? my_t : 0;
-  const long long it = wave_incl_scan64(my_t, lane), ic = wave_incl_scan64(my_c, lane);
-  const long long jf = wave_incl_scan64(my_f, lane), is = wave_incl_scan64(my_s, lane);
+  const int my_s = (short_last && v < a.Ne && kc == kmin) ? my_t : 0;
+  const int it = wave_incl_scan(my_t), jf = wave_incl_scan(my_f), is = wave_incl_scan(my_s);
+  const long long ic = wave_incl_scan64(my_c);
   if (lane == 63) { sh.wsum[w][0] = it; sh.wsum[w][1] = ic; sh.wsum[w][2] = jf; sh.wsum[w][3] = is; }
   __syncthreads();
   long long bt = 0, bc = 0, bf = 0, bs = 0;
@@ -327,11 +337,11 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
     r.fam = sh.fp[ve] + mi;
     // a down tile of the fused forward waits for the up tiles of its row block: one per 128
     // hidden units of the expert's group (F holds the group's width in kDown)
-    // (kDown: F holds the group's width, the up tiles are 128 hidden units wide; kDgradX: F holds
+    // (kDown: the reduction is the group's width, the up tiles are 128 hidden units wide; kDgradX:
     // twice the width, the dH tiles are 256 hidden units wide)
     r.need = !fused ? 0
-             : MODE == kDown ? (a.F[r.e / a.N] + kBN / 2 - 1) / (kBN / 2)
-             : MODE == kDgradX ? (a.F[r.e / a.N] / 2 + kBN - 1) / kBN : 0;
+             : MODE == kDown ? (sh.kc[ve] * kBK + kBN / 2 - 1) / (kBN / 2)
+             : MODE == kDgradX ? (sh.kc[ve] * kBK / 2 + kBN - 1) / kBN : 0;
     int pos = t;
     if (short_last) {
       int x = 0;                                   // the tile's XCD range
@@ -379,7 +389,7 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
 __global__ void __launch_bounds__(256) ffn_schedule_kernel(const TileArgs up, const TileArgs dn, int mask) {
   __shared__ SchedShared sh;
   if (mask == 7) {
-    // four workgroups per list (blockIdx.x = list + 2 * part)
+    // several workgroups per list (blockIdx.x = list + 2 * part)
     const int h = choose_tile_rows<kUp>(up, sh, true);
     const int part = blockIdx.x >> 1, nparts = gridDim.x >> 1;
     if ((blockIdx.x & 1) == 0) build_schedule<kUp>(up, sh, h, true, part, nparts);
@@ -1601,7 +1611,11 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
     // parts: 1 = the tile schedule only, 2 = the product launch only (on a schedule that no
     // launch has consumed yet), 3 = both
     if (parts & 1) {
-      hipLaunchKernelGGL(ffn_schedule_kernel, dim3(8), dim3(256), 0, s, up, dn, 7);
+      // a workgroup per list writes 256 records at a time: about two rounds each (four workgroups took 22 us
+      // for the 8000 tiles of a 16384-token call)
+      long long parts_per_list = max_tiles(L, false) / 512;
+      parts_per_list = parts_per_list < 4 ? 4 : parts_per_list > 32 ? 32 : parts_per_list;
+      hipLaunchKernelGGL(ffn_schedule_kernel, dim3((unsigned)(2 * parts_per_list)), dim3(256), 0, s, up, dn, 7);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
