@@ -460,6 +460,24 @@ __device__ __forceinline__ void async_copy16(const void* gptr, void* lds_uniform
       (__attribute__((address_space(3))) void*)lds_uniform_base, 16, 0, 0);
 }
 
+// The same copy for the modes with transposing LDS reads, as instructions the compiler does not model: in
+// front of a transposing read (an intrinsic) it waits for every modelled copy to LDS, whatever part that
+// copy fills, i.e. for all stages on their way, once per stage.  M0 holds the LDS destination (one wait
+// state before its use).  Both address forms write no register; completion is awaited by the explicit
+// vmcnt waits of the stages, as for the copies above.
+// lds_offset: byte offset in the workgroup's LDS, wave-uniform (the kernels have no static LDS, so the
+// dynamic buffer starts at 0).  Nothing else in these kernels uses M0.
+__device__ __forceinline__ void async_copy16_unmodelled(const void* gptr, int lds_offset) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               ::"v"(gptr), "s"(__builtin_amdgcn_readfirstlane(lds_offset)) : "memory");
+}
+// wave-uniform base, 32-bit byte offset per lane (half the registers).  (Wait states: one between M0 and its
+// use, five if the base registers were written by the vector unit.)
+__device__ __forceinline__ void async_copy16_unmodelled(const void* uniform_base, uint32_t offset, int lds_offset) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
+               ::"v"(offset), "s"(uniform_base), "s"(__builtin_amdgcn_readfirstlane(lds_offset)) : "memory");
+}
+
 #define MOHGE_PIN() __builtin_amdgcn_sched_barrier(0)
 
 // 16-byte store performed at device scope (the sc1 cache policy of a vector store): written
@@ -507,6 +525,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr bool TRA = tr_a(MODE), TRB = tr_b(MODE);   // operand read by transposing LDS reads
   constexpr bool WG = MODE == kWgrad;
   constexpr bool DH = MODE == kDgradH;
+  constexpr bool DG = TRB && !WG;          // the input-gradient modes: both operands as a wave-uniform base and
+                                           // 32-bit offsets (with 64-bit pointers their main loops spilled)
   long long ts[6] = {0, 0, 0, 0, 0, 0};
   PROBE_T(0);
   constexpr int BM = GEO::BM, BN = GEO::BN, BK = kBK;
@@ -548,7 +568,12 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // wave-wide load j fills tile rows (j*NWAVES + w)*RPL .. +RPL-1; lane l fills row l/CH,
   // physical chunk l%CH, which holds logical chunk (l%CH) ^ ((row >> SH) & (CH-1)).
   const int lrow = lane / CH, lpos = lane % CH;
-  const uint16_t* src_a[TRA ? 1 : A_LOADS];
+  const uint16_t* src_a[TRA || DG ? 1 : A_LOADS];
+  uint32_t off_a[DG ? A_LOADS : 1];
+  uint32_t off_b = 0;                             // DG
+  const uint16_t* base_b = nullptr;               // DG
+  // DG: first row of wave-wide load j, and from there the lane's row (at most 7 further: offsets stay small)
+  auto first_row = [&](int j) { return min((j * NWAVES + w) * RPL, rec.rows - 1); };
   const uint16_t* src_b[TRB ? 1 : B_LOADS];
   // Operands stored reduction-index major (rows = reduction index, features contiguous): a part
   // holds 64 reduction rows x BN features, TRB_ROW = 512 (256) bytes a row.  Wave-wide load j fills
@@ -577,11 +602,13 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     } else if constexpr (DH) {
       if (nb > F - 8) nb = F - 8;                 // W_down[e]: [d, F]
       tr_ldb = a.ldw[g];
-      src_b[0] = a.W[g] + ((long long)e_i * a.d + trow0) * a.ldw[g] + nb;
+      base_b = a.W[g] + (long long)e_i * a.d * a.ldw[g];
+      off_b = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
     } else {
       if (nb > a.d - 8) nb = a.d - 8;             // W13[e]: [2F, d]; F holds 2 F_g here
       tr_ldb = a.ldw[g];
-      src_b[0] = a.W[g] + ((long long)e_i * F + trow0) * a.ldw[g] + nb;
+      base_b = a.W[g] + (long long)e_i * F * a.ldw[g];
+      off_b = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
     }
   }
 #pragma unroll
@@ -593,7 +620,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     if constexpr (UP) src_row = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
     else src_row = pos;
     const int chunk = lpos ^ ((row >> SH) & (CH - 1));
-    src_a[j] = a.A + src_row * a.lda + chunk * 8;
+    if constexpr (DG) off_a[j] = ((uint32_t)(rr - first_row(j)) * (uint32_t)a.lda + chunk * 8) * 2u;
+    else src_a[j] = a.A + src_row * a.lda + chunk * 8;
   }
 #pragma unroll
   for (int j = 0; j < (TRB ? 0 : B_LOADS); ++j) {
@@ -685,16 +713,29 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     else return p;
   };
   auto issue_a = [&](int stage, int j) {
+    if constexpr (DG) {
+      const uint16_t* base = a.A + (unsigned long long)(unsigned)(rec.row_start + first_row(j)) * (unsigned)a.lda;
+      async_copy16_unmodelled(base + stage * BK, off_a[j], (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
+      return;
+    }
     const uint16_t* src;
     if constexpr (TRA) src = tr_src(src_a[0], a.lda, stage, j);
     else src = src_a[j] + stage * BK;
-    async_copy16(src, a_part(stage) + j * NWAVES * 1024 + ld_off);
+    if constexpr (TRA || TRB) async_copy16_unmodelled(src, (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
+    else async_copy16(src, a_part(stage) + j * NWAVES * 1024 + ld_off);
   };
   auto issue_b = [&](int stage, int slot, int j) {
+    if constexpr (DG) {
+      const unsigned t = stage * BK + TPL * NWAVES * j;           // row of this load, less trow0
+      async_copy16_unmodelled(base_b + (unsigned long long)t * tr_ldb, off_b,
+                              (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
+      return;
+    }
     const uint16_t* src;
     if constexpr (TRB) src = tr_src(src_b[0], tr_ldb, stage, j);
     else src = src_b[j] + stage * BK;
-    async_copy16(src, b_part(slot) + j * NWAVES * 1024 + ld_off);
+    if constexpr (TRA || TRB) async_copy16_unmodelled(src, (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
+    else async_copy16(src, b_part(slot) + j * NWAVES * 1024 + ld_off);
   };
 
   // prologue: request B(0), A(0), B(1), A(1), B(2) (those that exist), wait for the first
