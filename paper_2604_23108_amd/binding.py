@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from types import SimpleNamespace
 from typing import List, Optional, Sequence
 
 import torch
@@ -27,6 +28,16 @@ EXPORTS = ["mohge_route", "mohge_permute", "mohge_permute_static", "mohge_expert
            "mohge_expert_ffn_bwd", "mohge_route_bwd", "mohge_shared_routing", "mohge_combine_add",
            "mohge_decode_layer", "mohge_decode_layer_ctl_bytes",
            "mohge_workspace_size", "mohge_last_error"]
+
+# Argument kinds of the calls a layer makes on every pass (P pointer, Z size_t): with them declared,
+# addresses are handed over as plain integers.  Pointers as ctypes objects, the full stream object and a second walk
+# over the weight lists made the host the limit of small calls (a 64-token fp32 layer: 42 us of host work per pass
+# for 30 us on the GPU).
+_LAYER_ARGS = {"mohge_route": "P" * 11 + "ZP", "mohge_permute": "P" * 9 + "ZP", "mohge_expert_ffn": "P" * 8 + "ZP",
+               "mohge_expert_ffn_w8": "P" * 10 + "ZP", "mohge_expert_ffn_w4": "P" * 10 + "ZP",
+               "mohge_expert_ffn_train": "P" * 8 + "ZP", "mohge_expert_ffn_bwd": "P" * 12 + "ZP",
+               "mohge_combine": "P" * 6, "mohge_combine_add": "P" * 7, "mohge_combine_bwd": "P" * 8,
+               "mohge_aux_loss": "P" * 8 + "ZP", "mohge_route_bwd": "P" * 18 + "ZP", "mohge_decode_layer": "P" * 12 + "ZP"}
 
 _SIZE_RETURNS = ("mohge_workspace_size", "mohge_decode_layer_ctl_bytes")
 
@@ -63,6 +74,23 @@ def lib():
         l.mohge_last_error.restype = C.c_char_p
         _lib = l
     return _lib
+
+
+_calls = None
+
+
+def _layer_calls():
+    """The functions of _LAYER_ARGS with their argument types declared (objects of their own: lib()'s stay as they are)."""
+    global _calls
+    if _calls is None:
+        c = SimpleNamespace()
+        for n, kinds in _LAYER_ARGS.items():
+            f = lib()[n]
+            f.restype = C.c_int
+            f.argtypes = [C.c_void_p if k == "P" else C.c_size_t for k in kinds]
+            setattr(c, n, f)
+        _calls = c
+    return _calls
 
 
 class Config:
@@ -125,7 +153,37 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_raw_stream())
+
+
+def _addr(t: Optional[torch.Tensor]) -> Optional[int]:
+    """Address of a tensor handed to one of _LAYER_ARGS, with the checks of _ptr."""
+    if t is None:
+        return None
+    if not t.is_cuda:
+        raise MohgeError("tensors handed to the library must be on the GPU")
+    if not t.is_contiguous():
+        raise MohgeError("tensors handed to the library must be contiguous")
+    return t.data_ptr()
+
+
+def _addr_table(ts: Sequence[torch.Tensor]):
+    return (C.c_void_p * len(ts))(*[_addr(t) for t in ts])
+
+
+def _size(t: torch.Tensor) -> int:
+    return t.numel() * t.element_size()
+
+
+# the current stream of the current device as its handle (torch.cuda.current_stream() builds a Python object around
+# it: 3 us a call)
+_raw_handle = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _raw_stream() -> int:
+    if _raw_handle is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_handle(torch.cuda.current_device())
 
 
 def mohge_workspace_size(cfg: Config, which_call: int) -> int:
@@ -134,17 +192,17 @@ def mohge_workspace_size(cfg: Config, which_call: int) -> int:
 
 def mohge_route(cfg, x, w_group, w_expert, expert_logit_bias, group_idx, expert_idx, gates,
                 gs_out=None, es1_out=None, workspace=None):
-    _check(lib().mohge_route(cfg.ref(), _ptr(x), _ptr(w_group), _ptr(w_expert),
-                             _ptr(expert_logit_bias), _ptr(group_idx), _ptr(expert_idx),
-                             _ptr(gates), _ptr(gs_out), _ptr(es1_out), _ptr(workspace),
-                             _nbytes(workspace) if workspace is not None else C.c_size_t(0), _stream()),
+    _check(_layer_calls().mohge_route(cfg.ref(), _addr(x), _addr(w_group), _addr(w_expert),
+                                      _addr(expert_logit_bias), _addr(group_idx), _addr(expert_idx),
+                                      _addr(gates), _addr(gs_out), _addr(es1_out), _addr(workspace),
+                                      _size(workspace) if workspace is not None else 0, _raw_stream()),
            "mohge_route")
 
 
 def mohge_permute(cfg, expert_idx, counts, offsets, perm, inv_perm, x, x_perm, workspace):
-    _check(lib().mohge_permute(cfg.ref(), _ptr(expert_idx), _ptr(counts), _ptr(offsets), _ptr(perm),
-                               _ptr(inv_perm), _ptr(x), _ptr(x_perm), _ptr(workspace),
-                               C.c_size_t(workspace.numel() * workspace.element_size()), _stream()),
+    _check(_layer_calls().mohge_permute(cfg.ref(), _addr(expert_idx), _addr(counts), _addr(offsets), _addr(perm),
+                                        _addr(inv_perm), _addr(x), _addr(x_perm), _addr(workspace),
+                                        _size(workspace), _raw_stream()),
            "mohge_permute")
 
 
@@ -160,12 +218,9 @@ def _ptr_table(ts: Sequence[torch.Tensor]):
 
 def mohge_expert_ffn(cfg, x, perm, offsets, w13: Sequence[torch.Tensor], w2: Sequence[torch.Tensor],
                      y_perm, workspace):
-    for t in list(w13) + list(w2):
-        _ptr(t)
-    _check(lib().mohge_expert_ffn(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13),
-                                  _ptr_table(w2), _ptr(y_perm), _ptr(workspace),
-                                  C.c_size_t(workspace.numel() * workspace.element_size()),
-                                  _stream()), "mohge_expert_ffn")
+    _check(_layer_calls().mohge_expert_ffn(cfg.ref(), _addr(x), _addr(perm), _addr(offsets), _addr_table(w13),
+                                           _addr_table(w2), _addr(y_perm), _addr(workspace),
+                                           _size(workspace), _raw_stream()), "mohge_expert_ffn")
 
 
 def mohge_fused_status(cfg, which_call: int, workspace) -> int:
@@ -179,11 +234,9 @@ def mohge_fused_status(cfg, which_call: int, workspace) -> int:
 
 def mohge_decode_layer(cfg, x, w_group, w_expert, expert_logit_bias, w13, w2, group_idx, expert_idx, gates, y,
                        workspace):
-    for t in list(w13) + list(w2):
-        _ptr(t)
-    _check(lib().mohge_decode_layer(cfg.ref(), _ptr(x), _ptr(w_group), _ptr(w_expert), _ptr(expert_logit_bias),
-                                    _ptr_table(w13), _ptr_table(w2), _ptr(group_idx), _ptr(expert_idx),
-                                    _ptr(gates), _ptr(y), _ptr(workspace), _nbytes(workspace), _stream()),
+    _check(_layer_calls().mohge_decode_layer(cfg.ref(), _addr(x), _addr(w_group), _addr(w_expert), _addr(expert_logit_bias),
+                                             _addr_table(w13), _addr_table(w2), _addr(group_idx), _addr(expert_idx),
+                                             _addr(gates), _addr(y), _addr(workspace), _size(workspace), _raw_stream()),
            "mohge_decode_layer")
 
 
@@ -192,11 +245,9 @@ def mohge_decode_layer_ctl_bytes(cfg: Config) -> int:
 
 
 def mohge_expert_ffn_w8(cfg, x, perm, offsets, w13q, w13_scale, w2q, w2_scale, y_perm, workspace):
-    for t in list(w13q) + list(w13_scale) + list(w2q) + list(w2_scale):
-        _ptr(t)
-    _check(lib().mohge_expert_ffn_w8(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13q),
-                                     _ptr_table(w13_scale), _ptr_table(w2q), _ptr_table(w2_scale),
-                                     _ptr(y_perm), _ptr(workspace), _nbytes(workspace), _stream()),
+    _check(_layer_calls().mohge_expert_ffn_w8(cfg.ref(), _addr(x), _addr(perm), _addr(offsets), _addr_table(w13q),
+                                              _addr_table(w13_scale), _addr_table(w2q), _addr_table(w2_scale),
+                                              _addr(y_perm), _addr(workspace), _size(workspace), _raw_stream()),
            "mohge_expert_ffn_w8")
 
 
@@ -206,11 +257,9 @@ def mohge_fp8_decode(codes: torch.Tensor, out: torch.Tensor):
 
 
 def mohge_expert_ffn_w4(cfg, x, perm, offsets, w13q, w13_scale, w2q, w2_scale, y_perm, workspace):
-    for t in list(w13q) + list(w13_scale) + list(w2q) + list(w2_scale):
-        _ptr(t)
-    _check(lib().mohge_expert_ffn_w4(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13q),
-                                     _ptr_table(w13_scale), _ptr_table(w2q), _ptr_table(w2_scale),
-                                     _ptr(y_perm), _ptr(workspace), _nbytes(workspace), _stream()),
+    _check(_layer_calls().mohge_expert_ffn_w4(cfg.ref(), _addr(x), _addr(perm), _addr(offsets), _addr_table(w13q),
+                                              _addr_table(w13_scale), _addr_table(w2q), _addr_table(w2_scale),
+                                              _addr(y_perm), _addr(workspace), _size(workspace), _raw_stream()),
            "mohge_expert_ffn_w4")
 
 
@@ -235,13 +284,13 @@ def mohge_expert_ffn_down(cfg, h, offsets, w2: Sequence[torch.Tensor], y_perm):
 
 
 def mohge_combine(cfg, y_perm, inv_perm, gates, y):
-    _check(lib().mohge_combine(cfg.ref(), _ptr(y_perm), _ptr(inv_perm), _ptr(gates), _ptr(y),
-                               _stream()), "mohge_combine")
+    _check(_layer_calls().mohge_combine(cfg.ref(), _addr(y_perm), _addr(inv_perm), _addr(gates), _addr(y),
+                                        _raw_stream()), "mohge_combine")
 
 
 def mohge_combine_add(cfg, y_perm, inv_perm, gates, y_add, y):
-    _check(lib().mohge_combine_add(cfg.ref(), _ptr(y_perm), _ptr(inv_perm), _ptr(gates), _ptr(y_add),
-                                   _ptr(y), _stream()), "mohge_combine_add")
+    _check(_layer_calls().mohge_combine_add(cfg.ref(), _addr(y_perm), _addr(inv_perm), _addr(gates), _addr(y_add),
+                                            _addr(y), _raw_stream()), "mohge_combine_add")
 
 
 def mohge_shared_routing(cfg, expert_idx, gates, counts, offsets, perm, inv_perm):
@@ -251,10 +300,9 @@ def mohge_shared_routing(cfg, expert_idx, gates, counts, offsets, perm, inv_perm
 
 
 def mohge_aux_loss(cfg, gs, es1, group_idx, expert_idx, losses, stats, workspace):
-    _check(lib().mohge_aux_loss(cfg.ref(), _ptr(gs), _ptr(es1), _ptr(group_idx), _ptr(expert_idx),
-                                _ptr(losses), _ptr(stats), _ptr(workspace),
-                                C.c_size_t(workspace.numel() * workspace.element_size()),
-                                _stream()), "mohge_aux_loss")
+    _check(_layer_calls().mohge_aux_loss(cfg.ref(), _addr(gs), _addr(es1), _addr(group_idx), _addr(expert_idx),
+                                         _addr(losses), _addr(stats), _addr(workspace),
+                                         _size(workspace), _raw_stream()), "mohge_aux_loss")
 
 
 def _nbytes(t: torch.Tensor):
@@ -262,35 +310,31 @@ def _nbytes(t: torch.Tensor):
 
 
 def mohge_expert_ffn_train(cfg, x, perm, offsets, w13, w2, y_perm, saved):
-    for t in list(w13) + list(w2):
-        _ptr(t)
-    _check(lib().mohge_expert_ffn_train(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13),
-                                        _ptr_table(w2), _ptr(y_perm), _ptr(saved), _nbytes(saved),
-                                        _stream()), "mohge_expert_ffn_train")
+    _check(_layer_calls().mohge_expert_ffn_train(cfg.ref(), _addr(x), _addr(perm), _addr(offsets), _addr_table(w13),
+                                                 _addr_table(w2), _addr(y_perm), _addr(saved), _size(saved),
+                                                 _raw_stream()), "mohge_expert_ffn_train")
 
 
 def mohge_combine_bwd(cfg, dy, y_perm, inv_perm, gates, dgates, dy_perm):
-    _check(lib().mohge_combine_bwd(cfg.ref(), _ptr(dy), _ptr(y_perm), _ptr(inv_perm), _ptr(gates),
-                                   _ptr(dgates), _ptr(dy_perm), _stream()), "mohge_combine_bwd")
+    _check(_layer_calls().mohge_combine_bwd(cfg.ref(), _addr(dy), _addr(y_perm), _addr(inv_perm), _addr(gates),
+                                            _addr(dgates), _addr(dy_perm), _raw_stream()), "mohge_combine_bwd")
 
 
 def mohge_expert_ffn_bwd(cfg, x, perm, offsets, w13, w2, saved, dy_perm, dx_perm, dw13, dw2,
                          workspace):
-    for t in list(w13) + list(w2) + list(dw13) + list(dw2):
-        _ptr(t)
-    _check(lib().mohge_expert_ffn_bwd(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13),
-                                      _ptr_table(w2), _ptr(saved), _ptr(dy_perm), _ptr(dx_perm),
-                                      _ptr_table(dw13), _ptr_table(dw2), _ptr(workspace),
-                                      _nbytes(workspace), _stream()), "mohge_expert_ffn_bwd")
+    _check(_layer_calls().mohge_expert_ffn_bwd(cfg.ref(), _addr(x), _addr(perm), _addr(offsets), _addr_table(w13),
+                                               _addr_table(w2), _addr(saved), _addr(dy_perm), _addr(dx_perm),
+                                               _addr_table(dw13), _addr_table(dw2), _addr(workspace),
+                                               _size(workspace), _raw_stream()), "mohge_expert_ffn_bwd")
 
 
 def mohge_route_bwd(cfg, x, w_group, w_expert, gs, es1, group_idx, expert_idx, gates, dgates, stats,
                     dx_perm, inv_perm, dx, dw_group, dw_expert, dz_out, workspace):
-    _check(lib().mohge_route_bwd(cfg.ref(), _ptr(x), _ptr(w_group), _ptr(w_expert), _ptr(gs), _ptr(es1),
-                                 _ptr(group_idx), _ptr(expert_idx), _ptr(gates), _ptr(dgates),
-                                 _ptr(stats), _ptr(dx_perm), _ptr(inv_perm), _ptr(dx), _ptr(dw_group),
-                                 _ptr(dw_expert), _ptr(dz_out), _ptr(workspace), _nbytes(workspace),
-                                 _stream()), "mohge_route_bwd")
+    _check(_layer_calls().mohge_route_bwd(cfg.ref(), _addr(x), _addr(w_group), _addr(w_expert), _addr(gs), _addr(es1),
+                                          _addr(group_idx), _addr(expert_idx), _addr(gates), _addr(dgates),
+                                          _addr(stats), _addr(dx_perm), _addr(inv_perm), _addr(dx), _addr(dw_group),
+                                          _addr(dw_expert), _addr(dz_out), _addr(workspace), _size(workspace),
+                                          _raw_stream()), "mohge_route_bwd")
 
 
 def pack_w13(w_gate: torch.Tensor, w_up: torch.Tensor) -> torch.Tensor:
