@@ -411,9 +411,20 @@ static hipError_t launch_tn(const RouteArgs& a, int TN, dim3 grid, dim3 block, s
   }
 }
 
-// Split form: used for at most kSplitMaxT tokens; the workspace holds up to kSplitMax partial
-// sums of every logit.
-constexpr int kSplitMaxT = 256;
+// Split form: used for at most kSplitMaxT tokens; the workspace holds split_most() (up to 256 tokens
+// kSplitMax) partial sums of every logit.  (Above 2048 tokens every
+// second compute unit has a workgroup, and two kernels without a split took 28 us where one took 23: 4096
+// tokens, d = 2048.)
+constexpr int kSplitMaxT = 2048;
+
+// The most workgroups along d for T tokens: a power of two that keeps the launch within one workgroup per
+// compute unit (half of that for decode-sized calls, whose second kernel pays for every partial sum).
+static int split_most(int T) {
+  const int blocks = (T + 15) / 16, room = T <= 256 ? 128 : 256;
+  int ds = 1;
+  while (ds * 2 <= kSplitMax && blocks * ds * 2 <= room) ds *= 2;
+  return ds;
+}
 constexpr int kPrefillMinT = 8192;       // from here on the bf16 matrix-core form (measured: 96 against
                                          // 190 us at 16384 tokens, even at 8192, slower below)
 
@@ -441,7 +452,8 @@ size_t route_workspace_bytes(const LayerDesc& L, int dtype) {
     return (3 * rows * L.d * sizeof(uint16_t) + 255) / 256 * 256;
   }
   if (L.T > kSplitMaxT) return 0;
-  return ((size_t)kSplitMax * (L.T > 0 ? L.T : 1) * (L.Ng + L.Ne) * sizeof(double) + 255) / 256 * 256;
+  const int most = L.T <= 256 ? kSplitMax : split_most(L.T);
+  return ((size_t)most * (L.T > 0 ? L.T : 1) * (L.Ng + L.Ne) * sizeof(double) + 255) / 256 * 256;
 }
 
 hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const float* w_group,
@@ -459,15 +471,13 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   const int NW = (L.d % 256 == 0) ? 8 : (L.d % 128 == 0) ? 4 : 2;
   a.kslice = L.d / NW;
   // few tokens: split the reduction over more workgroups (a slice stays a whole number of
-  // 32-element steps) until there are about 128 of them
+  // 32-element steps)
   a.dsplit = 1;
   a.gpart = nullptr;
   if (ws && L.T <= kSplitMaxT && ws_bytes >= route_workspace_bytes(L, dtype)) {
-    const int blocks = (L.T + 15) / 16;
+    const int most = split_most(L.T);
     int ds = 1;
-    while (ds * 2 <= kSplitMax && blocks * ds * 2 <= 128 && (a.kslice / (ds * 2)) % 32 == 0 &&
-           a.kslice / (ds * 2) >= 32)
-      ds *= 2;
+    while (ds * 2 <= most && (a.kslice / (ds * 2)) % 32 == 0 && a.kslice / (ds * 2) >= 32) ds *= 2;
     if (ds > 1) {
       a.dsplit = ds;
       a.kslice /= ds;
@@ -535,6 +545,9 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
     if (e != hipSuccess) return e;
     attr_done = true;
   }
+  // (its own LDS: the first kernel's partial totals would leave room for one workgroup per compute unit)
+  a.region0 = (int)((size_t)NW * 5 * a.Nepad * sizeof(float));
+  smem = (size_t)a.region0 + (size_t)kFinishTokens * a.NOpad * sizeof(float);
   hipLaunchKernelGGL(route_finish_kernel, dim3((L.T + kFinishTokens - 1) / kFinishTokens), block, smem, s, a);
   return hipGetLastError();
 }

@@ -147,7 +147,7 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
 // memory latency: the work has to be spread, with several waves per SIMD.  With a wave per 256 columns
 // that walked all row passes and all tokens of a split alone, 777 tokens of a d = 1024 layer made 13
 // workgroups and took 43 us; 256 columns per wave also need 280 registers, one wave per SIMD (8192
-// tokens at d = 2048: 36 to 40 us with either split of the tokens).   With 128 columns, 120
+// tokens at d = 2048: 36 to 40 us with either split of the tokens).  With 128 columns, 120
 // registers: 9 us and 28 us.
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kZC = 32, kTU = 8, kWGradWaves = 4;
