@@ -45,10 +45,10 @@
 // chunks swizzled by the row), and its MFMA fragments are read with ds_read_b64_tr_b16, which
 // hands every lane four consecutive reduction indices of one feature.  No operand is
 // transposed in memory.  The ragged reduction of the weight gradients needs no padding
-// either: rows past the expert's last token are fetched from a row of zeros.  The
-// transposing read moves fewer bytes per clock than the 128-bit read (measured about 0.75x),
-// which costs these modes 15-20 % against a hypothetical pre-transposed operand; writing and
-// re-reading the transposed copies cost more than that.
+// either: rows past the expert's last token are fetched from a row of zeros.  These modes
+// run within 10 % of the forward's rate (8192 tokens, 24 experts, 412 GFLOP each: forward 409 us,
+// input gradients 446, weight gradients 423; 533 and 481 while the compiler made every stage
+// wait for the copies just requested, see async_copy16_unmodelled).
 #include <type_traits>
 
 #include "common.h"
@@ -1242,9 +1242,11 @@ __global__ void __launch_bounds__(Shape<M0>::THREADS) ffn_fused_kernel(const Til
 // ---------------------------------------------------------------------------------------
 // small tiles: launches that would leave compute units idle with 256 x 256 tiles
 // ---------------------------------------------------------------------------------------
-// Bound by the latency of its operand loads (a workgroup has one token stage and two weight stages on the
-// way, about 1.1 us per stage with the weights coming from HBM), which two workgroups per compute unit and
-// a whole grid of them overlap; a big tile alone on its compute unit cannot.
+// Bound by what the compute units draw from L2 and the last-level cache, twice the bytes per FLOP of a big tile:
+// a stage of both workgroups of a unit takes about 1.1 us, 15 TB/s over the chip.  More stages on the way do not
+// help (operands through registers, three stages ahead: 50 -> 65 us for 777 tokens of a 1024-wide layer, 107 ->
+// 140 for 64 experts x 144 rows; one 256 x 128 tile per unit with all of the LDS: 107 -> 135); what helps is
+// that one workgroup's prologue and epilogue run under the other's stages.
 // Same tile code, 128 x 128, two workgroups per compute unit, one tile per workgroup; no schedule:
 // a workgroup finds its tile from `offsets` with wave-wide scans, the grid covers the largest possible number
 // of tiles and the workgroups past the last one exit.  The two projections are two launches (the
@@ -1418,10 +1420,10 @@ static hipError_t launch_small(K kern, bool& attr_done, int grid, hipStream_t s,
 
 // Which geometry a bf16 call past decode size takes.  Measured (expert-network calls, schedule included, one
 // MI355X; big -> small, us): below 1.7 big up tiles per compute unit the small form wins because it fills the
-// chip and needs no schedule (1024 wide, 32 experts: 47 -> 30 at 256 tokens, 62 -> 50 at 777, 103 -> 71 at
-// 2048; backward 196 -> 106 at 777, 300 -> 234 at 2500; 2048 wide, 24 experts: 139 -> 103 at 1024), around 1.7
-// the two are even (119 -> 126 at 1.73; 150 -> 146 with 370 -> 368 backward at 2.3), above the big tile's
-// reuse of its operands wins (228 -> 279 at 2.25, backward 698 -> 779 at 3.0).  A forward call of a few rows
+// chip and needs no schedule (1024 wide, 32 experts: 47 -> 30 at 256 tokens, 62 -> 50 at 777, 115 -> 88 at
+// 2500; backward 138 -> 94 at 777, 230 -> 206 at 2500; 2048 wide, 24 experts: 139 -> 103 at 1024), around 1.75
+// the two are even (124 -> 124 with 268 -> 265 backward, 146 -> 149 with 315 -> 323), above the big tile's
+// reuse of its operands wins (228 -> 279 at 2.25).  A forward call of a few rows
 // per expert streams weights either way; there the small form is ahead however many tiles there are
 // (192 -> 176 at 47 rows, 180 -> 165 at 15 rows, 128 experts; 264 -> 252 at 6 rows, d = 2560) except with
 // the longest reductions, where the big tile's deeper prefetch counts (d = 4096: 359 -> 410 at 3 rows,
