@@ -1,5 +1,5 @@
-"""The fp32 expert networks at the edges of their tiles (64 token rows in fragments of 32, 128 weight
-rows, 32-deep stages), on a hand-made assignment of tokens to experts, against the CPU oracle."""
+"""The fp32 expert networks at the edges of their tiles (32 token rows, 64 weight rows, 64-deep
+stages), on a hand-made assignment of tokens to experts, against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,7 @@ from synth import Workload, generate
 
 pytestmark = pytest.mark.gpu
 
-# rows per expert: none, one, around one and two fragments, around one and several tiles
+# rows per expert: none, one, around one, two and several tiles
 COUNTS = [0, 1, 31, 32, 33, 63, 64, 65, 97, 130, 0, 200]
 
 
