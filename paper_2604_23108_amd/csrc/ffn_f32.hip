@@ -9,17 +9,24 @@
 // tiles.  Four waves: two weight fragments x two halves of every stage's reduction indices, which
 // meet in LDS at the end.
 // Measured on 512 tokens, d = 1024, 32 experts of width 256..896, six per token (10.9 GFLOP): the call
-// takes 165 us (66 TFLOP/s of a possible 154; 64-row tiles 180: whole tiles divide worse over the
-// compute units), the one-wave-per-output dot products that this replaced 1.68 ms.  At 4096 tokens of a
-// d = 2048 layer it runs at 97 TFLOP/s (64-row tiles 103).
+// takes 200 us (54 TFLOP/s of a possible 154; 179 with its sums in fp32 alone, see below), the one-wave-per-output
+// dot products that this replaced 1.42 ms.  At 4096 tokens of a d = 2048 layer it runs at 84 TFLOP/s.
+// (With fp32 sums, 64-row tiles were 8 % slower on the first, whose whole tiles divide worse over the compute units,
+// and 6 % faster on the second.)
 //
 // Operands go global -> LDS (global_load_lds, 256-byte row segments, 16-byte pieces XOR-swizzled by
 // the row) through two stages of 64 reduction indices (48 KB: three workgroups per compute unit), one
 // barrier per stage; the fragments of a stage are in registers while the next but one is on its way.
 // A lane's 128-bit fragment read holds four consecutive reduction indices of one row and feeds four
-// MFMAs; both operands use the same assignment.  The fp32 accumulators are folded into a second fp32
-// set every 64 reduction indices, which keeps the rounding error at that of short sums (measured
-// against float64: 2e-7, like a sum spread over 64 lanes).
+// MFMAs; both operands use the same assignment.
+//
+// Every product of an MFMA rounds the running sum, so a chain of n products carries about n/2 roundings.  A chain
+// here is the eight products of one such group; the sums of two groups are added, and the pairs go into an fp64
+// total that is rounded once: 6.5 roundings for any length of the reduction.  The conversions and fp64 additions of
+// a pair run under the MFMAs of the next one (left to the compiler they follow them, 12 % more time).
+// Error of the two projections against float64 (2-norm): 1.21e-7 at 64 indices, 1.25e-7 at 4096; with fp32 chains of
+// 64 in a second fp32 set it was 2.1e-7 and 3.1e-7, with the dot products (a sum spread over 64 lanes, then a
+// butterfly) 1.26e-7 and 2.6e-7.
 //
 // No schedule launch: a workgroup finds the expert of its row tile from `offsets` with a wave-wide
 // scan.  The grid covers the largest possible number of row tiles; the ones that do not exist exit.
@@ -50,7 +57,6 @@ constexpr int kFStages = 2;
 constexpr int kFChunks = kFK / 4;                      // 16-byte pieces of a stage row
 constexpr int kFLoads = (kFM + kFN) * kFChunks / (64 * kFW);   // loads per thread and stage
 constexpr int kFKW = 2 * kFK / kFW;                    // reduction indices of a stage per wave
-constexpr int kFFold = 64 / kFKW;                      // stages between folds: 64 reduction indices of a wave
 
 __device__ __forceinline__ void f32_copy16(const float* g, unsigned char* lds_uniform_base) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
@@ -129,7 +135,7 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
   for (int kt = 0; kt < kFStages; ++kt)
     if (kt < KT) issue(kt);
 
-  // wave: weight fragment wn (32 rows), and of every stage the reduction indices [16 kq, 16 kq + 16)
+  // wave: weight fragment wn (32 rows), and of every stage the reduction indices [kFKW kq, kFKW kq + kFKW)
   const int wn = w & 1, kq = w >> 1;
   const int fr = lane & 31, fh = lane >> 5, sw = fr & 15;
   constexpr int NK = kFKW / 8;
@@ -145,9 +151,15 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
       f.x[k] = *reinterpret_cast<const f32v4*>(pa + off);
     }
   };
-  f32x16 acc, tot;
+  // total so far, and the sum of the last two groups of eight products, not in it yet
+  double tot[16];
+  float pair[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[r] = 0.f; tot[r] = 0.f; }
+  for (int r = 0; r < 16; ++r) { tot[r] = 0.0; pair[r] = 0.f; }
+  auto fold = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tot[r] += (double)pair[r];
+  };
   // Stage kt, whose fragments are in `use`: once the loads of stage kt+1 have landed everywhere its
   // fragments are read into `nxt` (under the MFMAs of stage kt), and stage kt+2 is requested into the
   // slot of stage kt, which every wave has in registers by the barrier.
@@ -165,13 +177,25 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int k = 0; k < NK; ++k)
+    for (int k = 0; k < NK; k += 2) {
+      f32x16 n0, n1;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { n0[r] = 0.f; n1[r] = 0.f; }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][c], use.x[k][c], n0, 0, 0, 0);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][c], use.x[k][c], acc, 0, 0, 0);
-    if (kt % kFFold == kFFold - 1 || kt + 1 == KT) {             // 64 reduction indices of this wave
+        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + 1][c], use.x[k + 1][c], n1, 0, 0, 0);
+      fold();
 #pragma unroll
-      for (int r = 0; r < 16; ++r) { tot[r] += acc[r]; acc[r] = 0.f; }
+      for (int r = 0; r < 16; ++r) pair[r] = n0[r] + n1[r];
+      // the previous pair is folded under the MFMAs of this one
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);       // four of the 32 conversions and additions
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   Frags f0, f1;
@@ -184,17 +208,19 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
     stage(kt, f0, f1);
     if (kt + 1 < KT) stage(kt + 1, f1, f0);
   }
+  fold();
   // The two halves of the reduction meet in LDS and are added in order.
   __syncthreads();                                               // the stages have been read
-  float* ex = reinterpret_cast<float*>(lds) + wn * 1024;         // [wn][16][64]
+  double* ex = reinterpret_cast<double*>(lds) + wn * 1024;       // [wn][16][64]
   if (kq == 1)
 #pragma unroll
     for (int r = 0; r < 16; ++r) ex[r * 64 + lane] = tot[r];
   __syncthreads();
   // accumulator r of a lane: token lane%32, weight row 8*(r/4) + 4*(lane/32) + r%4 of the wave's 32
   if (kq == 1 || fr >= rows) return;
+  float sum[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) tot[r] += ex[r * 64 + lane];
+  for (int r = 0; r < 16; ++r) sum[r] = (float)(tot[r] + ex[r * 64 + lane]);
   float* crow = a.C + (long long)(row + fr) * a.ldc;
   if constexpr (UP) {
 #pragma unroll
@@ -203,7 +229,7 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
       float h[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float gt = tot[4 * q + j], up = tot[8 + 4 * q + j];
+        const float gt = sum[4 * q + j], up = sum[8 + 4 * q + j];
         h[j] = gt / (1.f + expf(-gt)) * up;
       }
       if (col < ncols) *reinterpret_cast<float4*>(crow + col) = make_float4(h[0], h[1], h[2], h[3]);
@@ -213,13 +239,13 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
     for (int q = 0; q < 4; ++q) {
       const int col = n0 + 32 * wn + 8 * q + 4 * fh;
       if (col < ncols)
-        *reinterpret_cast<float4*>(crow + col) = make_float4(tot[4 * q], tot[4 * q + 1], tot[4 * q + 2], tot[4 * q + 3]);
+        *reinterpret_cast<float4*>(crow + col) = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
     }
   }
 }
 
 template <bool UP>
-__global__ void __launch_bounds__(64 * kFW) ffn_f32_kernel(const F32Args a) {
+__global__ void __launch_bounds__(64 * kFW, 3) ffn_f32_kernel(const F32Args a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // The hardware hands workgroups to the 8 XCDs in turn: four neighbouring row tiles of one column

@@ -34,7 +34,40 @@ def test_ffn_f32_tile_edges(d, d_ff):
                              [t.f32 for t in inp.w_down], np.arange(T, dtype=np.int32), eidx.reshape(-1))
     got = L.y_perm.cpu().numpy()
     want = want[L.perm.cpu().numpy()]
-    # two fp32 dot products of at most 1024 terms, folded every 64: relative to the largest output the
-    # rounding error stays below 2^-24 * (64 + 16) with room to spare
+    # two fp32 dot products in chains of 8 with fp64 totals and the roundings between them: relative to the largest
+    # output the error stays below 2^-24 * (8 + 16) with room to spare
     assert np.isfinite(got).all()
     assert np.abs(got - want).max() <= 5e-6 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (128, (64, 256)), (512, (256, 448)), (1024, (192, 896)),
+                                    (4096, (768, 2048))])
+def test_ffn_f32_rounding_error(d, d_ff):
+    """Error of the fp32 expert networks against float64, as a 2-norm.  A rounding costs 2.5e-8 rms
+    (2^-24 / sqrt(3), averaged over the mantissa).  A dot product in chains of eight products, added in pairs to an
+    fp64 total, carries the roundings of 4.5 + 1 + 1 of its values: 6.4e-8, whatever its length.  Both operands of
+    SiLU(a) b have it, the first amplified by up to 1.5, SiLU and the product add about four roundings, the second
+    projection its own: sqrt(6.4^2 (1 + 1.5^2) + 4 * 2.5^2 + 6.4^2) = 14e-8."""
+    import paper_2604_23108_amd as M
+    from gpu_harness import DeviceLayer
+    T, n = 128, 2
+    w = Workload("f32_err", T=T, d=d, n_groups=2, experts_per_group=n, d_ff=d_ff, k_groups=1, k_experts=1,
+                 dtype="f32", seed=44)
+    dl = DeviceLayer(w, generate(w), training=False)
+    L = dl.layer
+    eidx = np.repeat(np.arange(4), T // 4).astype(np.int32).reshape(T, 1)
+    M.mohge_permute(dl.cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None,
+                    L.ws_permute)
+    print(f"[f32 error] d={d} d_ff={d_ff}", flush=True)
+    M.mohge_expert_ffn(dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2, L.y_perm, L.ws_ffn)
+    torch.cuda.synchronize()
+    rows = dl.x[L.perm.long()].cpu().double().view(4, T // 4, d)
+    want = []
+    for e in range(4):
+        g, i = divmod(e, n)
+        w13, w2 = L.w13[g][i].cpu().double(), L.w2[g][i].cpu().double()
+        a, b = (rows[e] @ w13.T).split(d_ff[g], dim=1)
+        want.append((a * torch.sigmoid(a) * b) @ w2.T)
+    want = torch.cat(want)
+    err = float((L.y_perm.cpu().double() - want).norm() / want.norm())
+    assert err <= 1.5e-7, err
