@@ -1354,7 +1354,7 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd1_kernel(const 
   }
   const int b = blockIdx.x - n_dh, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (b == 0 && threadIdx.x < 32) ga.zero_row[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
-  if (ga.perm == nullptr) return;
+  if (ga.perm == nullptr || ga.P <= 0) return;
   constexpr int R = kSmallGatherRows / 4;
   const int p0 = b * kSmallGatherRows + w * R;
   long long src[R];
@@ -1442,7 +1442,8 @@ hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileAr
                             const TileArgs& w13, const GatherArgs& ga, hipStream_t s) {
   static bool attr1 = false, attr2 = false;
   const int n_dh = small_grid(L, kDgradH);
-  const int gather = ga.perm ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
+  // at least one gather workgroup: it writes the row of zeros (a call without tokens still clears the weight gradients)
+  const int gather = ga.perm && ga.P > 0 ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
   hipError_t e = launch_small(ffn_small_bwd1_kernel, attr1, n_dh + gather, s, dh, ga, n_dh);
   if (e != hipSuccess) return e;
   const int n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);

@@ -57,3 +57,27 @@ def test_small_tiles_equal_big_tiles(d, d_ff):
     got, want = L.y_perm.float().cpu().numpy(), want[L.perm.cpu().numpy()]
     # h and y are rounded to bf16 once each: 2^-9 of the value and of a sum of such terms
     assert np.abs(got - want).max() <= 8e-3 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("with_perm", [True, False])
+def test_backward_of_a_call_without_tokens(with_perm):
+    """T = 0 is a valid call: the weight gradients are sums over no rows, zeros."""
+    import paper_2604_23108_amd as M
+    d, ff, n = 192, (64, 128), 3
+    cfg = M.Config(T=0, d=d, n_groups=2, experts_per_group=n, d_ff=ff, k_groups=1, k_experts=1,
+                   select_mode=M.SELECT_PER_GROUP, dtype=M.BF16)
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    row = lambda: torch.full((16, d), float("nan"), **bf)              # never read or written
+    perm = torch.full((16,), -1, dtype=torch.int32, device="cuda")
+    offsets = torch.zeros(2 * n + 1, dtype=torch.int32, device="cuda")
+    w13, w2 = [torch.ones((n, 2 * f, d), **bf) for f in ff], [torch.ones((n, d, f), **bf) for f in ff]
+    dw13, dw2 = [torch.full_like(w, float("nan")) for w in w13], [torch.full_like(w, float("nan")) for w in w2]
+    u8 = lambda call: torch.full((M.mohge_workspace_size(cfg, call),), 0xFF, dtype=torch.uint8, device="cuda")
+    dx_perm = row()
+    print(f"[no tokens] perm={with_perm}", flush=True)
+    M.mohge_expert_ffn_bwd(cfg, row(), perm if with_perm else None, offsets, w13, w2, u8(M.CALL_FFN_SAVED), row(), dx_perm,
+                           dw13, dw2, u8(M.CALL_EXPERT_FFN_BWD))
+    torch.cuda.synchronize()
+    for t in dw13 + dw2:
+        assert not t.any()
+    assert torch.isnan(dx_perm.float()).all()
