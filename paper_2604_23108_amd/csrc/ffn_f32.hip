@@ -248,9 +248,10 @@ template <bool UP>
 __global__ void __launch_bounds__(64 * kFW, 3) ffn_f32_kernel(const F32Args a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // The hardware hands workgroups to the 8 XCDs in turn: four neighbouring row tiles of one column
-  // tile (mostly one expert's: one weight panel) go to the same XCD.
-  const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
+  // The hardware hands workgroups to the 8 XCDs in turn (a row of the grid is a multiple of 8 long): four neighbouring
+  // row tiles of one column tile (mostly one expert's: one weight panel) go to the same XCD.
+  const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  const int xcd = wg % 8, idx = wg / 8;
   const int tile = ((idx / 4) * 8 + xcd) * 4 + idx % 4;
   const int m = tile % a.ntm, n = tile / a.ntm;
   if (n >= a.ntn) return;
@@ -261,19 +262,18 @@ __global__ void __launch_bounds__(64 * kFW, 3) ffn_f32_kernel(const F32Args a) {
   f32_tile<UP>(a, lds, e, row, rows, n0, w, lane);
 }
 
+// Workgroups in rows of at most kFGridX: a launch has fewer than 2^32 threads per grid dimension, which a call with
+// 64 GiB of hidden activations exceeds in one.
+constexpr long long kFGridX = 1ll << 20;
+
 template <bool UP>
 static hipError_t launch_f32(F32Args& a, hipStream_t s) {
   constexpr int smem = kFStages * kFStage;
-  auto kern = ffn_f32_kernel<UP>;
-  static bool attr_done = false;                 // more than 64 KB of dynamic LDS needs the opt-in
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  const long long tiles = (long long)a.ntm * a.ntn;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((tiles + 31) / 32 * 32)), dim3(64 * kFW), smem, s, a);
+  static_assert(smem <= 64 * 1024 && 2 * 16 * 64 * (int)sizeof(double) <= smem, "dynamic LDS without the opt-in; the sums");
+  const long long wgs = ((long long)a.ntm * a.ntn + 31) / 32 * 32;
+  const long long gx = wgs < kFGridX ? wgs : kFGridX, gy = (wgs + gx - 1) / gx;
+  if (gx * gy >= 1ll << 31) return hipErrorInvalidConfiguration;   // (terabytes of activations)
+  hipLaunchKernelGGL(ffn_f32_kernel<UP>, dim3((unsigned)gx, (unsigned)gy), dim3(64 * kFW), smem, s, a);
   return hipGetLastError();
 }
 

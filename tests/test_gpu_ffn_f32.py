@@ -71,3 +71,34 @@ def test_ffn_f32_rounding_error(d, d_ff):
     want = torch.cat(want)
     err = float((L.y_perm.cpu().double() - want).norm() / want.norm())
     assert err <= 1.5e-7, err
+
+
+def test_ffn_f32_more_workgroups_than_one_grid_dimension():
+    """2^20 routed rows of an expert 16384 wide: 2^24 workgroups of the first projection, whose threads do not fit one
+    dimension of a grid (64 GiB of hidden activations).  Rows repeat with a period of 4096, results have to as well."""
+    import paper_2604_23108_amd as M
+    T, d, F, period = 1 << 20, 64, 1 << 14, 4096
+    cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=1, d_ff=(F,), k_groups=1, k_experts=1,
+                   select_mode=M.SELECT_PER_GROUP, dtype=M.F32)
+    need = M.mohge_workspace_size(cfg, M.CALL_EXPERT_FFN)
+    assert need == T * F * 4
+    if torch.cuda.mem_get_info()[0] < need + (4 << 30):
+        pytest.skip("needs 68 GiB of free device memory")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    normal = lambda *s: torch.randn(s, generator=gen, device="cuda")
+    x = normal(period, d)
+    w13, w2 = normal(1, 2 * F, d) * 0.1, normal(1, d, F) * 0.02
+    offsets = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    y = torch.full((T, d), float("nan"), device="cuda")
+    print(f"[f32 grid] rows={T} width={F}", flush=True)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    M.mohge_expert_ffn(cfg, x.repeat(T // period, 1), None, offsets, [w13], [w2], y, ws)
+    torch.cuda.synchronize()
+    del ws
+    y = y.view(T // period, period, d)
+    assert torch.equal(y, y[:1].expand_as(y))
+    a, b = (x.double() @ w13[0].double().T.contiguous()).split(F, dim=1)
+    want = (a * torch.sigmoid(a) * b) @ w2[0].double().T.contiguous()
+    # the bound of the error test above
+    assert float((y[0].double() - want).norm() / want.norm()) <= 1.5e-7
+    torch.cuda.empty_cache()
