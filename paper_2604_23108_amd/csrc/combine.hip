@@ -141,9 +141,16 @@ hipError_t launch_shared_routing(const LayerDesc& L, int32_t* expert_idx, float*
 //   dgates[t,slot] = <dy_t, y_perm[r]>,   dy_perm[r] = gate[t,slot] * dy_t
 // One wave per token; lanes stride the row in 16-byte chunks; the dot product is folded with a
 // butterfly, so the result does not depend on scheduling.
+// Bound by memory: dy, K_e rows of y_perm and K_e rows of dy_perm per token.  NS slots at a time: dy is read once
+// for them and their rows of y_perm are in flight together (d = 4096, four slots: 24.4 -> 20.3 us at 1500 tokens,
+// 12.5 -> 6.8 at 100).  Past what the last-level cache holds one slot at a time is the faster walk, two rows read
+// and one written at a time instead of five and four: 164 against 171 to 181 us with four slots at 8192 tokens,
+// 129 against 137 to 144 with three (inputs not in the cache; 131 against 154 to 165 when calls follow each
+// other); at 300 MB the forms are even, at 180 MB four slots are 13 % ahead.
 // ---------------------------------------------------------------------------------------
 namespace mohge {
 
+template <int NS>
 __global__ void __launch_bounds__(256) combine_bwd_kernel(const uint4* __restrict__ dy,
                                                           const uint4* __restrict__ y_perm,
                                                           const int32_t* __restrict__ inv_perm,
@@ -154,48 +161,42 @@ __global__ void __launch_bounds__(256) combine_bwd_kernel(const uint4* __restric
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
-  // four slots at a time: dy is read once for them and their rows of y_perm are in flight together
-  // (one slot after the other: 63 us for 302 MB at 8192 tokens, d = 2048, four slots)
-  for (int s0 = 0; s0 < Ke; s0 += 4) {
-    float g[4], dot[4] = {0.f, 0.f, 0.f, 0.f};
-    int r[4];
+  for (int s0 = 0; s0 < Ke; s0 += NS) {
+    float g[NS], dot[NS];
+    int r[NS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const size_t at = (size_t)t * Ke + min(s0 + i, Ke - 1);
+    for (int i = 0; i < NS; ++i) {
+      const size_t at = (size_t)t * Ke + s0 + i;
       g[i] = gates[at];
       r[i] = inv_perm[at];
+      dot[i] = 0.f;
     }
     for (int v = lane; v < vec_per_row; v += 64) {
       const uint4 a = dy[(size_t)t * vec_per_row + v];
-      uint4 b[4];
+      uint4 b[NS];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (s0 + i < Ke) b[i] = y_perm[(size_t)r[i] * vec_per_row + v];
+      for (int i = 0; i < NS; ++i) b[i] = y_perm[(size_t)r[i] * vec_per_row + v];
       const uint32_t aw[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (s0 + i < Ke) {
-          const uint32_t bw[4] = {b[i].x, b[i].y, b[i].z, b[i].w};
-          uint32_t ow[4];
+      for (int i = 0; i < NS; ++i) {
+        const uint32_t bw[4] = {b[i].x, b[i].y, b[i].z, b[i].w};
+        uint32_t ow[4];
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const float a0 = __uint_as_float(aw[k] << 16), a1 = __uint_as_float(aw[k] & 0xffff0000u);
-            const float b0 = __uint_as_float(bw[k] << 16), b1 = __uint_as_float(bw[k] & 0xffff0000u);
-            dot[i] = fmaf(a0, b0, dot[i]);
-            dot[i] = fmaf(a1, b1, dot[i]);
-            ow[k] = pack_bf16x2(g[i] * a0, g[i] * a1);
-          }
-          dy_perm[(size_t)r[i] * vec_per_row + v] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+        for (int k = 0; k < 4; ++k) {
+          const float a0 = __uint_as_float(aw[k] << 16), a1 = __uint_as_float(aw[k] & 0xffff0000u);
+          const float b0 = __uint_as_float(bw[k] << 16), b1 = __uint_as_float(bw[k] & 0xffff0000u);
+          dot[i] = fmaf(a0, b0, dot[i]);
+          dot[i] = fmaf(a1, b1, dot[i]);
+          ow[k] = pack_bf16x2(g[i] * a0, g[i] * a1);
         }
+        dy_perm[(size_t)r[i] * vec_per_row + v] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
       }
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (s0 + i < Ke) {
+    for (int i = 0; i < NS; ++i) {
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) dot[i] += __shfl_xor(dot[i], off, 64);
-        if (lane == 0) dgates[(size_t)t * Ke + s0 + i] = dot[i];
-      }
+      for (int off = 32; off >= 1; off >>= 1) dot[i] += __shfl_xor(dot[i], off, 64);
+      if (lane == 0) dgates[(size_t)t * Ke + s0 + i] = dot[i];
     }
   }
 }
@@ -204,7 +205,10 @@ hipError_t launch_combine_bwd(const LayerDesc& L, const void* dy, const void* y_
                               const int32_t* inv_perm, const float* gates, float* dgates,
                               void* dy_perm, hipStream_t s) {
   const int vec_per_row = L.d * 2 / 16;
-  hipLaunchKernelGGL(combine_bwd_kernel, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s,
+  const bool one = (long long)L.T * (2 * L.Ke + 1) * L.d * 2 > (192ll << 20);
+  auto kern = one ? combine_bwd_kernel<1> : L.Ke % 4 == 0 ? combine_bwd_kernel<4> : L.Ke % 3 == 0 ? combine_bwd_kernel<3>
+              : L.Ke % 2 == 0 ? combine_bwd_kernel<2> : combine_bwd_kernel<1>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s,
                      static_cast<const uint4*>(dy), static_cast<const uint4*>(y_perm), inv_perm, gates,
                      dgates, static_cast<uint4*>(dy_perm), L.T, L.Ke, vec_per_row);
   return hipGetLastError();
