@@ -287,7 +287,6 @@ __global__ void __launch_bounds__(256, 3) decode_layer_kernel(const DecodeArgs a
   __shared__ int s_nlist;
   __shared__ int s_up[kMaxExperts + 1], s_dn[kMaxExperts + 1];   // units before expert e (experts with rows only)
   __shared__ int s_wsum[4][2];
-  __shared__ f32x4 red[kSplitLdsBytes / 16];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int total = (int)gridDim.x;
   int* const up_done = a.ctl + kDecCtlHead;      // finished up units per expert
@@ -411,8 +410,7 @@ __global__ void __launch_bounds__(256, 3) decode_layer_kernel(const DecodeArgs a
     } else if (!rows_ok) {
       if (threadIdx.x == 0) set_failed(a, 2);
     } else if (isup) {
-      const int blk = a.up.blk_prefix[g] + (e - g * a.r.N) * (a.up.F[g] / 64) + cb;
-      skinny_block<true, true>(a.up, blk, red);
+      skinny_wave_unit<true>(a.up, g, e - g * a.r.N, cb * 64 + 16 * w, row0, cnt);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's rows of H are written through
       __syncthreads();
       if (threadIdx.x == 0) {
@@ -424,8 +422,7 @@ __global__ void __launch_bounds__(256, 3) decode_layer_kernel(const DecodeArgs a
         }
       }
     } else {
-      const int blk = a.dn.blk_prefix[g] + (e - g * a.r.N) * a.ncb + cb;
-      skinny_block<false, true>(a.dn, blk, red);
+      skinny_wave_unit<false>(a.dn, g, e - g * a.r.N, cb * 128 + 32 * w, row0, cnt);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this wave's rows of y_perm are written through
       __syncthreads();
       // one thread per routed row of the expert: its token's counter for this feature block

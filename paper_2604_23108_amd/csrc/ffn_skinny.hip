@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(256, 3) ffn_skinny_kernel(const SkinnyArgs a, 
   if (!expert_of_slot(a, blockIdx.x / ncb, e, row0, cnt)) return;
   const int g = e / a.N;
   if (c0 >= (UP ? a.F[g] : a.d)) return;
-  skinny_unit<UP, false>(a, g, e - g * a.N, c0, row0, cnt, red);
+  skinny_unit<UP>(a, g, e - g * a.N, c0, row0, cnt, red);
 }
 
 // 16 E4M3 codes -> two operand fragments of 8 bf16 (codes 0..7 and 8..15)

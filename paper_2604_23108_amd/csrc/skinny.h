@@ -43,6 +43,36 @@ __device__ __forceinline__ void store8_device_scope(void* p, const uint2 v) {
   asm volatile("global_store_dwordx2 %0, %1, off sc1" ::"v"(p), "v"(q) : "memory");
 }
 
+// Weight rows 4q..4q+3 of each row set for one sorted row: the SwiGLU product [UP] or both sets as they are
+template <bool UP, bool COHERENT>
+__device__ __forceinline__ void skinny_store(const SkinnyArgs& a, const int c0, const int q, const int ncols, const int row,
+                                             const f32x4 s0, const f32x4 s1) {
+  uint16_t* crow = a.C + (long long)row * a.ldc;
+  if constexpr (UP) {
+    float v[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v[b] = s0[b] / (1.f + __expf(-s0[b])) * s1[b];
+    uint2 o;
+    o.x = pack_bf16x2(v[0], v[1]);
+    o.y = pack_bf16x2(v[2], v[3]);
+    if constexpr (COHERENT) store8_device_scope(crow + c0 + 4 * q, o);
+    else *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
+  } else {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      const f32x4 s = f ? s1 : s0;
+      const int col = c0 + 16 * f + 4 * q;
+      if (col < ncols) {
+        uint2 o;
+        o.x = pack_bf16x2(s[0], s[1]);
+        o.y = pack_bf16x2(s[2], s[3]);
+        if constexpr (COHERENT) store8_device_scope(crow + col, o);
+        else *reinterpret_cast<uint2*>(crow + col) = o;
+      }
+    }
+  }
+}
+
 // One unit of the bf16 decode kernels: 16 hidden units [UP: 16 W_gate rows and the matching 16 W_up rows] or
 // 32 output features [down] of one expert, all its rows, 32 at a time.  The four waves of the workgroup take
 // the same weight rows and a quarter of the reduction indices each; their partial sums meet in LDS and are
@@ -60,7 +90,7 @@ constexpr int kSplitLdsBytes = (kSplitWaves - 1) * 4 * 64 * 16;
 
 // expert e = group g, index i inside it; c0: first of 16 hidden units [UP] or 32 output features [down].
 // red: LDS, kSplitLdsBytes.  Called by the whole workgroup of 4 waves, the same arguments in all of them.
-template <bool UP, bool COHERENT>
+template <bool UP>
 __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, const int i, const int c0,
                                                   const int row0, const int cnt, f32x4* const red) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -160,32 +190,7 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
             for (int ww = 0; ww < kSplitWaves - 1; ++ww) acc[f][tb] += red[(ww * 4 + 2 * f + tb) * 64 + lane];
           const int tt = tb0 + 16 * tb + r;
           if (tt >= cnt) continue;
-          uint16_t* crow = a.C + (long long)(row0 + tt) * a.ldc;
-          if constexpr (UP) {
-            float v[4];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              const float gt = acc[0][tb][b], up = acc[1][tb][b];
-              v[b] = gt / (1.f + __expf(-gt)) * up;
-            }
-            uint2 o;
-            o.x = pack_bf16x2(v[0], v[1]);
-            o.y = pack_bf16x2(v[2], v[3]);
-            if constexpr (COHERENT) store8_device_scope(crow + c0 + 4 * q, o);
-            else *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
-          } else {
-#pragma unroll
-            for (int f = 0; f < 2; ++f) {
-              const int col = c0 + 16 * f + 4 * q;
-              if (col < ncols) {
-                uint2 o;
-                o.x = pack_bf16x2(acc[f][tb][0], acc[f][tb][1]);
-                o.y = pack_bf16x2(acc[f][tb][2], acc[f][tb][3]);
-                if constexpr (COHERENT) store8_device_scope(crow + col, o);
-                else *reinterpret_cast<uint2*>(crow + col) = o;
-              }
-            }
-          }
+          skinny_store<UP, false>(a, c0, q, ncols, row0 + tt, acc[0][tb], acc[1][tb]);
         }
       }
       __syncthreads();                                       // the sums have been read
@@ -195,23 +200,104 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
   }
 }
 
-// Workgroup `blk` of the numbering that has one unit per (expert, 64 hidden units) [UP] or (expert, 128
-// output features) [down]: four of the units above one after the other (the single-launch decode layer's
-// pieces of work).
-template <bool UP, bool COHERENT>
-__device__ __forceinline__ void skinny_block(const SkinnyArgs& a, const int blk, f32x4* const red) {
-  int g = 0;
-  while (g + 1 < a.Ng && blk >= a.blk_prefix[g + 1]) ++g;
-  const int ncols = UP ? a.F[g] : a.d;
-  constexpr int COLS_PER_BLOCK = UP ? 64 : 128;
-  const int blocks_per_expert = (ncols + COLS_PER_BLOCK - 1) / COLS_PER_BLOCK;
-  const int local = blk - a.blk_prefix[g];
-  const int i = local / blocks_per_expert, cb = local % blocks_per_expert;
-  const int e = g * a.N + i;
-  const int row0 = a.offsets[e], cnt = a.offsets[e + 1] - row0;
-  for (int sub = 0; sub < 4; ++sub) {
-    const int c0 = cb * COLS_PER_BLOCK + sub * (COLS_PER_BLOCK / 4);
-    if (c0 < ncols) skinny_unit<UP, COHERENT>(a, g, i, c0, row0, cnt, red);
+// The same rows of C for a wave by itself: 16 hidden units or 32 output features from c0, the four quarters of the
+// reduction one after the other, each summed by itself and the sums added in order, so that the bits are those of
+// skinny_unit.  For the single-launch decode layer, whose workgroups take 64 hidden units or 128 output features at a
+// time: four waves side by side need no barrier and no LDS, and the workgroup one pass.  (Four of the units above
+// after one another took the whole layer 2 to 17 % longer than a wave per 32 rows had, at most sizes: 205 -> 214 us at
+// one token of d = 4096, 64 experts, 32 -> 37 at d = 128; this form takes 195 and 30.)  128 indices at a time: with
+// 256, or with the waves starting at different quarters and four partial sums held, the layer's registers spill (1.7 to
+// 5 % more time).  The rows are stored at device scope, for a consumer in the same launch.
+template <bool UP>
+__device__ __forceinline__ void skinny_wave_unit(const SkinnyArgs& a, const int g, const int i, const int c0,
+                                                 const int row0, const int cnt) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, q = lane >> 4;
+  const int F = a.F[g];
+  const int K = UP ? a.d : F;
+  const int ncols = UP ? F : a.d;
+  if (c0 >= ncols) return;
+  const uint16_t* wp[2];
+  if constexpr (UP) {
+    const uint16_t* base = a.W[g] + (long long)i * 2 * F * K;
+    wp[0] = base + (long long)(c0 + r) * K + 8 * q;
+    wp[1] = base + (long long)(F + c0 + r) * K + 8 * q;
+  } else {
+    const uint16_t* base = a.W[g] + (long long)i * a.d * K;
+    int n1 = c0 + 16 + r;
+    if (n1 > a.d - 1) n1 = a.d - 1;
+    wp[0] = base + (long long)(c0 + r) * K + 8 * q;
+    wp[1] = base + (long long)n1 * K + 8 * q;
+  }
+  const int nb = K / 64;
+  for (int tb0 = 0; tb0 < cnt; tb0 += 32) {
+    auto pass = [&](auto NTBC) {
+      constexpr int NTB = decltype(NTBC)::value;             // token blocks of 16
+      const uint16_t* xp[NTB];
+      bool xv[NTB];
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        const int tt = tb0 + 16 * tb + r;
+        xv[tb] = tt < cnt;
+        const int pos = row0 + (xv[tb] ? tt : 0);
+        long long src;
+        if constexpr (UP) src = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
+        else src = pos;
+        xp[tb] = a.A + src * a.lda + 8 * q;
+      }
+      auto step = [&](f32x4 (&acc)[2][NTB], int k0, auto UC) {
+        constexpr int U = decltype(UC)::value;
+        Frag wf[2][U], xf[NTB][U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+          for (int f = 0; f < 2; ++f) wf[f][u].u = *reinterpret_cast<const uint4*>(wp[f] + k0 + 32 * u);
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) {
+            xf[tb][u].u = make_uint4(0u, 0u, 0u, 0u);
+            if (xv[tb]) xf[tb][u].u = *reinterpret_cast<const uint4*>(xp[tb] + k0 + 32 * u);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb)
+              acc[f][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[f][u].v, xf[tb][u].v, acc[f][tb], 0, 0, 0);
+      };
+      auto quarter = [&](f32x4 (&sum)[2][NTB], int qt) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) sum[f][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int k0 = nb * qt / kSplitWaves * 64;
+        const int ke = nb * (qt + 1) / kSplitWaves * 64;
+        for (; k0 + 128 <= ke; k0 += 128) step(sum, k0, std::integral_constant<int, 4>{});
+        for (; k0 < ke; k0 += 64) step(sum, k0, std::integral_constant<int, 2>{});
+      };
+      f32x4 acc[2][NTB];
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) acc[f][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int qt = 0; qt < kSplitWaves; ++qt) {
+        f32x4 part[2][NTB];
+        quarter(part, qt);
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int tb = 0; tb < NTB; ++tb) acc[f][tb] += part[f][tb];
+      }
+#pragma unroll
+      for (int tb = 0; tb < NTB; ++tb) {
+        const int tt = tb0 + 16 * tb + r;
+        if (tt < cnt) skinny_store<UP, true>(a, c0, q, ncols, row0 + tt, acc[0][tb], acc[1][tb]);
+      }
+    };
+    if (cnt - tb0 > 16) pass(std::integral_constant<int, 2>{});
+    else pass(std::integral_constant<int, 1>{});
   }
 }
 

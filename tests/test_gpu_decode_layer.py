@@ -81,7 +81,7 @@ def test_decode_layer_full_size_every_token(mode):
 @pytest.mark.parametrize("shape", ["decode", "odd"])
 def test_decode_layer_equals_the_separate_calls_bit_by_bit(shape):
     """The routing of the separate router call up to the last bits of the gates, and, given the
-    routing, the same bits in y: every unit runs the code of the separate launches."""
+    routing, the same bits in y: every unit adds in the order of the separate launches."""
     import paper_2604_23108_amd as M
     if shape == "decode":
         w = WORKLOADS["decode"]
