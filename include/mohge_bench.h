@@ -18,7 +18,11 @@ extern "C" {
 /*
  * Launch options of the bf16 matrix-core path (T > 32; ignored by the other paths).  They belong
  * to one call: there is no process-wide state.  Results do not depend on any of them, except a
- * negative spin_limit.  mohge_ffn_default_options fills in what the calls of mohge.h use.
+ * negative spin_limit.
+ * The calls of mohge.h take one of two forms by size: 256 x 256 tiles handed out from a schedule, or, where
+ * those would leave compute units idle, 128 x 128 tiles without one.  The options other than small_tiles describe
+ * the first; mohge_ffn_default_options fills in what mohge.h uses for them, and small_tiles = 0: the calls
+ * below take the first form unless the caller asks otherwise.
  */
 typedef struct mohge_ffn_options {
   int32_t tile_rows_up;    /* token-tile height of the up-projection list (forward) / of dH and dX
@@ -52,6 +56,8 @@ typedef struct mohge_ffn_options {
                               [1][w]: core clocks and 100 MHz ticks of w's first list, of its
                               second list, then the 100 MHz time stamps of w's start and end      */
   size_t cycles_bytes;
+  int32_t small_tiles;     /* 0: 256 x 256 tiles; 1: 128 x 128 tiles (then the options above have no effect, and
+                              parts must be 3); -1: by size, as the calls of mohge.h                */
 } mohge_ffn_options;
 
 void mohge_ffn_default_options(mohge_ffn_options* options);
@@ -59,14 +65,14 @@ size_t mohge_bench_cycles_bytes(void);
 
 /*
  * mohge_expert_ffn / mohge_expert_ffn_train / mohge_expert_ffn_bwd (same arguments, same kernels)
- * with explicit launch options (NULL = the defaults).
+ * with explicit launch options (NULL = the defaults: the 256 x 256 form at every size).
  * mohge_bench_expert_ffn, parts: on the fused matrix-core path the call is two launches: a small
  * kernel that turns `offsets` into the tile lists and hand-out counters (kept in the workspace),
  * and the launch that computes both projections from them.  parts = 1 issues the first, parts = 2
  * the second, parts = 3 both.  A parts = 2 call consumes the lists: each needs a parts = 1 call
  * with the same cfg, offsets, options and workspace before it, on the same stream or ordered after
  * it; without one it writes nothing useful to y_perm (no other harm).  parts 1 and 2 exist only
- * where the two launches do (MOHGE_BF16, T > 32, fused != 0); MOHGE_EINVAL otherwise.
+ * where the two launches do (MOHGE_BF16, T > 32, fused != 0, small_tiles = 0); MOHGE_EINVAL otherwise.
  */
 int mohge_bench_expert_ffn(const mohge_config* cfg, const void* x, const int32_t* perm,
                            const int32_t* offsets, const void* const* w13, const void* const* w2,

@@ -22,7 +22,7 @@ class _COptions(C.Structure):
     _fields_ = [("tile_rows_up", C.c_int32), ("tile_rows_down", C.c_int32), ("fused", C.c_int32),
                 ("spin_limit", C.c_int32), ("band_rows", C.c_int32), ("group_major", C.c_int32),
                 ("steal", C.c_int32), ("short_last", C.c_int32), ("defer_signal", C.c_int32), ("cycles_launch", C.c_int32), ("cycles", C.c_void_p),
-                ("cycles_bytes", C.c_size_t)]
+                ("cycles_bytes", C.c_size_t), ("small_tiles", C.c_int32)]
 
 
 _lib = None
@@ -45,7 +45,8 @@ def lib():
 
 
 class FfnOptions:
-    """Python mirror of `mohge_ffn_options`, starting from the library's defaults."""
+    """Python mirror of `mohge_ffn_options`, starting from the library's defaults (256 x 256 tiles at every size;
+    small_tiles=1: 128 x 128, -1: by size, as the layer's own calls)."""
 
     def __init__(self, cycles: Optional[torch.Tensor] = None, **kw):
         self._c = _COptions()

@@ -18,8 +18,13 @@ using namespace mohge;
 #define OPT(p) do { int rc_ = need((p), #p, false); if (rc_) return rc_; } while (0)
 
 static int to_options(const mohge_ffn_options* in, const LayerDesc& L, FfnOptions* o) {
-  o->small = 0;       // this library's options describe the schedule-driven 256 x 256 form
+  o->small = 0;       // the options describe the schedule-driven 256 x 256 form
   if (!in) return MOHGE_OK;
+  if (in->small_tiles < -1 || in->small_tiles > 1) {
+    set_error("mohge_ffn_options: small_tiles = %d (-1, 0 or 1)", in->small_tiles);
+    return MOHGE_EINVAL;
+  }
+  o->small = in->small_tiles;
   for (int i = 0; i < 2; ++i) {
     const int v = i == 0 ? in->tile_rows_up : in->tile_rows_down;
     if (v != 0 && v != 64 && v != 128 && v != 192 && v != 256) {
@@ -92,9 +97,9 @@ int mohge_bench_expert_ffn(const mohge_config* cfg, const void* x, const int32_t
   FfnOptions o;
   if ((rc = to_options(options, L, &o))) return rc;
   if (parts < 1 || parts > 3) { set_error("mohge_bench_expert_ffn: parts = %d (1, 2 or 3)", parts); return MOHGE_EINVAL; }
-  if (parts != 3 && (!ffn_parts_supported(L, cfg->dtype) || !o.fused)) {
+  if (parts != 3 && (!ffn_parts_supported(L, cfg->dtype) || !o.fused || o.small != 0)) {
     set_error("mohge_bench_expert_ffn: schedule and product launch are separate launches only in the fused form "
-              "of the matrix-core path (MOHGE_BF16, T > 32, options->fused != 0)");
+              "of the matrix-core path (MOHGE_BF16, T > 32, options->fused != 0, options->small_tiles = 0)");
     return MOHGE_EINVAL;
   }
   NEED(x); OPT(perm); NEED(offsets); NEED(y_perm); NEED(workspace);

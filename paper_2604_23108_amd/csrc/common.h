@@ -30,7 +30,7 @@ struct GroupPtrs {
 // of these (except a negative spin_limit, a test hook).
 struct FfnOptions {
   int tile_rows[2] = {0, 0};  // token-tile height of the up / down list: 0 = chosen per call, else 64..256
-  int small = -1;             // 128 x 128 tiles without a schedule: -1 = chosen by size, 0 = never, 1 = always
+  int small = -1;             // 128 x 128 tiles without a schedule: -1 = chosen by size, 0 = never, 1 = always (the rest: 256 x 256 form)
   int fused = 1;              // both projections (dH and dX; the two weight gradients) in one launch
   int spin_limit = 0;         // polls a dependent tile waits: 0 = default (about a second), < 0 = give up at once
   int band = 4;               // row blocks per band of the tile order inside an expert

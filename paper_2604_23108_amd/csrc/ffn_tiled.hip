@@ -1386,7 +1386,7 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd2_kernel(const 
 // ---------------------------------------------------------------------------------------
 // Workgroups of a small-tile list, a multiple of 64 (small_tile_index).  Token modes: the counts are not
 // known here; full row tiles of the widest group plus a partial one per expert that can have rows.
-static int small_grid(const LayerDesc& L, int mode) {
+static long long small_grid(const LayerDesc& L, int mode) {
   const int cp = is_up(mode) ? SmallTile::BN / 2 : SmallTile::BN;
   long long n = 0, widest = 0;
   for (int g = 0; g < L.Ng; ++g) {
@@ -1396,18 +1396,19 @@ static int small_grid(const LayerDesc& L, int mode) {
   }
   if (L.P * widest < n) n = L.P * widest;
   n += (long long)(L.P / SmallTile::BM) * widest;
-  return (int)((n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk));
+  return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
-static int small_wgrad_grid(const TileArgs& a) {
+static long long small_wgrad_grid(const TileArgs& a) {
   long long n = 0;
   for (int g = 0; g < a.Ng; ++g)
     n += (long long)a.N * ((a.Mrows[g] + SmallTile::BM - 1) / SmallTile::BM) * ((a.Ncols[g] + SmallTile::BN - 1) / SmallTile::BN);
-  return (int)((n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk));
+  return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
 template <typename K, typename... Args>
-static hipError_t launch_small(K kern, bool& attr_done, int grid, hipStream_t s, const Args&... args) {
+static hipError_t launch_small(K kern, bool& attr_done, long long grid, hipStream_t s, const Args&... args) {
+  if (grid * kSmallThreads >= 1ll << 32) return hipErrorInvalidConfiguration;      // (only if asked for beyond the rule below)
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds);
@@ -1441,13 +1442,13 @@ bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
 hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
                             const TileArgs& w13, const GatherArgs& ga, hipStream_t s) {
   static bool attr1 = false, attr2 = false;
-  const int n_dh = small_grid(L, kDgradH);
+  const long long n_dh = small_grid(L, kDgradH);
   // at least one gather workgroup: it writes the row of zeros (a call without tokens still clears the weight gradients)
   const int gather = ga.perm && ga.P > 0 ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
-  hipError_t e = launch_small(ffn_small_bwd1_kernel, attr1, n_dh + gather, s, dh, ga, n_dh);
+  hipError_t e = launch_small(ffn_small_bwd1_kernel, attr1, n_dh + gather, s, dh, ga, (int)n_dh);
   if (e != hipSuccess) return e;
-  const int n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
-  return launch_small(ffn_small_bwd2_kernel, attr2, n_dx + n_w2 + n_w13, s, dx, w2, w13, n_dx, n_w2);
+  const long long n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
+  return launch_small(ffn_small_bwd2_kernel, attr2, n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
 }
 
 void apply_options(TileArgs& t, const FfnOptions& o) {

@@ -30,12 +30,12 @@ def test_small_tiles_equal_big_tiles(d, d_ff):
                     L.ws_permute)
     L.dy_perm.copy_(to_dev(inp.dy, True)[L.perm.long()])
     outs = []
-    for small in (True, False):
+    for form in ("by size", "small", "big"):
         for t in [L.y_perm, L.dx_perm, *L.dw13, *L.dw2]:
             t.fill_(float("nan"))
-        print(f"[small tiles] d={d} d_ff={d_ff} small={small}", flush=True)
+        print(f"[small tiles] d={d} d_ff={d_ff} form={form}", flush=True)
         args = (dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2)
-        if small:
+        if form == "by size":
             M.mohge_expert_ffn(*args, L.y_perm, L.ws_ffn)
             y = L.y_perm.clone()
             M.mohge_expert_ffn_train(*args, L.y_perm, L.saved)
@@ -43,15 +43,16 @@ def test_small_tiles_equal_big_tiles(d, d_ff):
             for call, ws in ((M.CALL_EXPERT_FFN, L.ws_ffn), (M.CALL_FFN_SAVED, L.saved), (M.CALL_EXPERT_FFN_BWD, L.ws_ffn_bwd)):
                 assert M.mohge_fused_status(dl.cfg, call, ws) == 0
         else:
-            BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn)
+            o = BB.FfnOptions(small_tiles=int(form == "small"))
+            BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn, o)
             y = L.y_perm.clone()
-            BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved)
-            BB.mohge_bench_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd)
+            BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved, o)
+            BB.mohge_bench_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd, o)
         torch.cuda.synchronize()
         dl.check_guards()
         outs.append([t.clone().view(torch.int16) for t in [y, L.y_perm, L.dx_perm, *L.dw13, *L.dw2]])
-    for a, b in zip(*outs):
-        assert torch.equal(a, b)
+    for a, b, c in zip(*outs):
+        assert torch.equal(a, b) and torch.equal(b, c)
     want = oracle.expert_ffn(w, inp.x.f32, [t.f32 for t in inp.w_gate], [t.f32 for t in inp.w_up],
                              [t.f32 for t in inp.w_down], np.arange(T, dtype=np.int32), eidx.reshape(-1))
     got, want = L.y_perm.float().cpu().numpy(), want[L.perm.cpu().numpy()]
