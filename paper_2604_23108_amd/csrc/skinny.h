@@ -205,9 +205,9 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
 // skinny_unit.  For the single-launch decode layer, whose workgroups take 64 hidden units or 128 output features at a
 // time: four waves side by side need no barrier and no LDS, and the workgroup one pass.  (Four of the units above
 // after one another took the whole layer 2 to 17 % longer than a wave per 32 rows had, at most sizes: 205 -> 214 us at
-// one token of d = 4096, 64 experts, 32 -> 37 at d = 128; this form takes 195 and 30.)  128 indices at a time: with
-// 256, or with the waves starting at different quarters and four partial sums held, the layer's registers spill (1.7 to
-// 5 % more time).  The rows are stored at device scope, for a consumer in the same launch.
+// one token of d = 4096, 64 experts, 32 -> 37 at d = 128; this form takes 197 and 30.)  128 indices at a time: with
+// 256 the layer's registers spill.  All waves starting at the same quarter cost up to 7 % at 4 to 16 tokens.  The
+// rows are stored at device scope, for a consumer in the same launch.
 template <bool UP>
 __device__ __forceinline__ void skinny_wave_unit(const SkinnyArgs& a, const int g, const int i, const int c0,
                                                  const int row0, const int cnt) {
@@ -281,14 +281,33 @@ __device__ __forceinline__ void skinny_wave_unit(const SkinnyArgs& a, const int 
       for (int f = 0; f < 2; ++f)
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) acc[f][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (NTB == 1) {
+        // Starting at quarter w, which spreads the waves over the memory channels; added in order.
+        f32x4 p0[2], p1[2], p2[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) p0[f] = p1[f] = p2[f] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-      for (int qt = 0; qt < kSplitWaves; ++qt) {
-        f32x4 part[2][NTB];
-        quarter(part, qt);
+        for (int v = 0; v < kSplitWaves; ++v) {
+          const int qt = (w + v) & (kSplitWaves - 1);
+          f32x4 part[2][1];
+          quarter(part, qt);
+          if (qt == 0) { p0[0] = part[0][0]; p0[1] = part[1][0]; }
+          else if (qt == 1) { p1[0] = part[0][0]; p1[1] = part[1][0]; }
+          else if (qt == 2) { p2[0] = part[0][0]; p2[1] = part[1][0]; }
+          else { acc[0][0] = part[0][0]; acc[1][0] = part[1][0]; }
+        }
 #pragma unroll
-        for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < 2; ++f) { p0[f] += p1[f]; p0[f] += p2[f]; acc[f][0] = p0[f] + acc[f][0]; }
+      } else {
+#pragma unroll 1
+        for (int qt = 0; qt < kSplitWaves; ++qt) {
+          f32x4 part[2][NTB];
+          quarter(part, qt);
 #pragma unroll
-          for (int tb = 0; tb < NTB; ++tb) acc[f][tb] += part[f][tb];
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) acc[f][tb] += part[f][tb];
+        }
       }
 #pragma unroll
       for (int tb = 0; tb < NTB; ++tb) {
