@@ -1419,24 +1419,33 @@ static hipError_t launch_small(K kern, bool& attr_done, long long grid, hipStrea
   return hipGetLastError();
 }
 
-// Which geometry a bf16 call past decode size takes.  Measured (expert-network calls, schedule included, one
-// MI355X; big -> small, us): below 1.7 big up tiles per compute unit the small form wins because it fills the
-// chip and needs no schedule (1024 wide, 32 experts: 47 -> 30 at 256 tokens, 62 -> 50 at 777, 115 -> 88 at
-// 2500; backward 138 -> 94 at 777, 230 -> 206 at 2500; 2048 wide, 24 experts: 139 -> 103 at 1024), around 1.75
-// the two are even (124 -> 124 with 268 -> 265 backward, 146 -> 149 with 315 -> 323), above the big tile's
-// reuse of its operands wins (228 -> 279 at 2.25).  A forward call of a few rows
-// per expert streams weights either way; there the small form is ahead however many tiles there are
-// (192 -> 176 at 47 rows, 180 -> 165 at 15 rows, 128 experts; 264 -> 252 at 6 rows, d = 2560) except with
-// the longest reductions, where the big tile's deeper prefetch counts (d = 4096: 359 -> 410 at 3 rows,
-// 427 -> 439 at 10).
+// Which geometry a bf16 call past decode size takes.  Small tiles fill the chip, need no schedule launch and overlap one
+// workgroup's ends with the other's stages; big ones move half the operand bytes per FLOP.  The measure is the work
+// per compute unit in stages of a big tile, both projections, for evenly spread rows.  Time small / big over 17 layer
+// shapes (d = 768 to 8192, 8 to 128 experts, 4 to 1024 rows per expert), even and skewed routing:
+//   one row tile per expert in either form (up to 112 rows; at 128 half of the experts need two small ones), weights to
+//     move and little else:      forward up to 180 stages 0.50 to 1.01, mean 0.75, above 0.86 to 1.07, mean 1.00;
+//     backward up to 130 stages 0.41 to 1.08, mean 0.77, above 0.81 to 1.15, mean 1.00
+//   more rows, up to 80 stages:  forward 0.44 to 1.14, mean 0.77, backward 0.40 to 1.09, mean 0.78
+//              above:            forward 0.79 to 1.29, mean 1.07, backward 0.81 to 1.23, mean 1.08
+//     but above 48 where several big row tiles are nine tenths full (d = 2048, 24 experts x 500 rows: 188 -> 205 us)
+// The mean cost of a wrong choice is 0.9 % forward, 1.3 % backward (the largest, 1.14, where 576 up tiles start a second
+// round on 512 slots: d = 4096, 24 experts x 144 rows).  From 1.7 big up tiles per compute unit on the big form has no
+// idle units to lose to (d = 1024, 32 experts, 768 rows: 122 -> 127 us); that limit alone, whatever the length
+// of the reduction, cost 1.7 and 2.2 %, up to 1.29.
 bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
   if (o.small >= 0) return o.small != 0;
-  const int rows = L.P > L.Ne ? L.P / L.Ne : 1;           // per expert if they were spread evenly
-  long long tiles = 0;                                     // big up tiles then
-  for (int g = 0; g < L.Ng; ++g)
-    tiles += (long long)L.N * ((rows + kBM - 1) / kBM) * ((L.F[g] + kBN / 2 - 1) / (kBN / 2));
-  if (10 * tiles < 17 * (long long)tile_num_cus()) return true;
-  return !backward && rows <= 64 && L.d <= 2560;
+  const long long rows = L.P > L.Ne ? L.P / L.Ne : 1;     // per expert if they were spread evenly
+  long long big = 0, stages = 0;                          // big up tiles; stages of all big tiles
+  for (int g = 0; g < L.Ng; ++g) {
+    const long long blocks = L.N * ((rows + kBM - 1) / kBM), ut = (L.F[g] + kBN / 2 - 1) / (kBN / 2);
+    big += blocks * ut;
+    stages += blocks * (ut * (L.d / kBK) + (L.d + kBN - 1) / kBN * (long long)(L.F[g] / kBK));
+  }
+  const long long cus = tile_num_cus();
+  if (!backward && rows <= 112) return stages <= 180 * cus;
+  const bool full = rows > kBM && 10 * rows >= 9 * kBM * ((rows + kBM - 1) / kBM);
+  return 10 * big < 17 * cus && stages <= (rows <= 112 ? 130 : full ? 48 : 80) * cus;
 }
 
 hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,

@@ -60,6 +60,34 @@ def test_small_tiles_equal_big_tiles(d, d_ff):
     assert np.abs(got - want).max() <= 8e-3 * np.abs(want).max()
 
 
+@pytest.mark.parametrize("forward,backward", [(1, 0), (0, 1)])
+def test_forward_and_backward_in_different_forms(forward, backward):
+    """The two rules differ, so a layer may run its forward in small tiles and its backward in big ones: what the forward
+    keeps is the same in either form."""
+    from paper_2604_23108_amd import bench_binding as BB
+    from gpu_harness import DeviceLayer, to_dev
+    w = Workload("mixed_forms", T=333, d=192, n_groups=2, experts_per_group=4, d_ff=(320, 64), k_groups=2, k_experts=4,
+                 seed=59, training=True)
+    inp = generate(w)
+    dl = DeviceLayer(w, inp, backward=True, guard=True)
+    L, dy = dl.layer, to_dev(inp.dy, True)
+    outs = []
+    for f, b in ((forward, backward), (0, 0)):
+        for t in [L.y, L.dx, L.dx_perm, *L.dw13, *L.dw2]:
+            t.fill_(float("nan"))
+        L.saved.fill_(0xFF)
+        print(f"[mixed forms] forward small={f} backward small={b}", flush=True)
+        L.ffn_options = BB.FfnOptions(small_tiles=f)
+        L.forward(dl.x)
+        L.ffn_options = BB.FfnOptions(small_tiles=b)
+        L.backward(dl.x, dy)
+        torch.cuda.synchronize()
+        dl.check_guards()
+        outs.append([t.clone() for t in [L.y, L.dx, *L.dw13, *L.dw2, L.dw_expert]])
+    for a, b in zip(*outs):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b)
+
+
 @pytest.mark.parametrize("with_perm", [True, False])
 def test_backward_of_a_call_without_tokens(with_perm):
     """T = 0 is a valid call: the weight gradients are sums over no rows, zeros."""
