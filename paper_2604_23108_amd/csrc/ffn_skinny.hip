@@ -656,13 +656,16 @@ void skinny_args(const LayerDesc& L, const void* x, const int32_t* perm, const i
   dn.blk_prefix[kMaxGroups] = nd;
 }
 
-// FP8 weights: the split kernel while a wave per 32 weight rows of the experts that can have rows would be
-// fewer than 1200 waves (not five per compute unit), or fewer than 2500 with at most two rows per expert.
+// FP8 weights: which kernel.  `waves` is what a wave per 32 weight rows of the experts that can have rows gives the
+// staged kernel's up projection.  Split / staged time over 17 layer shapes, 1 to 32 tokens: below 1200 waves (not five per
+// compute unit) 0.50 to 0.99; with fewer rows than experts (one row in each expert that has any) 0.50 to 1.00 up to 2500 and to 1.21
+// beyond; with one row per expert on average 0.81 to 0.89 up to 1600, 1.08 at 1900; with more 0.81 to 1.07 around 1500, 1.02
+// to 1.27 from 1900 on.  (Skewed routing favours the split kernel throughout: 0.43 to 1.02.)
 static bool fp8_split(const LayerDesc& L) {
   long long f = 0;
   for (int g = 0; g < L.Ng; ++g) f += L.F[g];
   const long long waves = (L.P < L.Ne ? L.P : L.Ne) * (f / L.Ng) / 16;
-  return waves < 1200 || (waves < 2500 && L.P <= 2 * L.Ne);
+  return waves < (L.P < L.Ne ? 2500 : L.P == L.Ne ? 1600 : 1200);
 }
 
 hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* perm,
