@@ -462,20 +462,22 @@ __device__ __forceinline__ void async_copy16(const void* gptr, void* lds_uniform
 
 // The same copy for the modes with transposing LDS reads, as instructions the compiler does not model: in
 // front of a transposing read (an intrinsic) it waits for every modelled copy to LDS, whatever part that
-// copy fills, i.e. for all stages on their way, once per stage.  M0 holds the LDS destination (one wait
-// state before its use).  Both address forms write no register; completion is awaited by the explicit
-// vmcnt waits of the stages, as for the copies above.
-// lds_offset: byte offset in the workgroup's LDS, wave-uniform (the kernels have no static LDS, so the
-// dynamic buffer starts at 0).  Nothing else in these kernels uses M0.
-__device__ __forceinline__ void async_copy16_unmodelled(const void* gptr, int lds_offset) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               ::"v"(gptr), "s"(__builtin_amdgcn_readfirstlane(lds_offset)) : "memory");
+// copy fills, i.e. for all stages on their way, once per stage.  M0 holds the LDS destination; the compiler puts it
+// there (an operand bound to the register, so it knows what M0 holds before and after); five wait states cover any
+// way in which it or the base registers may have been written.  Both address forms write no register; completion
+// is awaited by the explicit vmcnt waits of the stages, as for the copies above.
+// lds_addr: address in the workgroup's LDS (lds_address() of the buffer plus an offset), wave-uniform.
+__device__ __forceinline__ int lds_address(const unsigned char* lds) {
+  return (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)lds;
 }
-// wave-uniform base, 32-bit byte offset per lane (half the registers).  (Wait states: one between M0 and its
-// use, five if the base registers were written by the vector unit.)
-__device__ __forceinline__ void async_copy16_unmodelled(const void* uniform_base, uint32_t offset, int lds_offset) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
-               ::"v"(offset), "s"(uniform_base), "s"(__builtin_amdgcn_readfirstlane(lds_offset)) : "memory");
+__device__ __forceinline__ void async_copy16_unmodelled(const void* gptr, int lds_addr) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, off"
+               ::"v"(gptr), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
+}
+// wave-uniform base, 32-bit byte offset per lane (half the registers)
+__device__ __forceinline__ void async_copy16_unmodelled(const void* uniform_base, uint32_t offset, int lds_addr) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
+               ::"v"(offset), "s"(uniform_base), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 
 #define MOHGE_PIN() __builtin_amdgcn_sched_barrier(0)
@@ -712,29 +714,30 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     if constexpr (WG) return t + trow0 < ntok ? p : zsrc;
     else return p;
   };
+  const int lds0 = lds_address(lds);
   auto issue_a = [&](int stage, int j) {
     if constexpr (DG) {
       const uint16_t* base = a.A + (unsigned long long)(unsigned)(rec.row_start + first_row(j)) * (unsigned)a.lda;
-      async_copy16_unmodelled(base + stage * BK, off_a[j], (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
+      async_copy16_unmodelled(base + stage * BK, off_a[j], lds0 + (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
       return;
     }
     const uint16_t* src;
     if constexpr (TRA) src = tr_src(src_a[0], a.lda, stage, j);
     else src = src_a[j] + stage * BK;
-    if constexpr (TRA || TRB) async_copy16_unmodelled(src, (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
+    if constexpr (TRA || TRB) async_copy16_unmodelled(src, lds0 + (int)(a_part(stage) - lds) + j * NWAVES * 1024 + ld_off);
     else async_copy16(src, a_part(stage) + j * NWAVES * 1024 + ld_off);
   };
   auto issue_b = [&](int stage, int slot, int j) {
     if constexpr (DG) {
       const unsigned t = stage * BK + TPL * NWAVES * j;           // row of this load, less trow0
       async_copy16_unmodelled(base_b + (unsigned long long)t * tr_ldb, off_b,
-                              (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
+                              lds0 + (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
       return;
     }
     const uint16_t* src;
     if constexpr (TRB) src = tr_src(src_b[0], tr_ldb, stage, j);
     else src = src_b[j] + stage * BK;
-    if constexpr (TRA || TRB) async_copy16_unmodelled(src, (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
+    if constexpr (TRA || TRB) async_copy16_unmodelled(src, lds0 + (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
     else async_copy16(src, b_part(slot) + j * NWAVES * 1024 + ld_off);
   };
 
