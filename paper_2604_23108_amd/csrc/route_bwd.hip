@@ -364,19 +364,20 @@ __global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a,
 // token splits of the weight-gradient reduction: enough for three workgroups per compute unit, at least
 // 32 tokens each (8 per wave: shorter stretches cost more in partial sums than they save in MFMAs), at
 // most 256 splits and at most 64 MB of partial sums.  A wide layer has its workgroups without many splits, but the
-// fp32 chain of a wave's tokens is what the rounding error grows with: a wave takes 48 tokens at most (a quarter of
-// a split), more only where 256 chains of 64 or 64 MB of partial sums would not cover the call either.  (d = 4096, 68
-// router rows, 8192 tokens: 20 splits, error against float64 1.52e-7; with the 8 that fill the compute units 2.16e-7,
-// and the whole call 249 us instead of 274.)
+// fp32 chain of a wave's tokens is what the rounding error grows with (half its length, and an eighth of the splits in
+// the final sum): no worse than chains of 64 tokens, at most 256 of them or 64 MB, added by eight threads each, which
+// takes a little over a quarter of their number, four waves to a split.  (d = 4096, 68 router rows, 8192 tokens: 16
+// splits, error against float64 1.64e-7 and 253 us for the call; with the 8 that fill the compute units 2.16e-7, 243 us.)
 static int wgrad_splits(const LayerDesc& L) {
   const long long per_split = (long long)((L.d + 127) / 128) * ((L.Ng + L.Ne + kZC - 1) / kZC);
   const long long cap = (64ll << 20) / ((long long)(L.Ng + L.Ne) * L.d * 4);
   long long s = (768 + per_split - 1) / per_split;
-  if (s > (L.T + 31) / 32) s = (L.T + 31) / 32;
   long long chains = (L.T + 63) / 64;
   if (chains > cap) chains = cap;
   if (chains > 256) chains = 256;
-  if (s < (chains + 2) / 3) s = (chains + 2) / 3;
+  const long long least = (chains + 3) / 4 + 1;
+  if (s < least) s = (least + s - 1) / s * s;             // (whole rounds of workgroups)
+  if (s > (L.T + 31) / 32) s = (L.T + 31) / 32;
   if (s > cap) s = cap;
   if (s > 256) s = 256;
   return s < 1 ? 1 : (int)s;
