@@ -89,7 +89,7 @@ hipError_t launch_combine(const LayerDesc& L, int dtype, const void* y_perm,
   const int vec_per_row = L.d * (bf ? 2 : 4) / 16;
   const long long total = (long long)L.T * vec_per_row;
   long long blocks = (total + 255) / 256;
-  if (blocks > 256 * 64) blocks = 256 * 64;
+  if (blocks > 1ll << 23) blocks = 1ll << 23;      // (a cap of 64 workgroups per compute unit cost 3 to 10 % from 16384 tokens on)
   if (bf)
     hipLaunchKernelGGL((combine_kernel<true>), dim3((unsigned)blocks), dim3(256), 0, s,
                        static_cast<const uint4*>(y_perm), inv_perm, gates,
