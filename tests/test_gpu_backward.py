@@ -205,11 +205,18 @@ def test_route_backward_fp32_chain_and_aux_terms():
     assert (L.dz == 0).all() and (L.dw_expert == 0).all() and (L.dx == 0).all()
 
 
-def test_training_forward_and_backward_determinism():
+@pytest.mark.parametrize("small_tiles", [-1, 0])
+def test_training_forward_and_backward_determinism(small_tiles):
+    from paper_2604_23108_amd import bench_binding as BB
     w = _medium(SELECT_PER_GROUP, 35, T=200)
     inp = generate(w)
     dl, fwd, dy = _run_backward(w, inp)
     L = dl.layer
+    # the tile form this size gets, and the one whose workgroups draw their tiles
+    L.ffn_options = None if small_tiles else BB.FfnOptions(small_tiles=0)
+    L.forward(dl.x)
+    L.backward(dl.x, dy)
+    assert np.array_equal(from_dev(L.y), fwd["y"])
     # the training forward gives the same y as the inference forward, bit for bit
     dl2 = DeviceLayer(w, inp, training=False)
     out2 = dl2.run()
@@ -408,7 +415,8 @@ def test_fused_status_reports_a_tile_that_gave_up_waiting():
     forward, backward); with the test hook that makes every dependent tile give up without
     looking (the host forces the condition, the kernels run to their normal end) it reports
     MOHGE_ETIMEOUT for each of them and the outputs hold NaN instead of numbers; afterwards
-    everything is back to normal and bit-identical."""
+    everything is back to normal and bit-identical, in the fused form and in the small tiles that calls of this
+    size take by themselves (nothing waits there: they leave the flag clear)."""
     import paper_2604_23108_amd as M
     from paper_2604_23108_amd import bench_binding as BB
     w = WORKLOADS["training"].replace(T=1500, d=512, d_ff=(128, 256, 384), seed=97)
@@ -427,6 +435,7 @@ def test_fused_status_reports_a_tile_that_gave_up_waiting():
 
     ws_inf = torch.empty(M.mohge_workspace_size(dl.cfg, M.CALL_EXPERT_FFN), dtype=torch.uint8, device="cuda")
     y_inf = torch.empty_like(L.y_perm)
+    L.ffn_options = BB.FfnOptions(fused=1, small_tiles=0)
     step()
     ref = (L.y.clone(), L.dx.clone(), [t.clone() for t in L.dw13])
     for call, ws in calls + ((M.CALL_EXPERT_FFN, lambda: ws_inf),):
@@ -441,13 +450,17 @@ def test_fused_status_reports_a_tile_that_gave_up_waiting():
     n = dl.cfg.n_pairs
     assert torch.isnan(y_inf[:n].float()).all() and torch.isnan(L.y.float()).all()
     assert torch.isnan(L.dx_perm[:n].float()).all()
-    L.ffn_options = None
-    step()
-    for call, ws in calls + ((M.CALL_EXPERT_FFN, lambda: ws_inf),):
-        assert M.mohge_fused_status(dl.cfg, call, ws()) == 0, call
-    assert torch.equal(L.y, ref[0]) and torch.equal(L.dx, ref[1])
-    for a, b in zip(L.dw13, ref[2]):
-        assert torch.equal(a, b)
+    for small in (0, -1):
+        L.ffn_options = BB.FfnOptions(spin_limit=-1)
+        step()
+        assert M.mohge_fused_status(dl.cfg, M.CALL_FFN_SAVED, L.saved) == -6
+        L.ffn_options = BB.FfnOptions(fused=1, small_tiles=small)
+        step()
+        for call, ws in calls + ((M.CALL_EXPERT_FFN, lambda: ws_inf),):
+            assert M.mohge_fused_status(dl.cfg, call, ws()) == 0, call
+        assert torch.equal(L.y, ref[0]) and torch.equal(L.dx, ref[1])
+        for a, b in zip(L.dw13, ref[2]):
+            assert torch.equal(a, b)
     # calls without such a launch answer at once
     wd = WORKLOADS["decode"].replace(T=8, d=512, d_ff=(128, 256, 384, 512), seed=98)
     cd = M.Config.from_workload(wd)

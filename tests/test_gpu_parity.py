@@ -470,26 +470,40 @@ def test_element_offsets_beyond_2_31():
     print(f"[big offsets] {n} y_perm rows compared", flush=True)
 
 
-def test_graph_replay_matches_eager():
+@pytest.mark.parametrize("backward", [False, True])
+@pytest.mark.parametrize("small_tiles", [-1, 0])
+def test_graph_replay_matches_eager(small_tiles, backward):
     # a captured step replayed several times, with eager work and synchronisations in between,
-    # must reproduce the eager result bit for bit on every replay
-    w = WORKLOADS["mid_prefill"].replace(T=1500, d=512, d_ff=(128, 256, 384))
+    # must reproduce the eager result bit for bit on every replay: with the tile form this size gets (two plain
+    # launches) and with the one whose schedule and counters have to start afresh on every replay
+    from gpu_harness import to_dev
+    from paper_2604_23108_amd import bench_binding as BB
+    w = WORKLOADS["mid_prefill"].replace(T=1500, d=512, d_ff=(128, 256, 384), training=backward)
     inp = generate(w)
     DeviceLayer = _dev()
-    dl = DeviceLayer(w, inp, training=False)
+    dl = DeviceLayer(w, inp, backward=backward)
     L = dl.layer
-    print(f"[graph] workload {w.name} T={w.T}", flush=True)
-    y_eager = L.forward(dl.x).clone()
-    idx_eager = L.expert_idx.clone()
+    dy = to_dev(inp.dy, True) if backward else None
+    L.ffn_options = None if small_tiles else BB.FfnOptions(small_tiles=0)
+    print(f"[graph] workload {w.name} T={w.T} small_tiles={small_tiles} backward={backward}", flush=True)
+
+    def results():
+        return [L.y, L.expert_idx] + ([L.dx, L.dw_group, L.dw_expert, *L.dw13, *L.dw2] if backward else [])
+
+    L.forward(dl.x)
+    if backward:
+        L.backward(dl.x, dy)
+    eager = [t.clone() for t in results()]
     torch.cuda.synchronize()
-    L.capture(dl.x)
+    L.capture(dl.x, dy)
     other = DeviceLayer(w.replace(seed=77), generate(w.replace(seed=77)), training=False)
     for i in range(4):
-        L.y.zero_(); L.expert_idx.zero_(); L.y_perm.zero_()
+        for t in results() + [L.y_perm]:
+            t.zero_()
         L.replay()
         torch.cuda.synchronize()
-        assert torch.equal(L.y, y_eager), f"replay {i}"
-        assert torch.equal(L.expert_idx, idx_eager)
+        for a, b in zip(results(), eager):
+            assert torch.equal(a, b), f"replay {i}"
         other.layer.forward(other.x)            # unrelated eager work between the replays
         torch.cuda.synchronize()
 
