@@ -93,8 +93,8 @@ typedef struct mohge_config {
  * slices (error about 1e-7).
  * workspace DEVICE, optional (NULL / 0 allowed), mohge_workspace_size(cfg, MOHGE_CALL_ROUTE) bytes
  * (0 where it has no use).  Without it the logits come from the fp32 matrix cores, one workgroup
- * per 16 tokens.  With it, two other forms are chosen by size: for few tokens (decode) the
- * reduction over d is spread over many workgroups, which leave partial sums there; from 8192
+ * per 16 tokens.  With it, two other forms are chosen by size: up to 2048 tokens the
+ * reduction over d is spread over several workgroups, which leave partial sums there; from 8192
  * bf16 tokens on, the router rows are first split there into three bf16 parts that add up to the
  * fp32 weight exactly, and the logits come from the bf16 matrix cores with exact products.  The
  * logits of the forms can differ in the last bit (the fp64 partial sums are grouped
@@ -152,8 +152,11 @@ int mohge_permute_static(const mohge_config* cfg, const int32_t* expert_idx, int
  * workspace DEVICE, at least mohge_workspace_size(cfg, MOHGE_CALL_EXPERT_FFN) bytes;
  * it holds h between the two projections.
  * bf16: products on the matrix cores with fp32 accumulation; h and y_perm are
- * rounded to bf16 once each.  fp32: plain fp32 arithmetic.
- * Residency: for bf16 and T > 32 both projections run as ONE persistent launch of one workgroup
+ * rounded to bf16 once each.  fp32: products on the fp32 matrix cores, sixteen at a time added in
+ * fp32 and their sums in fp64; h and y_perm are rounded to fp32 once each.
+ * Residency: for bf16 and T > 32 the call takes one of two forms by size, with the same bits.  Where
+ * tiles of 256 x 256 would leave compute units idle, each projection is a launch of 128 x 128 tiles and nothing
+ * waits inside it.  Otherwise both projections run as ONE persistent launch of one workgroup
  * per compute unit, in which the down-projection tiles of a row block wait until its
  * up-projection tiles are complete.  The tiles waited for are always in the hands of workgroups
  * that never wait themselves, so the launch finishes on a GPU of its own and also when another
@@ -172,7 +175,7 @@ int mohge_expert_ffn(const mohge_config* cfg, const void* x, const int32_t* perm
  * inside is the library's; MOHGE_EWORKSPACE if h_bytes is smaller, in either call);
  * mohge_expert_ffn_down reads it and writes y_perm.
  * mohge_expert_ffn(…, workspace) computes exactly up(…, workspace) followed by down(workspace, …)
- * (on the matrix-core path as one launch instead of two, with the same bits).
+ * (on the matrix-core path of many tokens as one launch instead of two, with the same bits).
  */
 int mohge_expert_ffn_up(const mohge_config* cfg, const void* x, const int32_t* perm,
                         const int32_t* offsets, const void* const* w13, void* h, size_t h_bytes,
@@ -387,7 +390,7 @@ int mohge_route_bwd(const mohge_config* cfg, const void* x, const float* w_group
 size_t mohge_workspace_size(const mohge_config* cfg, int which_call);
 
 /*
- * Diagnostic for the launches that run two dependent tile lists at once (the fused forms of
+ * Diagnostic for the launches that run two dependent tile lists at once (the one-launch forms of
  * mohge_expert_ffn, mohge_expert_ffn_train and mohge_expert_ffn_bwd): a tile of the second list
  * waits, for a bounded number of polls, until the tiles it depends on are complete; the design
  * guarantees they are already running, and a tile that gives up all the same writes NaN to its
@@ -397,7 +400,8 @@ size_t mohge_workspace_size(const mohge_config* cfg, int which_call);
  * MOHGE_CALL_FFN_SAVED the `saved` buffer) and returns MOHGE_OK, or MOHGE_ETIMEOUT when that
  * call's output holds NaN (MOHGE_CALL_DECODE_LAYER: also MOHGE_EINVAL when the counters in the
  * workspace were not zero at the start).
- * MOHGE_OK at once where the call has no such launch for cfg (fp32, decode sizes).
+ * MOHGE_OK at once where the call has no such launch for cfg (fp32, decode sizes); calls that take the form of
+ * 128 x 128 tiles wait for nothing and leave the flag clear.
  */
 int mohge_fused_status(const mohge_config* cfg, int which_call, const void* workspace,
                        size_t workspace_bytes, void* stream);

@@ -1062,8 +1062,7 @@ __global__ void __launch_bounds__(Shape<MODE>::THREADS) ffn_tile_kernel(const Ti
 // belongs to another XCD's range waits for tiles that were handed out there before any of
 // that XCD's down tiles.  The wait is bounded all the same (kSpinLimit polls, about a second);
 // if it ever expires the tile is computed regardless and a flag is left in the header of the
-// waiting list, which mohge_fused_status reports.  A negative limit (test hook, mohge_tune knob
-// 3) makes every dependent tile give up without looking.
+// waiting list, which mohge_fused_status reports.  A negative limit (test hook: mohge_ffn_options.spin_limit) makes every dependent tile give up without looking.
 constexpr int kSpinLimit = 1 << 22;
 
 // Output region of a tile of a token mode (rows x 256 columns of C) filled with bf16 NaNs.
@@ -1246,7 +1245,7 @@ __global__ void __launch_bounds__(Shape<M0>::THREADS) ffn_fused_kernel(const Til
 // small tiles: launches that would leave compute units idle with 256 x 256 tiles
 // ---------------------------------------------------------------------------------------
 // Bound by what the compute units draw from L2 and the last-level cache, twice the bytes per FLOP of a big tile:
-// a stage of both workgroups of a unit takes about 1.1 us, 15 TB/s over the chip.  More stages on the way do not
+// a stage of both workgroups of a unit takes about 1.1 us for its 64 KB, by the launch times 15 TB/s over the chip.  More stages on the way do not
 // help (operands through registers, three stages ahead: 50 -> 65 us for 777 tokens of a 1024-wide layer, 107 ->
 // 140 for 64 experts x 144 rows; one 256 x 128 tile per unit with all of the LDS: 107 -> 135); what helps is
 // that one workgroup's prologue and epilogue run under the other's stages.
@@ -1346,7 +1345,8 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_kernel(const TileA
 }
 
 // Backward, first launch: dH, and on the workgroups past its n_dh the rows of x in sorted order and the
-// row of zeros (kSmallGatherRows rows per workgroup, all loads of a wave's rows before the first store).
+// row of zeros (kSmallGatherRows rows per workgroup, four per wave: their loads are issued together, and the compiler keeps
+// three of the four pieces in private memory until their store, 80 bytes per lane).
 constexpr int kSmallGatherRows = 16;
 
 __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd1_kernel(const TileArgs dh, const GatherArgs ga, int n_dh) {

@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a,
 // token splits of the weight-gradient reduction: enough for three workgroups per compute unit, at least
 // 32 tokens each (8 per wave: shorter stretches cost more in partial sums than they save in MFMAs), at
 // most 256 splits and at most 64 MB of partial sums.  A wide layer has its workgroups without many splits, but the
-// fp32 chain of a wave's tokens is what the rounding error grows with (half its length, and an eighth of the splits in
+// fp32 chain of a wave's tokens is what the rounding error grows with (half its length, and a sixteenth of the splits in
 // the final sum): no worse than chains of 64 tokens, at most 256 of them or 64 MB, added by eight threads each, which
 // takes a little over a quarter of their number, four waves to a split.  (d = 4096, 68 router rows, 8192 tokens: 16
 // splits, error against float64 1.64e-7 and 253 us for the call; with the 8 that fill the compute units 2.16e-7, 243 us.)
