@@ -143,10 +143,10 @@ hipError_t launch_shared_routing(const LayerDesc& L, int32_t* expert_idx, float*
 // butterfly, so the result does not depend on scheduling.
 // Bound by memory: dy, K_e rows of y_perm and K_e rows of dy_perm per token.  NS slots at a time: dy is read once
 // for them and their rows of y_perm are in flight together (d = 4096, four slots: 24.4 -> 20.3 us at 1500 tokens,
-// 12.5 -> 6.8 at 100).  Past the 256 MB that the last-level cache holds one slot at a time is the faster walk, two rows
+// 12.5 -> 6.8 at 100).  Past what the last-level cache holds (256 MB) one slot at a time is the faster walk, two rows
 // read and one written at a time instead of five and four: at 8192 tokens 164 us against 171 to 181 with four slots,
 // 129 against 137 to 144 with three (inputs not in the cache; 131 against 154 to 165 when calls follow each
-// other); at 300 MB the forms are even, at 220 MB passes are 16 % ahead (2 % with inputs not in the cache).
+// other).  The line lies at 300 MB: at 302 million bytes four slots are still 3 to 6 % ahead, at 336 one slot 7 to 22 %.
 // ---------------------------------------------------------------------------------------
 namespace mohge {
 
@@ -205,7 +205,7 @@ hipError_t launch_combine_bwd(const LayerDesc& L, const void* dy, const void* y_
                               const int32_t* inv_perm, const float* gates, float* dgates,
                               void* dy_perm, hipStream_t s) {
   const int vec_per_row = L.d * 2 / 16;
-  const bool one = (long long)L.T * (2 * L.Ke + 1) * L.d * 2 > (256ll << 20);
+  const bool one = (long long)L.T * (2 * L.Ke + 1) * L.d * 2 > (300ll << 20);
   auto kern = one ? combine_bwd_kernel<1> : L.Ke % 4 == 0 ? combine_bwd_kernel<4> : L.Ke % 3 == 0 ? combine_bwd_kernel<3>
               : L.Ke % 2 == 0 ? combine_bwd_kernel<2> : combine_bwd_kernel<1>;
   hipLaunchKernelGGL(kern, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s,

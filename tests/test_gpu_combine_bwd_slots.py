@@ -1,5 +1,5 @@
 """The backward of the gated combine with one to four slots per pass (small calls) and slot after slot (calls past
-256 MB), against the definition."""
+300 MB), against the definition."""
 import pytest
 import torch
 
@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6])
-@pytest.mark.parametrize("T,d", [(1, 64), (7, 1088), (330, 576), (131072, 384)])
+@pytest.mark.parametrize("T,d", [(1, 64), (7, 1088), (330, 576), (131072, 448)])
 def test_combine_backward_slots(T, d, k):
     import paper_2604_23108_amd as M
     cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=8, d_ff=(64,), k_groups=1, k_experts=k,
