@@ -1,5 +1,5 @@
-"""The fp32 expert networks at the edges of their tiles (32 token rows, 64 weight rows, 64-deep
-stages), on a hand-made assignment of tokens to experts, against the CPU oracle."""
+"""The fp32 expert networks at the edges of their tiles (32 token rows, 128 weight rows, stages of 32
+indices), on a hand-made assignment of tokens to experts, against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -34,7 +34,7 @@ def test_ffn_f32_tile_edges(d, d_ff):
                              [t.f32 for t in inp.w_down], np.arange(T, dtype=np.int32), eidx.reshape(-1))
     got = L.y_perm.cpu().numpy()
     want = want[L.perm.cpu().numpy()]
-    # two fp32 dot products in chains of 8 with fp64 totals and the roundings between them: relative to the largest
+    # two fp32 dot products with a rounding per 8 products and the roundings between them: relative to the largest
     # output the error stays below 2^-24 * (8 + 16) with room to spare
     assert np.isfinite(got).all()
     assert np.abs(got - want).max() <= 5e-6 * np.abs(want).max()
@@ -44,10 +44,11 @@ def test_ffn_f32_tile_edges(d, d_ff):
                                     (4096, (768, 2048))])
 def test_ffn_f32_rounding_error(d, d_ff):
     """Error of the fp32 expert networks against float64, as a 2-norm.  A rounding costs 2.5e-8 rms
-    (2^-24 / sqrt(3), averaged over the mantissa).  A dot product in chains of eight products, added in pairs to an
-    fp64 total, carries the roundings of 4.5 + 1 + 1 of its values: 6.4e-8, whatever its length.  Both operands of
-    SiLU(a) b have it, the first amplified by up to 1.5, SiLU and the product add about four roundings, the second
-    projection its own: sqrt(6.4^2 (1 + 1.5^2) + 4 * 2.5^2 + 6.4^2) = 14e-8."""
+    (2^-24 / sqrt(3), averaged over the mantissa).  A dot product whose chains of 64 products round once per eight and
+    are added with compensation carries the roundings of 4.5 of its values and its own: 5.9e-8, whatever its length.
+    Both operands of SiLU(a) b have it, the first amplified by up to 1.5, the product is rounded once, the second
+    projection has its own: sqrt(5.9^2 (1 + 1.5^2) + 2.5^2 + 5.9^2) = 12.4e-8; the bound is that of four roundings
+    between the projections and 6.5 in them."""
     import paper_2604_23108_amd as M
     from gpu_harness import DeviceLayer
     T, n = 128, 2
@@ -71,6 +72,32 @@ def test_ffn_f32_rounding_error(d, d_ff):
     want = torch.cat(want)
     err = float((L.y_perm.cpu().double() - want).norm() / want.norm())
     assert err <= 1.5e-7, err
+
+
+def test_ffn_f32_operands_without_a_finite_bf16_part():
+    """An fp32 number near the largest one rounds to infinity in bf16, and infinities and NaN have no remainder: such sums
+    are evaluated again, and the rows beside them stay as they are."""
+    import paper_2604_23108_amd as M
+    T, d, F = 6, 192, 64
+    cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=1, d_ff=(F,), k_groups=1, k_experts=1,
+                   select_mode=M.SELECT_PER_GROUP, dtype=M.F32)
+    gen = torch.Generator().manual_seed(9)
+    x = torch.randn((T, d), generator=gen)
+    w13, w2 = torch.randn((1, 2 * F, d), generator=gen) * 0.1, torch.randn((1, d, F), generator=gen) * 0.1
+    w13[0, :, 70] *= 1e-37
+    x[1, 5], x[2, 150], x[3, 70], x[4] = float("inf"), float("nan"), 3.4e38, x[4] * 2.0 ** 55
+    a, b = (x.double() @ w13[0].double().T).split(F, dim=1)
+    want = (a * torch.sigmoid(a) * b) @ w2[0].double().T
+    offsets = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    y = torch.zeros((T, d), device="cuda")
+    ws = torch.empty(M.mohge_workspace_size(cfg, M.CALL_EXPERT_FFN), dtype=torch.uint8, device="cuda")
+    print("[f32 extremes]", flush=True)
+    M.mohge_expert_ffn(cfg, x.cuda(), None, offsets, [w13.cuda()], [w2.cuda()], y, ws)
+    y = y.cpu().double()
+    assert not torch.isfinite(y[1:3]).any()
+    for t in (0, 3, 4, 5):
+        # the bound of the error test above, per row of 192 values instead of over all of them
+        assert float((y[t] - want[t]).norm() / want[t].norm()) <= 3e-7, t
 
 
 def test_ffn_f32_more_workgroups_than_one_grid_dimension():
