@@ -94,163 +94,200 @@ __device__ __forceinline__ void fp4x8_to_bf16(const uint32_t c, const float scal
   o.u = make_uint4(p0.u, p1.u, p2.u, p3.u);
 }
 
-// FP8 weights with the reduction split over the four waves, like the bf16 kernel: a unit of the reduction is
-// 64 bytes of a weight row, lane (r, q) holds 16 codes of its row (two MFMA steps) and reads its token's
-// matching indices straight from L1/L2; weights run one step of four units ahead, tokens 128 indices.
-// Taken where few experts have rows (fp8_split): the staged kernel below then leaves compute units
-// idle or pays its staging for too few rows.  Up + down, staged -> split, us: d = 4096, 64 experts: 53 -> 25 at 1
-// token, 88 -> 72 at 4; d = 1024, 32 experts: 25.8 -> 23.4 at 7, 26.5 -> 24.6 at 32; 128 experts: 38 -> 28 at 4.
-// With many rows the token loads cost more than the staging (d = 4096: 187 -> 204 at 32 tokens), and so they do
-// for MXFP4 weights, whose 16-byte load needs four of them and a byte of scales (55 -> 107 at 7 tokens).
-template <bool UP>
-__global__ void __launch_bounds__(256, 3) ffn_skinny_fp8_split_kernel(const SkinnyArgs a, const int ncb) {
-  constexpr int UK = 64;                      // reduction indices per unit: 64 bytes of a weight row
+// Quantised weights (BITS = 8: FP8 E4M3, BITS = 4: MXFP4), split form: a wave has 2 x 16 weight rows and half of the
+// reduction, two waves side by side and two along it.  A unit of the reduction is 64 bytes of a weight row: lane (r, q) holds 16
+// bytes of its row, 16 (FP8) or 32 (MXFP4) consecutive indices, used as two or four MFMA steps.  Bound by the weight
+// stream, i.e. by the loads in flight.  With fewer bytes per weight, what is not weights has to stay out of
+// the vector memory path:
+//  - every wave stages its half of the tokens (16 per pass) in LDS of its own, in chunks sized to the token
+//    count, without a barrier, and reads them from there right before each MFMA; rows are padded by 16 bytes against
+//    bank conflicts and zero-filled past the reduction length;
+//  - MXFP4: a lane loads the block scales of one of the step's four units, and the lanes of a row exchange them (a scale
+//    byte per lane and block straight from memory is a 16-line request for 64 useful bytes);
+//  - the weights of the next step (4 units) are requested before the current one is converted and multiplied.
+// Token columns past the expert's count hold copies of its last staged token; MFMA columns are
+// independent and those outputs are never stored.
+// Up + down, us, at 1 / 4 / 12 tokens (before: staged kernel for MXFP4, staged or a split one with tokens straight from
+// memory for FP8): MXFP4 d = 4096 31 / 48 / 74 -> 21 / 38 / 83, d = 2560 41 / 48 / 80 -> 21 / 40 / 66, d = 1344 24 / 27 / 35 ->
+// 16 / 17 / 23; FP8 d = 4096 26 / 54 / 127 -> 26 / 53 / 120, d = 2048 16 / 27 / 38 -> 17 / 23 / 34.  A quarter of the reduction per
+// wave: 20 / 38 / 85 and 23 / 52 / 120 at d = 4096 but 17 / 23 / 45 for 17 / 22 / 37 at d = 1024 with 128 experts; all of it: 30 / 43 / 89
+// and 37 / 60 / 143.  Several column blocks per workgroup with the tokens kept: 24 / 57 / 136 (FP8, two) and registers spilled.
+constexpr int kWaveTokens = 8448;             // bytes of staged token rows per wave; three workgroups per compute unit
+constexpr int kWavePieces = 8192 / 16;        // ... less the padding of 16 rows, in 16-byte pieces
+constexpr int kQSplit = 2;                    // waves along the reduction
+
+template <bool UP, int BITS>
+__global__ void __launch_bounds__(256, 3) ffn_skinny_q_split_kernel(const SkinnyArgs a, const int ncb) {
+  static_assert(BITS == 4 || BITS == 8, "MXFP4 or FP8 codes");
+  constexpr int UK = 512 / BITS;              // reduction indices per unit: 64 bytes of a weight row
   constexpr int LK = UK / 4;                  // ... per lane
   constexpr int NJ = LK / 8;                  // MFMA steps per unit
   constexpr int U = 4;                        // units per step
-  constexpr int XG = 128 / UK;                // units whose token fragments are requested together
-  __shared__ f32x4 red[(kSplitWaves - 1) * 2 * 64];
+  __shared__ uint4 xs[kSplitWaves][kWaveTokens / 16];
+  __shared__ f32x4 red[kSplitWaves * 2 * 64];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, q = lane >> 4;
-  const int c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
+  const int kw = w % kQSplit;                      // this wave's part of the reduction
+  const int c0 = ((blockIdx.x % ncb) * (kSplitWaves / kQSplit) + w / kQSplit) * (UP ? 16 : 32);
   int e, row0, cnt;
   if (!expert_of_slot(a, blockIdx.x / ncb, e, row0, cnt)) return;
   const int g = e / a.N, i = e - g * a.N, F = a.F[g];
   const int K = UP ? a.d : F;
   const int ncols = UP ? F : a.d;
-  if (c0 >= ncols) return;
+  if ((int)(blockIdx.x % ncb) * (kSplitWaves / kQSplit) * (UP ? 16 : 32) >= ncols) return;
+  const bool active = c0 < ncols;             // (a wave past the last column meets the barriers)
   long long wrow[2];
   if constexpr (UP) {
-    wrow[0] = (long long)i * 2 * F + c0 + r;
-    wrow[1] = (long long)i * 2 * F + F + c0 + r;
+    wrow[0] = (long long)i * 2 * F + (active ? c0 : 0) + r;
+    wrow[1] = wrow[0] + F;
   } else {
-    int n1 = c0 + 16 + r;
-    if (n1 > a.d - 1) n1 = a.d - 1;
-    wrow[0] = (long long)i * a.d + c0 + r;
-    wrow[1] = (long long)i * a.d + n1;
+    wrow[0] = (long long)i * a.d + (active ? c0 : 0) + r;      // (d is a multiple of 64)
+    wrow[1] = wrow[0] + 16;
   }
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.W[g]);
-  const uint8_t* wp[2] = {wbase + wrow[0] * K + 16 * q, wbase + wrow[1] * K + 16 * q};
-  const int nu = K / UK;                      // (K is a multiple of 64)
-  const int ub = nu * w / kSplitWaves, ue = nu * (w + 1) / kSplitWaves;
-  auto load_w = [&](uint4 (&wq)[2][U], int u0) {
+  const uint8_t* wp[2] = {wbase + wrow[0] * (K * BITS / 8) + 16 * q, wbase + wrow[1] * (K * BITS / 8) + 16 * q};
+  const int nu = (K + UK - 1) / UK;           // (K is a multiple of 64: the last MXFP4 unit may be half a unit)
+  const int ub = nu * kw / kQSplit, ue = active ? nu * (kw + 1) / kQSplit : ub;
+  struct Step { uint4 w[2][U]; uint32_t s[2]; };
+  auto load_w = [&](Step& st, int u0, int n) {       // the first n units from u0 on
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
-        wq[f][u] = make_uint4(0u, 0u, 0u, 0u);
-        if (u0 + u < ue)
-          wq[f][u] = *reinterpret_cast<const uint4*>(wp[f] + (long long)(u0 + u) * 64);
+        st.w[f][u] = make_uint4(0u, 0u, 0u, 0u);
+        if (u < n && u0 + u < ue && (BITS == 8 || (u0 + u) * UK + LK * q < K))
+          st.w[f][u] = *reinterpret_cast<const uint4*>(wp[f] + (long long)(u0 + u) * 64);
       }
+    // block scales of unit u0 + q, all four lanes of the row (a scale of 1 past the end)
+    if constexpr (BITS == 4) {
+      const int nblk = K >> 5, b0 = 4 * (u0 + q);
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        st.s[f] = 0x7f7f7f7fu;
+        const uint8_t* sr = a.S4[g] + wrow[f] * nblk + b0;
+        if (u0 + q < ue) {
+          if (!(nblk & 3)) st.s[f] = *reinterpret_cast<const uint32_t*>(sr);
+          else st.s[f] = *reinterpret_cast<const uint16_t*>(sr) |                      // (an even number of blocks)
+                         (b0 + 2 < nblk ? (uint32_t)*reinterpret_cast<const uint16_t*>(sr + 2) << 16 : 0x7f7f0000u);
+        }
+      }
+    }
   };
 
   for (int tb0 = 0; tb0 < cnt; tb0 += 16) {
-    uint4 wc[2][U];
-    load_w(wc, ub);
-    const int tt = tb0 + r;
-    const bool xv = tt < cnt;
-    const int pos = row0 + (xv ? tt : 0);
-    long long src;
-    if constexpr (UP) src = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
-    else src = pos;
-    const uint16_t* const xp = a.A + src * a.lda + LK * q;
-    auto load_x = [&](Frag (&xf)[XG][NJ], int u0) {
-#pragma unroll
-      for (int u = 0; u < XG; ++u)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-          xf[u][j].u = make_uint4(0u, 0u, 0u, 0u);
-          if (xv && u0 + u < ue)
-            xf[u][j].u = *reinterpret_cast<const uint4*>(xp + (u0 + u) * UK + 8 * j);
-        }
-    };
-    Frag xc[XG][NJ];
-    load_x(xc, ub);
+    const int ns = min(cnt - tb0, 16);        // tokens of this pass
+    // units per chunk whose ns token rows fit this wave's buffer, and per step: whole steps of U units, or a chunk of
+    // fewer (two or one with many tokens) is a step of its own
+    int cu = (ue - ub + U - 1) / U * U;
+    while (cu > 1 && (ns * (cu * UK * 2 + 16) > kWaveTokens || ns * cu * (UK / 8) > kWavePieces))
+      cu = cu > U ? cu / 2 / U * U : cu / 2;
+    const int su = min(cu, U);
+    Step cur;
+    load_w(cur, ub, su);
+    const int pitch = cu * UK * 2 + 16;
+    unsigned char* const lds = reinterpret_cast<unsigned char*>(xs[w]);
+    const unsigned char* const xrow = lds + (r < ns ? r : ns - 1) * pitch + 2 * LK * q;
     f32x4 acc[2];
     acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
     acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int u0 = ub; u0 < ue; u0 += U) {
-      uint4 wn[2][U];
-      load_w(wn, u0 + U);
+    for (int uc = ub; uc < ue; uc += cu) {
+      // Staging, with every load issued before the first store (LDS operations of a wave complete in order: nobody
+      // else reads this buffer)
+      const int ppr = min(cu, ue - uc) * (UK / 8);          // 16-byte pieces per token row
+      const int npieces = ns * ppr;                         // at most kWavePieces
+      uint4 tv[kWavePieces / 64];
 #pragma unroll
-      for (int ug = 0; ug < U; ug += XG) {
-        Frag xn[XG][NJ];
-        load_x(xn, u0 + ug + XG);
+      for (int it = 0; it < kWavePieces / 64; ++it) {
+        const int idx = lane + 64 * it;
+        tv[it] = make_uint4(0u, 0u, 0u, 0u);
+        if (idx < npieces) {
+          const int rr = idx / ppr, k = uc * UK + 8 * (idx - rr * ppr);
+          if (BITS == 8 || k < K) {
+            const int pos = row0 + tb0 + rr;
+            long long src;
+            if constexpr (UP) src = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
+            else src = pos;
+            tv[it] = *reinterpret_cast<const uint4*>(a.A + src * a.lda + k);
+          }
+        }
+      }
 #pragma unroll
-        for (int x = 0; x < XG; ++x) {
-          const int u = ug + x;
-          if (u0 + u < ue) {                  // wave-uniform
+      for (int it = 0; it < kWavePieces / 64; ++it) {
+        const int idx = lane + 64 * it;
+        if (idx < npieces) {
+          const int rr = idx / ppr;
+          *reinterpret_cast<uint4*>(lds + rr * pitch + 16 * (idx - rr * ppr)) = tv[it];
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int uend = min(uc + cu, ue);
+      for (int u0 = uc; u0 < uend; u0 += su) {
+        Step next;
+        load_w(next, u0 + su, su);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (u < su && u0 + u < uend) {                // wave-uniform
+            const unsigned char* xu = xrow + (u0 - uc + u) * (UK * 2);
+            Frag xf[NJ];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) xf[j].u = *reinterpret_cast<const uint4*>(xu + 16 * j);
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-              Frag wlo, whi;
-              fp8x16_to_bf16(wc[f][u], wlo, whi);
-              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, xc[x][0].v, acc[f], 0, 0, 0);
-              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, xc[x][1].v, acc[f], 0, 0, 0);
+              if constexpr (BITS == 4) {
+                const uint32_t s4 = __builtin_amdgcn_ds_bpermute(4 * (16 * u + r), cur.s[f]);
+                const float scale = e8m0_to_f32((s4 >> (8 * q)) & 255u);
+                const uint32_t cw[4] = {cur.w[f][u].x, cur.w[f][u].y, cur.w[f][u].z, cur.w[f][u].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                  Frag wf;
+                  fp4x8_to_bf16(cw[j], scale, wf);
+                  acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf.v, xf[j].v, acc[f], 0, 0, 0);
+                }
+              } else {
+                Frag wlo, whi;
+                fp8x16_to_bf16(cur.w[f][u], wlo, whi);
+                acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, xf[0].v, acc[f], 0, 0, 0);
+                acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, xf[1].v, acc[f], 0, 0, 0);
+              }
             }
           }
         }
-#pragma unroll
-        for (int x = 0; x < XG; ++x)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) xc[x][j] = xn[x][j];
+        cur = next;
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int f = 0; f < 2; ++f) wc[f][u] = wn[f][u];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    if (w > 0)
+    if (kw > 0)
 #pragma unroll
-      for (int f = 0; f < 2; ++f) red[((w - 1) * 2 + f) * 64 + lane] = acc[f];
+      for (int f = 0; f < 2; ++f) red[(w * 2 + f) * 64 + lane] = acc[f];
     __syncthreads();
-    if (w == 0) {
+    const int tt = tb0 + r;
+    if (kw == 0 && active) {
 #pragma unroll
       for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int ww = 0; ww < kSplitWaves - 1; ++ww) acc[f] += red[(ww * 2 + f) * 64 + lane];
+        for (int ww = 1; ww < kQSplit; ++ww) acc[f] += red[((w + ww) * 2 + f) * 64 + lane];
       // lane holds token r of the pass, weight rows 4q..4q+3 of each row set
-      // FP8: the scale of the weight row of accumulator element b multiplies the sum
+      if constexpr (BITS == 8) {
+        // FP8: the scale of the weight row of accumulator element b multiplies the sum
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          long long row;
-          if constexpr (UP) row = (long long)i * 2 * F + (long long)f * F + c0 + 4 * q + b;
-          else {
-            int n = c0 + 16 * f + 4 * q + b;
-            if (n > a.d - 1) n = a.d - 1;
-            row = (long long)i * a.d + n;
-          }
-          acc[f][b] *= a.S[g][row];
-        }
-      if (xv) {
-        uint16_t* crow = a.C + (long long)(row0 + tt) * a.ldc;
-        if constexpr (UP) {
-          float v[4];
+        for (int f = 0; f < 2; ++f)
 #pragma unroll
           for (int b = 0; b < 4; ++b) {
-            const float gt = acc[0][b], up = acc[1][b];
-            v[b] = gt / (1.f + __expf(-gt)) * up;
-          }
-          uint2 o;
-          o.x = pack_bf16x2(v[0], v[1]);
-          o.y = pack_bf16x2(v[2], v[3]);
-          *reinterpret_cast<uint2*>(crow + c0 + 4 * q) = o;
-        } else {
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            const int col = c0 + 16 * f + 4 * q;
-            if (col < ncols) {
-              uint2 o;
-              o.x = pack_bf16x2(acc[f][0], acc[f][1]);
-              o.y = pack_bf16x2(acc[f][2], acc[f][3]);
-              *reinterpret_cast<uint2*>(crow + col) = o;
+            long long row;
+            if constexpr (UP) row = (long long)i * 2 * F + (long long)f * F + c0 + 4 * q + b;
+            else {
+              int n = c0 + 16 * f + 4 * q + b;
+              if (n > a.d - 1) n = a.d - 1;
+              row = (long long)i * a.d + n;
             }
+            acc[f][b] *= a.S[g][row];
           }
-        }
       }
+      if (tt < cnt) skinny_store<UP, false>(a, c0, q, ncols, row0 + tt, acc[0], acc[1]);
     }
-    __syncthreads();                          // the sums have been read
+    __syncthreads();                           // the sums have been read
   }
 }
 
@@ -656,16 +693,22 @@ void skinny_args(const LayerDesc& L, const void* x, const int32_t* perm, const i
   dn.blk_prefix[kMaxGroups] = nd;
 }
 
-// FP8 weights: which kernel.  `waves` is what a wave per 32 weight rows of the experts that can have rows gives the
-// staged kernel's up projection.  Split / staged time over 17 layer shapes, 1 to 32 tokens: below 1200 waves (not five per
-// compute unit) 0.50 to 0.99; with fewer rows than experts (one row in each expert that has any) 0.50 to 1.00 up to 2500 and to 1.21
-// beyond; with one row per expert on average 0.81 to 0.89 up to 1600, 1.08 at 1900; with more 0.81 to 1.07 around 1500, 1.02
-// to 1.27 from 1900 on.  (Skewed routing favours the split kernel throughout: 0.43 to 1.02.)
-static bool fp8_split(const LayerDesc& L) {
+// Quantised weights: split or staged kernel.  The staged one shares its tokens and scales among 128 weight rows, which
+// pays once there are rounds of its workgroups to spare.  `waves`: a wave per 32 weight rows of the experts that can have
+// rows, up projection.  Split / staged time, six layer shapes, 1 to 32 tokens:
+//   FP8: 0.48 to 1.01 up to 5632 waves, or 10500 times the rows per expert; 1.06 to 1.13 past 7000 waves (d = 1024, 128 experts).
+//   MXFP4: where a reduction length is no multiple of 128 the staged kernel loads its scales byte by byte: 0.51 to 1.03 up
+//   to 15000 waves times the rows per expert, 1.08 beyond.  Elsewhere 0.68 to 0.93 below 2000 waves, or 4 M with their
+//   reduction, with few rows; 1.02 to 1.04 at 1536 waves with two rows per expert and more, 1.04 to 1.27 from 2352 waves on at
+//   d = 4096 and from 4896 on at d = 1024.
+static bool q_split(const LayerDesc& L, bool fp8) {
   long long f = 0;
-  for (int g = 0; g < L.Ng; ++g) f += L.F[g];
-  const long long waves = (L.P < L.Ne ? L.P : L.Ne) * (f / L.Ng) / 16;
-  return waves < (L.P < L.Ne ? 2500 : L.P == L.Ne ? 1600 : 1200);
+  bool whole = L.d % 128 == 0;
+  for (int g = 0; g < L.Ng; ++g) { f += L.F[g]; whole = whole && L.F[g] % 128 == 0; }
+  const long long live = L.P < L.Ne ? L.P : L.Ne, waves = live * (f / L.Ng) / 16;
+  if (fp8) return waves < 6500 && waves * L.P < 10500 * live;
+  if (!whole) return waves * L.P < 15000 * live;
+  return waves * L.P < 3000 * live && (waves < 2000 || waves * L.d < (4ll << 20));
 }
 
 hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* perm,
@@ -686,8 +729,16 @@ hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* p
     if (stages & 1) hipLaunchKernelGGL(ku, dim3(nu), dim3(256), 0, s, up);
     if (stages & 2) hipLaunchKernelGGL(kd, dim3(nd), dim3(256), 0, s, dn);
   };
-  if (w4) launch_staged(ffn_skinny_q_kernel<true, 4>, ffn_skinny_q_kernel<false, 4>);
-  else if (w8 && fp8_split(L)) launch(ffn_skinny_fp8_split_kernel<true>, ffn_skinny_fp8_split_kernel<false>);
+  auto launch_split = [&](auto ku, auto kd) {
+    constexpr int per = kSplitWaves / kQSplit;                   // column blocks per workgroup
+    const int pu = (cu + per - 1) / per, pd = (cd + per - 1) / per;
+    if (stages & 1) hipLaunchKernelGGL(ku, dim3(slots * pu), dim3(256), 0, s, up, pu);
+    if (stages & 2) hipLaunchKernelGGL(kd, dim3(slots * pd), dim3(256), 0, s, dn, pd);
+  };
+  if ((w4 || w8) && q_split(L, w8)) {
+    if (w4) launch_split(ffn_skinny_q_split_kernel<true, 4>, ffn_skinny_q_split_kernel<false, 4>);
+    else launch_split(ffn_skinny_q_split_kernel<true, 8>, ffn_skinny_q_split_kernel<false, 8>);
+  } else if (w4) launch_staged(ffn_skinny_q_kernel<true, 4>, ffn_skinny_q_kernel<false, 4>);
   else if (w8) launch_staged(ffn_skinny_q_kernel<true, 8>, ffn_skinny_q_kernel<false, 8>);
   else launch(ffn_skinny_kernel<true>, ffn_skinny_kernel<false>);
   return hipGetLastError();
