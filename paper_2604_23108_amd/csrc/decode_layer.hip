@@ -243,7 +243,7 @@ __device__ __forceinline__ void decode_select(const DecodeArgs& a, int task, uns
     int(*hist)[kMaxExperts] = reinterpret_cast<int(*)[kMaxExperts]>(smem);
     int* wtot = reinterpret_cast<int*>(smem + sizeof(int) * kWavesPerBlock * kMaxExperts);
     __syncthreads();
-    permute_small_body(a.p, hist, wtot);
+    permute_small_body<kSegPairs / 64, kWavesPerBlock>(a.p, hist, wtot);
     wg_signal<false>(&a.ctl[kCtlReady]);
   }
 }

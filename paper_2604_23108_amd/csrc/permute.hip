@@ -1,22 +1,27 @@
 // Token permutation for gfx950: a deterministic, stable counting sort of the
 // P = T*K_e (token, slot) pairs by expert id.
 //
-// The pair list is cut into wave segments of 512 consecutive pairs.  Every wave
+// The pair list is cut into wave segments of 64 to 512 consecutive pairs.  Every wave
 // (1) histograms its segment in LDS, (2) a scan turns the [segment][expert] counts
 // into the first output position of every (segment, expert), (3) every wave walks its
 // segment again 64 pairs at a time and ranks equal experts inside the 64 with ballots
 // (one ballot per bit of the expert id), so the order inside a bucket is the pair order.
 // Integer LDS atomics only feed counts, so nothing depends on execution order.
-// Up to 2048 pairs the three steps run in one single-workgroup kernel;
-// while segments x experts <= 8192 the scan is folded into the scatter kernel (two launches
-// instead of three).  (One workgroup of sixteen waves for up to 32768 pairs, a single launch, was
-// slower than the two launches: 15 against 11 us at 16384 pairs, 28 against 12 us at 32768.)
+// Bound by latency: the steps of a wave's walk depend on each other through the bucket cursors, so segments are as short
+// as the size of the count matrix allows.  Up to 4096 pairs one workgroup of sixteen waves does everything in one
+// kernel (four waves with segments of 512: 6.0 us at 640 pairs, 6.2 at 2048; now 3.0 and 3.9; 4096 pairs in two kernels
+// 9.2, now 5.4; at 6144 pairs, eight steps a wave, one kernel and two are even at 7.2).  While segments x experts <= 8192 the
+// scan is folded into the scatter kernel (two launches instead of three); segments are shortened while
+// the matrix, which every scatter workgroup reads, stays within 4096 cells (segments of 512: 10.0 us at 8192 pairs of 64
+// experts, now 6.9; 9.9 at 16384, now 8.1).
 #include <mutex>
 
 #include "common.h"
 #include "permute_small.h"
 
 namespace mohge {
+
+constexpr int kSmallWaves = 16;                // of the single-workgroup kernel
 
 // Segment histograms of mohge_permute_static: the one scratch buffer of the permutation, held in
 // the library's own device memory so that the call needs no workspace from the caller.  Every GPU
@@ -45,11 +50,12 @@ static hipError_t static_scratch(void** out) {
   return hipSuccess;
 }
 
+template <int NI>
 __global__ void __launch_bounds__(256) permute_hist_kernel(const PermArgs a) {
   __shared__ int hist[kWavesPerBlock][kMaxExperts];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int seg = blockIdx.x * kWavesPerBlock + w;
-  const SegIds ids = load_segment(a, seg, lane);
+  const SegIds<NI> ids = load_segment<NI>(a, seg, lane);
   for (int e = threadIdx.x; e < kWavesPerBlock * kMaxExperts; e += blockDim.x) (&hist[0][0])[e] = 0;
   __syncthreads();
   wave_histogram(ids, hist[w]);
@@ -95,13 +101,13 @@ __global__ void __launch_bounds__(1024) permute_scan_kernel(const PermArgs a) {
 // FUSED: the segment histograms are still raw counts; every workgroup sums them itself
 // (column totals -> offsets, counts of earlier segments -> its own bases) instead of reading
 // the output of a separate scan kernel.  Used while the number of segments is small.
-template <bool FUSED>
+template <bool FUSED, int NI>
 __global__ void __launch_bounds__(256) permute_scatter_kernel(const PermArgs a) {
   __shared__ int base[kWavesPerBlock][kMaxExperts];
   __shared__ int wtot[4];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int seg = blockIdx.x * kWavesPerBlock + w;
-  const SegIds ids = load_segment(a, seg, lane);
+  const SegIds<NI> ids = load_segment<NI>(a, seg, lane);
   if constexpr (FUSED) {
     // stage the whole [segment][expert] count matrix in LDS with independent, coalesced
     // loads (one memory round trip), then walk it per expert
@@ -150,10 +156,11 @@ __global__ void __launch_bounds__(256) permute_scatter_kernel(const PermArgs a) 
   wave_scatter(a, ids, seg, lane, base[w]);
 }
 
-__global__ void __launch_bounds__(256) permute_small_kernel(const PermArgs a) {
-  __shared__ int hist[kWavesPerBlock][kMaxExperts];
-  __shared__ int wtot[kWavesPerBlock];
-  permute_small_body(a, hist, wtot);
+template <int NI>
+__global__ void __launch_bounds__(64 * kSmallWaves) permute_small_kernel(const PermArgs a) {
+  __shared__ int hist[kSmallWaves][kMaxExperts];
+  __shared__ int wtot[4];
+  permute_small_body<NI, kSmallWaves>(a, hist, wtot);
 }
 
 template <typename V>
@@ -169,8 +176,15 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const V* __restrict__ 
   for (int i = lane; i < vec_per_row; i += 64) dst[i] = src[i];
 }
 
+// Steps of 64 pairs in a wave's segment: the fewest that keep the count matrix within 4096 cells.
+static int segment_steps(const LayerDesc& L) {
+  for (int ni = 1; ni < kSegPairs / 64; ni *= 2)
+    if (((long long)L.P + 64 * ni - 1) / (64 * ni) * L.Ne <= 4096) return ni;
+  return kSegPairs / 64;
+}
+
 size_t permute_workspace_bytes(const LayerDesc& L) {
-  const size_t nseg = ((size_t)L.P + kSegPairs - 1) / kSegPairs;
+  const size_t seg = 64 * (size_t)segment_steps(L), nseg = ((size_t)L.P + seg - 1) / seg;
   const size_t b = (nseg > 0 ? nseg : 1) * (size_t)L.Ne * sizeof(int32_t);
   return (b + 255) / 256 * 256;
 }
@@ -182,20 +196,30 @@ hipError_t launch_permute(const LayerDesc& L, int dtype, const int32_t* expert_i
   a.eidx = expert_idx; a.counts = counts; a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
   a.seg_hist = static_cast<int32_t*>(ws);
   a.P = L.P; a.Ne = L.Ne;
-  a.nseg = (L.P + kSegPairs - 1) / kSegPairs;
+  const int ni = segment_steps(L);
+  a.nseg = (int)(((long long)L.P + 64 * ni - 1) / (64 * ni));
   a.nbits = 0;
   while ((1 << a.nbits) < L.Ne) ++a.nbits;
-  if (L.P <= kBlockPairs) {
-    hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(256), 0, s, a);
+  const int nblk = (a.nseg + kWavesPerBlock - 1) / kWavesPerBlock;
+  auto launch = [&](auto hist, auto scatter) {
+    hipLaunchKernelGGL(hist, dim3(nblk), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(scatter, dim3(nblk), dim3(256), 0, s, a);
+  };
+  if (L.P <= 64 * kSmallWaves) {
+    hipLaunchKernelGGL(permute_small_kernel<1>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+  } else if (L.P <= 2 * 64 * kSmallWaves) {
+    hipLaunchKernelGGL(permute_small_kernel<2>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+  } else if (L.P <= 4 * 64 * kSmallWaves) {
+    hipLaunchKernelGGL(permute_small_kernel<4>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
+  } else if ((long long)a.nseg * a.Ne <= kFusedMaxCells) {
+    if (ni == 1) launch(permute_hist_kernel<1>, permute_scatter_kernel<true, 1>);
+    else if (ni == 2) launch(permute_hist_kernel<2>, permute_scatter_kernel<true, 2>);
+    else if (ni == 4) launch(permute_hist_kernel<4>, permute_scatter_kernel<true, 4>);
+    else launch(permute_hist_kernel<8>, permute_scatter_kernel<true, 8>);
   } else {
-    const int nblk = (a.nseg + kWavesPerBlock - 1) / kWavesPerBlock;
-    hipLaunchKernelGGL(permute_hist_kernel, dim3(nblk), dim3(256), 0, s, a);
-    if (a.nseg * a.Ne <= kFusedMaxCells) {
-      hipLaunchKernelGGL(permute_scatter_kernel<true>, dim3(nblk), dim3(256), 0, s, a);
-    } else {
-      hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, a);
-      hipLaunchKernelGGL(permute_scatter_kernel<false>, dim3(nblk), dim3(256), 0, s, a);
-    }
+    hipLaunchKernelGGL(permute_hist_kernel<8>, dim3(nblk), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((permute_scatter_kernel<false, 8>), dim3(nblk), dim3(256), 0, s, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

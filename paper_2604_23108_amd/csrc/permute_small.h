@@ -6,7 +6,7 @@
 
 namespace mohge {
 
-constexpr int kSegPairs = 512;                 // pairs per wave segment
+constexpr int kSegPairs = 512;                 // pairs per wave segment (the most)
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlockPairs = kSegPairs * kWavesPerBlock;
 constexpr int kFusedMaxCells = 8192;            // segments x experts that the fused scatter stages in LDS
@@ -38,32 +38,36 @@ __device__ __forceinline__ int load_expert(const PermArgs& a, int p) {
   return e < 0 ? 0 : (e >= a.Ne ? a.Ne - 1 : e);
 }
 
-// The expert ids of a segment, lane l of register i holds pair seg * kSegPairs + 64 i + l (-1 past
+// The expert ids of a segment of 64 NI pairs, lane l of register i holds pair 64 (seg * NI + i) + l (-1 past
 // the end): all loads in flight at once (a load per step made a walk of eight memory latencies).
-struct SegIds { int e[kSegPairs / 64]; };
+template <int NI>
+struct SegIds { int e[NI]; };
 
-__device__ __forceinline__ SegIds load_segment(const PermArgs& a, int seg, int lane) {
-  SegIds s;
+template <int NI>
+__device__ __forceinline__ SegIds<NI> load_segment(const PermArgs& a, int seg, int lane) {
+  SegIds<NI> s;
 #pragma unroll
-  for (int i = 0; i < kSegPairs / 64; ++i) {
-    const int p = seg * kSegPairs + 64 * i + lane;
+  for (int i = 0; i < NI; ++i) {
+    const int p = 64 * (seg * NI + i) + lane;
     s.e[i] = (unsigned)p < (unsigned)a.P ? load_expert(a, p) : -1;      // (unsigned: P may be close to 2^31)
   }
   return s;
 }
 
-__device__ __forceinline__ void wave_histogram(const SegIds& s, int* hist) {
+template <int NI>
+__device__ __forceinline__ void wave_histogram(const SegIds<NI>& s, int* hist) {
 #pragma unroll
-  for (int i = 0; i < kSegPairs / 64; ++i)
+  for (int i = 0; i < NI; ++i)
     if (s.e[i] >= 0) atomicAdd(&hist[s.e[i]], 1);
 }
 
 // base[e] = first free output position for expert e in this segment (LDS, wave private)
-__device__ __forceinline__ void wave_scatter(const PermArgs& a, const SegIds& s, int seg, int lane, int* base) {
+template <int NI>
+__device__ __forceinline__ void wave_scatter(const PermArgs& a, const SegIds<NI>& s, int seg, int lane, int* base) {
 #pragma unroll
-  for (int i = 0; i < kSegPairs / 64; ++i) {
-    const int p = seg * kSegPairs + 64 * i + lane;
-    if ((unsigned)(seg * kSegPairs + 64 * i) >= (unsigned)a.P) break;      // (wave-uniform)
+  for (int i = 0; i < NI; ++i) {
+    const int p = 64 * (seg * NI + i) + lane;
+    if ((unsigned)(64 * (seg * NI + i)) >= (unsigned)a.P) break;      // (wave-uniform)
     const bool active = s.e[i] >= 0;
     const int e = active ? s.e[i] : 0;
     const unsigned long long m = match_mask(e, a.nbits, active);
@@ -88,21 +92,23 @@ __device__ __forceinline__ void wave_scatter(const PermArgs& a, const SegIds& s,
   }
 }
 
-// P <= kBlockPairs: histogram, scan and scatter in one workgroup.
-// hist: LDS, [kWavesPerBlock][kMaxExperts]; wtot: LDS, [kWavesPerBlock].  Called by all 256 threads.
+// P <= 64 NI NW: histogram, scan and scatter in one workgroup of NW waves (at least four: an expert per thread), a segment
+// of 64 NI pairs each.  hist: LDS, [NW][kMaxExperts]; wtot: LDS, [4].  Called by all its threads.
+template <int NI, int NW>
 __device__ __forceinline__ void permute_small_body(const PermArgs& a, int (*hist)[kMaxExperts], int* wtot) {
+  static_assert(NW >= 4, "an expert per thread");
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const SegIds ids = load_segment(a, w, lane);
-  for (int e = threadIdx.x; e < kWavesPerBlock * kMaxExperts; e += blockDim.x) (&hist[0][0])[e] = 0;
+  const SegIds<NI> ids = load_segment<NI>(a, w, lane);
+  for (int e = threadIdx.x; e < NW * kMaxExperts; e += 64 * NW) (&hist[0][0])[e] = 0;
   __syncthreads();
   wave_histogram(ids, hist[w]);
   __syncthreads();
-  // one expert per thread (Ne <= 256): its count over the four segments, then an exclusive scan
+  // one expert per thread (Ne <= 256): its count over the segments, then an exclusive scan
   // over the experts (inside the waves by shuffles, across them through LDS)
   const int e = threadIdx.x;
-  int h[kWavesPerBlock], c = 0;
+  int h[NW], c = 0;
 #pragma unroll
-  for (int ww = 0; ww < kWavesPerBlock; ++ww) {
+  for (int ww = 0; ww < NW; ++ww) {
     h[ww] = e < a.Ne ? hist[ww][e] : 0;
     c += h[ww];
   }
@@ -112,14 +118,14 @@ __device__ __forceinline__ void permute_small_body(const PermArgs& a, int (*hist
     const int up = __shfl_up(incl, off, 64);
     if (lane >= off) incl += up;
   }
-  if (lane == 63) wtot[w] = incl;
+  if (lane == 63 && w < 4) wtot[w] = incl;
   __syncthreads();
-  int off_e = incl - c;
-  for (int ww = 0; ww < w; ++ww) off_e += wtot[ww];
   if (e < a.Ne) {
+    int off_e = incl - c;
+    for (int ww = 0; ww < w; ++ww) off_e += wtot[ww];
     int run = off_e;
 #pragma unroll
-    for (int ww = 0; ww < kWavesPerBlock; ++ww) {
+    for (int ww = 0; ww < NW; ++ww) {
       hist[ww][e] = run;            // becomes the base of (segment ww, expert e)
       run += h[ww];
     }
