@@ -1481,7 +1481,8 @@ static hipError_t launch_small(K kern, bool& attr_done, long long grid, hipStrea
 // The mean cost of a wrong choice is 0.9 % forward, 1.3 % backward (the largest, 1.14, where 576 up tiles start a second
 // round on 512 slots: d = 4096, 24 experts x 144 rows).  From 1.7 big up tiles per compute unit on the big form has no
 // idle units to lose to (d = 1024, 32 experts, 768 rows: 122 -> 127 us); that limit alone, whatever the length
-// of the reduction, cost 1.7 and 2.2 %, up to 1.29.
+// of the reduction, cost 1.7 and 2.2 %, up to 1.29.  Forward, where the big row tiles are not nearly full, it lies at 2.0 (1.73 to
+// 1.76 tiles per unit, d = 1024 and 1344, 520 to 675 rows: 0.83 to 0.98).
 bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
   if (o.small >= 0) return o.small != 0;
   const long long rows = L.P > L.Ne ? L.P / L.Ne : 1;     // per expert if they were spread evenly
@@ -1494,7 +1495,7 @@ bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
   const long long cus = tile_num_cus();
   if (!backward && rows <= 112) return stages <= 180 * cus;
   const bool full = rows > kBM && 10 * rows >= 9 * kBM * ((rows + kBM - 1) / kBM);
-  return 10 * big < 17 * cus && stages <= (rows <= 112 ? 130 : full ? 48 : 80) * cus;
+  return 10 * big < (full || backward ? 17 : 20) * cus && stages <= (rows <= 112 ? 130 : full ? 48 : 80) * cus;
 }
 
 hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
