@@ -101,6 +101,14 @@ __global__ void __launch_bounds__(1024) aux_final_kernel(const AuxArgs a) {
   if (r < R) {
     double s0 = 0.0, s1 = 0.0;
     int b = r;
+    // eight rows requested before the first is added (two at a time: 8.6 us with 512 rows, now 7.8)
+    for (; b + 7 * R < a.nblk; b += 8 * R) {
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = a.part[(size_t)(b + i * R) * C + col];
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) { s0 += v[i]; s1 += v[i + 1]; }
+    }
     for (; b + R < a.nblk; b += 2 * R) {
       s0 += a.part[(size_t)b * C + col];
       s1 += a.part[(size_t)(b + R) * C + col];
