@@ -15,7 +15,7 @@
 // Kernels: (1) one wave per token for the scalar chain above; (2) the two weight gradients as a
 // reduction over tokens, split over the grid with partial sums added in a fixed order (no
 // atomics: bit-identical from run to run); (3) the input gradient, up to 8 tokens per thread so
-// that every router weight is fetched once per 8 tokens.
+// that every router weight is fetched once per 8 tokens, in one launch with the partial sums of (2).
 #include "common.h"
 
 namespace mohge {
@@ -43,43 +43,67 @@ struct RouteBwdArgs {
   float ratio[kMaxGroups];
 };
 
+// Value of position i of a row spread over a wave (64 per register), i the same in every lane
+template <typename T>
+__device__ __forceinline__ T row_value(const T (&v)[4], int i) {
+  const T m = i < 64 ? v[0] : i < 128 ? v[1] : i < 192 ? v[2] : v[3];
+  return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, m), i & 63));
+}
+
+// A wave's token: everything of its rows is requested at once and read from other lanes' registers (loaded where it was
+// needed, every sum over kept experts was a chain of three loads per expert: 8.0 us at 777 tokens, now 7.5; 11.3 at
+// 8192, now 10.5).
 __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs a) {
   __shared__ float sh_v[kMaxExperts], sh_u[kMaxGroups];
   __shared__ float ex[4][3][kMaxExperts];   // per wave: ES', dES'', dES'
   __shared__ float gq[4][4][kMaxGroups];    // per wave: sigma, sum v ES', sum dES'' ES', sum dES' ES'
+  __shared__ float s_gs[4][kMaxGroups];     // per wave: GS
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const float invT = 1.f / (float)a.T;
+  const int t = blockIdx.x * 4 + w;
+  const bool live = t < a.T;
+  const int tt = live ? t : a.T - 1;         // idle waves redo the last token and store nothing
+  float es[4] = {0.f, 0.f, 0.f, 0.f}, dg[4] = {0.f, 0.f, 0.f, 0.f}, gt[4] = {0.f, 0.f, 0.f, 0.f};
+  float g0[4] = {0.f, 0.f, 0.f, 0.f};
+  int ei[4] = {0, 0, 0, 0}, gi[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {              // (K_e <= N_e <= 256)
+    const int i = lane + 64 * j;
+    if (i < a.Ne) es[j] = a.es1[(size_t)tt * a.Ne + i];
+    if (i < a.Ke) {
+      const size_t at = (size_t)tt * a.Ke + i;
+      ei[j] = a.eidx[at]; dg[j] = a.dgates[at]; gt[j] = a.gates[at];
+    }
+  }
+  if (lane < a.Ng) g0[0] = a.gs[(size_t)tt * a.Ng + lane];
+  if (lane < a.Kg) gi[0] = a.gidx[(size_t)tt * a.Kg + lane];
   for (int e = threadIdx.x; e < a.Ne; e += 256)
     sh_v[e] = a.stats ? a.alpha_e * a.stats[2 * a.Ng + e] * invT : 0.f;
   if (threadIdx.x < a.Ng)
     sh_u[threadIdx.x] = a.stats ? a.alpha_g * a.ratio[threadIdx.x] * a.stats[threadIdx.x] * invT : 0.f;
-  const int t = blockIdx.x * 4 + w;
-  const bool live = t < a.T;
-  const int tt = live ? t : a.T - 1;         // idle waves redo the last token and store nothing
-  const float* gs = a.gs + (size_t)tt * a.Ng;
-  const float* es1 = a.es1 + (size_t)tt * a.Ne;
-  const int32_t* eidx = a.eidx + (size_t)tt * a.Ke;
-  const int32_t* gidx = a.gidx + (size_t)tt * a.Kg;
-  const float* dgate = a.dgates + (size_t)tt * a.Ke;
-  const float* gate = a.gates + (size_t)tt * a.Ke;
+  if (lane < a.Ng) s_gs[w][lane] = g0[0];
+  const float* const gs = s_gs[w];
 
   // gates -> ES''
-  float D = 0.f, gd = 0.f;
+  float D = 0.f, gd = 0.f, d2[4] = {0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < a.Ke; ++s) {
-    const int e = eidx[s];
-    D += es1[e] * gs[e / a.N];
-    gd = fmaf(dgate[s], gate[s], gd);
+    const int e = row_value(ei, s);
+    D += row_value(es, e) * row_value(g0, e / a.N);
+    gd = fmaf(row_value(dg, s), row_value(gt, s), gd);
   }
   const float invD = 1.f / D;
+  for (int s = 0; s < a.Ke; ++s) {
+    const int e = row_value(ei, s);
+    const float v = (row_value(dg, s) - gd) * invD;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d2[j] = e == lane + 64 * j ? v : d2[j];
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int e = lane + 64 * j;
     if (e < a.Ne) {
-      float d2 = 0.f;
-      for (int s = 0; s < a.Ke; ++s)
-        if (eidx[s] == e) d2 = (dgate[s] - gd) * invD;
-      ex[w][0][e] = es1[e];
-      ex[w][1][e] = d2;
+      ex[w][0][e] = es[j];
+      ex[w][1][e] = d2[j];
     }
   }
   __syncthreads();
@@ -100,7 +124,7 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
     if (e < a.Ne) {
       const int g = e / a.N;
       bool kept = false;
-      for (int s = 0; s < a.Kg; ++s) kept |= gidx[s] == g;
+      for (int s = 0; s < a.Kg; ++s) kept |= row_value(gi, s) == g;
       float d1 = 0.f;
       if (kept) {
         const float den = gq[w][0][g] + a.eps;
@@ -119,7 +143,7 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
     for (int j = 0; j < a.Ng; ++j) S += gs[j];
     for (int j = 0; j < a.Ng; ++j) us = fmaf(sh_u[j], gs[j] / S, us);
     bool kept = false;
-    for (int s = 0; s < a.Kg; ++s) kept |= gidx[s] == g;
+    for (int s = 0; s < a.Kg; ++s) kept |= row_value(gi, s) == g;
     const float dGS = (kept ? gq[w][2][g] : 0.f) + (sh_u[g] - us) / S;
     if (live) a.dz[(size_t)t * a.Z + g] = dGS * gs[g] * (1.f - gs[g]);
   }
@@ -152,19 +176,21 @@ __global__ void __launch_bounds__(256) route_bwd_token_kernel(const RouteBwdArgs
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kZC = 32, kTU = 8, kWGradWaves = 4;
 
-__global__ void __launch_bounds__(64 * kWGradWaves, 3) route_bwd_wgrad_kernel(const RouteBwdArgs a) {
-  __shared__ float4 red[(kWGradWaves - 1) * 16 * 64];        // 48 KB: three workgroups per compute unit
+constexpr int kWGradLds = (kWGradWaves - 1) * 16 * 64 * 16;   // 48 KB: three workgroups per compute unit
+
+// block (bx, by, bz) of the reduction's grid; red: LDS, kWGradLds
+__device__ __forceinline__ void wgrad_block(const RouteBwdArgs& a, int bx, int by, int bz, float4* red) {
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int j = lane & 31, k = lane >> 5;
-  const int c = blockIdx.x * 128 + 4 * j;
+  const int c = bx * 128 + 4 * j;
   const bool col_ok = c < a.d;
   const int cc = col_ok ? c : 0;
-  const int s0 = blockIdx.z * a.tok_per_split;
+  const int s0 = bz * a.tok_per_split;
   const int s1 = min(a.T, s0 + a.tok_per_split);
   // (an even number of tokens per wave; a wave past the end adds zeros)
   const int per_wave = ((s1 - s0 + 2 * kWGradWaves - 1) / (2 * kWGradWaves)) * 2;
   const int t0 = min(s1, s0 + w * per_wave), t1 = min(s1, t0 + per_wave);
-  const int z0 = blockIdx.y * kZC, zl = z0 + j;
+  const int z0 = by * kZC, zl = z0 + j;
   // step at token t: this lane's token is t + k (dz = 0 past the stretch or past Z)
   auto load = [&](int t, uint2& xv, float& dzv) {
     const int tok = t + k, tt = min(tok, a.T - 1);
@@ -215,7 +241,7 @@ __global__ void __launch_bounds__(64 * kWGradWaves, 3) route_bwd_wgrad_kernel(co
           const float4 v = red[(ww * 16 + r) * 64 + lane];
           s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
         }
-        *reinterpret_cast<float4*>(a.part + ((size_t)blockIdx.z * a.Z + z) * a.d + c) = s;
+        *reinterpret_cast<float4*>(a.part + ((size_t)bz * a.Z + z) * a.d + c) = s;
       }
     }
   }
@@ -255,12 +281,11 @@ __global__ void __launch_bounds__(256) route_bwd_wsum_kernel(const RouteBwdArgs 
 // router weights come from L2 once per TB tokens, two rows ahead of their use; TB = 8 where that still
 // gives every compute unit two workgroups, fewer tokens otherwise.
 template <int TB>
-__global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a, int tpr) {
-  extern __shared__ __align__(16) unsigned char dx_smem[];
+__device__ __forceinline__ void dx_block(const RouteBwdArgs& a, int tpr, int bx, int by, unsigned char* dx_smem) {
   // tpr threads per row of this column block (a power of two up to 256), 256 / tpr token blocks
   const int sub = threadIdx.x / tpr, nsub = 256 / tpr;
-  const int c = (blockIdx.y * 256 + (int)(threadIdx.x % tpr)) * 8;     // c >= d: helps staging only
-  const int b0 = blockIdx.x * nsub * TB;                               // first token of the workgroup
+  const int c = (by * 256 + (int)(threadIdx.x % tpr)) * 8;     // c >= d: helps staging only
+  const int b0 = bx * nsub * TB;                               // first token of the workgroup
   const int t0 = b0 + sub * TB;
   float* dzs = reinterpret_cast<float*>(dx_smem);                      // [nsub * TB][Z]
   int* rows = reinterpret_cast<int*>(dzs + nsub * TB * a.Z);           // [nsub * TB][Ke]
@@ -361,6 +386,22 @@ __global__ void __launch_bounds__(256) route_bwd_dx_kernel(const RouteBwdArgs a,
   }
 }
 
+// The partial sums of dW and dx in one launch: both need dz only, the first is bound by its matrix instructions, the
+// second by memory.  The n_w workgroups of the first come first: 777 tokens, d = 1024, 8.5 + 11.5 us one after the other, 14
+// together; 8192 tokens, d = 2048: 28 + 54, 79 together (in turn, eight and eight, 83).
+template <int TB>
+__global__ void __launch_bounds__(256, 3) route_bwd_main_kernel(const RouteBwdArgs a, int tpr, int n_w, int dx_cb) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  static_assert(64 * kWGradWaves == 256, "one workgroup shape");
+  const int b = blockIdx.x;
+  if (b < n_w) {
+    const int cols = (a.d + 127) / 128, rows = (a.Z + kZC - 1) / kZC;
+    wgrad_block(a, b % cols, b / cols % rows, b / (cols * rows), reinterpret_cast<float4*>(smem));
+  } else {
+    dx_block<TB>(a, tpr, (b - n_w) / dx_cb, (b - n_w) % dx_cb, smem);
+  }
+}
+
 // token splits of the weight-gradient reduction: enough for three workgroups per compute unit, at least
 // 32 tokens each (8 per wave: shorter stretches cost more in partial sums than they save in MFMAs), at
 // most 256 splits and at most 64 MB of partial sums.  A wide layer has its workgroups without many splits, but the
@@ -391,12 +432,13 @@ size_t route_bwd_workspace_bytes(const LayerDesc& L) {
   return up256(T * Z * 4) + up256((size_t)wgrad_splits(L) * Z * L.d * 4);
 }
 
-static void launch_dx(const RouteBwdArgs& a, hipStream_t s) {
+static void launch_main(const RouteBwdArgs& a, hipStream_t s) {
   // threads per row: a power of two that covers a row of up to 2048 columns; the staged dz and row
   // numbers of the workgroup's tokens stay below 32 KB
   int tpr = 8;
   while (tpr < 256 && tpr * 8 < a.d) tpr *= 2;
   const unsigned cb = (unsigned)((a.d + 2047) / 2048);
+  const unsigned n_w = (unsigned)((a.d + 127) / 128) * ((a.Z + kZC - 1) / kZC) * a.S;
   for (int TB = 8; TB >= 2; TB /= 2) {
     auto lds = [&](int t) { return (size_t)(256 / t) * TB * (a.Z + a.Ke) * 4; };
     int t = tpr;
@@ -404,8 +446,9 @@ static void launch_dx(const RouteBwdArgs& a, hipStream_t s) {
     const int per_wg = 256 / t * TB;
     const unsigned tb = (unsigned)((a.T + per_wg - 1) / per_wg);
     if (TB > 2 && (long long)tb * cb < 512) continue;
-    auto kern = TB == 8 ? route_bwd_dx_kernel<8> : TB == 4 ? route_bwd_dx_kernel<4> : route_bwd_dx_kernel<2>;
-    hipLaunchKernelGGL(kern, dim3(tb, cb), dim3(256), lds(t), s, a, t);
+    auto kern = TB == 8 ? route_bwd_main_kernel<8> : TB == 4 ? route_bwd_main_kernel<4> : route_bwd_main_kernel<2>;
+    const size_t smem = lds(t) > (size_t)kWGradLds ? lds(t) : (size_t)kWGradLds;
+    hipLaunchKernelGGL(kern, dim3(n_w + tb * cb), dim3(256), smem, s, a, t, (int)n_w, (int)cb);
     return;
   }
 }
@@ -433,11 +476,8 @@ hipError_t launch_route_bwd(const LayerDesc& L, const mohge_config& cfg, const v
   a.dz = dz_out ? dz_out : reinterpret_cast<float*>(base);
   a.part = reinterpret_cast<float*>(base + dz_bytes);
   hipLaunchKernelGGL(route_bwd_token_kernel, dim3((unsigned)((L.T + 3) / 4)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(route_bwd_wgrad_kernel,
-                     dim3((unsigned)((L.d + 127) / 128), (unsigned)((a.Z + kZC - 1) / kZC), (unsigned)a.S),
-                     dim3(64 * kWGradWaves), 0, s, a);
+  launch_main(a, s);
   hipLaunchKernelGGL(route_bwd_wsum_kernel, dim3((unsigned)(((size_t)a.Z * L.d / 4 + 31) / 32)), dim3(256), 0, s, a);
-  launch_dx(a, s);
   return hipGetLastError();
 }
 
