@@ -61,7 +61,8 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) tot[tm][tn][i] = 0.0;
       }
-    const int kbeg = ((int)blockIdx.y * NW + w) * a.kslice, kend = kbeg + a.kslice;
+    // (the last slices may be short or empty: d need not be a multiple of the slices together)
+    const int kbeg = ((int)blockIdx.y * NW + w) * a.kslice, kend = min(kbeg + a.kslice, a.d);
     // The token rows are read exactly once from HBM in small pieces (16 rows x 64 bytes per
     // wave-wide load), so the loop is bound by memory latency unless many loads are in
     // flight: all token loads of a chunk of up to XS 32-element steps are requested up
@@ -468,22 +469,20 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   a.NO = L.Ng + L.Ne;
   a.NOpad = ((a.NO + 15) / 16) * 16 + 4;
   a.Nepad = ((L.Ne + 63) / 64) * 64;
-  const int NW = (L.d % 256 == 0) ? 8 : (L.d % 128 == 0) ? 4 : 2;
-  a.kslice = L.d / NW;
-  // few tokens: split the reduction over more workgroups (a slice stays a whole number of
-  // 32-element steps)
+  // Slices of the hidden dimension, whole 32-element steps: one per wave, eight waves.  Few tokens: spread over more
+  // workgroups as well, down to one step.  (With equal slices only, two or four waves where d is no multiple of 256 and
+  // no spreading where the slices would not stay whole: d = 1344, 30 router rows, 32 to 1000 tokens 52 us, now 13; d = 2560, 66
+  // rows, 23, now 17; d = 128, 15 rows, where four waves more share the selection, 10, now 7.)
+  constexpr int NW = 8;
+  const int steps = L.d / 32;
   a.dsplit = 1;
   a.gpart = nullptr;
   if (ws && L.T <= kSplitMaxT && ws_bytes >= route_workspace_bytes(L, dtype)) {
     const int most = split_most(L.T);
-    int ds = 1;
-    while (ds * 2 <= most && (a.kslice / (ds * 2)) % 32 == 0 && a.kslice / (ds * 2) >= 32) ds *= 2;
-    if (ds > 1) {
-      a.dsplit = ds;
-      a.kslice /= ds;
-      a.gpart = static_cast<double*>(ws);
-    }
+    while (a.dsplit * 2 <= most && NW * a.dsplit * 2 <= steps) a.dsplit *= 2;
+    if (a.dsplit > 1) a.gpart = static_cast<double*>(ws);
   }
+  a.kslice = 32 * ((steps + NW * a.dsplit - 1) / (NW * a.dsplit));
   const int tiles = (a.NO + 15) / 16;
   // many bf16 tokens and a workspace for the split router rows: the bf16 matrix-core form
   if (prefill_form(L, dtype) && ws && ws_bytes >= route_workspace_bytes(L, dtype)) {

@@ -1,0 +1,38 @@
+"""The router at hidden sizes that its waves and workgroups cannot share evenly, against float64."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 704, 1344, 2624])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_route_uneven_slices(d, dtype):
+    import paper_2604_23108_amd as M
+    ng, n, kg, ke = 5, 5, 2, 4
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    wg, we = (torch.randn((r, d), generator=gen, device="cuda") * 0.05 for r in (ng, ng * n))
+    for T in (1, 17, 300, 2049, 4100):
+        x = torch.randn((T, d), generator=gen, device="cuda")
+        x = x.bfloat16() if dtype == "bf16" else x
+        cfg = M.Config(T=T, d=d, n_groups=ng, experts_per_group=n, d_ff=(64,) * ng, k_groups=kg, k_experts=ke,
+                       select_mode=M.SELECT_GLOBAL, dtype=M.BF16 if dtype == "bf16" else M.F32)
+        new = lambda k, t: torch.full((T, k), -1, dtype=t, device="cuda")
+        gi, ei, gates = new(kg, torch.int32), new(ke, torch.int32), new(ke, torch.float32)
+        nb = M.mohge_workspace_size(cfg, M.CALL_ROUTE)
+        ws = torch.empty(nb, dtype=torch.uint8, device="cuda") if nb else None
+        print(f"[route] d={d} T={T} {dtype}", flush=True)
+        M.mohge_route(cfg, x, wg, we, None, gi, ei, gates, None, None, ws)
+        X = x.double()
+        zg, ze = X @ wg.double().T.contiguous(), X @ we.double().T.contiguous()
+        kept = zg.gather(1, gi.long())
+        out = zg.scatter(1, gi.long(), float("-inf"))
+        assert (kept.min(1).values >= out.max(1).values - 1e-6).all()      # margins below the error of a logit are ties
+        e2 = torch.softmax(ze.view(T, ng, n), -1) * torch.sigmoid(zg)[:, :, None]
+        mask = torch.zeros_like(zg).scatter(1, gi.long(), 1.0)
+        e2 = (e2 * mask[:, :, None]).view(T, -1)
+        sel = e2.gather(1, ei.long())
+        assert (sel.min(1).values >= e2.scatter(1, ei.long(), -1.0).max(1).values - 1e-6).all()
+        assert (ei[:, 1:] > ei[:, :-1]).all()
+        # gates: fp32 logits to about 1e-7, expf to about an ulp
+        assert (gates.double() - sel / sel.sum(1, keepdim=True)).abs().max() <= 1e-6
