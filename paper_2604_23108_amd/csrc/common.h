@@ -74,6 +74,21 @@ __device__ __forceinline__ float swiglu(float g, float u) {
   return g * u * __builtin_amdgcn_rcpf(1.f + __expf(-g));
 }
 
+// Inclusive sums over the lanes of a wave in six register steps (row shifts, then the two broadcasts across rows); a
+// shuffle goes through LDS and costs a round trip per step.  Called by whole waves.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_or_zero(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1
+  v += dpp_or_zero<0x112, 0xf>(v);      // row_shr:2
+  v += dpp_or_zero<0x114, 0xf>(v);      // row_shr:4
+  v += dpp_or_zero<0x118, 0xf>(v);      // row_shr:8
+  v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // launchers implemented in the kernel files; each returns a hipError_t from the launch
 hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const float* w_group,
                         const float* w_expert, const float* bias, int32_t* group_idx,

@@ -68,12 +68,7 @@ __device__ __forceinline__ bool f32_row_tile(const F32Args& a, int m, int lane, 
     const int ee = v < a.Ne ? a.order[v / a.N] * a.N + v % a.N : 0;
     const int lo = a.offsets[ee], cnt = v < a.Ne ? a.offsets[ee + 1] - lo : 0;
     const int nt = (cnt + kFM - 1) / kFM;
-    int incl = nt;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
+    const int incl = wave_incl_scan(nt);
     const int first = before + incl - nt;                // tiles before this expert
     const unsigned long long hit = __ballot(m >= first && m < first + nt);
     if (hit) {

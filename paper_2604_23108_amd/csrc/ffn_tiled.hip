@@ -97,22 +97,7 @@ struct Shape {
 // schedule: one workgroup of 256 threads per projection; thread v <-> expert at visiting
 // position v for the per-expert quantities, then threads stride over the tiles
 // ---------------------------------------------------------------------------------------
-// Inclusive sums over the lanes of a wave in six register steps (row shifts, then the two broadcasts across
-// rows): a shuffle through LDS per step made the scans half of the schedule's arithmetic time.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_or_zero(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
-
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  v += dpp_or_zero<0x111, 0xf>(v);      // row_shr:1
-  v += dpp_or_zero<0x112, 0xf>(v);      // row_shr:2
-  v += dpp_or_zero<0x114, 0xf>(v);      // row_shr:4
-  v += dpp_or_zero<0x118, 0xf>(v);      // row_shr:8
-  v += dpp_or_zero<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-  v += dpp_or_zero<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
-// the same for 64-bit values (not negative): three parts of 24 bits, each summed by itself (64 x 2^24 fits an int)
+// wave_incl_scan for 64-bit values (not negative): three parts of 24 bits, each summed by itself (64 x 2^24 fits an int)
 __device__ __forceinline__ long long wave_incl_scan64(long long v) {
   const int lo = wave_incl_scan((int)(v & 0xffffff)), mid = wave_incl_scan((int)((v >> 24) & 0xffffff));
   const int hi = wave_incl_scan((int)(v >> 48));
@@ -1320,12 +1305,7 @@ __device__ __forceinline__ bool small_token_tile(const TileArgs& a, int t, int l
     const int lo = a.offsets[e], cnt = v < a.Ne ? a.offsets[e + 1] - lo : 0;
     const int nt = ((red_d(MODE) ? a.F[g] : a.d) + NCPT - 1) / NCPT;
     const int n = (cnt + BM - 1) / BM * nt;
-    int incl = n;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
+    const int incl = wave_incl_scan(n);
     const int first = before + incl - n;
     const unsigned long long hit = __ballot(t >= first && t < first + n);
     if (hit) {

@@ -9,11 +9,11 @@
 // Integer LDS atomics only feed counts, so nothing depends on execution order.
 // Bound by latency: the steps of a wave's walk depend on each other through the bucket cursors, so segments are as short
 // as the size of the count matrix allows.  Up to 4096 pairs one workgroup of sixteen waves does everything in one
-// kernel (four waves with segments of 512: 6.0 us at 640 pairs, 6.2 at 2048; now 3.0 and 3.9; 4096 pairs in two kernels
-// 9.2, now 5.4; at 6144 pairs, eight steps a wave, one kernel and two are even at 7.2).  While segments x experts <= 8192 the
+// kernel (four waves with segments of 512: 6.0 us at 640 pairs, 6.2 at 2048; now 2.7 and 3.6; 4096 pairs in two kernels
+// 9.2, now 5.0; at 6144 pairs, eight steps a wave, one kernel and two are even at 7).  While segments x experts <= 8192 the
 // scan is folded into the scatter kernel (two launches instead of three); segments are shortened while
 // the matrix, which every scatter workgroup reads, stays within 4096 cells (segments of 512: 10.0 us at 8192 pairs of 64
-// experts, now 6.9; 9.9 at 16384, now 8.1).
+// experts, now 6.6; 9.9 at 16384, now 7.9).
 #include <mutex>
 
 #include "common.h"
@@ -74,12 +74,7 @@ __global__ void __launch_bounds__(1024) permute_scan_kernel(const PermArgs a) {
     for (int s0 = 0; s0 < a.nseg; s0 += 64) {
       const int s = s0 + lane;
       const int v = (s < a.nseg) ? a.seg_hist[(size_t)s * a.Ne + e] : 0;
-      int incl = v;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int up = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += up;
-      }
+      const int incl = wave_incl_scan(v);
       if (s < a.nseg) a.seg_hist[(size_t)s * a.Ne + e] = carry + incl - v;
       carry += __shfl(incl, 63, 64);
     }
@@ -129,12 +124,7 @@ __global__ void __launch_bounds__(256) permute_scatter_kernel(const PermArgs a) 
       }
     }
     // exclusive scan of the totals over the experts
-    int incl = run;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int up = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += up;
-    }
+    const int incl = wave_incl_scan(run);
     if (lane == 63) wtot[w] = incl;
     __syncthreads();
     int off_e = incl - run;

@@ -112,12 +112,7 @@ __device__ __forceinline__ void permute_small_body(const PermArgs& a, int (*hist
     h[ww] = e < a.Ne ? hist[ww][e] : 0;
     c += h[ww];
   }
-  int incl = c;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int up = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += up;
-  }
+  const int incl = wave_incl_scan(c);
   if (lane == 63 && w < 4) wtot[w] = incl;
   __syncthreads();
   if (e < a.Ne) {
