@@ -43,7 +43,8 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
     int t = t0 + 16 * tm + r;
     xrow[tm] = (size_t)(t < a.T ? t : a.T - 1) * a.d;
   }
-  for (int nc = 0; nc < a.NO; nc += NC) {
+  // passes over the router rows: one workgroup after the other, or (split form) side by side
+  for (int nc = blockIdx.z * NC; nc < a.NO; nc += NC * gridDim.z) {
     const float* wrow[TN];
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn) {
@@ -518,7 +519,13 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
       }
     }
   }
-  const int TN = tiles <= 1 ? 1 : tiles == 2 ? 2 : tiles == 3 ? 3 : 5;
+  // Column tiles of 16 router rows per workgroup.  Split form, few tokens: one, and the passes over the router rows side by
+  // side: what counts is the length of a wave's chain (one after the other with up to five: d = 4096, 68 rows, 32
+  // tokens 12.9 us, now 10.0, 160 tokens 15.4 and 12.0; d = 1024, 136 rows, 32 tokens 21.7 and 14.1, 40 rows 9.7 and 8.5).  From about
+  // 400 tokens on reading the tokens once per column tile costs more (d = 1024, 40 rows: even at 400, 10.6 to 11.7 at 1000).
+  int TN = tiles <= 1 ? 1 : tiles == 2 ? 2 : tiles == 3 ? 3 : 5;
+  if (a.dsplit > 1 && L.T <= 400) TN = 1;
+  const int passes = a.dsplit > 1 ? (tiles + TN - 1) / TN : 1;
   int TM = (L.T >= 16384 && TN <= 2) ? 2 : 1;   // wider combinations would spill registers
   size_t smem = 0;
   for (;; TM = 1) {
@@ -529,7 +536,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
     if (smem <= 96 * 1024 || TM == 1) break;
   }
   const int BT = 16 * TM;
-  dim3 grid((L.T + BT - 1) / BT, a.dsplit), block(64 * NW);
+  dim3 grid((L.T + BT - 1) / BT, a.dsplit, passes), block(64 * NW);
   const bool bf = dtype == MOHGE_BF16;
   hipError_t e;
   if (TM == 2) e = bf ? launch_tn<true, 2>(a, TN, grid, block, smem, s)
