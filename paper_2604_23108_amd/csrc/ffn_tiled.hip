@@ -244,7 +244,7 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
   const long long ctot = sh.cp[256];
   // expert (visiting position) of tile t: last v with tp[v] <= t
   auto expert_of = [&](int t) {
-    int lo = 0, hi = 255;
+    int lo = 0, hi = a.Ne - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (sh.tp[mid] <= t) lo = mid; else hi = mid - 1;
@@ -260,52 +260,63 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
   // XCD x starts at the first tile whose preceding cost is >= x/8 of the total.  The cost before
   // the tile at position rel of an expert follows from the band order in closed form, so the tile
   // is found by bisection once the expert is known.
-  if (v <= kXcds) {
-    int tile = total;
-    if (v < kXcds) {
-      const long long target = (ctot * v + kXcds - 1) / kXcds;
-      int lo = 0, hi = 255;                  // last expert with cp[ve] <= target
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (sh.cp[mid] <= target) lo = mid; else hi = mid - 1;
-      }
-      const int ve = lo;
-      const int c = sh.cnt[ve], kcv = sh.kc[ve], ntv = sh.nt[ve];
-      const long long rem = target - sh.cp[ve];
-      if (rem <= 0 || c == 0 || kcv == 0 || ntv == 0) {
-        tile = (int)sh.tp[ve];               // (cp[ve] == target: the expert's first tile)
-        if (rem > 0) tile = (int)sh.tp[ve + 1];
-      } else {
-        const int mt = (c + h - 1) / h, units = (c + 63) / 64, hu = h / 64;
-        auto cost_before = [&](int rel) -> long long {
-          if (rel >= mt * ntv) return ((long long)kTileCost * mt + units) * ntv * kcv;
-          const int bnd = rel / (RB * ntv), rel2 = rel - bnd * RB * ntv;
-          const int rb = min(RB, mt - bnd * RB);
-          const int ni = rel2 / rb, mi2 = rel2 % rb;
-          const int ub = min(units - bnd * RB * hu, RB * hu);       // 64-row units of this band
-          return ((long long)kTileCost * rel + (long long)bnd * RB * hu * ntv + (long long)ni * ub +
-                  min(mi2 * hu, ub)) * kcv;
-        };
-        int rl = 0, rh = mt * ntv;           // smallest rel with cost_before(rel) >= rem
-        while (rl < rh) {
-          const int mid = (rl + rh) >> 1;
-          if (cost_before(mid) >= rem) rh = mid; else rl = mid + 1;
-        }
-        tile = (int)sh.tp[ve] + rl;
-        if (tile > (int)sh.tp[ve + 1]) tile = (int)sh.tp[ve + 1];
-      }
+  // (a wave takes two of the eight ranges and its lanes look at 64 positions at once: one thread per range, bisecting
+  // over 256 experts: 13.7 us for the launch at 24 experts x 683 rows, now 11.9)
+  for (int x = w; x < kXcds; x += 4) {
+    const long long target = (ctot * x + kXcds - 1) / kXcds;
+    int lo = 0, hi = a.Ne - 1;               // last expert with cp[ve] <= target
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (sh.cp[mid] <= target) lo = mid; else hi = mid - 1;
     }
-    if (part == 0) a.hdr->xcd_begin[v] = tile;
-    sh.xb[v] = tile;
+    const int ve = lo;
+    const int c = sh.cnt[ve], kcv = sh.kc[ve], ntv = sh.nt[ve];
+    const long long rem = target - sh.cp[ve];
+    int tile;
+    if (rem <= 0 || c == 0 || kcv == 0 || ntv == 0) {
+      tile = (int)sh.tp[ve];                 // (cp[ve] == target: the expert's first tile)
+      if (rem > 0) tile = (int)sh.tp[ve + 1];
+    } else {
+      const int mt = (c + h - 1) / h, units = (c + 63) / 64, hu = h / 64;
+      auto cost_before = [&](int rel) -> long long {
+        if (rel >= mt * ntv) return ((long long)kTileCost * mt + units) * ntv * kcv;
+        const int bnd = rel / (RB * ntv), rel2 = rel - bnd * RB * ntv;
+        const int rb = min(RB, mt - bnd * RB);
+        const int ni = rel2 / rb, mi2 = rel2 % rb;
+        const int ub = min(units - bnd * RB * hu, RB * hu);         // 64-row units of this band
+        return ((long long)kTileCost * rel + (long long)bnd * RB * hu * ntv + (long long)ni * ub +
+                min(mi2 * hu, ub)) * kcv;
+      };
+      // smallest rel in [0, mt * ntv] with cost_before(rel) >= rem (the last one has it): lane l looks at the end of
+      // the l-th of 64 stretches, and the first that qualifies holds it
+      int rl = 0, len = mt * ntv + 1;
+      while (len > 1) {
+        const int step = (len + 63) / 64, at = min((lane + 1) * step, len) - 1;
+        const unsigned long long ok = __ballot(cost_before(rl + at) >= rem);
+        const int first = ok ? (int)__builtin_ctzll(ok) : 63;
+        rl += first * step;
+        len = min(step, len - first * step);
+      }
+      tile = min((int)sh.tp[ve] + rl, (int)sh.tp[ve + 1]);
+    }
+    if (lane == 0) {
+      if (part == 0) a.hdr->xcd_begin[x] = tile;
+      sh.xb[x] = tile;
+    }
+  }
+  if (v == kXcds) {
+    if (part == 0) a.hdr->xcd_begin[v] = total;
+    sh.xb[v] = total;
   }
   __syncthreads();
   // tiles of the shortest reduction before tile t (t may be `total`)
-  auto short_before = [&](int t) {
-    if (t >= total) return sh.sp[256];
-    const int ve = expert_of(t);
+  auto short_before = [&](int t, int ve) {         // ve: the tile's expert
     return sh.sp[ve] + ((sh.sp[ve + 1] > sh.sp[ve]) ? t - (int)sh.tp[ve] : 0);
   };
-  if (v <= kXcds) sh.xs[v] = short_last ? short_before(sh.xb[v]) : 0;
+  if (v <= kXcds) {
+    const int t = sh.xb[v];
+    sh.xs[v] = !short_last ? 0 : t >= total ? sh.sp[256] : short_before(t, expert_of(t));
+  }
   __syncthreads();
   for (int t = v + 256 * part; t < total; t += 256 * nparts) {
     const int ve = expert_of(t);
@@ -331,7 +342,7 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
     if (short_last) {
       int x = 0;                                   // the tile's XCD range
       while (x + 1 < kXcds && t >= sh.xb[x + 1]) ++x;
-      const int sb = short_before(t) - sh.xs[x];   // short tiles of the range before t
+      const int sb = short_before(t, ve) - sh.xs[x];   // short tiles of the range before t
       const int nlong = (sh.xb[x + 1] - sh.xb[x]) - (sh.xs[x + 1] - sh.xs[x]);
       const bool is_short = sh.sp[ve + 1] > sh.sp[ve];
       pos = is_short ? sh.xb[x] + nlong + sb : sh.xb[x] + (t - sh.xb[x]) - sb;
