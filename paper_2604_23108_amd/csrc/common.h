@@ -1,6 +1,7 @@
 // Internal declarations shared by the host entry points and the gfx950 kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <atomic>
 #include <stdint.h>
 
 #include "mohge.h"
@@ -49,6 +50,19 @@ int check_config(const mohge_config* cfg, LayerDesc* out);
 // pointer check shared by the entry points: NULL (when required) and 16-byte alignment
 int need(const void* p, const char* name, bool required);
 int hip_rc(hipError_t e, const char* what);
+
+// A kernel launched with more than 64 KB of dynamic LDS has to be allowed to, once per GPU (`done`: a bit per GPU; the
+// attribute may be set twice by threads that race, which is harmless)
+inline hipError_t allow_lds(const void* kern, int bytes, std::atomic<unsigned long long>& done) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = 1ull << (dev & 63);
+  if (dev < 64 && (done.load(std::memory_order_relaxed) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
 
 // bf16 <-> fp32 on the device, bit level (round to nearest even on the way down)
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {

@@ -348,13 +348,9 @@ static hipError_t launch_f32(const F32Args& a, hipStream_t s) {
   constexpr int smem = kFStages * kFStage;
   static_assert(smem >= kFW * 16 * 64 * (int)sizeof(double), "the exchanged sums");
   auto kern = ffn_f32_kernel<UP>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static std::atomic<unsigned long long> allowed{0};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), smem, allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy), dim3(64 * kFW), smem, s, a);
   return hipGetLastError();
 }
@@ -370,13 +366,15 @@ hipError_t launch_ffn_f32(const LayerDesc& L, const void* x, const int32_t* perm
   // every expert with rows adds at most one partial tile
   const long long live = L.P < L.Ne ? L.P : L.Ne;
   up.ntm = (int)(((long long)L.P + (kFM - 1) * live) / kFM);
-  up.ntn = (L.Fmax / (kFN / 2) + 7) / 8 * 8;
+  // (rows of column tiles of a multiple of 8, see the kernel; fewer than 8 would mostly start workgroups for nothing)
+  auto row8 = [](int n) { return n < 8 ? n : (n + 7) / 8 * 8; };
+  up.ntn = row8(L.Fmax / (kFN / 2));
   F32Args dn = up;
   dn.A = static_cast<const float*>(ws);
   dn.perm = nullptr;
   dn.C = static_cast<float*>(y_perm);
   dn.lda = L.Fmax; dn.ldc = L.d;
-  dn.ntn = ((L.d + kFN - 1) / kFN + 7) / 8 * 8;
+  dn.ntn = row8((L.d + kFN - 1) / kFN);
   for (int g = 0; g < kMaxGroups; ++g) up.order[g] = g;
   for (int i = 1; i < L.Ng; ++i)
     for (int j = i; j > 0 && L.F[up.order[j]] > L.F[up.order[j - 1]]; --j) {

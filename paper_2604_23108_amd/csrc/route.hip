@@ -391,13 +391,9 @@ __global__ void __launch_bounds__(512) route_finish_kernel(const RouteArgs a) {
 template <bool BF16, int TM, int TN>
 static hipError_t launch_one(const RouteArgs& a, dim3 grid, dim3 block, size_t smem, hipStream_t s) {
   auto kern = route_kernel<BF16, TM, TN>;
-  static bool attr_done = false;      // more than 64 KB of dynamic LDS needs the opt-in
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static std::atomic<unsigned long long> allowed{0};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), 160 * 1024, allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, grid, block, smem, s, a);
   return hipGetLastError();
 }
