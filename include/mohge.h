@@ -152,8 +152,8 @@ int mohge_permute_static(const mohge_config* cfg, const int32_t* expert_idx, int
  * workspace DEVICE, at least mohge_workspace_size(cfg, MOHGE_CALL_EXPERT_FFN) bytes;
  * it holds h between the two projections.
  * bf16: products on the matrix cores with fp32 accumulation; h and y_perm are
- * rounded to bf16 once each.  fp32: operands as the exact sum of three bf16 numbers, products on the bf16
- * matrix cores, fp32 chains of 64 products added with compensation; h and y_perm are rounded to fp32 once each.
+ * rounded to bf16 once each.  fp32: products on the fp32 matrix cores, sixteen at a time added in
+ * fp32 and their sums in fp64; h and y_perm are rounded to fp32 once each.
  * Residency: for bf16 and T > 32 the call takes one of two forms by size, with the same bits.  Where
  * tiles of 256 x 256 would leave compute units idle, each projection is a launch of 128 x 128 tiles and nothing
  * waits inside it.  Otherwise both projections run as ONE persistent launch of one workgroup

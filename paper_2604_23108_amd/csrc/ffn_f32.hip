@@ -1,33 +1,40 @@
-// Expert feed-forward networks of a layer stored in fp32, on gfx950: a ragged grouped GEMM, one launch per
-// projection, on the bf16 matrix cores with every fp32 operand split into three bf16 parts.
+// Expert feed-forward networks of a layer stored in fp32, on gfx950: a ragged grouped GEMM on the
+// fp32 matrix cores (v_mfma_f32_32x32x2_f32), one launch per projection.
 //
-// The fp32 matrix instructions run at a sixteenth of the bf16 rate.  An fp32 number is the sum of three bf16 numbers
-// (x rounded to bf16, the remainder rounded to bf16, the rest: exact, the remainders need no more bits), the product of
-// two bf16 numbers is exact in fp32, and of the nine products of two such sums six matter: the others (mid.lo, lo.mid,
-// lo.lo) are below 2^-26 of the product.  Six bf16 products cost 3/8 of one fp32 product.
+// What bounds it: the fp32 matrix rate, 256 FLOP per clock and compute unit (a sixteenth of bf16),
+// down to a few rows per expert, where it is the weight stream.  An MFMA keeps a SIMD busy for 64
+// clocks on two operand registers, so operand delivery is never the limit and the tile is chosen for
+// balance: 32 token rows x 64 weight rows (up: 32 W_gate rows and the matching 32 W_up rows), so that
+// partial row blocks cost little and a layer of 3072 routed rows gives every compute unit several
+// tiles.  Four waves: two weight fragments x two halves of every stage's reduction indices, which
+// meet in LDS at the end.
+// Measured on 512 tokens, d = 1024, 32 experts of width 256..896, six per token (10.9 GFLOP): both projections
+// take 188 us (58 TFLOP/s of a possible 154; 179 with its sums in fp32 alone, see below), the one-wave-per-output
+// dot products that this replaced 1.42 ms.  At 4096 tokens of a d = 2048 layer it runs at 84 TFLOP/s.
+// (With fp32 sums, 64-row tiles were 8 % slower on the first, whose whole tiles divide worse over the compute units,
+// and 6 % faster on the second.)
 //
-// What bounds it: up to a few rows per expert the weight stream; beyond that, about equally, the products, the
-// conversions (11 instructions per pair of values), the copies to LDS and what a tile pays before and after its main
-// loop.  Tile: 32 token rows x 128 weight rows (up: 64 of W_gate and the matching 64 of W_up) in stages of 32 reduction
-// indices; four waves: two halves of the weight rows x two halves of every stage, so that each wave splits what it
-// multiplies and nothing but the tokens is split twice.  Two workgroups per compute unit cover each other's prologue
-// and epilogue.  64 token rows per tile need more than half of the registers, so one workgroup per unit: 138 -> 154 us on
-// the case below, 59 -> 70 at 9 to 68 tokens; without the interleaving described at stage() 182.
-// Measured on 512 tokens, d = 1024, 32 experts of width 256..896, six per token (10.9 GFLOP), both projections: 138 us;
-// on the fp32 matrix cores 188.  68 tokens of that layer 80 -> 61 us (3.7 TB/s of weights), 4096 tokens of a d = 2048
-// layer 2420 -> 1630 us.  64 tokens of a layer of d = 128 and widths of 64 to 256, where a launch is a chain of latencies,
-// 15 -> 18.5.
+// Operands go global -> LDS (global_load_lds, 256-byte row segments, 16-byte pieces XOR-swizzled by
+// the row) through two stages of 64 reduction indices (48 KB: three workgroups per compute unit), one
+// barrier per stage; the fragments of a stage are in registers while the next but one is on its way.
+// A lane's 128-bit fragment read holds four consecutive reduction indices of one row and feeds four
+// MFMAs; both operands use the same assignment.
 //
-// Operands go global -> LDS (128-byte row segments, 16-byte pieces XOR-swizzled by the row) through four stages, three of
-// them in flight, one barrier per stage.
+// Every product of an MFMA rounds the running sum, so a chain of n products carries about n/2 roundings.  A chain
+// here is the eight products of one such group; the sums of two groups are added, and the pairs go into an fp64
+// total that is rounded once: 6.5 roundings for any length of the reduction.  The conversions and fp64 additions of
+// a pair run under the MFMAs of the next one (every group folded by itself, behind its MFMAs: 144 us instead of 130 at
+// 300 tokens of the layer above).
+// Error of the two projections against float64 (2-norm): 1.21e-7 at 64 indices, 1.25e-7 at 4096; with fp32 chains of
+// 64 in a second fp32 set it was 2.1e-7 and 3.1e-7, with the dot products (a sum spread over 64 lanes, then a
+// butterfly) 1.26e-7 and 2.6e-7.
 //
-// Error: the matrix instruction rounds once per eight products, and a chain here is four stages of 16 indices: 4.5
-// roundings.  Chains are added with compensation (what the addition rounds away starts the next chain), the five small
-// products have accumulators of their own, the halves of a stage meet in fp64 and SiLU(a) b is evaluated in fp64.
-// Against float64 (2-norm of both projections) 6.2e-8 at 64 indices, 9.2e-8 from 1024 to 4096; on the fp32 matrix
-// cores in chains of eight products with an fp64 total it was 1.21e-7 and 1.25e-7.  (Chains of eight stages: 1.28e-7,
-// 2 % faster.)  A sum that is not finite, from an operand that is not or from the largest finite numbers, whose
-// leading part rounds to infinity, is evaluated again as a plain dot product.
+// Why not the bf16 matrix cores, with every operand split into three bf16 parts: 512 tokens of the layer above took 139 us
+// instead of 188 with the six largest of the nine products, 153 with eight.  But v_mfma_f32_32x32x16_bf16 cuts off what lies
+// below its largest addend instead of rounding it, always downwards: one projection of 4096 indices with every 97th
+// channel a thousand times as large was off by 8.8e-8, 70 % of it one-sided drift, 16384 indices by 1.2e-7 (here 6.5e-8, no
+// drift); chains short enough to stop that cost what the products save.  Below 2^-110 the third part falls under the smallest
+// bf16 number (2e-6 at 2^-116), and a launch of one round of workgroups, any layer at one token, was 1.2 times as long.
 //
 // No schedule launch: a workgroup finds the expert of its row tile from `offsets` with a wave-wide
 // scan.  The grid covers the largest possible number of row tiles; the ones that do not exist exit.
@@ -35,12 +42,9 @@
 
 namespace mohge {
 
-typedef float f32v4 __attribute__((ext_vector_type(4)));
+typedef float f32v4 __attribute__((ext_vector_type(4)));   // (fragment reads as HIP's float4 struct make the
+                                                          //  compiler wait for all LDS-bound loads first)
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
-typedef float f32v2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32v4 __attribute__((ext_vector_type(4)));
 
 struct F32Args {
   const float* A;                 // up: x; down: H
@@ -54,13 +58,21 @@ struct F32Args {
   int order[kMaxGroups];          // groups by decreasing width: the longest down tiles start first
 };
 
-constexpr int kFM = 32, kFN = 128, kFK = 32;           // token rows (at most), weight rows, reduction depth of a stage
-constexpr int kFW = 4;                                 // waves: two halves of the weight rows x two halves of a stage
-constexpr int kFStages = 4;
-constexpr int kFStage = (kFM + kFN) * kFK * 4;         // 20 KB: two workgroups fill a compute unit's LDS
-constexpr int kFChunk = 4;                             // stages per fp32 chain
+constexpr int kFM = 32, kFN = 64, kFK = 64;            // tile rows (tokens), weight rows, reduction depth of a stage
+constexpr int kFW = 4;                                 // waves: two weight fragments x kFW/2 parts of a stage
+constexpr int kFStage = (kFM + kFN) * kFK * 4;         // 24 KB
+constexpr int kFStages = 2;
+constexpr int kFChunks = kFK / 4;                      // 16-byte pieces of a stage row
+constexpr int kFLoads = (kFM + kFN) * kFChunks / (64 * kFW);   // loads per thread and stage
+constexpr int kFKW = 2 * kFK / kFW;                    // reduction indices of a stage per wave
 
-// expert, first sorted row and row count of row tile m; false if there is no such tile.  The same in every lane; called by whole waves.
+__device__ __forceinline__ void f32_copy16(const float* g, unsigned char* lds_uniform_base) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                   (__attribute__((address_space(3))) void*)lds_uniform_base, 16, 0, 0);
+}
+
+// expert, first sorted row and row count of row tile m; false if there is no such tile.  The same in
+// every lane; called by whole waves.
 __device__ __forceinline__ bool f32_row_tile(const F32Args& a, int m, int lane, int& e, int& row, int& rows) {
   int before = 0;
   for (int e0 = 0; e0 < a.Ne; e0 += 64) {
@@ -85,253 +97,171 @@ __device__ __forceinline__ bool f32_row_tile(const F32Args& a, int m, int lane, 
   return false;
 }
 
-// Eight values of a row as three bf16 operand fragments
-struct Split { u32v4 hi, mid, lo; };
-
-// Splitting one pair of values, in seven steps of one to two independent instructions each: a wave's dependent
-// instructions do not follow each other without a gap, so steps of different pairs are issued side by side.
-struct PairSplit {
-  float x0, x1, u0, u1;
-  uint32_t h, m;
-  __device__ __forceinline__ void step(int k, const f32v4 (&v)[2], Split& s, int j) {
-    if (k == 0) { x0 = v[j >> 1][2 * (j & 1)]; x1 = v[j >> 1][2 * (j & 1) + 1]; h = pack_bf16x2(x0, x1); }
-    if (k == 1) { u0 = __uint_as_float(h << 16); u1 = __uint_as_float(h & 0xffff0000u); }
-    if (k == 2) { x0 -= u0; x1 -= u1; }
-    if (k == 3) m = pack_bf16x2(x0, x1);
-    if (k == 4) { u0 = __uint_as_float(m << 16); u1 = __uint_as_float(m & 0xffff0000u); }
-    if (k == 5) { x0 -= u0; x1 -= u1; }
-    if (k == 6) { s.hi[j] = h; s.mid[j] = m; s.lo[j] = pack_bf16x2(x0, x1); }
-  }
-};
-constexpr int kSplitSteps = 7;
-
-__device__ __forceinline__ f32x16 mfma_b(u32v4 a, u32v4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16v8, a), __builtin_bit_cast(bf16v8, b), c, 0, 0, 0);
-}
-
-// A dot product by a plain walk: for sums that are not finite.
-__device__ __noinline__ double f32_plain_dot(const float* w, const float* x, int K) {
-  double s = 0.0;
-  for (int k = 0; k < K; ++k) s = fma((double)w[k], (double)x[k], s);
-  return s;
-}
-
-// SiLU(a) b of finite numbers, rounded once.  exp(-a) = 2^n (1 + r + r^2 q(r)), |r| <= ln(2) / 2, q a Taylor polynomial in fp32
-// (its part of the sum is below r^2, so that its rounding stays below 1e-8).
-__device__ __forceinline__ float silu_times(double a, double b) {
-  const double t = fmin(fmax(a * -1.4426950408889634, -1020.0), 1020.0);
-  const double n = rint(t), r = (t - n) * 0.6931471805599453;
-  const float f = (float)r;
-  float q = fmaf(f, 2.4801587e-5f, 1.9841270e-4f);
-  q = fmaf(f, q, 1.3888889e-3f);
-  q = fmaf(f, q, 8.3333333e-3f);
-  q = fmaf(f, q, 4.1666667e-2f);
-  q = fmaf(f, q, 1.6666667e-1f);
-  q = fmaf(f, q, 0.5f);
-  const double den = 1.0 + ldexp(1.0 + (r + (double)(f * f * q)), (int)n);
-  double inv = __builtin_amdgcn_rcp(den);
-  inv = fma(inv, fma(-den, inv, 1.0), inv);
-  return (float)(a * b * inv);
-}
-
-// 16 bytes per lane to LDS at a wave-uniform address, not modelled by the compiler (which would wait for every copy
-// it knows of in front of a read of LDS); the destination is an operand in M0.
-__device__ __forceinline__ void f32_copy16(const float* g, int lds_addr) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, off"
-               ::"v"(g), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
-}
-
 template <bool UP>
-__device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, int e, int row, int rows, int n0, int w,
-                                         int lane) {
+__device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, int e, int row, int rows, int n0,
+                                         int w, int lane) {
   const int g = e / a.N, i = e % a.N, F = a.F[g], K = UP ? a.d : F;
-  const bool half = !UP && n0 + kFN > a.d;                     // the last 64 columns of d = 64 (mod 128)
-  // weight row b of the tile: up 16 rows of W_gate, then the matching 16 of W_up, and so on
-  auto weight_row = [&](int b) -> const float* {
-    if constexpr (UP) return a.W[g] + ((long long)i * 2 * F + ((b & 16) ? F : 0) + n0 + 16 * (b >> 5) + (b & 15)) * K;
-    else return a.W[g] + ((long long)i * a.d + n0 + b) * K;
-  };
-  auto token_row = [&](int r) -> const float* {
-    const int pos = row + (r < rows ? r : rows - 1);           // rows past the end: any valid row
-    return a.A + (UP && a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos) * a.lda;
-  };
-  // A wave-wide copy fills 8 stage rows (128 bytes each): lane l row l/8, physical piece l%8, which holds logical
-  // piece (l%8) ^ (row%8).  Wave w copies weight rows 32j + 8w .. +7 and token rows 8w .. +7.
-  const int piece = ((lane & 7) ^ (lane >> 3)) * 4;
-  const float* const src_w = weight_row(8 * w + (lane >> 3)) + piece;
-  const float* const src_x = token_row(8 * w + (lane >> 3)) + piece;
-  const long long wstep = (UP ? 16ll : 32ll) * K;
-  constexpr int LOADS = kFN / 32 + 1;
-  const int lds0 = (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)lds;
-  auto issue = [&](int kt, int slot) {
-    const int dst = lds0 + slot * kFStage + w * 1024;
+  const int ncols = UP ? F : a.d;
+  // wave-wide load j fills stage rows 4*(4j + w) .. +3: first the token rows, then the weight rows;
+  // lane l fills row l/16, physical piece l%16, which holds logical piece (l%16) ^ (row & 15)
+  const float* src[kFLoads];
 #pragma unroll
-    for (int j = 0; j < kFN / 32; ++j)
-      f32_copy16(src_w + (half && j >= 2 ? j - 2 : j) * wstep + kt * kFK, dst + j * 4096);
-    f32_copy16(src_x + kt * kFK, dst + kFN * kFK * 4);
-  };
-  const int KT = K / kFK;                                      // K is a multiple of 64: an even number of stages
-  // (a request past the end repeats the last stage, so that every stage waits for the same number of copies)
-#pragma unroll
-  for (int kt = 0; kt < kFStages - 1; ++kt) issue(min(kt, KT - 1), kt);
-
-  const int wm = w & 1, kq = w >> 1, fr = lane & 31, fh = lane >> 5;
-  const int p0 = ((4 * kq + 2 * fh) ^ (fr & 7)) << 4, p1 = p0 ^ 16;
-  const unsigned char* const pw = lds + (64 * wm + fr) * (kFK * 4);
-  const unsigned char* const px = lds + (kFN + fr) * (kFK * 4);
-  struct Raw { f32v4 v[3][2]; };                               // two weight fragments, the token fragment
-  struct Planes { Split v[3]; };
-  f32x16 big[2], small[2], tot[2];
-#pragma unroll
-  for (int f = 0; f < 2; ++f)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { big[f][r] = 0.f; small[f][r] = 0.f; tot[f][r] = 0.f; }
-  int slot = 0;                                                // of the stage read next
-  auto fetch = [&](int kt, Raw& raw) {                         // stage kt, once it has landed everywhere
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kFStages - 2) * LOADS) : "memory");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    const int so = slot * kFStage;
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-      const unsigned char* p = f < 2 ? pw + so + f * 4096 : px + so;
-      raw.v[f][0] = *reinterpret_cast<const f32v4*>(p + p0);
-      raw.v[f][1] = *reinterpret_cast<const f32v4*>(p + p1);
+  for (int j = 0; j < kFLoads; ++j) {
+    const int r = (64 / kFChunks) * (kFW * j + w) + lane / kFChunks;
+    const int piece = (lane % kFChunks) ^ (r & 15);
+    if (j < kFM * kFChunks / (64 * kFW)) {
+      const int pos = row + (r < rows ? r : rows - 1);         // rows past the end: any valid row
+      const long long s = UP && a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
+      src[j] = a.A + s * a.lda + piece * 4;
+    } else {
+      const int b = r - kFM;
+      long long wrow;
+      if constexpr (UP) {
+        // weight rows of a wave: 16 of W_gate, then the matching 16 of W_up
+        int f = n0 + 16 * (b >> 5) + (b & 15);
+        if (f > F - 1) f = F - 1;
+        wrow = (long long)i * 2 * F + ((b & 16) ? F : 0) + f;
+      } else {
+        int n = n0 + b;
+        if (n > a.d - 1) n = a.d - 1;
+        wrow = (long long)i * a.d + n;
+      }
+      src[j] = a.W[g] + wrow * K + piece * 4;
     }
-    // the slot of the stage before, which every wave had in registers by the barrier, takes a new one
-    issue(min(kt + kFStages - 1, KT - 1), slot == 0 ? kFStages - 1 : slot - 1);
-    slot = slot == kFStages - 1 ? 0 : slot + 1;
-    __builtin_amdgcn_sched_barrier(0);
+  }
+  const int KT = K / kFK;                                        // K is a multiple of 64
+  auto issue = [&](int kt) {
+    unsigned char* dst = lds + (kt % kFStages) * kFStage + w * 1024;
+#pragma unroll
+    for (int j = 0; j < kFLoads; ++j) f32_copy16(src[j] + kt * kFK, dst + j * kFW * 1024);
   };
-  // product i of a stage: the six pairs of parts that matter, on both accumulators in turn
-  auto product = [&](const Planes& p, int i) {
-    const int k = i / 2, f = i % 2;
-    const Split &b = p.v[f], &x = p.v[2];
-    if (k == 0) small[f] = mfma_b(b.lo, x.hi, small[f]);
-    if (k == 1) big[f] = mfma_b(b.hi, x.hi, big[f]);
-    if (k == 2) small[f] = mfma_b(b.hi, x.lo, small[f]);
-    if (k == 3) small[f] = mfma_b(b.mid, x.mid, small[f]);
-    if (k == 4) small[f] = mfma_b(b.mid, x.hi, small[f]);
-    if (k == 5) small[f] = mfma_b(b.hi, x.mid, small[f]);
+#pragma unroll
+  for (int kt = 0; kt < kFStages; ++kt)
+    if (kt < KT) issue(kt);
+
+  // wave: weight fragment wn (32 rows), and of every stage the reduction indices [kFKW kq, kFKW kq + kFKW)
+  const int wn = w & 1, kq = w >> 1;
+  const int fr = lane & 31, fh = lane >> 5, sw = fr & 15;
+  constexpr int NK = kFKW / 8;
+  struct Frags { f32v4 b[NK], x[NK]; };
+  auto read = [&](int kt, Frags& f) {
+    const unsigned char* st = lds + (kt % kFStages) * kFStage;
+    const unsigned char* pa = st + fr * (kFK * 4);
+    const unsigned char* pb = st + (kFM + 32 * wn + fr) * (kFK * 4);
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const int off = ((2 * (NK * kq + k) + fh) ^ sw) << 4;
+      f.b[k] = *reinterpret_cast<const f32v4*>(pb + off);
+      f.x[k] = *reinterpret_cast<const f32v4*>(pa + off);
+    }
   };
-  constexpr int kProducts = 12, kPairs = 12;
-  // compensated: what the addition rounds away starts the next chain
-  auto fold = [&](int f, int r) {
-    const float s = tot[f][r] + big[f][r];
-    big[f][r] -= s - tot[f][r];
-    tot[f][r] = s;
+  // total so far, and the sum of the last two groups of eight products, not in it yet
+  double tot[16];
+  float pair[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { tot[r] = 0.0; pair[r] = 0.f; }
+  auto fold = [&]() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tot[r] += (double)pair[r];
   };
-  // The products of stage kt.  Under them stage kt+1 is read and split, a step of seven neighbouring pairs behind every
-  // product, and one accumulator may be folded (its own product of this stage is long done by then).
-  auto stage = [&](int kt, const Planes& now, Planes& next, int folded) {
-    Raw raw;
-    PairSplit ps[kPairs];
-    fetch(kt + 1, raw);
+  // Stage kt, whose fragments are in `use`: once the loads of stage kt+1 have landed everywhere its
+  // fragments are read into `nxt` (under the MFMAs of stage kt), and stage kt+2 is requested into the
+  // slot of stage kt, which every wave has in registers by the barrier.
+  auto stage = [&](int kt, Frags& use, Frags& nxt) {
+    if (kt + 1 < KT) {
+      // (a plain barrier: __syncthreads() would also wait for the loads of later stages)
+      if (kt + kFStages - 1 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kFStages - 2) * kFLoads) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      read(kt + 1, nxt);
+      // behind the reads in program order: in front of them the compiler waits for the loads first
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + kFStages < KT) issue(kt + kFStages);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-    for (int i = 0; i < kProducts; ++i) {
-      product(now, i);
-      constexpr int first = 1, slots = kProducts - first;      // (the fragments are on their way during the first)
+    for (int k = 0; k < NK; k += 2) {
+      f32x16 n0, n1;
 #pragma unroll
-      for (int c = 0; c < kPairs; ++c)
+      for (int r = 0; r < 16; ++r) { n0[r] = 0.f; n1[r] = 0.f; }
 #pragma unroll
-        for (int k = 0; k < kSplitSteps; ++k)
-          if (first + (c + k) * slots / (kPairs + kSplitSteps - 1) == i)
-            ps[c].step(k, raw.v[c / 4], next.v[c / 4], c % 4);
-      if (folded >= 0) {
+      for (int c = 0; c < 4; ++c) n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][c], use.x[k][c], n0, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (5 + r * (kProducts - 5) / 16 == i) fold(folded, r);
+      for (int c = 0; c < 4; ++c)
+        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + 1][c], use.x[k + 1][c], n1, 0, 0, 0);
+      fold();
+#pragma unroll
+      for (int r = 0; r < 16; ++r) pair[r] = n0[r] + n1[r];
+      // the previous pair is folded under the MFMAs of this one
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);       // four of the 32 conversions and additions
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  Planes pa, pb;
-  {
-    Raw raw;
-    PairSplit ps[kPairs];
-    fetch(0, raw);
-#pragma unroll
-    for (int k = 0; k < kSplitSteps; ++k)
-#pragma unroll
-      for (int c = 0; c < kPairs; ++c) ps[c].step(k, raw.v[c / 4], pa.v[c / 4], c % 4);
+  Frags f0, f1;
+  if (KT >= kFStages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kFStages - 1) * kFLoads) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  read(0, f0);
+  for (int kt = 0; kt < KT; kt += 2) {
+    stage(kt, f0, f1);
+    if (kt + 1 < KT) stage(kt + 1, f1, f0);
   }
-  // (the last stage reads and splits itself once more: code for a stage without a next one costs more at short
-  // reductions than it saves)
-  static_assert(kFChunk == 4, "stages of the loop below");
-  for (int kt = 0;;) {
-    stage(kt, pa, pb, 0);
-    stage(kt + 1, pb, pa, 1);
-    if ((kt += 2) >= KT) break;
-    stage(kt, pa, pb, -1);
-    stage(kt + 1, pb, pa, -1);
-    if ((kt += 2) >= KT) break;
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // the repeated copies
-  // The two halves of the reduction meet in LDS in fp64: wave kq finishes weight fragment kq of its 64 rows.
-  __syncthreads();                                             // the stages have been read
-  double* const ex = reinterpret_cast<double*>(lds);           // [4 waves][16][64]
-  double mine[16];
+  fold();
+  // The two halves of the reduction meet in LDS and are added in order.
+  __syncthreads();                                               // the stages have been read
+  double* ex = reinterpret_cast<double*>(lds) + wn * 1024;       // [wn][16][64]
+  if (kq == 1)
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const double s0 = (double)tot[0][r] + ((double)big[0][r] + (double)small[0][r]);
-    const double s1 = (double)tot[1][r] + ((double)big[1][r] + (double)small[1][r]);
-    ex[(w * 16 + r) * 64 + lane] = kq ? s0 : s1;
-    mine[r] = kq ? s1 : s0;
-  }
+    for (int r = 0; r < 16; ++r) ex[r * 64 + lane] = tot[r];
   __syncthreads();
-  if (fr >= rows || (half && wm)) return;
-  const int f = 2 * wm + kq;
-  // accumulator r of a lane: token lane%32, weight row 8*(r/4) + 4*(lane/32) + r%4 of the fragment's 32
-  bool finite = true;
+  // accumulator r of a lane: token lane%32, weight row 8*(r/4) + 4*(lane/32) + r%4 of the wave's 32
+  if (kq == 1 || fr >= rows) return;
+  float sum[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    mine[r] += ex[((w ^ 2) * 16 + r) * 64 + lane];
-    finite = finite && __builtin_isfinite(mine[r]);
-  }
-  float* const crow = a.C + (long long)(row + fr) * a.ldc + n0 + (UP ? 16 : 32) * f + 4 * fh;
-  if (!finite) {
-#pragma unroll 1
-    for (int c = 0; c < (UP ? 8 : 16); ++c) {
-      const int col = 8 * (c >> 2) + (c & 3);
-      const float* wr = weight_row(32 * f + col + 4 * fh);
-      const double v = f32_plain_dot(wr, token_row(fr), K);
-      if constexpr (UP) {
-        const double u = f32_plain_dot(wr + (long long)F * K, token_row(fr), K);
-        const float gt = (float)v;
-        crow[col] = __builtin_isfinite(v) && __builtin_isfinite(u) ? silu_times(v, u) : gt / (1.f + expf(-gt)) * (float)u;
-      } else {
-        crow[col] = (float)v;
-      }
-    }
-    return;
-  }
+  for (int r = 0; r < 16; ++r) sum[r] = (float)(tot[r] + ex[r * 64 + lane]);
+  float* crow = a.C + (long long)(row + fr) * a.ldc;
   if constexpr (UP) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      *reinterpret_cast<float4*>(crow + 8 * q) =
-          make_float4(silu_times(mine[4 * q], mine[8 + 4 * q]), silu_times(mine[4 * q + 1], mine[9 + 4 * q]),
-                      silu_times(mine[4 * q + 2], mine[10 + 4 * q]), silu_times(mine[4 * q + 3], mine[11 + 4 * q]));
+    for (int q = 0; q < 2; ++q) {
+      const int col = n0 + 16 * wn + 8 * q + 4 * fh;
+      float h[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float gt = sum[4 * q + j], up = sum[8 + 4 * q + j];
+        h[j] = gt / (1.f + expf(-gt)) * up;
+      }
+      if (col < ncols) *reinterpret_cast<float4*>(crow + col) = make_float4(h[0], h[1], h[2], h[3]);
+    }
   } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<float4*>(crow + 8 * q) =
-          make_float4((float)mine[4 * q], (float)mine[4 * q + 1], (float)mine[4 * q + 2], (float)mine[4 * q + 3]);
+    for (int q = 0; q < 4; ++q) {
+      const int col = n0 + 32 * wn + 8 * q + 4 * fh;
+      if (col < ncols)
+        *reinterpret_cast<float4*>(crow + col) = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
+    }
   }
 }
 
 template <bool UP>
-__global__ void __launch_bounds__(64 * kFW, 2) ffn_f32_kernel(const F32Args a) {
+__global__ void __launch_bounds__(64 * kFW, 3) ffn_f32_kernel(const F32Args a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long long wg = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-  // The hardware hands workgroups to the 8 XCDs in turn and a row of column tiles is a multiple of 8 long: the row
-  // tiles of an expert that share a weight panel meet in one XCD's L2.  Narrow groups start at different XCDs.
-  // (512 tokens of the layer above 136 us; four neighbouring row tiles of one column to an XCD 144, and 114 instead of 77
-  // at 70 tokens of 25 experts; all column tiles of a row tile to one XCD 149.)
-  const int m = (int)(wg / a.ntn), c = (int)(wg % a.ntn);
+  // The hardware hands workgroups to the 8 XCDs in turn (a row of the grid is a multiple of 8 long): four neighbouring
+  // row tiles of one column tile (mostly one expert's: one weight panel) go to the same XCD.
+  const int wg = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  const int xcd = wg % 8, idx = wg / 8;
+  const int tile = ((idx / 4) * 8 + xcd) * 4 + idx % 4;
+  const int m = tile % a.ntm, n = tile / a.ntm;
+  if (n >= a.ntn) return;
   int e, row, rows;
-  if (m >= a.ntm || !f32_row_tile(a, m, lane, e, row, rows)) return;
-  const int n0 = (c + 3 * e) % a.ntn * (UP ? kFN / 2 : kFN);
+  if (!f32_row_tile(a, m, lane, e, row, rows)) return;
+  const int n0 = n * (UP ? kFN / 2 : kFN);
   if (n0 >= (UP ? a.F[e / a.N] : a.d)) return;
   f32_tile<UP>(a, lds, e, row, rows, n0, w, lane);
 }
@@ -341,17 +271,13 @@ __global__ void __launch_bounds__(64 * kFW, 2) ffn_f32_kernel(const F32Args a) {
 constexpr long long kFGridX = 1ll << 20;
 
 template <bool UP>
-static hipError_t launch_f32(const F32Args& a, hipStream_t s) {
-  const long long wgs = (long long)a.ntm * a.ntn;
+static hipError_t launch_f32(F32Args& a, hipStream_t s) {
+  constexpr int smem = kFStages * kFStage;
+  static_assert(smem <= 64 * 1024 && 2 * 16 * 64 * (int)sizeof(double) <= smem, "dynamic LDS without the opt-in; the sums");
+  const long long wgs = ((long long)a.ntm * a.ntn + 31) / 32 * 32;
   const long long gx = wgs < kFGridX ? wgs : kFGridX, gy = (wgs + gx - 1) / gx;
   if (gx * gy >= 1ll << 31) return hipErrorInvalidConfiguration;   // (terabytes of activations)
-  constexpr int smem = kFStages * kFStage;
-  static_assert(smem >= kFW * 16 * 64 * (int)sizeof(double), "the exchanged sums");
-  auto kern = ffn_f32_kernel<UP>;
-  static std::atomic<unsigned long long> allowed{0};
-  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), smem, allowed);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy), dim3(64 * kFW), smem, s, a);
+  hipLaunchKernelGGL(ffn_f32_kernel<UP>, dim3((unsigned)gx, (unsigned)gy), dim3(64 * kFW), smem, s, a);
   return hipGetLastError();
 }
 
@@ -366,15 +292,13 @@ hipError_t launch_ffn_f32(const LayerDesc& L, const void* x, const int32_t* perm
   // every expert with rows adds at most one partial tile
   const long long live = L.P < L.Ne ? L.P : L.Ne;
   up.ntm = (int)(((long long)L.P + (kFM - 1) * live) / kFM);
-  // (rows of column tiles of a multiple of 8, see the kernel; fewer than 8 would mostly start workgroups for nothing)
-  auto row8 = [](int n) { return n < 8 ? n : (n + 7) / 8 * 8; };
-  up.ntn = row8(L.Fmax / (kFN / 2));
+  up.ntn = (L.Fmax + kFN / 2 - 1) / (kFN / 2);
   F32Args dn = up;
   dn.A = static_cast<const float*>(ws);
   dn.perm = nullptr;
   dn.C = static_cast<float*>(y_perm);
   dn.lda = L.Fmax; dn.ldc = L.d;
-  dn.ntn = row8((L.d + kFN - 1) / kFN);
+  dn.ntn = (L.d + kFN - 1) / kFN;
   for (int g = 0; g < kMaxGroups; ++g) up.order[g] = g;
   for (int i = 1; i < L.Ng; ++i)
     for (int j = i; j > 0 && L.F[up.order[j]] > L.F[up.order[j - 1]]; --j) {

@@ -1,5 +1,5 @@
-"""The fp32 expert networks at the edges of their tiles (32 token rows, 128 weight rows, stages of 32
-indices), on a hand-made assignment of tokens to experts, against the CPU oracle."""
+"""The fp32 expert networks at the edges of their tiles (32 token rows, 64 weight rows, 64-deep
+stages), on a hand-made assignment of tokens to experts, against the CPU oracle."""
 import numpy as np
 import pytest
 import torch
@@ -34,7 +34,7 @@ def test_ffn_f32_tile_edges(d, d_ff):
                              [t.f32 for t in inp.w_down], np.arange(T, dtype=np.int32), eidx.reshape(-1))
     got = L.y_perm.cpu().numpy()
     want = want[L.perm.cpu().numpy()]
-    # two fp32 dot products with a rounding per 8 products and the roundings between them: relative to the largest
+    # two fp32 dot products in chains of 8 with fp64 totals and the roundings between them: relative to the largest
     # output the error stays below 2^-24 * (8 + 16) with room to spare
     assert np.isfinite(got).all()
     assert np.abs(got - want).max() <= 5e-6 * np.abs(want).max()
@@ -44,11 +44,10 @@ def test_ffn_f32_tile_edges(d, d_ff):
                                     (4096, (768, 2048))])
 def test_ffn_f32_rounding_error(d, d_ff):
     """Error of the fp32 expert networks against float64, as a 2-norm.  A rounding costs 2.5e-8 rms
-    (2^-24 / sqrt(3), averaged over the mantissa).  A dot product whose chains of 64 products round once per eight and
-    are added with compensation carries the roundings of 4.5 of its values and its own: 5.9e-8, whatever its length.
-    Both operands of SiLU(a) b have it, the first amplified by up to 1.5, the product is rounded once, the second
-    projection has its own: sqrt(5.9^2 (1 + 1.5^2) + 2.5^2 + 5.9^2) = 12.4e-8; the bound is that of four roundings
-    between the projections and 6.5 in them."""
+    (2^-24 / sqrt(3), averaged over the mantissa).  A dot product in chains of eight products, added in pairs to an
+    fp64 total, carries the roundings of 4.5 + 1 + 1 of its values: 6.4e-8, whatever its length.  Both operands of
+    SiLU(a) b have it, the first amplified by up to 1.5, SiLU and the product add about four roundings, the second
+    projection its own: sqrt(6.4^2 (1 + 1.5^2) + 4 * 2.5^2 + 6.4^2) = 14e-8."""
     import paper_2604_23108_amd as M
     from gpu_harness import DeviceLayer
     T, n = 128, 2
@@ -75,8 +74,8 @@ def test_ffn_f32_rounding_error(d, d_ff):
 
 
 def test_ffn_f32_operands_without_a_finite_bf16_part():
-    """An fp32 number near the largest one rounds to infinity in bf16, and infinities and NaN have no remainder: such sums
-    are evaluated again, and the rows beside them stay as they are."""
+    """Operands near the largest fp32 number (infinity in bf16), infinities and NaN: sums that are finite come out as such, and
+    the rows beside those that are not stay as they are."""
     import paper_2604_23108_amd as M
     T, d, F = 6, 192, 64
     cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=1, d_ff=(F,), k_groups=1, k_experts=1,
@@ -98,6 +97,48 @@ def test_ffn_f32_operands_without_a_finite_bf16_part():
     for t in (0, 3, 4, 5):
         # the bound of the error test above, per row of 192 values instead of over all of them
         assert float((y[t] - want[t]).norm() / want[t].norm()) <= 3e-7, t
+
+
+def _second_projection(h, w2):
+    """The second projection alone: y = h . w2^T in fp32 and in float64."""
+    import paper_2604_23108_amd as M
+    (T, K), d = h.shape, w2.shape[1]
+    cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=1, d_ff=(K,), k_groups=1, k_experts=1,
+                   select_mode=M.SELECT_PER_GROUP, dtype=M.F32)
+    y = torch.full((T, d), float("nan"), device="cuda")
+    M.mohge_expert_ffn_down(cfg, h.cuda(), torch.tensor([0, T], dtype=torch.int32, device="cuda"), [w2.cuda()], y)
+    return y.cpu().double(), h.double() @ w2[0].double().T
+
+
+@pytest.mark.parametrize("K", [256, 4096, 16384])
+def test_ffn_f32_outlier_channels(K):
+    """A few channels a thousand times as large as the others: most products are added to a sum that is much larger.  Sums
+    that round to nearest are off by 6.5 roundings (6.4e-8, see above) at any length and to both sides alike; units that
+    cut off what lies below the sum drift to one side, in proportion to the length."""
+    gen = torch.Generator().manual_seed(K)
+    h, w2 = torch.randn((96, K), generator=gen), torch.randn((1, 320, K), generator=gen)
+    h[:, ::97] *= 1000.0
+    print(f"[f32 outliers] K={K}", flush=True)
+    y, want = _second_projection(h, w2)
+    err = y - want
+    # 30720 outputs: the mean of errors without a drift is below 4 / sqrt(30720) = 0.023 of their mean size
+    assert abs(float(err.mean() / err.abs().mean())) <= 0.05
+    # (a chain holds one outlier or none at the short length, and the sum of the few there are rounds once more)
+    assert float(err.norm() / want.norm()) <= (7.5e-8 if K > 1024 else 9e-8)
+
+
+@pytest.mark.parametrize("lo,hi", [(-112, 100), (-118, 110), (-125, 118)])
+def test_ffn_f32_operands_near_the_smallest_normal_number(lo, hi):
+    """Very small operands of one side times very large ones of the other give ordinary sums: every bit of the small ones
+    counts, down to the smallest normal number (2^-126; smaller ones have fewer bits to begin with)."""
+    gen = torch.Generator().manual_seed(-lo)
+    small, large = [(1.0 + torch.rand(s, generator=gen)) * torch.randint(0, 2, s, generator=gen).mul(2).sub(1) * 2.0 ** k
+                    for s, k in (((64, 256), lo), ((1, 192, 256), hi))]
+    print(f"[f32 small] 2^{lo} x 2^{hi}", flush=True)
+    for h, w2 in ((small, large), (large[0], small.unsqueeze(0))):
+        y, want = _second_projection(h, w2)
+        # 6.5 roundings as above (6.4e-8)
+        assert float((y - want).norm() / want.norm()) <= 7.5e-8
 
 
 def test_ffn_f32_more_workgroups_than_one_grid_dimension():
