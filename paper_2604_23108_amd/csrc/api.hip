@@ -179,13 +179,13 @@ int mohge_permute(const mohge_config* cfg, const int32_t* expert_idx, int32_t* c
   NEED(expert_idx); NEED(counts); NEED(offsets); NEED(perm); NEED(inv_perm);
   OPT(x); OPT(x_perm); NEED(workspace);
   if (x_perm && !x) { set_error("x_perm requested but x is NULL"); return MOHGE_ENULL; }
-  if (workspace_bytes < permute_workspace_bytes(L)) {
+  if (workspace_bytes < permute_workspace_min(L)) {
     set_error("permute workspace: %zu bytes given, %zu needed", workspace_bytes,
-              permute_workspace_bytes(L));
+              permute_workspace_min(L));
     return MOHGE_EWORKSPACE;
   }
   return hip_rc(launch_permute(L, cfg->dtype, expert_idx, counts, offsets, perm, inv_perm, x,
-                               x_perm, workspace, (hipStream_t)stream),
+                               x_perm, workspace, workspace_bytes, (hipStream_t)stream),
                 "mohge_permute");
 }
 
@@ -198,9 +198,9 @@ int mohge_permute_static(const mohge_config* cfg, const int32_t* expert_idx, int
   NEED(expert_idx); NEED(counts); NEED(offsets); NEED(perm); NEED(inv_perm);
   OPT(x); OPT(x_perm);
   if (x_perm && !x) { set_error("x_perm requested but x is NULL"); return MOHGE_ENULL; }
-  if (permute_workspace_bytes(L) > (size_t)MOHGE_PERMUTE_STATIC_BYTES) {
+  if (permute_workspace_min(L) > (size_t)MOHGE_PERMUTE_STATIC_BYTES) {
     set_error("mohge_permute_static: this configuration needs %zu bytes of scratch, the static buffer holds %zu "
-              "(use mohge_permute with a workspace)", permute_workspace_bytes(L),
+              "(use mohge_permute with a workspace)", permute_workspace_min(L),
               (size_t)MOHGE_PERMUTE_STATIC_BYTES);
     return MOHGE_EWORKSPACE;
   }

@@ -118,10 +118,11 @@ hipError_t launch_expert_ffn_w4(const LayerDesc& L, const void* x, const int32_t
                                 const int32_t* offsets, const GroupPtrs& Wq, const void* const* b13,
                                 const void* const* b2, void* y_perm, void* ws, hipStream_t s);
 hipError_t launch_mxfp4_decode(const void* packed, const void* scales, float* out, long long n, hipStream_t s);
+size_t permute_workspace_min(const LayerDesc& L);
 size_t permute_workspace_bytes(const LayerDesc& L);
 hipError_t launch_permute(const LayerDesc& L, int dtype, const int32_t* expert_idx,
                           int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
-                          const void* x, void* x_perm, void* ws, hipStream_t s);
+                          const void* x, void* x_perm, void* ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_permute_static(const LayerDesc& L, int dtype, const int32_t* expert_idx,
                                  int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
                                  const void* x, void* x_perm, hipStream_t s);

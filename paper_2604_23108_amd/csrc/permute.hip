@@ -22,6 +22,7 @@
 namespace mohge {
 
 constexpr int kSmallWaves = 16;                // of the single-workgroup kernel
+constexpr int kSmallPairs = 4 * 64 * kSmallWaves;   // ... which serves up to this many
 
 // Segment histograms of mohge_permute_static: the one scratch buffer of the permutation, held in
 // the library's own device memory so that the call needs no workspace from the caller.  Every GPU
@@ -166,27 +167,39 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const V* __restrict__ 
   for (int i = lane; i < vec_per_row; i += 64) dst[i] = src[i];
 }
 
-// Steps of 64 pairs in a wave's segment: the fewest that keep the count matrix within 4096 cells.
-static int segment_steps(const LayerDesc& L) {
-  for (int ni = 1; ni < kSegPairs / 64; ni *= 2)
-    if (((long long)L.P + 64 * ni - 1) / (64 * ni) * L.Ne <= 4096) return ni;
+// Cells of the [segment][expert] count matrix up to which segments are shortened.
+constexpr int kShortCells = 4096;
+
+// Steps of 64 pairs in a wave's segment: the fewest whose count matrix stays within kShortCells and within the workspace.
+static int segment_steps(const LayerDesc& L, size_t ws_bytes) {
+  for (int ni = 1; ni < kSegPairs / 64; ni *= 2) {
+    const long long cells = ((long long)L.P + 64 * ni - 1) / (64 * ni) * L.Ne;
+    if (cells <= kShortCells && cells * (long long)sizeof(int32_t) <= (long long)ws_bytes) return ni;
+  }
   return kSegPairs / 64;
 }
 
-size_t permute_workspace_bytes(const LayerDesc& L) {
-  const size_t seg = 64 * (size_t)segment_steps(L), nseg = ((size_t)L.P + seg - 1) / seg;
+// The least a call works with: the counts of segments of 512.
+size_t permute_workspace_min(const LayerDesc& L) {
+  const size_t nseg = ((size_t)L.P + kSegPairs - 1) / kSegPairs;
   const size_t b = (nseg > 0 ? nseg : 1) * (size_t)L.Ne * sizeof(int32_t);
   return (b + 255) / 256 * 256;
 }
 
+// What lets every call take its shortest segments, also one with fewer pairs in the same workspace: never falls as P grows.
+size_t permute_workspace_bytes(const LayerDesc& L) {
+  const size_t least = permute_workspace_min(L), shortest = kShortCells * sizeof(int32_t);
+  return L.P <= kSmallPairs || least > shortest ? least : shortest;
+}
+
 hipError_t launch_permute(const LayerDesc& L, int dtype, const int32_t* expert_idx,
                           int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
-                          const void* x, void* x_perm, void* ws, hipStream_t s) {
+                          const void* x, void* x_perm, void* ws, size_t ws_bytes, hipStream_t s) {
   PermArgs a;
   a.eidx = expert_idx; a.counts = counts; a.offsets = offsets; a.perm = perm; a.inv_perm = inv_perm;
   a.seg_hist = static_cast<int32_t*>(ws);
   a.P = L.P; a.Ne = L.Ne;
-  const int ni = segment_steps(L);
+  const int ni = segment_steps(L, ws_bytes);
   a.nseg = (int)(((long long)L.P + 64 * ni - 1) / (64 * ni));
   a.nbits = 0;
   while ((1 << a.nbits) < L.Ne) ++a.nbits;
@@ -199,7 +212,7 @@ hipError_t launch_permute(const LayerDesc& L, int dtype, const int32_t* expert_i
     hipLaunchKernelGGL(permute_small_kernel<1>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
   } else if (L.P <= 2 * 64 * kSmallWaves) {
     hipLaunchKernelGGL(permute_small_kernel<2>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
-  } else if (L.P <= 4 * 64 * kSmallWaves) {
+  } else if (L.P <= kSmallPairs) {
     hipLaunchKernelGGL(permute_small_kernel<4>, dim3(1), dim3(64 * kSmallWaves), 0, s, a);
   } else if ((long long)a.nseg * a.Ne <= kFusedMaxCells) {
     if (ni == 1) launch(permute_hist_kernel<1>, permute_scatter_kernel<true, 1>);
@@ -229,11 +242,12 @@ hipError_t launch_permute(const LayerDesc& L, int dtype, const int32_t* expert_i
 hipError_t launch_permute_static(const LayerDesc& L, int dtype, const int32_t* expert_idx,
                                  int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
                                  const void* x, void* x_perm, hipStream_t s) {
-  if (permute_workspace_bytes(L) > (size_t)MOHGE_PERMUTE_STATIC_BYTES) return hipErrorInvalidValue;
+  if (permute_workspace_min(L) > (size_t)MOHGE_PERMUTE_STATIC_BYTES) return hipErrorInvalidValue;
   void* ws = nullptr;
   hipError_t e = static_scratch(&ws);
   if (e != hipSuccess) return e;
-  return launch_permute(L, dtype, expert_idx, counts, offsets, perm, inv_perm, x, x_perm, ws, s);
+  return launch_permute(L, dtype, expert_idx, counts, offsets, perm, inv_perm, x, x_perm, ws,
+                        (size_t)MOHGE_PERMUTE_STATIC_BYTES, s);
 }
 
 }  // namespace mohge
