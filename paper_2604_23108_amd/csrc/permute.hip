@@ -12,8 +12,8 @@
 // kernel (four waves with segments of 512: 6.0 us at 640 pairs, 6.2 at 2048; now 2.7 and 3.6; 4096 pairs in two kernels
 // 9.2, now 5.0; at 6144 pairs, eight steps a wave, one kernel and two are even at 7).  While segments x experts <= 8192 the
 // scan is folded into the scatter kernel (two launches instead of three); segments are shortened while
-// the matrix, which every scatter workgroup reads, stays within 4096 cells (segments of 512: 10.0 us at 8192 pairs of 64
-// experts, now 6.6; 9.9 at 16384, now 7.9).
+// the matrix, which every scatter workgroup reads, stays within 4096 cells and 128 segments (segments of 512: 10.3 us at 8192
+// pairs of 64 experts, now 7.0; 10.1 at 16384, now 8.1).
 #include <mutex>
 
 #include "common.h"
@@ -167,14 +167,17 @@ __global__ void __launch_bounds__(256) gather_rows_kernel(const V* __restrict__ 
   for (int i = lane; i < vec_per_row; i += 64) dst[i] = src[i];
 }
 
-// Cells of the [segment][expert] count matrix up to which segments are shortened.
-constexpr int kShortCells = 4096;
+// Cells of the [segment][expert] count matrix, and segments, up to which segments are shortened: every scatter workgroup
+// reads the matrix and walks the counts of an expert one after the other.  (Without the second limit 8 experts, 32768 pairs,
+// 512 segments: 14.5 us, with it 9.3, segments of 512 10.0; one expert, 262144 pairs, 4096 segments: 119, now 18.4.  A limit of 64
+// or 96: 9.7, and 8.3 for 7.6 at 16384 pairs of 16 experts.)
+constexpr int kShortCells = 4096, kShortSegments = 128;
 
-// Steps of 64 pairs in a wave's segment: the fewest whose count matrix stays within kShortCells and within the workspace.
+// Steps of 64 pairs in a wave's segment: the fewest whose count matrix stays within these limits and within the workspace.
 static int segment_steps(const LayerDesc& L, size_t ws_bytes) {
   for (int ni = 1; ni < kSegPairs / 64; ni *= 2) {
-    const long long cells = ((long long)L.P + 64 * ni - 1) / (64 * ni) * L.Ne;
-    if (cells <= kShortCells && cells * (long long)sizeof(int32_t) <= (long long)ws_bytes) return ni;
+    const long long nseg = ((long long)L.P + 64 * ni - 1) / (64 * ni), cells = nseg * L.Ne;
+    if (nseg <= kShortSegments && cells <= kShortCells && cells * sizeof(int32_t) <= ws_bytes) return ni;
   }
   return kSegPairs / 64;
 }
