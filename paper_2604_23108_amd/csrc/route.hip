@@ -517,10 +517,13 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   }
   // Column tiles of 16 router rows per workgroup.  Split form, few tokens: one, and the passes over the router rows side by
   // side: what counts is the length of a wave's chain (one after the other with up to five: d = 4096, 68 rows, 32
-  // tokens 12.9 us, now 10.0, 160 tokens 15.4 and 12.0; d = 1024, 136 rows, 32 tokens 21.7 and 14.1, 40 rows 9.7 and 8.5).  From about
-  // 400 tokens on reading the tokens once per column tile costs more (d = 1024, 40 rows: even at 400, 10.6 to 11.7 at 1000).
+  // tokens 12.9 us, now 10.0, 160 tokens 15.4 and 12.0; d = 1024, 136 rows, 32 tokens 21.7 and 14.1, 40 rows 9.7 and 8.5).  It
+  // pays while a pass leaves compute units free.  Time of one tile / of all in a workgroup, d = 512 to 8192, bf16 and fp32:
+  // two tiles 0.88 to 0.96 up to 120 workgroups per pass, 0.95 to 1.12 from 136 on; three 0.85 to 0.97 up to 152, 1.06 to 1.16 from
+  // 176 on; five 0.74 to 0.97 up to 152, 0.96 to 1.09 at 176 to 200; more 0.5 to 0.98 up to 176, 0.9 to 1.06 at 200.  (Two tiles
+  // per workgroup, side by side: 1.15 to 1.25 where five are 1.0.)
   int TN = tiles <= 1 ? 1 : tiles == 2 ? 2 : tiles == 3 ? 3 : 5;
-  if (a.dsplit > 1 && L.T <= 400) TN = 1;
+  if (a.dsplit > 1 && L.T <= 400 && (L.T + 15) / 16 * a.dsplit <= (tiles == 2 ? 128 : 160)) TN = 1;
   const int passes = a.dsplit > 1 ? (tiles + TN - 1) / TN : 1;
   int TM = (L.T >= 16384 && TN <= 2) ? 2 : 1;   // wider combinations would spill registers
   size_t smem = 0;
