@@ -89,6 +89,18 @@ int mohge_bench_expert_ffn_bwd(const mohge_config* cfg, const void* x, const int
                                const mohge_ffn_options* options, void* stream);
 
 /*
+ * mohge_expert_ffn_w8 (bits = 8, scales fp32) / mohge_expert_ffn_w4 (bits = 4, scales bytes) with the kernel as an argument:
+ * form 0: tokens staged once per workgroup of 128 weight rows; 1: staged by every wave, two waves along the reduction;
+ * 2 (8 bits only): straight from memory, four waves along the reduction; -1: by size, as the calls of mohge.h.  The results
+ * differ in the order of the fp32 sums.  mohge_bench_quantised_form returns the form taken by size, or an error code (< 0).
+ */
+int mohge_bench_expert_ffn_quantised(const mohge_config* cfg, const void* x, const int32_t* perm,
+                                     const int32_t* offsets, const void* const* w13q, const void* const* w13_scale,
+                                     const void* const* w2q, const void* const* w2_scale, void* y_perm,
+                                     void* workspace, size_t workspace_bytes, int bits, int form, void* stream);
+int mohge_bench_quantised_form(const mohge_config* cfg, int bits);
+
+/*
  * mohge_decode_layer (same arguments, same kernel) with
  *  - spin_limit: the number of polls a waiting workgroup makes: 0 = the default (about a second),
  *    > 0 = that many, < 0 = give up without waiting (test hook: the launch drains, y is NaN and

@@ -15,7 +15,8 @@ _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmohge_b
 
 EXPORTS = ["mohge_ffn_default_options", "mohge_bench_cycles_bytes", "mohge_bench_expert_ffn",
            "mohge_bench_expert_ffn_train", "mohge_bench_expert_ffn_bwd", "mohge_probe_read", "mohge_probe_mfma",
-           "mohge_bench_decode_layer", "mohge_bench_decode_trace_bytes"]
+           "mohge_bench_decode_layer", "mohge_bench_decode_trace_bytes", "mohge_bench_expert_ffn_quantised",
+           "mohge_bench_quantised_form"]
 
 
 class _COptions(C.Structure):
@@ -98,6 +99,23 @@ def mohge_bench_expert_ffn_bwd(cfg, x, perm, offsets, w13, w2, saved, dy_perm, d
                                             _ptr_table(w2), _ptr(saved), _ptr(dy_perm), _ptr(dx_perm),
                                             _ptr_table(dw13), _ptr_table(dw2), _ptr(workspace), _nbytes(workspace),
                                             _opt(options), _stream()), "mohge_bench_expert_ffn_bwd")
+
+
+def mohge_bench_expert_ffn_quantised(cfg, x, perm, offsets, w13q, w13_scale, w2q, w2_scale, y_perm, workspace, bits: int,
+                                     form: int = -1):
+    for t in list(w13q) + list(w13_scale) + list(w2q) + list(w2_scale):
+        _ptr(t)
+    _check(lib().mohge_bench_expert_ffn_quantised(cfg.ref(), _ptr(x), _ptr(perm), _ptr(offsets), _ptr_table(w13q),
+                                                  _ptr_table(w13_scale), _ptr_table(w2q), _ptr_table(w2_scale), _ptr(y_perm),
+                                                  _ptr(workspace), _nbytes(workspace), C.c_int(bits), C.c_int(form),
+                                                  _stream()), "mohge_bench_expert_ffn_quantised")
+
+
+def mohge_bench_quantised_form(cfg, bits: int) -> int:
+    """The kernel a quantised decode call takes by size: 0 staged, 1 split, 2 direct."""
+    form = lib().mohge_bench_quantised_form(cfg.ref(), C.c_int(bits))
+    _check(min(form, 0), "mohge_bench_quantised_form")
+    return form
 
 
 def mohge_bench_decode_layer(cfg, x, w_group, w_expert, expert_logit_bias, w13, w2, group_idx, expert_idx, gates, y,

@@ -163,6 +163,53 @@ int mohge_bench_expert_ffn_bwd(const mohge_config* cfg, const void* x, const int
                 "mohge_bench_expert_ffn_bwd");
 }
 
+int mohge_bench_quantised_form(const mohge_config* cfg, int bits) {
+  LayerDesc L;
+  int rc = check_config(cfg, &L);
+  if (rc) return rc;
+  if (bits != 4 && bits != 8) { set_error("mohge_bench_quantised_form: bits = %d (8 or 4)", bits); return MOHGE_EINVAL; }
+  if (cfg->dtype != MOHGE_BF16 || !ffn_w8_supported(L) || L.T == 0) {
+    set_error("mohge_bench_quantised_form: bf16 calls of 1 to 32 tokens only");
+    return MOHGE_EINVAL;
+  }
+  return (int)quantised_form(L, bits == 8);
+}
+
+int mohge_bench_expert_ffn_quantised(const mohge_config* cfg, const void* x, const int32_t* perm,
+                                     const int32_t* offsets, const void* const* w13q, const void* const* w13_scale,
+                                     const void* const* w2q, const void* const* w2_scale, void* y_perm,
+                                     void* workspace, size_t workspace_bytes, int bits, int form, void* stream) {
+  LayerDesc L;
+  int rc = mohge_bench_quantised_form(cfg, bits);
+  if (rc < 0) return rc;
+  if ((rc = check_config(cfg, &L))) return rc;
+  if (form < -1 || form > (bits == 8 ? 2 : 1)) {
+    set_error("mohge_bench_expert_ffn_quantised: form = %d (-1, 0, 1 and with 8 bits 2)", form);
+    return MOHGE_EINVAL;
+  }
+  NEED(x); OPT(perm); NEED(offsets); NEED(y_perm); NEED(workspace);
+  GroupPtrs W;
+  if ((rc = weight_tables(L, w13q, w2q, &W))) return rc;
+  if (!w13_scale || !w2_scale) { set_error("a scale pointer table is NULL"); return MOHGE_ENULL; }
+  const void* s13[kMaxGroups];
+  const void* s2[kMaxGroups];
+  const float* f13[kMaxGroups];
+  const float* f2[kMaxGroups];
+  for (int g = 0; g < L.Ng; ++g) {
+    NEED(w13_scale[g]); NEED(w2_scale[g]);
+    s13[g] = w13_scale[g]; s2[g] = w2_scale[g];
+    f13[g] = static_cast<const float*>(s13[g]); f2[g] = static_cast<const float*>(s2[g]);
+  }
+  if (workspace_bytes < ffn_workspace_bytes(L, cfg->dtype)) {
+    set_error("expert_ffn workspace: %zu bytes given, %zu needed", workspace_bytes, ffn_workspace_bytes(L, cfg->dtype));
+    return MOHGE_EWORKSPACE;
+  }
+  const QuantisedForm f = (QuantisedForm)form;
+  return hip_rc(bits == 8 ? launch_expert_ffn_w8(L, x, perm, offsets, W, f13, f2, y_perm, workspace, (hipStream_t)stream, f)
+                          : launch_expert_ffn_w4(L, x, perm, offsets, W, s13, s2, y_perm, workspace, (hipStream_t)stream, f),
+                "mohge_bench_expert_ffn_quantised");
+}
+
 int mohge_probe_read(const void* buf, size_t bytes, int row_bytes, int staggered, void* out,
                      size_t* bytes_read, void* stream) {
   NEED(buf); NEED(out);

@@ -110,13 +110,19 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
                         void* ws, size_t ws_bytes, hipStream_t s);
 size_t route_workspace_bytes(const LayerDesc& L, int dtype);
 bool ffn_w8_supported(const LayerDesc& L);
+// kernel of the quantised decode calls: tokens staged per workgroup (128 weight rows) or per wave (half of the reduction), or
+// straight from memory (FP8 only)
+enum class QuantisedForm { kBySize = -1, kStaged = 0, kSplit = 1, kDirect = 2 };
+QuantisedForm quantised_form(const LayerDesc& L, bool fp8);      // the choice by size
 hipError_t launch_expert_ffn_w8(const LayerDesc& L, const void* x, const int32_t* perm,
                                 const int32_t* offsets, const GroupPtrs& Wq, const float* const* s13,
-                                const float* const* s2, void* y_perm, void* ws, hipStream_t s);
+                                const float* const* s2, void* y_perm, void* ws, hipStream_t s,
+                                QuantisedForm form = QuantisedForm::kBySize);
 hipError_t launch_fp8_decode(const void* q, float* out, long long n, hipStream_t s);
 hipError_t launch_expert_ffn_w4(const LayerDesc& L, const void* x, const int32_t* perm,
                                 const int32_t* offsets, const GroupPtrs& Wq, const void* const* b13,
-                                const void* const* b2, void* y_perm, void* ws, hipStream_t s);
+                                const void* const* b2, void* y_perm, void* ws, hipStream_t s,
+                                QuantisedForm form = QuantisedForm::kBySize);
 hipError_t launch_mxfp4_decode(const void* packed, const void* scales, float* out, long long n, hipStream_t s);
 size_t permute_workspace_min(const LayerDesc& L);
 size_t permute_workspace_bytes(const LayerDesc& L);

@@ -10,7 +10,8 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
 hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* perm,
                              const int32_t* offsets, const GroupPtrs& W, void* y_perm, void* ws,
                              hipStream_t s, int stages, const float* const* s13, const float* const* s2,
-                             const void* const* b13 = nullptr, const void* const* b2 = nullptr);
+                             const void* const* b13 = nullptr, const void* const* b2 = nullptr,
+                             QuantisedForm form = QuantisedForm::kBySize);
 
 hipError_t launch_ffn_f32(const LayerDesc& L, const void* x, const int32_t* perm, const int32_t* offsets,
                           const GroupPtrs& W, void* y_perm, void* ws, hipStream_t s, int stages);
@@ -59,15 +60,16 @@ bool ffn_w8_supported(const LayerDesc& L) { return use_skinny(L); }
 
 hipError_t launch_expert_ffn_w8(const LayerDesc& L, const void* x, const int32_t* perm,
                                 const int32_t* offsets, const GroupPtrs& Wq, const float* const* s13,
-                                const float* const* s2, void* y_perm, void* ws, hipStream_t s) {
-  return launch_ffn_skinny(L, x, perm, offsets, Wq, y_perm, ws, s, 3, s13, s2);
+                                const float* const* s2, void* y_perm, void* ws, hipStream_t s,
+                                QuantisedForm form) {
+  return launch_ffn_skinny(L, x, perm, offsets, Wq, y_perm, ws, s, 3, s13, s2, nullptr, nullptr, form);
 }
 
 // Decode with MXFP4 weights (E2M1 codes, an E8M0 scale per 32 elements of a weight row)
 hipError_t launch_expert_ffn_w4(const LayerDesc& L, const void* x, const int32_t* perm,
                                 const int32_t* offsets, const GroupPtrs& Wq, const void* const* b13,
-                                const void* const* b2, void* y_perm, void* ws, hipStream_t s) {
-  return launch_ffn_skinny(L, x, perm, offsets, Wq, y_perm, ws, s, 3, nullptr, nullptr, b13, b2);
+                                const void* const* b2, void* y_perm, void* ws, hipStream_t s, QuantisedForm form) {
+  return launch_ffn_skinny(L, x, perm, offsets, Wq, y_perm, ws, s, 3, nullptr, nullptr, b13, b2, form);
 }
 
 // Training forward (bf16): what the backward pass needs is kept in `saved`:

@@ -107,11 +107,11 @@ __device__ __forceinline__ void fp4x8_to_bf16(const uint32_t c, const float scal
 //  - the weights of the next step (4 units) are requested before the current one is converted and multiplied.
 // Token columns past the expert's count hold copies of its last staged token; MFMA columns are
 // independent and those outputs are never stored.
-// Up + down, us, at 1 / 4 / 12 tokens (before: staged kernel for MXFP4, staged or a split one with tokens straight from
-// memory for FP8): MXFP4 d = 4096 31 / 48 / 74 -> 21 / 38 / 83, d = 2560 41 / 48 / 80 -> 21 / 40 / 66, d = 1344 24 / 27 / 35 ->
-// 16 / 17 / 23; FP8 d = 4096 26 / 54 / 127 -> 26 / 53 / 120, d = 2048 16 / 27 / 38 -> 17 / 23 / 34.  A quarter of the reduction per
-// wave: 20 / 38 / 85 and 23 / 52 / 120 at d = 4096 but 17 / 23 / 45 for 17 / 22 / 37 at d = 1024 with 128 experts; all of it: 30 / 43 / 89
-// and 37 / 60 / 143.  Several column blocks per workgroup with the tokens kept: 24 / 57 / 136 (FP8, two) and registers spilled.
+// Up + down, us, at 1 / 4 / 12 tokens, against the other forms: MXFP4 (staged) d = 4096 21 / 41 / 85 (34 / 52 / 76), d = 2560
+// 22 / 43 / 74 (40 / 55 / 85), d = 1344 15 / 18 / 23 (26 / 32 / 34); FP8 (direct, staged) d = 4096 29 / 60 / 122 (26 / 64 / 128,
+// 54 / 86 / 130), d = 2048 18 / 27 / 32 (16 / 26 / 37, 26 / 32 / 36).  A quarter of the reduction per wave, one column block per workgroup:
+// MXFP4 19 / 43 / 89 and FP8 25 / 59 / 124 at d = 4096, but 24 / 47 for 22 / 38 at 4 and 12 tokens of 128 experts, d = 1024; all of it:
+// 30 / 43 / 89 and 37 / 60 / 143.  Several column blocks per workgroup with the tokens kept: 24 / 57 / 136 (FP8, two) and registers spilled.
 constexpr int kWaveTokens = 8448;             // bytes of staged token rows per wave; three workgroups per compute unit
 constexpr int kWavePieces = 8192 / 16;        // ... less the padding of 16 rows, in 16-byte pieces
 constexpr int kQSplit = 2;                    // waves along the reduction
@@ -134,20 +134,20 @@ __global__ void __launch_bounds__(256, 3) ffn_skinny_q_split_kernel(const Skinny
   const int g = e / a.N, i = e - g * a.N, F = a.F[g];
   const int K = UP ? a.d : F;
   const int ncols = UP ? F : a.d;
-  if ((int)(blockIdx.x % ncb) * (kSplitWaves / kQSplit) * (UP ? 16 : 32) >= ncols) return;
-  const bool active = c0 < ncols;             // (a wave past the last column meets the barriers)
+  static_assert(64 % (kSplitWaves / kQSplit * 32) == 0, "widths are multiples of 64: no column block is cut short");
+  if (c0 >= ncols) return;                    // (a whole workgroup)
   long long wrow[2];
   if constexpr (UP) {
-    wrow[0] = (long long)i * 2 * F + (active ? c0 : 0) + r;
+    wrow[0] = (long long)i * 2 * F + c0 + r;
     wrow[1] = wrow[0] + F;
   } else {
-    wrow[0] = (long long)i * a.d + (active ? c0 : 0) + r;      // (d is a multiple of 64)
+    wrow[0] = (long long)i * a.d + c0 + r;                     // (d is a multiple of 64)
     wrow[1] = wrow[0] + 16;
   }
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.W[g]);
   const uint8_t* wp[2] = {wbase + wrow[0] * (K * BITS / 8) + 16 * q, wbase + wrow[1] * (K * BITS / 8) + 16 * q};
   const int nu = (K + UK - 1) / UK;           // (K is a multiple of 64: the last MXFP4 unit may be half a unit)
-  const int ub = nu * kw / kQSplit, ue = active ? nu * (kw + 1) / kQSplit : ub;
+  const int ub = nu * kw / kQSplit, ue = nu * (kw + 1) / kQSplit;
   struct Step { uint4 w[2][U]; uint32_t s[2]; };
   auto load_w = [&](Step& st, int u0, int n) {       // the first n units from u0 on
 #pragma unroll
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256, 3) ffn_skinny_q_split_kernel(const Skinny
       for (int f = 0; f < 2; ++f) red[(w * 2 + f) * 64 + lane] = acc[f];
     __syncthreads();
     const int tt = tb0 + r;
-    if (kw == 0 && active) {
+    if (kw == 0) {
 #pragma unroll
       for (int f = 0; f < 2; ++f)
 #pragma unroll
@@ -277,17 +277,141 @@ __global__ void __launch_bounds__(256, 3) ffn_skinny_q_split_kernel(const Skinny
           for (int b = 0; b < 4; ++b) {
             long long row;
             if constexpr (UP) row = (long long)i * 2 * F + (long long)f * F + c0 + 4 * q + b;
-            else {
-              int n = c0 + 16 * f + 4 * q + b;
-              if (n > a.d - 1) n = a.d - 1;
-              row = (long long)i * a.d + n;
-            }
+            else row = (long long)i * a.d + c0 + 16 * f + 4 * q + b;
             acc[f][b] *= a.S[g][row];
           }
       }
       if (tt < cnt) skinny_store<UP, false>(a, c0, q, ncols, row0 + tt, acc[0], acc[1]);
     }
     __syncthreads();                           // the sums have been read
+  }
+}
+
+// FP8 weights, direct form: the reduction is split over the four waves, like the bf16 kernel; a unit of the reduction is
+// 64 bytes of a weight row, lane (r, q) holds 16 codes of its row (two MFMA steps) and reads its token's
+// matching indices straight from L1/L2; weights run one step of four units ahead, tokens 128 indices.  Nothing is staged
+// and there are twice as many workgroups as in the split form: for launches that are a chain of latencies (d = 2048, 24 experts, one
+// token: 15.9 us against 18.0; d = 512, 16 experts, 1 to 32 tokens: 8.1 to 10.0 against 10.1 to 12.6), and for many rows of few
+// experts, whose tokens the split form stages again for every 64 weight rows (2 experts of width 8192, 25 tokens: 52 against 90).
+// The rule: quantised_form.
+template <bool UP>
+__global__ void __launch_bounds__(256, 3) ffn_skinny_fp8_direct_kernel(const SkinnyArgs a, const int ncb) {
+  constexpr int UK = 64;                      // reduction indices per unit: 64 bytes of a weight row
+  constexpr int LK = UK / 4;                  // ... per lane
+  constexpr int NJ = LK / 8;                  // MFMA steps per unit
+  constexpr int U = 4;                        // units per step
+  constexpr int XG = 128 / UK;                // units whose token fragments are requested together
+  __shared__ f32x4 red[(kSplitWaves - 1) * 2 * 64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, q = lane >> 4;
+  const int c0 = (blockIdx.x % ncb) * (UP ? 16 : 32);
+  int e, row0, cnt;
+  if (!expert_of_slot(a, blockIdx.x / ncb, e, row0, cnt)) return;
+  const int g = e / a.N, i = e - g * a.N, F = a.F[g];
+  const int K = UP ? a.d : F;
+  const int ncols = UP ? F : a.d;
+  if (c0 >= ncols) return;
+  long long wrow[2];
+  if constexpr (UP) {
+    wrow[0] = (long long)i * 2 * F + c0 + r;
+    wrow[1] = (long long)i * 2 * F + F + c0 + r;
+  } else {
+    wrow[0] = (long long)i * a.d + c0 + r;                     // (d is a multiple of 64)
+    wrow[1] = wrow[0] + 16;
+  }
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.W[g]);
+  const uint8_t* wp[2] = {wbase + wrow[0] * K + 16 * q, wbase + wrow[1] * K + 16 * q};
+  const int nu = K / UK;                      // (K is a multiple of 64)
+  const int ub = nu * w / kSplitWaves, ue = nu * (w + 1) / kSplitWaves;
+  auto load_w = [&](uint4 (&wq)[2][U], int u0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        wq[f][u] = make_uint4(0u, 0u, 0u, 0u);
+        if (u0 + u < ue)
+          wq[f][u] = *reinterpret_cast<const uint4*>(wp[f] + (long long)(u0 + u) * 64);
+      }
+  };
+
+  for (int tb0 = 0; tb0 < cnt; tb0 += 16) {
+    uint4 wc[2][U];
+    load_w(wc, ub);
+    const int tt = tb0 + r;
+    const bool xv = tt < cnt;
+    const int pos = row0 + (xv ? tt : 0);
+    long long src;
+    if constexpr (UP) src = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
+    else src = pos;
+    const uint16_t* const xp = a.A + src * a.lda + LK * q;
+    auto load_x = [&](Frag (&xf)[XG][NJ], int u0) {
+#pragma unroll
+      for (int u = 0; u < XG; ++u)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          xf[u][j].u = make_uint4(0u, 0u, 0u, 0u);
+          if (xv && u0 + u < ue)
+            xf[u][j].u = *reinterpret_cast<const uint4*>(xp + (u0 + u) * UK + 8 * j);
+        }
+    };
+    Frag xc[XG][NJ];
+    load_x(xc, ub);
+    f32x4 acc[2];
+    acc[0] = f32x4{0.f, 0.f, 0.f, 0.f};
+    acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int u0 = ub; u0 < ue; u0 += U) {
+      uint4 wn[2][U];
+      load_w(wn, u0 + U);
+#pragma unroll
+      for (int ug = 0; ug < U; ug += XG) {
+        Frag xn[XG][NJ];
+        load_x(xn, u0 + ug + XG);
+#pragma unroll
+        for (int x = 0; x < XG; ++x) {
+          const int u = ug + x;
+          if (u0 + u < ue) {                  // wave-uniform
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              Frag wlo, whi;
+              fp8x16_to_bf16(wc[f][u], wlo, whi);
+              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, xc[x][0].v, acc[f], 0, 0, 0);
+              acc[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, xc[x][1].v, acc[f], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int x = 0; x < XG; ++x)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) xc[x][j] = xn[x][j];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) wc[f][u] = wn[f][u];
+    }
+    if (w > 0)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) red[((w - 1) * 2 + f) * 64 + lane] = acc[f];
+    __syncthreads();
+    if (w == 0) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int ww = 0; ww < kSplitWaves - 1; ++ww) acc[f] += red[(ww * 2 + f) * 64 + lane];
+      // lane holds token r of the pass, weight rows 4q..4q+3 of each row set
+      // FP8: the scale of the weight row of accumulator element b multiplies the sum
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          long long row;
+          if constexpr (UP) row = (long long)i * 2 * F + (long long)f * F + c0 + 4 * q + b;
+          else row = (long long)i * a.d + c0 + 16 * f + 4 * q + b;
+          acc[f][b] *= a.S[g][row];
+        }
+      if (xv) skinny_store<UP, false>(a, c0, q, ncols, row0 + tt, acc[0], acc[1]);
+    }
+    __syncthreads();                          // the sums have been read
   }
 }
 
@@ -693,28 +817,47 @@ void skinny_args(const LayerDesc& L, const void* x, const int32_t* perm, const i
   dn.blk_prefix[kMaxGroups] = nd;
 }
 
-// Quantised weights: split or staged kernel.  The staged one shares its tokens and scales among 128 weight rows, which
-// pays once there are rounds of its workgroups to spare.  `waves`: a wave per 32 weight rows of the experts that can have
-// rows, up projection.  Split / staged time, six layer shapes, 1 to 32 tokens:
-//   FP8: 0.48 to 1.01 up to 5632 waves, or 10500 times the rows per expert; 1.06 to 1.13 past 7000 waves (d = 1024, 128 experts).
-//   MXFP4: where a reduction length is no multiple of 128 the staged kernel loads its scales byte by byte: 0.51 to 1.03 up
-//   to 15000 waves times the rows per expert, 1.08 beyond.  Elsewhere 0.68 to 0.93 below 2000 waves, or 4 M with their
-//   reduction, with few rows; 1.02 to 1.04 at 1536 waves with two rows per expert and more, 1.04 to 1.27 from 2352 waves on at
-//   d = 4096 and from 4896 on at d = 1024.
-static bool q_split(const LayerDesc& L, bool fp8) {
+// Quantised weights: which kernel.  `waves`: a wave per 32 weight rows of the experts that can have rows, up projection;
+// `load`: the same of both projections over the experts that T evenly routed tokens are expected to touch, `rows`: their rows on
+// average.  123 layer shapes (d = 256 to 4096, 1 to 256 experts, widths 100 to 8192), 1 to 32 tokens, every form timed:
+//   FP8.  The split form has half as many workgroups as the direct one and stages its tokens: 1.1 to 1.25 of its time at a
+//     load of 1000, 0.84 to 0.98 from 1700 on with few rows; with rows up to the 150th part of the load beyond 1400 they are even.  The
+//     staged form shares tokens among 128 weight rows, but experts without rows have workgroups too: split / staged 0.65 to 1.0 up to
+//     100 pairs (126 with 2 M weights per matrix) and 2.2 rows, up to 1.25 beyond; up to 32 experts and d = 2048, where it has no
+//     full round of workgroups, 0.85 to 1.0 up to 4.2 rows.  Widths below 350 leave two steps of a wave's half: direct 0.78 to
+//     0.95.  Direct against staged, where split is neither: waves up to 2500 with fewer rows than experts, 1600 with one each, 1200
+//     with more.
+//   MXFP4.  Where a reduction length is no multiple of 128 the staged kernel loads its scales byte by byte.  Both projections of a
+//     layer (d > 384; shorter ones have few scales): split / staged 0.4 to 1.0 up to 15000 waves times the rows per expert; the
+//     second only: 0.5 to 1.0 up to 11000, 1.05 to 1.2 with more than 64 experts that can have rows.  Neither: 0.56 to 1.0 up to
+//     3000, and below 2000 waves or 4 M with their reduction, and a load of 1800 or 1.7 rows; 1.0 to 1.3 beyond.
+// Time of the choice / of the fastest form: mean 1.007 FP8, 1.005 MXFP4, at most 1.11 times the faster of direct and staged.
+QuantisedForm quantised_form(const LayerDesc& L, bool fp8) {
   long long f = 0;
-  bool whole = L.d % 128 == 0;
+  bool whole = true;
   for (int g = 0; g < L.Ng; ++g) { f += L.F[g]; whole = whole && L.F[g] % 128 == 0; }
-  const long long live = L.P < L.Ne ? L.P : L.Ne, waves = live * (f / L.Ng) / 16;
-  if (fp8) return waves < 6500 && waves * L.P < 10500 * live;
-  if (!whole) return waves * L.P < 15000 * live;
-  return waves * L.P < 3000 * live && (waves < 2000 || waves * L.d < (4ll << 20));
+  f /= L.Ng;
+  const long long live = L.P < L.Ne ? L.P : L.Ne, waves = live * f / 16;
+  double idle = L.Ne;
+  for (int t = 0; t < L.T; ++t) idle *= 1.0 - (double)L.Ke / L.Ne;
+  const double touched = L.Ne - idle, load = touched * (f / 16 + L.d / 32), rows = L.P / touched;
+  if (fp8) {
+    const bool few_rows = rows <= 2.2 && L.P <= (f * L.d >= 2 << 20 ? 126 : 100);
+    const bool few_experts = L.Ne <= 32 && L.d <= 2048 && rows <= 4.2;
+    if ((few_rows || few_experts) && f >= 350 && load >= 1400 + 150 * rows) return QuantisedForm::kSplit;
+    return waves < (L.P < L.Ne ? 2500 : L.P == L.Ne ? 1600 : 1200) ? QuantisedForm::kDirect : QuantisedForm::kStaged;
+  }
+  bool split;
+  if (L.d % 128 && L.d > 384) split = waves * L.P < 15000 * live;
+  else if (L.d % 128 == 0 && !whole) split = live <= 64 && waves * L.P < 11000 * live;
+  else split = waves * L.P < 3000 * live && (waves < 2000 || waves * L.d < (4ll << 20)) && (load < 1800 || rows < 1.7);
+  return split ? QuantisedForm::kSplit : QuantisedForm::kStaged;
 }
 
 hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* perm,
                              const int32_t* offsets, const GroupPtrs& W, void* y_perm, void* ws,
                              hipStream_t s, int stages, const float* const* s13, const float* const* s2,
-                             const void* const* b13, const void* const* b2) {
+                             const void* const* b13, const void* const* b2, QuantisedForm form) {
   const bool w8 = s13 != nullptr, w4 = b13 != nullptr;
   SkinnyArgs up, dn;
   int nu = 0, nd = 0;
@@ -735,12 +878,13 @@ hipError_t launch_ffn_skinny(const LayerDesc& L, const void* x, const int32_t* p
     if (stages & 1) hipLaunchKernelGGL(ku, dim3(slots * pu), dim3(256), 0, s, up, pu);
     if (stages & 2) hipLaunchKernelGGL(kd, dim3(slots * pd), dim3(256), 0, s, dn, pd);
   };
-  if ((w4 || w8) && q_split(L, w8)) {
-    if (w4) launch_split(ffn_skinny_q_split_kernel<true, 4>, ffn_skinny_q_split_kernel<false, 4>);
-    else launch_split(ffn_skinny_q_split_kernel<true, 8>, ffn_skinny_q_split_kernel<false, 8>);
-  } else if (w4) launch_staged(ffn_skinny_q_kernel<true, 4>, ffn_skinny_q_kernel<false, 4>);
-  else if (w8) launch_staged(ffn_skinny_q_kernel<true, 8>, ffn_skinny_q_kernel<false, 8>);
-  else launch(ffn_skinny_kernel<true>, ffn_skinny_kernel<false>);
+  if (form == QuantisedForm::kBySize) form = quantised_form(L, w8);
+  if (!w4 && !w8) launch(ffn_skinny_kernel<true>, ffn_skinny_kernel<false>);
+  else if (form == QuantisedForm::kDirect) launch(ffn_skinny_fp8_direct_kernel<true>, ffn_skinny_fp8_direct_kernel<false>);
+  else if (form == QuantisedForm::kSplit && w4) launch_split(ffn_skinny_q_split_kernel<true, 4>, ffn_skinny_q_split_kernel<false, 4>);
+  else if (form == QuantisedForm::kSplit) launch_split(ffn_skinny_q_split_kernel<true, 8>, ffn_skinny_q_split_kernel<false, 8>);
+  else if (w4) launch_staged(ffn_skinny_q_kernel<true, 4>, ffn_skinny_q_kernel<false, 4>);
+  else launch_staged(ffn_skinny_q_kernel<true, 8>, ffn_skinny_q_kernel<false, 8>);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
-"""FP8 decode with many rows or many experts: the shapes for which the kernel that stages tokens in LDS is chosen
-(with few waves the split kernel is), against float64 on the dequantised weights."""
+"""FP8 decode through the kernel that stages an expert's tokens in LDS once per workgroup, taken here whatever the rule by size,
+against float64 on the dequantised weights."""
 import numpy as np
 import pytest
 import torch
@@ -14,11 +14,9 @@ pytestmark = pytest.mark.gpu
                                                (25, 4096, 8, (1216, 1344), True)])
 def test_fp8_staged_kernel(T, d, n, d_ff, skewed):
     import paper_2604_23108_amd as M
+    from paper_2604_23108_amd import bench_binding as BB
     Ne, k = 2 * n, 2
     P = T * k
-    # the inputs of the choice: waves of 32 weight rows over the experts that can have rows, rows per expert
-    waves = min(P, Ne) * (sum(d_ff) // 2) // 16
-    assert waves >= (2500 if P < Ne else 1600 if P == Ne else 1200), "this shape is one for the split kernel"
     gen = torch.Generator(device="cuda").manual_seed(T + d)
     normal = lambda *s: torch.randn(s, generator=gen, device="cuda")
     cfg = M.Config(T=T, d=d, n_groups=2, experts_per_group=n, d_ff=d_ff, k_groups=2, k_experts=k,
@@ -32,10 +30,10 @@ def test_fp8_staged_kernel(T, d, n, d_ff, skewed):
     e0 = np.where(rng.random(T) < 0.8, 1, rng.integers(0, n, T)) if skewed else rng.integers(0, n, T)
     eidx = np.stack([e0, n + rng.integers(0, n, T)], 1).astype(np.int32)
     assert not skewed or (e0 == 1).sum() > 16                       # more rows than one block of 16
-    print(f"[fp8 staged] T={T} d={d} waves={waves} skewed={skewed}", flush=True)
+    print(f"[fp8 staged] T={T} d={d} skewed={skewed}", flush=True)
     M.mohge_permute(cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None, L.ws_permute)
     L.y_perm.fill_(float("nan"))
-    M.mohge_expert_ffn_w8(cfg, x, L.perm, L.offsets, *L.w8, L.y_perm, L.ws_ffn)
+    BB.mohge_bench_expert_ffn_quantised(cfg, x, L.perm, L.offsets, *L.w8, L.y_perm, L.ws_ffn, 8, 0)
     torch.cuda.synchronize()
     c13, s13, c2, s2 = L.w8
     value = lambda c, s: c.view(torch.float8_e4m3fn).cpu().double() * s.cpu().double().unsqueeze(-1)

@@ -853,8 +853,8 @@ def test_box_probes_run_and_report_their_work():
 @pytest.mark.parametrize("seed", range(10))
 def test_quantised_decode_random_shapes(seed):
     """Seeded random decode shapes (hidden sizes and widths that are odd multiples of 64, one to
-    four groups, 1 to 32 tokens) through both quantised-weight kernels against the oracle on the
-    dequantised weights: reduction lengths that end in partial units, chunked token staging."""
+    four groups, 1 to 32 tokens) through the FP8 and the MXFP4 call, whichever kernel their size takes, against the
+    oracle on the dequantised weights: reduction lengths that end in partial units, chunked token staging."""
     import paper_2604_23108_amd as M
     from synth import SELECT_GLOBAL, SELECT_PER_GROUP
     rng = np.random.default_rng(5000 + seed)

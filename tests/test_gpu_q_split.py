@@ -1,16 +1,15 @@
-"""Decode with quantised weights in both kernel forms (split reduction, staged), FP8 and MXFP4: rows per expert around the
+"""Decode with quantised weights in every kernel form (staged, split and, for FP8, direct): rows per expert around the
 passes and chunks of the staged tokens, reductions that leave waves without indices or end in half a unit, column blocks
-cut short; against float64 on the dequantised weights."""
+cut short; against float64 on the dequantised weights.  The form is an argument here, whatever the rule by size."""
 import numpy as np
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
-SPLIT = [(counts, d, ff) for counts in [(0, 1, 0, 0), (1, 0, 15, 16), (17, 2, 0, 9), (4, 3, 5, 8)]
-         for d, ff in [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448)), (4096, (64, 832))]]
-# shapes that choose the staged kernel: experts of one or two rows, widths that end in partial column blocks
-STAGED = [("fp8", 192, 64, (1600, 1728)), ("mxfp4", 1152, 64, (768, 896))]
+EDGES = [(counts, d, ff) for counts in [(0, 1, 0, 0), (1, 0, 15, 16), (17, 2, 0, 9), (4, 3, 5, 8), (0, 32, 0, 0)]
+         for d, ff in [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448)), (2112, (1088, 576)), (4096, (64, 832))]]
+FORMS = {"staged": 0, "split": 1, "direct": 2}
 
 
 def _value(kind, codes, scale):
@@ -23,8 +22,9 @@ def _value(kind, codes, scale):
     return v * s
 
 
-def _check(kind, T, d, n, d_ff, eidx):
+def _check(kind, form, T, d, n, d_ff, eidx):
     import paper_2604_23108_amd as M
+    from paper_2604_23108_amd import bench_binding as BB
     Ne, k = 2 * n, eidx.shape[1]
     gen = torch.Generator(device="cuda").manual_seed(T + d)
     normal = lambda *s: torch.randn(s, generator=gen, device="cuda")
@@ -35,10 +35,10 @@ def _check(kind, T, d, n, d_ff, eidx):
     w2 = [(normal(n, d, f) * 0.05).bfloat16() for f in d_ff]
     L = M.MoHGELayer(cfg, normal(2, d) * 0.02, normal(Ne, d) * 0.02, w13, w2)
     L.use_fp8_weights() if kind == "fp8" else L.use_mxfp4_weights()
-    q, call = (L.w8, M.mohge_expert_ffn_w8) if kind == "fp8" else (L.w4, M.mohge_expert_ffn_w4)
+    q, bits = (L.w8, 8) if kind == "fp8" else (L.w4, 4)
     M.mohge_permute(cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None, L.ws_permute)
     L.y_perm.fill_(float("nan"))
-    call(cfg, x, L.perm, L.offsets, *q, L.y_perm, L.ws_ffn)
+    BB.mohge_bench_expert_ffn_quantised(cfg, x, L.perm, L.offsets, *q, L.y_perm, L.ws_ffn, bits, FORMS[form])
     torch.cuda.synchronize()
     off, tok, xs = L.offsets.tolist(), L.perm.cpu().long() // k, x.cpu().double()
     want = torch.zeros((T * k, d), dtype=torch.float64)
@@ -55,19 +55,9 @@ def _check(kind, T, d, n, d_ff, eidx):
     assert (got - want).abs().max() <= 8e-3 * want.abs().max()
 
 
-@pytest.mark.parametrize("kind", ["fp8", "mxfp4"])
-@pytest.mark.parametrize("counts,d,d_ff", SPLIT)
-def test_split_kernel_edges(kind, counts, d, d_ff):
+@pytest.mark.parametrize("kind,form", [("fp8", "staged"), ("fp8", "split"), ("fp8", "direct"), ("mxfp4", "staged"), ("mxfp4", "split")])
+@pytest.mark.parametrize("counts,d,d_ff", EDGES)
+def test_kernel_edges(kind, form, counts, d, d_ff):
     eidx = np.random.default_rng(5).permutation(np.repeat(np.arange(4), counts)).astype(np.int32).reshape(-1, 1)
-    print(f"[q split] {kind} counts={counts} d={d} d_ff={d_ff}", flush=True)
-    _check(kind, sum(counts), d, 2, d_ff, eidx)
-
-
-@pytest.mark.parametrize("kind,d,n,d_ff", STAGED)
-def test_staged_kernel(kind, d, n, d_ff):
-    T, rng = 32, np.random.default_rng(7)
-    waves = min(2 * T, 2 * n) * (sum(d_ff) // 2) // 16
-    assert waves >= (6500 if kind == "fp8" else 3000) and (kind == "fp8" or not any(f % 128 for f in d_ff)), "a shape for the split kernel"
-    eidx = np.stack([rng.integers(0, n, T), n + rng.integers(0, n, T)], 1).astype(np.int32)
-    print(f"[q staged] {kind} d={d} waves={waves}", flush=True)
-    _check(kind, T, d, n, d_ff, eidx)
+    print(f"[quantised] {kind} {form} counts={counts} d={d} d_ff={d_ff}", flush=True)
+    _check(kind, form, sum(counts), d, 2, d_ff, eidx)
