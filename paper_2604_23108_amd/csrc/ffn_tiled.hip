@@ -1472,8 +1472,9 @@ static hipError_t launch_small(K kern, bool& attr_done, long long grid, hipStrea
 // The mean cost of a wrong choice is 0.9 % forward, 1.3 % backward (the largest, 1.14, where 576 up tiles start a second
 // round on 512 slots: d = 4096, 24 experts x 144 rows).  From 1.7 big up tiles per compute unit on the big form has no
 // idle units to lose to (d = 1024, 32 experts, 768 rows: 122 -> 127 us); that limit alone, whatever the length
-// of the reduction, cost 1.7 and 2.2 %, up to 1.29.  Forward, where the big row tiles are not nearly full, it lies at 2.0 (1.73 to
-// 1.76 tiles per unit, d = 1024 and 1344, 520 to 675 rows: 0.83 to 0.98).
+// of the reduction, cost 1.7 and 2.2 %, up to 1.29.  Forward, where the big row tiles are not nearly full, it lies at 2.0: 26 layers
+// and token counts with 1.69 to 1.76 tiles per unit 0.58 to 0.99, mean 0.87 (rows spread evenly 0.70 to 1.03, 0.92), 13 with 1.83 to
+// 2.0, d = 768 to 1856, 137 to 1375 rows, 0.77 to 1.05, mean 0.91 (0.75 to 1.07, 0.93).
 bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
   if (o.small >= 0) return o.small != 0;
   const long long rows = L.P > L.Ne ? L.P / L.Ne : 1;     // per expert if they were spread evenly
