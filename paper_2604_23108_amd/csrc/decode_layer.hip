@@ -562,23 +562,24 @@ hipError_t launch_decode_layer(const LayerDesc& L, const void* x, const float* w
   const size_t smem = sel > srt ? (sel > red ? sel : red) : (srt > red ? srt : red);
   // persistent workgroups: as many as the device holds at once, no more than there are pieces of work
   // (progress does not depend on their all being resident: work is drawn in dependency order)
-  static size_t occ_smem = ~(size_t)0;
-  static int occ_blocks = 0;
-  if (occ_smem != smem) {
+  static std::atomic<unsigned long long> occupancy{0};          // LDS size << 32 | workgroups per compute unit, as last asked
+  unsigned long long occ = occupancy.load(std::memory_order_relaxed);
+  if (occ >> 32 != smem) {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, decode_layer_kernel, 256, smem) != hipSuccess || nb < 1) nb = 1;
-    occ_blocks = nb;
-    occ_smem = smem;
+    occ = (unsigned long long)smem << 32 | (unsigned)nb;
+    occupancy.store(occ, std::memory_order_relaxed);
   }
-  int dev = 0, cus = 256;
-  hipDeviceProp_t prop;
-  static int cached_cus = 0;
-  if (!cached_cus) {
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
-      cus = prop.multiProcessorCount;
-    cached_cus = cus;
+  static std::atomic<int> known_cus{0};                          // (GPUs of one kind: any thread's answer serves)
+  int cus = known_cus.load(std::memory_order_relaxed);
+  if (!cus) {
+    int dev = 0;
+    hipDeviceProp_t prop;
+    cus = hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0
+              ? prop.multiProcessorCount : 256;
+    known_cus.store(cus, std::memory_order_relaxed);
   }
-  long long grid = (long long)cached_cus * occ_blocks;
+  long long grid = (long long)cus * (long long)(occ & 0xffffffffu);
   const long long work = (long long)a.n_route + a.n_select + a.n_up + a.n_down;
   if (grid > work) grid = work;
   if (grid < 1) grid = 1;

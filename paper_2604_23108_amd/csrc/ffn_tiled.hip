@@ -1447,14 +1447,10 @@ static long long small_wgrad_grid(const TileArgs& a) {
 }
 
 template <typename K, typename... Args>
-static hipError_t launch_small(K kern, bool& attr_done, long long grid, hipStream_t s, const Args&... args) {
+static hipError_t launch_small(K kern, std::atomic<unsigned long long>& allowed, long long grid, hipStream_t s, const Args&... args) {
   if (grid * kSmallThreads >= 1ll << 32) return hipErrorInvalidConfiguration;      // (only if asked for beyond the rule below)
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), kSmallLds, allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSmallThreads), kSmallLds, s, args...);
   return hipGetLastError();
 }
@@ -1492,14 +1488,14 @@ bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
 
 hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
                             const TileArgs& w13, const GatherArgs& ga, hipStream_t s) {
-  static bool attr1 = false, attr2 = false;
+  static std::atomic<unsigned long long> allowed1{0}, allowed2{0};
   const long long n_dh = small_grid(L, kDgradH);
   // at least one gather workgroup: it writes the row of zeros (a call without tokens still clears the weight gradients)
   const int gather = ga.perm && ga.P > 0 ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
-  hipError_t e = launch_small(ffn_small_bwd1_kernel, attr1, n_dh + gather, s, dh, ga, (int)n_dh);
+  hipError_t e = launch_small(ffn_small_bwd1_kernel, allowed1, n_dh + gather, s, dh, ga, (int)n_dh);
   if (e != hipSuccess) return e;
   const long long n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
-  return launch_small(ffn_small_bwd2_kernel, attr2, n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
+  return launch_small(ffn_small_bwd2_kernel, allowed2, n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
 }
 
 void apply_options(TileArgs& t, const FfnOptions& o) {
@@ -1544,7 +1540,8 @@ long long tile_capacity(const LayerDesc& L, int mode) {
 }
 
 int tile_num_cus() {
-  static int n = 0;
+  static std::atomic<int> known{0};       // (GPUs of one kind: any thread's answer serves)
+  int n = known.load(std::memory_order_relaxed);
   if (!n) {
     int dev = 0;
     hipDeviceProp_t p;
@@ -1552,6 +1549,7 @@ int tile_num_cus() {
       n = p.multiProcessorCount;
     if (n < kXcds) n = 256;
     n = n / kXcds * kXcds;
+    known.store(n, std::memory_order_relaxed);
   }
   return n;
 }
@@ -1560,13 +1558,9 @@ template <int MODE>
 static hipError_t launch_stage(const TileArgs& a, hipStream_t s) {
   constexpr size_t smem = (size_t)(kStagesA * kBM + kStagesB * kBN) * kBK * 2;
   auto kern = ffn_tile_kernel<MODE>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static std::atomic<unsigned long long> allowed{0};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), (int)smem, allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.ncu), dim3(Shape<MODE>::THREADS), smem, s, a);
   return hipGetLastError();
 }
@@ -1576,13 +1570,9 @@ static hipError_t launch_fused(const TileArgs& up, const TileArgs& dn_in, hipStr
   const TileArgs& dn = dn_in;
   constexpr size_t smem = (size_t)(kStagesA * kBM + kStagesB * kBN) * kBK * 2;
   auto kern = ffn_fused_kernel<M0, M1, DEP>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static std::atomic<unsigned long long> allowed{0};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), (int)smem, allowed);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(up.ncu), dim3(Shape<M0>::THREADS), smem, s, up, dn);
   return hipGetLastError();
 }
@@ -1693,12 +1683,12 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
   if (parts == 3 && use_small_tiles(L, o, false)) {
-    static bool attr_up = false, attr_save = false, attr_dn = false;
+    static std::atomic<unsigned long long> allowed_up{0}, allowed_save{0}, allowed_dn{0};
     hipError_t e = hipSuccess;
     if (stages & 1)
-      e = pre ? launch_small(ffn_small_kernel<kUpSave>, attr_save, small_grid(L, kUp), s, up)
-              : launch_small(ffn_small_kernel<kUp>, attr_up, small_grid(L, kUp), s, up);
-    if (e == hipSuccess && (stages & 2)) e = launch_small(ffn_small_kernel<kDown>, attr_dn, small_grid(L, kDown), s, dn);
+      e = pre ? launch_small(ffn_small_kernel<kUpSave>, allowed_save, small_grid(L, kUp), s, up)
+              : launch_small(ffn_small_kernel<kUp>, allowed_up, small_grid(L, kUp), s, up);
+    if (e == hipSuccess && (stages & 2)) e = launch_small(ffn_small_kernel<kDown>, allowed_dn, small_grid(L, kDown), s, dn);
     return e;
   }
   // the whole forward in one launch: up and down tiles share the persistent workgroups

@@ -345,13 +345,9 @@ template <int TG, int TN>
 static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* planes, int plane_rows, size_t smem,
                                  hipStream_t s) {
   auto kern = route_prefill_kernel<TG, TN>;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
+  static std::atomic<unsigned long long> allowed{0};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), 160 * 1024, allowed);
+  if (e != hipSuccess) return e;
   constexpr int BT = 16 * TG;
   hipLaunchKernelGGL(kern, dim3((T + BT - 1) / BT), dim3(512), smem, s, a, planes, plane_rows);
   return hipGetLastError();
@@ -427,12 +423,14 @@ constexpr int kPrefillMinT = 8192;       // from here on the bf16 matrix-core fo
                                          // 190 us at 16384 tokens, even at 8192, slower below)
 
 static int tile_cus() {
-  static int n = 0;
+  static std::atomic<int> known{0};       // (GPUs of one kind: any thread's answer serves)
+  int n = known.load(std::memory_order_relaxed);
   if (!n) {
     int dev = 0;
     hipDeviceProp_t p;
     n = (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&p, dev) == hipSuccess && p.multiProcessorCount > 0)
             ? p.multiProcessorCount : 256;
+    known.store(n, std::memory_order_relaxed);
   }
   return n;
 }
@@ -543,14 +541,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   else e = bf ? launch_tn<true, 1>(a, TN, grid, block, smem, s)
               : launch_tn<false, 1>(a, TN, grid, block, smem, s);
   if (e != hipSuccess || a.dsplit == 1) return e;
-  static bool attr_done = false;
-  if (!attr_done) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(route_finish_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  // (its own LDS: the first kernel's partial totals would leave room for one workgroup per compute unit)
+  // (its own LDS, at most 45 KB: the first kernel's partial totals would leave room for one workgroup per compute unit)
   a.region0 = (int)((size_t)NW * 5 * a.Nepad * sizeof(float));
   smem = (size_t)a.region0 + (size_t)kFinishTokens * a.NOpad * sizeof(float);
   hipLaunchKernelGGL(route_finish_kernel, dim3((L.T + kFinishTokens - 1) / kFinishTokens), block, smem, s, a);
