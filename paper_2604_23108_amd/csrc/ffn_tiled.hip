@@ -515,15 +515,16 @@ __device__ __forceinline__ void swiglu_bwd8(const uint4 dh, const uint4 pv, cons
 // Short tiles.  A stage of a full tile takes about as long as its operands take to arrive, two stages ahead; a tile of
 // fewer rows has less to multiply per stage but waited just as long (64, 128, 192, 256 rows: 1934, 2021, 2075, 2174
 // clocks).  Its token parts are short, so the same LDS holds more stages of both operands: four up to 64 rows of a 256-row
-// tile, three up to 128, and three up to 64 of a 128-row tile.  Where every expert has a few rows and its weights are the
+// tile, three up to 128.  Where every expert has a few rows and its weights are the
 // work, d = 4096, 64 experts: 40 tokens 406 -> 373 us, 100 tokens 417 ->
 // 381, 600 tokens 435 -> 401; unchanged where full tiles dominate.  (The backward products, bound by their transposing
-// reads, gain nothing: 0.99 to 1.04 of the time.)
+// reads, gain nothing: 0.99 to 1.04 of the time.  Three stages up to 64 rows of a 128-row tile, ten layers, 33 to 400 tokens:
+// 0.94 to 1.065 of the time, slower at d = 2048 with 24 experts and d = 4096 with 8.)
 template <typename GEO>
 constexpr int short_depth(int mode, int nact) {
   if (tr_b(mode)) return 0;
   if (GEO::BM == kBM) return nact == 1 ? 4 : nact == 2 ? 3 : 0;
-  return nact == 1 ? 3 : 0;
+  return 0;
 }
 
 // One tile with NACT active 32-row token fragments per wave (tile rows <= 64*NACT).
