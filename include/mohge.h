@@ -114,7 +114,8 @@ int mohge_route(const mohge_config* cfg, const void* x, const float* w_group,
  *      perm DEVICE [P], perm[r] = p; inv_perm DEVICE [P], inv_perm[p] = r.
  *      If x_perm != NULL (then x must be given): x_perm DEVICE [P,d] (dtype),
  *      x_perm[r,:] = x[perm[r] / K_e, :].
- * workspace DEVICE, at least mohge_workspace_size(cfg, MOHGE_CALL_PERMUTE) bytes.
+ * workspace DEVICE, at least mohge_workspace_size(cfg, MOHGE_CALL_PERMUTE) bytes (never less for more
+ * tokens: one sized for the largest call serves the smaller ones).
  */
 int mohge_permute(const mohge_config* cfg, const int32_t* expert_idx, int32_t* counts,
                   int32_t* offsets, int32_t* perm, int32_t* inv_perm, const void* x,
