@@ -81,6 +81,8 @@ constexpr bool red_d(int mode) { return is_up(mode) || mode == kDgradH; }
 // launches that would leave compute units idle with big tiles, see use_small_tiles).
 struct BigTile { static constexpr int BM = kBM, BN = kBN, WGM = kWGM, WGN = kWGN; };
 struct SmallTile { static constexpr int BM = 128, BN = 128, WGM = 2, WGN = 2; };
+// Tall: the small form's token modes, up to 192 rows of one expert (see small_token_tile)
+struct TallTile { static constexpr int BM = 192, BN = 128, WGM = 2, WGN = 2; };
 
 template <int MODE>
 struct Shape {
@@ -520,8 +522,10 @@ __device__ __forceinline__ void swiglu_bwd8(const uint4 dh, const uint4 pv, cons
 // 381, 600 tokens 435 -> 401; unchanged where full tiles dominate.  (The backward products, bound by their transposing
 // reads, gain nothing: 0.99 to 1.04 of the time.  Three stages up to 64 rows of a 128-row tile, ten layers, 33 to 400 tokens:
 // 0.94 to 1.065 of the time, slower at d = 2048 with 24 experts and d = 4096 with 8.)
+// Tall tiles of more than 128 rows: two stages of both operands (2 x 24 KB of tokens and 2 x 16 KB of weights).
 template <typename GEO>
 constexpr int short_depth(int mode, int nact) {
+  if (GEO::BM == TallTile::BM && nact == 3) return 2;
   if (tr_b(mode)) return 0;
   if (GEO::BM == kBM) return nact == 1 ? 4 : nact == 2 ? 3 : 0;
   return 0;
@@ -543,7 +547,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   long long ts[6] = {0, 0, 0, 0, 0, 0};
   PROBE_T(0);
   constexpr int BM = GEO::BM, BN = GEO::BN, BK = kBK;
-  static_assert(BM == BN, "one part size for both operands");
+  static_assert(BM == BN || !TRA, "one part size for both operands");
   constexpr int WGM = GEO::WGM, WGN = GEO::WGN, NWAVES = WGM * WGN, NT = 64 * NWAVES;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int MF = WTM / 32, NF = WTN / 32;
@@ -555,7 +559,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // (NACT active fragments per wave cover the tile rows [0, NACT * 32 * WGM))
   constexpr int A_LOADS = TRA ? BM * CH / NT : NACT * (32 * WGM / (NWAVES * RPL));
   static_assert((32 * WGM) % (NWAVES * RPL) == 0 && B_LOADS * NWAVES * RPL == BN, "whole wave-wide loads");
-  constexpr int PART = BM * ROWB;                 // 32 (16) KB: one token part or one weight part
+  constexpr int PART = BN * ROWB;                 // 32 (16) KB: one weight part, or a token part of as many rows
   constexpr int NM = NACT * NF;     // MFMAs per k-step
   constexpr int NR = NACT + NF;     // fragment reads per k-step
   static_assert(NACT >= 1 && NACT <= MF, "active fragments");
@@ -567,6 +571,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr int APART = DEEP ? NACT * 32 * WGM * ROWB : PART, SLOTS = DEEP ? DEPTH : kStagesB;
   constexpr int BBASE = DEEP ? DEPTH * APART : kStagesA * PART;
   static_assert(BBASE + SLOTS * PART <= (kStagesA + kStagesB) * PART, "LDS of a workgroup");
+  static_assert(DEEP || NACT * 32 * WGM * ROWB <= PART, "a stage's tokens fit their part");
   // (token part of stage kt, whose weights are in `slot`)
   auto a_part = [&](int stage, int slot) { return lds + (DEEP ? slot : stage & 1) * APART; };
   auto b_part = [&](int slot) { return lds + BBASE + slot * PART; };
@@ -601,7 +606,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // l/TCH, which holds logical chunk (l%TCH) ^ (4*(t&3)): the four rows a transposing read touches
   // at once then sit in different banks.
   constexpr int TRB_ROW = BN * 2, TCH = BN / 8, TPL = 1024 / TRB_ROW;
-  static_assert(!(TRA || TRB) || (NWAVES * TPL % 4 == 0 && B_LOADS == BM * CH / NT), "part layout");
+  static_assert(!(TRA || TRB) || (NWAVES * TPL % 4 == 0 && B_LOADS == BN * CH / NT), "part layout");
   const int trow0 = TPL * w + lane / TCH;         // row of load 0; load j: + TPL*NWAVES*j
   const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3));
   const uint16_t* zsrc = nullptr;
@@ -1026,12 +1031,12 @@ template <int MODE, typename GEO = BigTile>
 __device__ __forceinline__ void run_tile_rows(const TileArgs& a, const TileRec& rec, unsigned char* lds, int lane,
                                               int w, int* signal) {
   constexpr int UNIT = 32 * GEO::WGM, MF = GEO::BM / UNIT;
-  static_assert(MF == 2 || MF == 4, "two or four token fragments per wave");
+  static_assert(MF >= 2 && MF <= 4, "two to four token fragments per wave");
   const int nact = (rec.rows + UNIT - 1) / UNIT;
-  if constexpr (MF == 4) {
+  if constexpr (MF == 4)
     if (nact == 4) { run_tile<MODE, 4, GEO>(a, rec, lds, lane, w, signal); return; }
+  if constexpr (MF >= 3)
     if (nact == 3) { run_tile<MODE, 3, GEO>(a, rec, lds, lane, w, signal); return; }
-  }
   if (nact >= 2) run_tile<MODE, 2, GEO>(a, rec, lds, lane, w, signal);
   else run_tile<MODE, 1, GEO>(a, rec, lds, lane, w, signal);
 }
@@ -1306,31 +1311,48 @@ __device__ __forceinline__ int small_tile_index(int b) {
   return ((q / kSmallChunk) * kXcds + xcd) * kSmallChunk + q % kSmallChunk;
 }
 
+// Tall tiles.  An expert of 129 to 192 rows as two row tiles has every weight fetched twice, the second time for a few
+// rows.  Where at least three quarters of the experts are of that size they are one tile of 192 rows each (two stages of both
+// operands instead of two and three, the same 80 KB).  Layer calls, two tiles -> one, rows spread evenly: 64 experts x 139 rows, d = 1024
+// 136 -> 131.5 us, 32 x 169 67.5 -> 63.9, 25 x 160, d = 1344 79.2 -> 71.9; training step 64 x 141 500 -> 472, 24 x 167,
+// d = 2048 435 -> 410, 32 x 146 207.7 -> 205.5.  With few such experts, or a remainder of up to 64 rows joined to the last of
+// several tiles, the longer tiles end later than what they save: 64 x 112 121 -> 125, 24 x 183 skewed 140 -> 145.
+__device__ __forceinline__ bool small_tall(int cnt) { return cnt > SmallTile::BM && cnt <= TallTile::BM; }
+__device__ __forceinline__ int small_row_tiles(int cnt, bool tall) {
+  return tall && small_tall(cnt) ? 1 : (cnt + SmallTile::BM - 1) / SmallTile::BM;
+}
+
 // tile t of the list of a token mode; false if there is none.  The same in every lane; called by whole waves.
-template <int MODE>
+template <int MODE, bool TALL>
 __device__ __forceinline__ bool small_token_tile(const TileArgs& a, int t, int lane, TileRec& rec) {
-  constexpr int BM = SmallTile::BM, NCPT = is_up(MODE) ? SmallTile::BN / 2 : SmallTile::BN;
-  int before = 0;
+  constexpr int NCPT = is_up(MODE) ? TallTile::BN / 2 : TallTile::BN;
+  int before = 0, n_tall = 0;
+  for (int v0 = TALL && a.Ne > 64 ? 0 : a.Ne; v0 < a.Ne; v0 += 64) {
+    const int v = min(v0 + lane, a.Ne - 1);
+    n_tall += __popcll(__ballot(v0 + lane < a.Ne && small_tall(a.offsets[v + 1] - a.offsets[v])));
+  }
   for (int v0 = 0; v0 < a.Ne; v0 += 64) {
     const int v = v0 + lane;                       // groups by decreasing width: the longest tiles start first
     const int g = a.order[(v < a.Ne ? v : 0) / a.N], e = g * a.N + (v < a.Ne ? v : 0) % a.N;
     const int lo = a.offsets[e], cnt = v < a.Ne ? a.offsets[e + 1] - lo : 0;
     const int nt = ((red_d(MODE) ? a.F[g] : a.d) + NCPT - 1) / NCPT;
-    const int n = (cnt + BM - 1) / BM * nt;
+    if (TALL && a.Ne <= 64) n_tall = __popcll(__ballot(small_tall(cnt)));
+    const bool tall = TALL && 4 * n_tall >= 3 * a.Ne;
+    const int n = small_row_tiles(cnt, tall) * nt;
     const int incl = wave_incl_scan(n);
     const int first = before + incl - n;
     const unsigned long long hit = __ballot(t >= first && t < first + n);
     if (hit) {
       const int l = (int)__builtin_ctzll(hit);
       const int rel = t - __builtin_amdgcn_readlane(first, l), ntv = __builtin_amdgcn_readlane(nt, l);
-      const int c = __builtin_amdgcn_readlane(cnt, l), mt = (c + BM - 1) / BM;
+      const int c = __builtin_amdgcn_readlane(cnt, l), mt = small_row_tiles(c, tall);
       // bands of four row tiles; inside a band column tile major, row tile minor
       constexpr int RB = 4;
       const int bnd = rel / (RB * ntv), rel2 = rel - bnd * RB * ntv, rb = min(RB, mt - bnd * RB);
       const int ni = rel2 / rb, mi = bnd * RB + rel2 % rb;
       rec.e = __builtin_amdgcn_readlane(e, l);
-      rec.row_start = __builtin_amdgcn_readlane(lo, l) + mi * BM;
-      rec.rows = min(BM, c - mi * BM);
+      rec.row_start = __builtin_amdgcn_readlane(lo, l) + mi * SmallTile::BM;
+      rec.rows = mt == 1 ? c : min(SmallTile::BM, c - mi * SmallTile::BM);
       rec.n0 = ni * NCPT;
       rec.fam = 0;
       rec.need = 0;
@@ -1364,22 +1386,22 @@ __device__ __forceinline__ bool small_wgrad_tile(const TileArgs& a, int t, TileR
 constexpr int kSmallThreads = 64 * SmallTile::WGM * SmallTile::WGN;
 constexpr int kSmallLds = (kStagesA * SmallTile::BM + kStagesB * SmallTile::BN) * kBK * 2;
 
-template <int MODE>
+template <int MODE, bool TALL = false>
 __device__ __forceinline__ void small_tile(const TileArgs& a, int b, unsigned char* lds) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   TileRec rec;
   bool ok;
   if constexpr (MODE == kWgrad) ok = small_wgrad_tile(a, small_tile_index(b), rec);
-  else ok = small_token_tile<MODE>(a, small_tile_index(b), lane, rec);
-  if (ok) run_tile_rows<MODE, SmallTile>(a, rec, lds, lane, w, nullptr);
+  else ok = small_token_tile<MODE, TALL>(a, small_tile_index(b), lane, rec);
+  if (ok) run_tile_rows<MODE, typename std::conditional<TALL, TallTile, SmallTile>::type>(a, rec, lds, lane, w, nullptr);
 }
 
-template <int MODE>
+template <int MODE, bool TALL>
 __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_kernel(const TileArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   // (nothing waits here: the flag that mohge_fused_status reads stays clear)
   if (MODE == kDown && blockIdx.x == 0 && threadIdx.x == 0) a.hdr->pad[0] = 0;
-  small_tile<MODE>(a, blockIdx.x, lds);
+  small_tile<MODE, TALL>(a, blockIdx.x, lds);
 }
 
 // Backward, first launch: dH, and on the workgroups past its n_dh the rows of x in sorted order and the
@@ -1387,10 +1409,11 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_kernel(const TileA
 // three of the four pieces in private memory until their store, 80 bytes per lane).
 constexpr int kSmallGatherRows = 16;
 
+template <bool TALL>
 __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd1_kernel(const TileArgs dh, const GatherArgs ga, int n_dh) {
   extern __shared__ __align__(1024) unsigned char lds[];
   if ((int)blockIdx.x < n_dh) {
-    small_tile<kDgradH>(dh, blockIdx.x, lds);
+    small_tile<kDgradH, TALL>(dh, blockIdx.x, lds);
     return;
   }
   const int b = blockIdx.x - n_dh, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1412,12 +1435,13 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd1_kernel(const 
 }
 
 // Backward, second launch: dX (the longest reductions first), then both weight gradients
+template <bool TALL>
 __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd2_kernel(const TileArgs dx, const TileArgs w2,
                                                                           const TileArgs w13, int n_dx, int n_w2) {
   extern __shared__ __align__(1024) unsigned char lds[];
   const int b = blockIdx.x;
   if (b == 0 && threadIdx.x == 0) dx.hdr->pad[0] = 0;
-  if (b < n_dx) small_tile<kDgradX>(dx, b, lds);
+  if (b < n_dx) small_tile<kDgradX, TALL>(dx, b, lds);
   else if (b < n_dx + n_w2) small_tile<kWgrad>(w2, b - n_dx, lds);
   else small_tile<kWgrad>(w13, b - n_dx - n_w2, lds);
 }
@@ -1440,6 +1464,11 @@ static long long small_grid(const LayerDesc& L, int mode) {
   return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
+// Launches in which tall tiles are looked for: outside, an even spread leaves fewer than three quarters of the experts
+// with 129 to 192 rows (135 and 187 per expert: 1.01 to 1.02 of the time), and the instantiation without them is up to
+// 1 % faster where it finds none.
+static bool may_be_tall(const LayerDesc& L) { return L.P >= 140ll * L.Ne && L.P <= 184ll * L.Ne; }
+
 static long long small_wgrad_grid(const TileArgs& a) {
   long long n = 0;
   for (int g = 0; g < a.Ng; ++g)
@@ -1447,12 +1476,13 @@ static long long small_wgrad_grid(const TileArgs& a) {
   return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
-template <typename K, typename... Args>
-static hipError_t launch_small(K kern, std::atomic<unsigned long long>& allowed, long long grid, hipStream_t s, const Args&... args) {
+template <auto KERN, typename... Args>
+static hipError_t launch_small(long long grid, hipStream_t s, const Args&... args) {
+  static std::atomic<unsigned long long> allowed{0};
   if (grid * kSmallThreads >= 1ll << 32) return hipErrorInvalidConfiguration;      // (only if asked for beyond the rule below)
-  const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), kSmallLds, allowed);
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(KERN), kSmallLds, allowed);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kSmallThreads), kSmallLds, s, args...);
+  hipLaunchKernelGGL(KERN, dim3((unsigned)grid), dim3(kSmallThreads), kSmallLds, s, args...);
   return hipGetLastError();
 }
 
@@ -1489,14 +1519,16 @@ bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
 
 hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileArgs& dx, const TileArgs& w2,
                             const TileArgs& w13, const GatherArgs& ga, hipStream_t s) {
-  static std::atomic<unsigned long long> allowed1{0}, allowed2{0};
   const long long n_dh = small_grid(L, kDgradH);
   // at least one gather workgroup: it writes the row of zeros (a call without tokens still clears the weight gradients)
   const int gather = ga.perm && ga.P > 0 ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
-  hipError_t e = launch_small(ffn_small_bwd1_kernel, allowed1, n_dh + gather, s, dh, ga, (int)n_dh);
+  const bool tall = may_be_tall(L);
+  hipError_t e = tall ? launch_small<ffn_small_bwd1_kernel<true>>(n_dh + gather, s, dh, ga, (int)n_dh)
+                      : launch_small<ffn_small_bwd1_kernel<false>>(n_dh + gather, s, dh, ga, (int)n_dh);
   if (e != hipSuccess) return e;
   const long long n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
-  return launch_small(ffn_small_bwd2_kernel, allowed2, n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
+  return tall ? launch_small<ffn_small_bwd2_kernel<true>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2)
+              : launch_small<ffn_small_bwd2_kernel<false>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
 }
 
 void apply_options(TileArgs& t, const FfnOptions& o) {
@@ -1684,12 +1716,17 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
   if (parts == 3 && use_small_tiles(L, o, false)) {
-    static std::atomic<unsigned long long> allowed_up{0}, allowed_save{0}, allowed_dn{0};
+    const bool tall = may_be_tall(L);
     hipError_t e = hipSuccess;
-    if (stages & 1)
-      e = pre ? launch_small(ffn_small_kernel<kUpSave>, allowed_save, small_grid(L, kUp), s, up)
-              : launch_small(ffn_small_kernel<kUp>, allowed_up, small_grid(L, kUp), s, up);
-    if (e == hipSuccess && (stages & 2)) e = launch_small(ffn_small_kernel<kDown>, allowed_dn, small_grid(L, kDown), s, dn);
+    if (stages & 1) {
+      const long long n = small_grid(L, kUp);
+      if (pre) e = tall ? launch_small<ffn_small_kernel<kUpSave, true>>(n, s, up) : launch_small<ffn_small_kernel<kUpSave, false>>(n, s, up);
+      else e = tall ? launch_small<ffn_small_kernel<kUp, true>>(n, s, up) : launch_small<ffn_small_kernel<kUp, false>>(n, s, up);
+    }
+    if (e == hipSuccess && (stages & 2)) {
+      const long long n = small_grid(L, kDown);
+      e = tall ? launch_small<ffn_small_kernel<kDown, true>>(n, s, dn) : launch_small<ffn_small_kernel<kDown, false>>(n, s, dn);
+    }
     return e;
   }
   // the whole forward in one launch: up and down tiles share the persistent workgroups

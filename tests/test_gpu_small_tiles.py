@@ -60,6 +60,46 @@ def test_small_tiles_equal_big_tiles(d, d_ff):
     assert np.abs(got - want).max() <= 8e-3 * np.abs(want).max()
 
 
+# rows per expert where most experts are one tall tile: its edges, and one expert of each other kind; too few for it
+TALL = [129, 192, 191, 160, 130, 161, 144, 180, 128, 193, 150, 190]
+FEW_TALL = [129, 192, 191, 64, 130, 161, 65, 257, 128, 193, 150, 320]
+
+
+@pytest.mark.parametrize("counts", [TALL, FEW_TALL], ids=["tall", "few"])
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448))])
+def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
+    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage.)"""
+    import paper_2604_23108_amd as M
+    from paper_2604_23108_amd import bench_binding as BB
+    from gpu_harness import DeviceLayer, to_dev
+    T = sum(counts)
+    assert 140 * 12 <= T <= 184 * 12
+    w = Workload("tall_tiles", T=T, d=d, n_groups=2, experts_per_group=6, d_ff=d_ff, k_groups=1, k_experts=1, seed=47,
+                 training=True)
+    inp = generate(w)
+    dl = DeviceLayer(w, inp, backward=True, guard=True)
+    L = dl.layer
+    eidx = np.random.default_rng(6).permutation(np.repeat(np.arange(12), counts)).astype(np.int32).reshape(T, 1)
+    M.mohge_permute(dl.cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None,
+                    L.ws_permute)
+    L.dy_perm.copy_(to_dev(inp.dy, True)[L.perm.long()])
+    outs = []
+    for small in (1, 0):
+        for t in [L.y_perm, L.dx_perm, *L.dw13, *L.dw2]:
+            t.fill_(float("nan"))
+        print(f"[tall tiles] d={d} d_ff={d_ff} small={small}", flush=True)
+        args, o = (dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2), BB.FfnOptions(small_tiles=small)
+        BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn, o)
+        y = L.y_perm.clone()
+        BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved, o)
+        BB.mohge_bench_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd, o)
+        torch.cuda.synchronize()
+        dl.check_guards()
+        outs.append([t.clone() for t in [y, L.y_perm, L.dx_perm, *L.dw13, *L.dw2]])
+    for a, b in zip(*outs):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b)
+
+
 @pytest.mark.parametrize("forward,backward", [(1, 0), (0, 1)])
 def test_forward_and_backward_in_different_forms(forward, backward):
     """The two rules differ, so a layer may run its forward in small tiles and its backward in big ones: what the forward
