@@ -173,17 +173,32 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
 //
 // A small kernel first splits the router rows into the three bf16 planes (workspace:
 // [3][rows padded to whole passes][d], padding rows zero).  In the main kernel a workgroup of 8
-// waves owns 16*TG tokens: waves = TG token groups of 16 x (8/TG) parts of every 128-deep chunk
+// waves owns 16*TG tokens: waves = TG token groups of 16 x (8/TG) parts of every 64- or 128-deep chunk
 // of the hidden dimension.  A wave loads its token fragments straight from global memory in
 // operand layout (several chunks ahead); the three planes of a chunk go global -> LDS without
-// passing registers (global_load_lds, double buffered, 16-byte pieces XOR-swizzled by the row so
+// passing registers (global_load_lds, up to three chunks ahead, 16-byte pieces XOR-swizzled by the row so
 // that the 128-bit fragment reads are conflict free).  The waves of a token group add their fp64
 // totals through LDS in fixed order.  Router rows are processed 16*TN at a time (TN <= 5 column
 // tiles: more would not fit the registers); wider routers make several passes over the token rows.
+// The logits go to the workspace and a second kernel selects, one wave per token: inside this one, with two waves per SIMD, the
+// selection of a workgroup's 64 tokens took as long as a pass (d = 1024, 136 rows, 12000 tokens: 119 us for the call with
+// it, 93 without).
+// Bound by the planes, which every compute unit reads from L2 (1.9 MB at 68 rows, d = 4096) and its waves from LDS.
 // ---------------------------------------------------------------------------------------
 typedef __bf16 rbf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kPfChunk = 128;            // hidden elements per chunk
+constexpr int kPfDepth = 128;            // the hidden size is a multiple of it
+
+// Hidden elements per chunk and chunks in LDS: four where they fit, so that several are on their way while one is used.  (One
+// workgroup per compute unit has all of its LDS.  Two chunks: 68 router rows, d = 4096, 16384 tokens 80 us for the call, now 67.)
+// Not DEEP: two chunks and registers for two workgroups per compute unit, where there are more of them than units and two would
+// otherwise fit (27 rows, d = 2048, 32768 tokens: 46 us, one workgroup per unit 60).
+template <int TG, int TN, bool DEEP>
+struct PrefillShape {
+  static constexpr int CH = TG == 4 && TN >= 4 ? 64 : 128;
+  static constexpr int NB = DEEP && 4 * 3 * 16 * TN * CH * 2 <= 150 * 1024 ? 4 : 2;
+  static constexpr int LDS = NB * 3 * 16 * TN * CH * 2;
+};
 
 // planes[p][row][k], p = 0 (leading bits), 1, 2; rows >= NO are zero
 __global__ void __launch_bounds__(256) route_split_kernel(const float* __restrict__ wg, const float* __restrict__ we,
@@ -211,23 +226,26 @@ __global__ void __launch_bounds__(256) route_split_kernel(const float* __restric
   *reinterpret_cast<uint2*>(planes + 2 * plane + at) = make_uint2((lo[0] >> 16) | lo[1], (lo[2] >> 16) | lo[3]);
 }
 
-template <int TG, int TN>
-__global__ void __launch_bounds__(512) route_prefill_kernel(const RouteArgs a, const uint16_t* __restrict__ planes,
+template <int TG, int TN, bool DEEP>
+__global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const RouteArgs a, const uint16_t* __restrict__ planes,
                                                             int plane_rows) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr int KQ = 8 / TG;                 // waves along the hidden dimension
-  constexpr int KS = 4 / KQ;                 // 32-deep MFMA steps of a wave per chunk
+  constexpr int CH = PrefillShape<TG, TN, DEEP>::CH, NB = PrefillShape<TG, TN, DEEP>::NB;
+  constexpr int KS = CH / 32 / KQ;           // 32-deep MFMA steps of a wave per chunk
   constexpr int BT = 16 * TG, NC = 16 * TN;
-  constexpr int PLANE = NC * 256, BUF = 3 * PLANE;
-  constexpr int NCOPY = 3 * NC / 4;          // wave-wide copies (4 rows x 256 bytes) per chunk
-  constexpr int XP = 4;                      // token chunks in flight
+  constexpr int ROW = CH * 2, PLANE = NC * ROW, BUF = 3 * PLANE;
+  constexpr int RPC = 1024 / ROW, PPR = ROW / 16;   // rows per wave-wide copy, 16-byte pieces per row
+  constexpr int NCOPY = 3 * NC / RPC;        // wave-wide copies per chunk
+  constexpr int WCOPY = (NCOPY + 7) / 8;     // ... per wave (the last ones twice: the same bytes to the same place)
+  constexpr int XP = 512 / CH;               // token chunks in flight
+  static_assert(KS >= 1 && NC % RPC == 0 && XP % NB == 0 && (NB - 1) * (WCOPY + KS) + KS <= 63, "waits");
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int tg = w / KQ, kq = w % KQ;
   const int r = lane & 15, q = lane >> 4;
   const int t0 = blockIdx.x * BT;
-  float* lg = reinterpret_cast<float*>(smem + a.region0);         // [BT][NOpad]
   double* red = reinterpret_cast<double*>(smem);                  // [BT][NC], after the chunk loop
-  const int nchunks = a.d / kPfChunk;
+  const int nchunks = a.d / CH;
 
   const int tok = t0 + tg * 16 + r;
   const uint16_t* xrow = static_cast<const uint16_t*>(a.x) + (size_t)(tok < a.T ? tok : a.T - 1) * a.d +
@@ -244,13 +262,15 @@ __global__ void __launch_bounds__(512) route_prefill_kernel(const RouteArgs a, c
 #pragma unroll
       for (int i = 0; i < 4; ++i) tot[tn][i] = 0.0;
     }
-    // copy idx (wave-uniform) of a chunk: plane idx / (NC/4), rows 4*(idx % (NC/4)) .. +3 of the
-    // pass; lane l fills row l/16, physical piece l%16, which holds logical piece (l%16) ^ (row & 15)
+    // copy idx (wave-uniform) of a chunk: plane idx / (NC/RPC), rows RPC*(idx % (NC/RPC)) .. of the
+    // pass; lane l fills row l/PPR, physical piece l%PPR, which holds logical piece (l%PPR) ^ (row % PPR)
     auto copy_w = [&](int c, int b) {
-      for (int idx = w; idx < NCOPY; idx += 8) {
-        const int p = idx / (NC / 4), row = 4 * (idx % (NC / 4)) + (lane >> 4);
-        const int piece = (lane & 15) ^ (row & 15);
-        const uint16_t* src = planes + p * plane_elems + (size_t)(nc + row) * a.d + (size_t)c * kPfChunk + piece * 8;
+#pragma unroll
+      for (int i = 0; i < WCOPY; ++i) {
+        const int idx = min(w + 8 * i, NCOPY - 1);
+        const int p = idx / (NC / RPC), row = RPC * (idx % (NC / RPC)) + lane / PPR;
+        const int piece = (lane % PPR) ^ (row % PPR);
+        const uint16_t* src = planes + p * plane_elems + (size_t)(nc + row) * a.d + (size_t)c * CH + piece * 8;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                          (__attribute__((address_space(3))) void*)(smem + b * BUF + idx * 1024),
                                          16, 0, 0);
@@ -260,46 +280,50 @@ __global__ void __launch_bounds__(512) route_prefill_kernel(const RouteArgs a, c
     auto load_x = [&](int c, int slot) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        xr[slot][ks] = *reinterpret_cast<const uint4*>(xrow + (size_t)c * kPfChunk + 32 * ks);
+        xr[slot][ks] = *reinterpret_cast<const uint4*>(xrow + (size_t)c * CH + 32 * ks);
     };
 
     __syncthreads();                     // the previous pass has left the buffers
-    copy_w(0, 0);
+#pragma unroll
+    for (int u = 0; u < NB - 1; ++u)
+      if (u < nchunks) copy_w(u, u);
 #pragma unroll
     for (int u = 0; u < XP; ++u)
       if (u < nchunks) load_x(u, u);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    for (int c0 = 0; c0 < nchunks; c0 += XP) {
+    // vmcnt(0), known to the compiler: the loop's waits then count what the loop itself requests
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    // XP chunks from c0 on.  FULL: all that they request exists, so there are no branches between the requests and the
+    // compiler's own waits for the token fragments are exact (behind a branch it waits for everything on its way).
+    auto group = [&](int c0, auto FULL) {
+      constexpr bool full = decltype(FULL)::value;
 #pragma unroll
       for (int u = 0; u < XP; ++u) {
         const int c = c0 + u;
-        if (c < nchunks) {
-          rbf16x8 xa[KS];
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) xa[ks] = __builtin_bit_cast(rbf16x8, xr[u][ks]);
-          // the next chunk's planes into the other buffer (nobody reads it any more: barrier at
-          // the end of the previous chunk), then the token fragments of a later chunk
-          if (c + 1 < nchunks) copy_w(c + 1, (u + 1) & 1);
+        if (full || c < nchunks) {
+          // a later chunk's planes into the buffer that the previous chunk had (nobody reads it any more:
+          // barrier at its end); behind the products the token fragments of a later chunk
+          if (full || c + NB - 1 < nchunks) copy_w(c + NB - 1, (u + NB - 1) % NB);
           __builtin_amdgcn_sched_barrier(0);
-          if (c + XP < nchunks) load_x(c + XP, u);
-          __builtin_amdgcn_sched_barrier(0);
-          const unsigned char* fb = smem + (u & 1) * BUF + r * 256;
+          const unsigned char* fb = smem + (u % NB) * BUF + r * ROW;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
-            const int piece = ((kq * KS + ks) * 4 + q) ^ r;
+            const int piece = ((kq * KS + ks) * 4 + q) ^ (r % PPR);
+            const rbf16x8 xa = __builtin_bit_cast(rbf16x8, xr[u][ks]);
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-              const unsigned char* f = fb + 16 * tn * 256 + piece * 16;
+              const unsigned char* f = fb + 16 * tn * ROW + piece * 16;
               const rbf16x8 bh = *reinterpret_cast<const rbf16x8*>(f);
               const rbf16x8 bm = *reinterpret_cast<const rbf16x8*>(f + PLANE);
               const rbf16x8 bl = *reinterpret_cast<const rbf16x8*>(f + 2 * PLANE);
-              acc_h[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bh, acc_h[tn], 0, 0, 0);
-              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bm, acc_l[tn], 0, 0, 0);
-              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bl, acc_l[tn], 0, 0, 0);
+              acc_h[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bh, acc_h[tn], 0, 0, 0);
+              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bm, acc_l[tn], 0, 0, 0);
+              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bl, acc_l[tn], 0, 0, 0);
             }
             // the large part goes into the fp64 totals after every 64 hidden elements of this wave
-            if (KS == 2 ? ks == 1 : ((u & 1) || c + 1 == nchunks)) {
+            if (KS == 2 ? ks == 1 : ((u & 1) || (!full && c + 1 == nchunks))) {
 #pragma unroll
               for (int tn = 0; tn < TN; ++tn) {
 #pragma unroll
@@ -308,14 +332,21 @@ __global__ void __launch_bounds__(512) route_prefill_kernel(const RouteArgs a, c
               }
             }
           }
-          // my pieces of the next chunk's planes have landed when at most the token loads issued
-          // after them are outstanding (loads complete in order)
-          if (c + XP < nchunks) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KS) : "memory");
-          else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          __syncthreads();
+          // (behind the last use of the registers: in front of it the compiler copies them, once all of them have landed)
+          __builtin_amdgcn_sched_barrier(0);
+          if (full || c + XP < nchunks) load_x(c + XP, u);
+          // my pieces of the next chunk's planes have landed when at most what was issued after them is outstanding
+          // (loads complete in order): the planes of NB - 2 further chunks and the token loads of NB - 1
+          if (full || c + XP < nchunks) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NB - 2) * WCOPY + (NB - 1) * KS) : "memory");
+          else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+          __builtin_amdgcn_s_barrier();
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
-    }
+    };
+    int c0 = 0;
+    for (; c0 + 2 * XP <= nchunks; c0 += XP) group(c0, std::true_type{});
+    for (; c0 < nchunks; c0 += XP) group(c0, std::false_type{});
     // the small parts, then the waves of a token group in fixed order
 #pragma unroll
     for (int tn = 0; tn < TN; ++tn)
@@ -332,19 +363,19 @@ __global__ void __launch_bounds__(512) route_prefill_kernel(const RouteArgs a, c
             double v = tot[tn][i];
             if (step > 0) v += red[tl * NC + ol];
             if (step < KQ - 1) red[tl * NC + ol] = v;
-            else if (nc + ol < a.NO) lg[tl * a.NOpad + nc + ol] = (float)v;
+            else if (nc + ol < a.NO && t0 + tl < a.T) a.glog[(size_t)(t0 + tl) * a.NO + nc + ol] = (float)v;
           }
       }
       __syncthreads();
     }
   }
-  route_select(a, smem, lg, t0, BT, 8, w, lane);
 }
 
-template <int TG, int TN>
-static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* planes, int plane_rows, size_t smem,
-                                 hipStream_t s) {
-  auto kern = route_prefill_kernel<TG, TN>;
+template <int TG, int TN, bool DEEP = true>
+static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* planes, int plane_rows, hipStream_t s) {
+  constexpr size_t smem = PrefillShape<TG, TN, DEEP>::LDS;
+  static_assert(16 * TG * 16 * TN * sizeof(double) <= smem, "the sums");
+  auto kern = route_prefill_kernel<TG, TN, DEEP>;
   static std::atomic<unsigned long long> allowed{0};
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), 160 * 1024, allowed);
   if (e != hipSuccess) return e;
@@ -359,16 +390,22 @@ static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* plan
 // they were a chain of up to 16 memory latencies, most of the 9 to 14 us this kernel took.
 constexpr int kSplitMax = 16;            // the most partial sums of a logit
 constexpr int kFinishTokens = 4;
+constexpr int kPrefillTokens = 8;
 
+// SUMS: fp64 partial sums in gpart, else finished logits in glog
+template <int BT, bool SUMS>
 __global__ void __launch_bounds__(512) route_finish_kernel(const RouteArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int NW = blockDim.x >> 6;
-  constexpr int BT = kFinishTokens;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t0 = blockIdx.x * BT;
   float* lg = reinterpret_cast<float*>(smem + a.region0);         // [BT][NOpad]
   for (int idx = threadIdx.x; idx < BT * a.NO; idx += blockDim.x) {
     const int tl = idx / a.NO, o = idx % a.NO;
+    if constexpr (!SUMS) {
+      lg[tl * a.NOpad + o] = t0 + tl < a.T ? a.glog[(size_t)(t0 + tl) * a.NO + o] : 0.f;
+      continue;
+    }
     double sum = 0.0;
     if (t0 + tl < a.T) {
       const double* p = a.gpart + (size_t)(t0 + tl) * a.NO + o;
@@ -419,8 +456,10 @@ static int split_most(int T) {
   while (ds * 2 <= kSplitMax && blocks * ds * 2 <= room) ds *= 2;
   return ds;
 }
-constexpr int kPrefillMinT = 8192;       // from here on the bf16 matrix-core form (measured: 96 against
-                                         // 190 us at 16384 tokens, even at 8192, slower below)
+// From here on the bf16 matrix-core form: up to 4096 tokens every compute unit has one workgroup of the fp32 form, beyond
+// some have two.  Whole call, fp32 form -> this: 5000 tokens d = 2048, 27 rows 29 -> 21 us, d = 1024, 136 rows 80 -> 48;
+// 6000 tokens d = 4096, 68 rows 90 -> 50; 4096 tokens 16 -> 23 (27 rows), 46 -> 45 (68 rows, d = 4096).
+constexpr int kPrefillMinT = 4097;
 
 static int tile_cus() {
   static std::atomic<int> known{0};       // (GPUs of one kind: any thread's answer serves)
@@ -437,15 +476,17 @@ static int tile_cus() {
 
 // the bf16 matrix-core form: bf16 tokens, enough of them, whole 128-deep chunks
 static bool prefill_form(const LayerDesc& L, int dtype) {
-  return dtype == MOHGE_BF16 && L.T >= kPrefillMinT && L.d % kPfChunk == 0;
+  return dtype == MOHGE_BF16 && L.T >= kPrefillMinT && L.d % kPfDepth == 0;
 }
+
+static size_t plane_bytes(size_t rows, int d) { return (3 * rows * d * sizeof(uint16_t) + 255) / 256 * 256; }
 
 size_t route_workspace_bytes(const LayerDesc& L, int dtype) {
   if (prefill_form(L, dtype)) {
     // the three bf16 planes of the router rows, rows padded to whole passes of 16 * TN
     const int tiles = (L.Ng + L.Ne + 15) / 16, TNp = tiles >= 5 ? 5 : tiles;
     const size_t rows = (size_t)(tiles + TNp - 1) / TNp * TNp * 16;
-    return (3 * rows * L.d * sizeof(uint16_t) + 255) / 256 * 256;
+    return plane_bytes(rows, L.d) + ((size_t)L.T * (L.Ng + L.Ne) * sizeof(float) + 255) / 256 * 256;
   }
   if (L.T > kSplitMaxT) return 0;
   const int most = L.T <= 256 ? kSplitMax : split_most(L.T);
@@ -472,6 +513,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   const int steps = L.d / 32;
   a.dsplit = 1;
   a.gpart = nullptr;
+  a.glog = nullptr;
   if (ws && L.T <= kSplitMaxT && ws_bytes >= route_workspace_bytes(L, dtype)) {
     const int most = split_most(L.T);
     while (a.dsplit * 2 <= most && NW * a.dsplit * 2 <= steps) a.dsplit *= 2;
@@ -489,29 +531,33 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
                        planes, L.Ng, a.NO, plane_rows, L.d);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t buf = (size_t)2 * 3 * 16 * TNp * 256;
-    const size_t rows_bytes = (size_t)8 * 5 * a.Nepad * sizeof(float);
-    // 64 tokens per workgroup when that still gives every compute unit one, else 32
-    for (int TG = (L.T >= 64 * tile_cus()) ? 4 : 2; TG >= 2; TG -= 2) {
-      const size_t red = (size_t)16 * TG * 16 * TNp * sizeof(double);
-      size_t r0 = buf > rows_bytes ? buf : rows_bytes;
-      if (red > r0) r0 = red;
-      a.region0 = (int)((r0 + 15) / 16 * 16);
-      const size_t smem_p = (size_t)a.region0 + (size_t)16 * TG * a.NOpad * sizeof(float);
-      if (smem_p > 160 * 1024) continue;
+    a.glog = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + plane_bytes(plane_rows, L.d));
+    // 32 tokens per workgroup while every compute unit has at most one, else 64 (in two rounds: 68 rows, d = 4096, 11000
+    // tokens 91 us, in one 61)
+    const int TG = L.T <= 32 * tile_cus() ? 2 : 4;
+    auto logits = [&]() {
       switch (TNp * 2 + (TG == 4)) {
-        case 2: return launch_prefill<2, 1>(a, L.T, planes, plane_rows, smem_p, s);
-        case 3: return launch_prefill<4, 1>(a, L.T, planes, plane_rows, smem_p, s);
-        case 4: return launch_prefill<2, 2>(a, L.T, planes, plane_rows, smem_p, s);
-        case 5: return launch_prefill<4, 2>(a, L.T, planes, plane_rows, smem_p, s);
-        case 6: return launch_prefill<2, 3>(a, L.T, planes, plane_rows, smem_p, s);
-        case 7: return launch_prefill<4, 3>(a, L.T, planes, plane_rows, smem_p, s);
-        case 8: return launch_prefill<2, 4>(a, L.T, planes, plane_rows, smem_p, s);
-        case 9: return launch_prefill<4, 4>(a, L.T, planes, plane_rows, smem_p, s);
-        case 10: return launch_prefill<2, 5>(a, L.T, planes, plane_rows, smem_p, s);
-        default: return launch_prefill<4, 5>(a, L.T, planes, plane_rows, smem_p, s);
+        case 2: return launch_prefill<2, 1>(a, L.T, planes, plane_rows, s);
+        case 3: return launch_prefill<4, 1>(a, L.T, planes, plane_rows, s);
+        case 4: return launch_prefill<2, 2>(a, L.T, planes, plane_rows, s);
+        case 5:
+          if (L.T > 64 * tile_cus()) return launch_prefill<4, 2, false>(a, L.T, planes, plane_rows, s);
+          return launch_prefill<4, 2>(a, L.T, planes, plane_rows, s);
+        case 6: return launch_prefill<2, 3>(a, L.T, planes, plane_rows, s);
+        case 7: return launch_prefill<4, 3>(a, L.T, planes, plane_rows, s);
+        case 8: return launch_prefill<2, 4>(a, L.T, planes, plane_rows, s);
+        case 9: return launch_prefill<4, 4>(a, L.T, planes, plane_rows, s);
+        case 10: return launch_prefill<2, 5>(a, L.T, planes, plane_rows, s);
+        default: return launch_prefill<4, 5>(a, L.T, planes, plane_rows, s);
       }
-    }
+    };
+    e = logits();
+    if (e != hipSuccess) return e;
+    a.region0 = (int)((size_t)NW * 5 * a.Nepad * sizeof(float));
+    const size_t smem_f = (size_t)a.region0 + (size_t)kPrefillTokens * a.NOpad * sizeof(float);
+    hipLaunchKernelGGL((route_finish_kernel<kPrefillTokens, false>), dim3((L.T + kPrefillTokens - 1) / kPrefillTokens),
+                       dim3(64 * NW), smem_f, s, a);
+    return hipGetLastError();
   }
   // Column tiles of 16 router rows per workgroup.  Split form, few tokens: one, and the passes over the router rows side by
   // side: what counts is the length of a wave's chain (one after the other with up to five: d = 4096, 68 rows, 32
@@ -544,7 +590,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
   // (its own LDS, at most 45 KB: the first kernel's partial totals would leave room for one workgroup per compute unit)
   a.region0 = (int)((size_t)NW * 5 * a.Nepad * sizeof(float));
   smem = (size_t)a.region0 + (size_t)kFinishTokens * a.NOpad * sizeof(float);
-  hipLaunchKernelGGL(route_finish_kernel, dim3((L.T + kFinishTokens - 1) / kFinishTokens), block, smem, s, a);
+  hipLaunchKernelGGL((route_finish_kernel<kFinishTokens, true>), dim3((L.T + kFinishTokens - 1) / kFinishTokens), block, smem, s, a);
   return hipGetLastError();
 }
 

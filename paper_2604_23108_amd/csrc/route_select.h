@@ -26,6 +26,7 @@ struct RouteArgs {
   int dsplit;    // > 1: the hidden dimension is also split over grid.y workgroups, which leave
                  //   their fp64 logit sums in gpart; route_finish_kernel adds them and selects
   double* gpart; // [dsplit][T][NO]
+  float* glog;   // prefill form: logits [T][NO]
 };
 
 template <bool BF16>

@@ -5,14 +5,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d", [64, 128, 192, 704, 1344, 2624])
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_route_uneven_slices(d, dtype):
+def _check(d, dtype, ng, n, tokens):
     import paper_2604_23108_amd as M
-    ng, n, kg, ke = 5, 5, 2, 4
+    kg, ke = 2, 4
     gen = torch.Generator(device="cuda").manual_seed(d)
     wg, we = (torch.randn((r, d), generator=gen, device="cuda") * 0.05 for r in (ng, ng * n))
-    for T in (1, 17, 300, 2049, 4100):
+    for T in tokens:
         x = torch.randn((T, d), generator=gen, device="cuda")
         x = x.bfloat16() if dtype == "bf16" else x
         cfg = M.Config(T=T, d=d, n_groups=ng, experts_per_group=n, d_ff=(64,) * ng, k_groups=kg, k_experts=ke,
@@ -36,3 +34,17 @@ def test_route_uneven_slices(d, dtype):
         assert (ei[:, 1:] > ei[:, :-1]).all()
         # gates: fp32 logits to about 1e-7, expf to about an ulp
         assert (gates.double() - sel / sel.sum(1, keepdim=True)).abs().max() <= 1e-6
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 704, 1344, 2624])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_route_uneven_slices(d, dtype):
+    _check(d, dtype, 5, 5, (1, 17, 300, 2049, 4100))
+
+
+@pytest.mark.parametrize("ng,n", [(2, 4), (3, 8), (5, 7), (2, 32), (8, 16)])
+@pytest.mark.parametrize("d", [128, 384, 640, 1152])
+def test_route_many_tokens(d, ng, n):
+    """One to five and more column tiles of router rows, one chunk of the hidden dimension to several groups of them, 32 and 64
+    tokens per workgroup, more workgroups than compute units."""
+    _check(d, "bf16", ng, n, (4097, 8192, 8193, 16400))
