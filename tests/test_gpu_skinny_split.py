@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("counts", [(0, 1, 0, 0), (1, 0, 15, 16), (17, 0, 0, 15), (0, 0, 32, 0)])
-@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448))])
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448)), (2112, (1600, 576))])
 def test_skinny_split_edges(d, d_ff, counts):
     import paper_2604_23108_amd as M
     from gpu_harness import DeviceLayer
@@ -36,7 +36,7 @@ def test_skinny_split_edges(d, d_ff, counts):
 
 
 @pytest.mark.parametrize("counts", [(0, 1, 0, 0), (1, 0, 15, 16), (17, 0, 0, 15)])
-@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448))])
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1088, (192, 448)), (2112, (1600, 576))])
 def test_fp8_split_edges(d, d_ff, counts):
     """The same with FP8 weights (at these sizes the direct form), against the oracle on the dequantised weights."""
     import paper_2604_23108_amd as M
