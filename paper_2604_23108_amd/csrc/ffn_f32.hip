@@ -2,7 +2,10 @@
 // fp32 matrix cores (v_mfma_f32_32x32x2_f32), one launch per projection.
 //
 // What bounds it: the fp32 matrix rate, 256 FLOP per clock and compute unit (a sixteenth of bf16),
-// down to a few rows per expert, where it is the weight stream.  An MFMA keeps a SIMD busy for 64
+// and the vector instructions beside it, which the fp32 MFMA does not run in parallel with: eight of them take 522 clocks of a
+// SIMD, with the 48 additions and conversions that their sums need 790, however many waves there are (a loop of
+// nothing else); so every vector instruction in the main loop counts.
+// Down to a few rows per expert it is the weight stream.  An MFMA keeps a SIMD busy for 64
 // clocks on two operand registers, so operand delivery is never the limit and the tile is chosen for
 // balance: 32 token rows x 64 weight rows (up: 32 W_gate rows and the matching 32 W_up rows), so that
 // partial row blocks cost little and a layer of 3072 routed rows gives every compute unit several
@@ -10,7 +13,7 @@
 // meet in LDS at the end.
 // Measured on 512 tokens, d = 1024, 32 experts of width 256..896, six per token (10.9 GFLOP): both projections
 // take 188 us (58 TFLOP/s of a possible 154; 179 with its sums in fp32 alone, see below), the one-wave-per-output
-// dot products that this replaced 1.42 ms.  At 4096 tokens of a d = 2048 layer it runs at 84 TFLOP/s.
+// dot products that this replaced 1.42 ms.  One 64-bit addition per request's address instead of two: the layer call 203 -> 199.  At 4096 tokens of a d = 2048 layer it runs at 84 TFLOP/s.
 // (With fp32 sums, 64-row tiles were 8 % slower on the first, whose whole tiles divide worse over the compute units,
 // and 6 % faster on the second.)
 //
@@ -130,10 +133,14 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
     }
   }
   const int KT = K / kFK;                                        // K is a multiple of 64
+  // stages are requested in order: running pointers, one vector addition per request
   auto issue = [&](int kt) {
     unsigned char* dst = lds + (kt % kFStages) * kFStage + w * 1024;
 #pragma unroll
-    for (int j = 0; j < kFLoads; ++j) f32_copy16(src[j] + kt * kFK, dst + j * kFW * 1024);
+    for (int j = 0; j < kFLoads; ++j) {
+      f32_copy16(src[j], dst + j * kFW * 1024);
+      src[j] += kFK;
+    }
   };
 #pragma unroll
   for (int kt = 0; kt < kFStages; ++kt)
