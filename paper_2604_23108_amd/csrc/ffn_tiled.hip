@@ -1716,7 +1716,9 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
   if (parts == 3 && use_small_tiles(L, o, false)) {
-    const bool tall = may_be_tall(L);
+    // the down launch alone has nothing else to fill its units: 512 tiles of 128 rows, two per unit, take 16.3 us, 256 tall ones
+    // 20.7 (d = 1024, 32 experts x 146 rows); 1024 of 128 rows 38.8, 512 tall ones 37.1 (64 x 144)
+    const bool tall = may_be_tall(L), tall_dn = tall && (long long)L.Ne * ((L.d + 127) / 128) > up.ncu;
     hipError_t e = hipSuccess;
     if (stages & 1) {
       const long long n = small_grid(L, kUp);
@@ -1725,7 +1727,7 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
     }
     if (e == hipSuccess && (stages & 2)) {
       const long long n = small_grid(L, kDown);
-      e = tall ? launch_small<ffn_small_kernel<kDown, true>>(n, s, dn) : launch_small<ffn_small_kernel<kDown, false>>(n, s, dn);
+      e = tall_dn ? launch_small<ffn_small_kernel<kDown, true>>(n, s, dn) : launch_small<ffn_small_kernel<kDown, false>>(n, s, dn);
     }
     return e;
   }

@@ -66,9 +66,10 @@ FEW_TALL = [129, 192, 191, 64, 130, 161, 65, 257, 128, 193, 150, 320]
 
 
 @pytest.mark.parametrize("counts", [TALL, FEW_TALL], ids=["tall", "few"])
-@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448))])
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448)), (2816, (128, 320))])
 def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
-    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage.)"""
+    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage;
+    d = 2816: enough down tiles for that launch to take tall ones.)"""
     import paper_2604_23108_amd as M
     from paper_2604_23108_amd import bench_binding as BB
     from gpu_harness import DeviceLayer, to_dev
