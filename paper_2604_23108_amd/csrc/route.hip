@@ -66,81 +66,124 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
     const int kbeg = ((int)blockIdx.y * NW + w) * a.kslice, kend = min(kbeg + a.kslice, a.d);
     // The token rows are read exactly once from HBM in small pieces (16 rows x 64 bytes per
     // wave-wide load), so the loop is bound by memory latency unless many loads are in
-    // flight: all token loads of a chunk of up to XS 32-element steps are requested up
+    // flight: all token loads of a chunk of 32-element steps are requested up
     // front and kept packed in registers; the router rows (L2 resident) are requested one
     // step ahead.  The fp32 accumulators are folded into the fp64 totals after every pair of
     // steps (64 elements).
-    constexpr int XS = BF16 ? 16 : 4;
-    typedef typename std::conditional<BF16, uint4, float4>::type xraw_t;
-    constexpr int XR = BF16 ? 1 : 2;                 // raw registers-of-16-bytes per step
-    // NS steps from kc on, without a branch between requests: behind one the compiler waits for everything on its way,
-    // the router rows just requested included.  (Whole call, with a check before every request -> this: d = 2048, 27 rows, 4096
-    // tokens 16.2 -> 14.8 us, 700 10.4 -> 9.7; d = 4096, 68 rows 47.1 -> 45.2; d = 2560, 66 rows, 1500 tokens 26.8 -> 25.4.)
-    auto chunk = [&](int kc, auto NSC) {
-      constexpr int NS = decltype(NSC)::value;
-      xraw_t xraw[TM][NS][XR];
+    if constexpr (!BF16) {
+      // fp32 tokens: four steps at a time, each with a check.  (Whole runs of steps without one, as below, take more
+      // registers here, with two token tiles one workgroup per compute unit instead of two: d = 512, 15 rows,
+      // 32768 tokens 28.2 us, without checks 41.1; d = 4096, 68 rows, 4096 tokens 51.4 and 58.9.)
+      constexpr int XS = 4;
+      for (int kc = kbeg; kc < kend; kc += 32 * XS) {
+        float4 xraw[TM][XS][2];
 #pragma unroll
-      for (int st = 0; st < NS; ++st)
+        for (int st = 0; st < XS; ++st)
+          if (kc + 32 * st < kend) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-          const xraw_t* p = reinterpret_cast<const xraw_t*>(
-              static_cast<const char*>(a.x) + (xrow[tm] + kc + 32 * st + 8 * q) * (BF16 ? 2 : 4));
+            for (int tm = 0; tm < TM; ++tm) {
+              const float4* p = reinterpret_cast<const float4*>(static_cast<const char*>(a.x) +
+                                                                (xrow[tm] + kc + 32 * st + 8 * q) * 4);
+              xraw[tm][st][0] = p[0];
+              xraw[tm][st][1] = p[1];
+            }
+          }
+        float wb[2][TN][8];
 #pragma unroll
-          for (int u = 0; u < XR; ++u) xraw[tm][st][u] = p[u];
+        for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(kc + 8 * q), wb[0][tn]);
+#pragma unroll
+        for (int st = 0; st < XS; ++st) {
+          const int k = kc + 32 * st;
+          if (k < kend) {
+            if (st + 1 < XS && k + 32 < kend) {
+#pragma unroll
+              for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(k + 32 + 8 * q), wb[(st + 1) & 1][tn]);
+            }
+            float xa[TM][8];
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm) {
+              const float4 lo = xraw[tm][st][0], hi = xraw[tm][st][1];
+              xa[tm][0] = lo.x; xa[tm][1] = lo.y; xa[tm][2] = lo.z; xa[tm][3] = lo.w;
+              xa[tm][4] = hi.x; xa[tm][5] = hi.y; xa[tm][6] = hi.z; xa[tm][7] = hi.w;
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+              for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+                  acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[tm][j], wb[st & 1][tn][j], acc[tm][tn], 0, 0, 0);
+            if ((st & 1) || k + 32 >= kend) {
+#pragma unroll
+              for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn) {
+#pragma unroll
+                  for (int i = 0; i < 4; ++i) tot[tm][tn][i] += (double)acc[tm][tn][i];
+                  acc[tm][tn] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+          }
         }
-      float wb[2][TN][8];
+      }
+    } else {
+      // NS steps from kc on, without a branch between requests: behind one the compiler waits for everything on its way,
+      // the router rows just requested included.  (Whole call, with a check before every request -> this: d = 2048, 27 rows, 4096
+      // tokens 16.2 -> 14.8 us, 700 10.4 -> 9.7; d = 4096, 68 rows 47.1 -> 45.2; d = 2560, 66 rows, 1500 tokens 26.8 -> 25.4.)
+      auto chunk = [&](int kc, auto NSC) {
+        constexpr int NS = decltype(NSC)::value;
+        uint4 xraw[TM][NS];
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(kc + 8 * q), wb[0][tn]);
+        for (int st = 0; st < NS; ++st)
 #pragma unroll
-      for (int st = 0; st < NS; ++st) {
-        if (st + 1 < NS) {
+          for (int tm = 0; tm < TM; ++tm)
+            xraw[tm][st] = *reinterpret_cast<const uint4*>(static_cast<const char*>(a.x) + (xrow[tm] + kc + 32 * st + 8 * q) * 2);
+        float wb[2][TN][8];
 #pragma unroll
-          for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(kc + 32 * st + 32 + 8 * q), wb[(st + 1) & 1][tn]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        float xa[TM][8];
+        for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(kc + 8 * q), wb[0][tn]);
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) {
-          if constexpr (BF16) {
-            const uint4 u = xraw[tm][st][0];
+        for (int st = 0; st < NS; ++st) {
+          if (st + 1 < NS) {
+#pragma unroll
+            for (int tn = 0; tn < TN; ++tn) load8<false>(wrow[tn], (size_t)(kc + 32 * st + 32 + 8 * q), wb[(st + 1) & 1][tn]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          float xa[TM][8];
+#pragma unroll
+          for (int tm = 0; tm < TM; ++tm) {
+            const uint4 u = xraw[tm][st];
             xa[tm][0] = __uint_as_float(u.x << 16); xa[tm][1] = __uint_as_float(u.x & 0xffff0000u);
             xa[tm][2] = __uint_as_float(u.y << 16); xa[tm][3] = __uint_as_float(u.y & 0xffff0000u);
             xa[tm][4] = __uint_as_float(u.z << 16); xa[tm][5] = __uint_as_float(u.z & 0xffff0000u);
             xa[tm][6] = __uint_as_float(u.w << 16); xa[tm][7] = __uint_as_float(u.w & 0xffff0000u);
-          } else {
-            const float4 lo = xraw[tm][st][0], hi = xraw[tm][st][XR - 1];
-            xa[tm][0] = lo.x; xa[tm][1] = lo.y; xa[tm][2] = lo.z; xa[tm][3] = lo.w;
-            xa[tm][4] = hi.x; xa[tm][5] = hi.y; xa[tm][6] = hi.z; xa[tm][7] = hi.w;
           }
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+              for (int tn = 0; tn < TN; ++tn)
+                acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[tm][j], wb[st & 1][tn][j], acc[tm][tn], 0, 0, 0);
+          if ((st & 1) || st + 1 == NS) {
+#pragma unroll
+            for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+              for (int tn = 0; tn < TN; ++tn) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tot[tm][tn][i] += (double)acc[tm][tn][i];
+                acc[tm][tn] = f32x4{0.f, 0.f, 0.f, 0.f};
+              }
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-          for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn)
-              acc[tm][tn] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[tm][j], wb[st & 1][tn][j], acc[tm][tn], 0, 0, 0);
-        if ((st & 1) || st + 1 == NS) {
-#pragma unroll
-          for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-            for (int tn = 0; tn < TN; ++tn) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) tot[tm][tn][i] += (double)acc[tm][tn][i];
-              acc[tm][tn] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    int kc = kbeg;
-    for (; kend - kc >= 32 * XS; kc += 32 * XS) chunk(kc, std::integral_constant<int, XS>{});
-    if constexpr (XS == 16) {
+      };
+      int kc = kbeg;
+      for (; kend - kc >= 512; kc += 512) chunk(kc, std::integral_constant<int, 16>{});
       if (kend - kc >= 256) { chunk(kc, std::integral_constant<int, 8>{}); kc += 256; }
       if (kend - kc >= 128) { chunk(kc, std::integral_constant<int, 4>{}); kc += 128; }
+      if (kend - kc >= 64) { chunk(kc, std::integral_constant<int, 2>{}); kc += 64; }
+      if (kend - kc >= 32) chunk(kc, std::integral_constant<int, 1>{});
     }
-    if (kend - kc >= 64) { chunk(kc, std::integral_constant<int, 2>{}); kc += 64; }
-    if (kend - kc >= 32) chunk(kc, std::integral_constant<int, 1>{});
     // Accumulator element i of lane (r, q) is token 4q+i, router row r of the 16x16 tile.
     // Every wave stores its fp64 totals in its own slice; then they are added in wave order.
 #pragma unroll
