@@ -506,11 +506,6 @@ static int split_most(int T) {
   while (ds * 2 <= kSplitMax && blocks * ds * 2 <= room) ds *= 2;
   return ds;
 }
-// From here on the bf16 matrix-core form: up to 4096 tokens every compute unit has one workgroup of the fp32 form, beyond
-// some have two.  Whole call, fp32 form -> this: 5000 tokens d = 2048, 27 rows 29 -> 21 us, d = 1024, 136 rows 80 -> 48;
-// 6000 tokens d = 4096, 68 rows 90 -> 50; 4096 tokens 16 -> 23 (27 rows), 46 -> 45 (68 rows, d = 4096).
-constexpr int kPrefillMinT = 4097;
-
 static int tile_cus() {
   static std::atomic<int> known{0};       // (GPUs of one kind: any thread's answer serves)
   int n = known.load(std::memory_order_relaxed);
@@ -524,17 +519,27 @@ static int tile_cus() {
   return n;
 }
 
-// the bf16 matrix-core form: bf16 tokens, enough of them, whole 128-deep chunks
+// column tiles of 16 router rows: in all, and per pass of the bf16 matrix-core form
+static int router_tiles(const LayerDesc& L) { return (L.Ng + L.Ne + 15) / 16; }
+static int pass_tiles(const LayerDesc& L) { const int t = router_tiles(L); return t >= 5 ? 5 : t; }
+
+// The bf16 matrix-core form: bf16 tokens, enough of them, whole 128-deep chunks.  Up to 4096 tokens every compute unit has one
+// workgroup of the fp32 form; beyond, some have two.  The fp32 form stays up to 8191 tokens where there is little to
+// multiply: with one column tile, and with two of a short reduction.  Whole call in us, fp32 form / this, 4097 and 8191
+// tokens: one tile, d = 128 6.4 / 11.6 and 7.3 / 11.5, d = 4096 20 / 23 and 25 / 31; two tiles (27 rows), d = 256 12.6 / 13.1 and
+// 13.6 / 14.7, d = 512 14.7 / 14.3 and 16.1 / 16.2, d = 4096 39.5 / 28 and 45.5 / 35; 68 rows, d = 1024 32.5 / 23 and 34.5 / 26.
 static bool prefill_form(const LayerDesc& L, int dtype) {
-  return dtype == MOHGE_BF16 && L.T >= kPrefillMinT && L.d % kPfDepth == 0;
+  if (dtype != MOHGE_BF16 || L.T <= 4096 || L.d % kPfDepth != 0) return false;
+  const int tiles = router_tiles(L);
+  return L.T >= 8192 || tiles > 2 || (tiles == 2 && L.d >= 512);
 }
 
 static size_t plane_bytes(size_t rows, int d) { return (3 * rows * d * sizeof(uint16_t) + 255) / 256 * 256; }
 
 size_t route_workspace_bytes(const LayerDesc& L, int dtype) {
   if (prefill_form(L, dtype)) {
-    // the three bf16 planes of the router rows, rows padded to whole passes of 16 * TN
-    const int tiles = (L.Ng + L.Ne + 15) / 16, TNp = tiles >= 5 ? 5 : tiles;
+    // the three bf16 planes of the router rows, rows padded to whole passes of 16 * TN, and the logits
+    const int tiles = router_tiles(L), TNp = pass_tiles(L);
     const size_t rows = (size_t)(tiles + TNp - 1) / TNp * TNp * 16;
     return plane_bytes(rows, L.d) + ((size_t)L.T * (L.Ng + L.Ne) * sizeof(float) + 255) / 256 * 256;
   }
@@ -570,10 +575,10 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
     if (a.dsplit > 1) a.gpart = static_cast<double*>(ws);
   }
   a.kslice = 32 * ((steps + NW * a.dsplit - 1) / (NW * a.dsplit));
-  const int tiles = (a.NO + 15) / 16;
+  const int tiles = router_tiles(L);
   // many bf16 tokens and a workspace for the split router rows: the bf16 matrix-core form
   if (prefill_form(L, dtype) && ws && ws_bytes >= route_workspace_bytes(L, dtype)) {
-    const int TNp = tiles >= 5 ? 5 : tiles;                       // column tiles per pass
+    const int TNp = pass_tiles(L);
     const int plane_rows = (tiles + TNp - 1) / TNp * TNp * 16;
     uint16_t* planes = static_cast<uint16_t*>(ws);
     const long long quads = (long long)plane_rows * (L.d / 4);
