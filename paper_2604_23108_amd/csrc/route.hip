@@ -234,7 +234,8 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
 // tiles: more would not fit the registers); wider routers make several passes over the token rows.
 // The logits go to the workspace and a second kernel selects, one wave per token: inside this one, with two waves per SIMD, the
 // selection of a workgroup's 64 tokens took as long as a pass (d = 1024, 136 rows, 12000 tokens: 119 us for the call with
-// it, 93 without).
+// it, 93 without).  SEL: it selects all the same, which saves the second kernel and the logits' way through memory.  That
+// is faster where the reduction is short or two workgroups fit a compute unit: see prefill_plan.
 // Bound by the planes, which every compute unit reads from L2 (1.9 MB at 68 rows, d = 4096) and its waves from LDS.
 // ---------------------------------------------------------------------------------------
 typedef __bf16 rbf16x8 __attribute__((ext_vector_type(8)));
@@ -243,12 +244,11 @@ constexpr int kPfDepth = 128;            // the hidden size is a multiple of it
 
 // Hidden elements per chunk and chunks in LDS: four where they fit, so that several are on their way while one is used.  (One
 // workgroup per compute unit has all of its LDS.  Two chunks: 68 router rows, d = 4096, 16384 tokens 80 us for the call, now 67.)
-// Not DEEP: two chunks and registers for two workgroups per compute unit, where there are more of them than units and two would
-// otherwise fit (27 rows, d = 2048, 32768 tokens: 46 us, one workgroup per unit 60).
-template <int TG, int TN, bool DEEP>
+// SEL (up to two column tiles, or three with 32 tokens): two chunks, registers and LDS for two workgroups per compute unit.
+template <int TG, int TN, bool SEL>
 struct PrefillShape {
-  static constexpr int CH = TG == 4 && TN >= 4 ? 64 : 128;
-  static constexpr int NB = DEEP && 4 * 3 * 16 * TN * CH * 2 <= 150 * 1024 ? 4 : 2;
+  static constexpr int CH = !SEL && TG == 4 && TN >= 4 ? 64 : 128;
+  static constexpr int NB = !SEL && 4 * 3 * 16 * TN * CH * 2 <= 150 * 1024 ? 4 : 2;
   static constexpr int LDS = NB * 3 * 16 * TN * CH * 2;
 };
 
@@ -278,12 +278,12 @@ __global__ void __launch_bounds__(256) route_split_kernel(const float* __restric
   *reinterpret_cast<uint2*>(planes + 2 * plane + at) = make_uint2((lo[0] >> 16) | lo[1], (lo[2] >> 16) | lo[3]);
 }
 
-template <int TG, int TN, bool DEEP>
-__global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const RouteArgs a, const uint16_t* __restrict__ planes,
+template <int TG, int TN, bool SEL>
+__global__ void __launch_bounds__(512, SEL ? 4 : 2) route_prefill_kernel(const RouteArgs a, const uint16_t* __restrict__ planes,
                                                             int plane_rows) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr int KQ = 8 / TG;                 // waves along the hidden dimension
-  constexpr int CH = PrefillShape<TG, TN, DEEP>::CH, NB = PrefillShape<TG, TN, DEEP>::NB;
+  constexpr int CH = PrefillShape<TG, TN, SEL>::CH, NB = PrefillShape<TG, TN, SEL>::NB;
   constexpr int KS = CH / 32 / KQ;           // 32-deep MFMA steps of a wave per chunk
   constexpr int BT = 16 * TG, NC = 16 * TN;
   constexpr int ROW = CH * 2, PLANE = NC * ROW, BUF = 3 * PLANE;
@@ -297,6 +297,7 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
   const int r = lane & 15, q = lane >> 4;
   const int t0 = blockIdx.x * BT;
   double* red = reinterpret_cast<double*>(smem);                  // [BT][NC], after the chunk loop
+  float* lg = reinterpret_cast<float*>(smem + a.region0);         // SEL: [BT][NOpad]
   const int nchunks = a.d / CH;
 
   const int tok = t0 + tg * 16 + r;
@@ -315,16 +316,20 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
     }
     // copy idx (wave-uniform) of a chunk: plane idx / (NC/RPC), rows RPC*(idx % (NC/RPC)) .. of the
     // pass; lane l fills row l/PPR, physical piece l%PPR, which holds logical piece (l%PPR) ^ (row % PPR)
+    auto copy_one = [&](int c, int b, int idx) {
+      const int p = idx / (NC / RPC), row = RPC * (idx % (NC / RPC)) + lane / PPR;
+      const int piece = (lane % PPR) ^ (row % PPR);
+      const uint16_t* src = planes + p * plane_elems + (size_t)(nc + row) * a.d + (size_t)c * CH + piece * 8;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                       (__attribute__((address_space(3))) void*)(smem + b * BUF + idx * 1024),
+                                       16, 0, 0);
+    };
     auto copy_w = [&](int c, int b) {
+      if constexpr (SEL) {               // (unrolled, its addresses would take the second workgroup's registers)
+        for (int idx = w; idx < NCOPY; idx += 8) copy_one(c, b, idx);
+      } else {
 #pragma unroll
-      for (int i = 0; i < WCOPY; ++i) {
-        const int idx = min(w + 8 * i, NCOPY - 1);
-        const int p = idx / (NC / RPC), row = RPC * (idx % (NC / RPC)) + lane / PPR;
-        const int piece = (lane % PPR) ^ (row % PPR);
-        const uint16_t* src = planes + p * plane_elems + (size_t)(nc + row) * a.d + (size_t)c * CH + piece * 8;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                         (__attribute__((address_space(3))) void*)(smem + b * BUF + idx * 1024),
-                                         16, 0, 0);
+        for (int i = 0; i < WCOPY; ++i) copy_one(c, b, min(w + 8 * i, NCOPY - 1));
       }
     };
     uint4 xr[XP][KS];
@@ -354,15 +359,21 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
       for (int u = 0; u < XP; ++u) {
         const int c = c0 + u;
         if (full || c < nchunks) {
+          rbf16x8 xa[KS];
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) xa[ks] = __builtin_bit_cast(rbf16x8, xr[u][ks]);
           // a later chunk's planes into the buffer that the previous chunk had (nobody reads it any more:
-          // barrier at its end); behind the products the token fragments of a later chunk
+          // barrier at its end), then the token fragments of a later chunk
           if (full || c + NB - 1 < nchunks) copy_w(c + NB - 1, (u + NB - 1) % NB);
           __builtin_amdgcn_sched_barrier(0);
+          if constexpr (SEL) {
+            if (c + XP < nchunks) load_x(c + XP, u);
+            __builtin_amdgcn_sched_barrier(0);
+          }
           const unsigned char* fb = smem + (u % NB) * BUF + r * ROW;
 #pragma unroll
           for (int ks = 0; ks < KS; ++ks) {
             const int piece = ((kq * KS + ks) * 4 + q) ^ (r % PPR);
-            const rbf16x8 xa = __builtin_bit_cast(rbf16x8, xr[u][ks]);
             f32x4 h[TN];
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
@@ -370,9 +381,9 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
               const rbf16x8 bh = *reinterpret_cast<const rbf16x8*>(f);
               const rbf16x8 bm = *reinterpret_cast<const rbf16x8*>(f + PLANE);
               const rbf16x8 bl = *reinterpret_cast<const rbf16x8*>(f + 2 * PLANE);
-              h[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bh, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bm, acc_l[tn], 0, 0, 0);
-              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, bl, acc_l[tn], 0, 0, 0);
+              h[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bh, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bm, acc_l[tn], 0, 0, 0);
+              acc_l[tn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[ks], bl, acc_l[tn], 0, 0, 0);
             }
             // the large part goes into the fp64 totals at once.  (Every second time, which of two sums are added in fp32 first depends
             // on the tokens per workgroup: error 3.9e-8 with 32 and 5.0e-8 with 64 at d = 128, 4.9e-8 with both from d = 1024 on.  Time
@@ -382,11 +393,13 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
 #pragma unroll
               for (int i = 0; i < 4; ++i) tot[tn][i] += (double)h[tn][i];
           }
-          // (behind the last use of the registers: in front of it the compiler copies them, once all of them have landed)
+          // (not SEL: behind the last use of the registers; in front of it the compiler copies them, once all of them have landed)
           __builtin_amdgcn_sched_barrier(0);
-          if (full || c + XP < nchunks) load_x(c + XP, u);
+          if constexpr (!SEL)
+            if (full || c + XP < nchunks) load_x(c + XP, u);
           // my pieces of the next chunk's planes have landed when at most what was issued after them is outstanding
-          // (loads complete in order): the planes of NB - 2 further chunks and the token loads of NB - 1
+          // (loads complete in order): the planes of NB - 2 further chunks and the token loads of NB - 1 (SEL: NB is 2, whatever
+          // a wave's number of copies)
           if (full || c + XP < nchunks) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NB - 2) * WCOPY + (NB - 1) * KS) : "memory");
           else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
           __builtin_amdgcn_s_barrier();
@@ -395,7 +408,8 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
       }
     };
     int c0 = 0;
-    for (; c0 + 2 * XP <= nchunks; c0 += XP) group(c0, std::true_type{});
+    if constexpr (!SEL)
+      for (; c0 + 2 * XP <= nchunks; c0 += XP) group(c0, std::true_type{});
     for (; c0 < nchunks; c0 += XP) group(c0, std::false_type{});
     // the small parts, then the waves of a token group in fixed order
 #pragma unroll
@@ -413,24 +427,34 @@ __global__ void __launch_bounds__(512, DEEP ? 2 : 4) route_prefill_kernel(const 
             double v = tot[tn][i];
             if (step > 0) v += red[tl * NC + ol];
             if (step < KQ - 1) red[tl * NC + ol] = v;
-            else if (nc + ol < a.NO && t0 + tl < a.T) a.glog[(size_t)(t0 + tl) * a.NO + nc + ol] = (float)v;
+            else if (nc + ol < a.NO) {
+              if constexpr (SEL) lg[tl * a.NOpad + nc + ol] = (float)v;
+              else if (t0 + tl < a.T) a.glog[(size_t)(t0 + tl) * a.NO + nc + ol] = (float)v;
+            }
           }
       }
       __syncthreads();
     }
   }
+  if constexpr (SEL) route_select(a, smem, lg, t0, BT, 8, w, lane);
 }
 
-template <int TG, int TN, bool DEEP = true>
-static hipError_t launch_prefill(const RouteArgs& a, int T, const uint16_t* planes, int plane_rows, hipStream_t s) {
-  constexpr size_t smem = PrefillShape<TG, TN, DEEP>::LDS;
-  static_assert(16 * TG * 16 * TN * sizeof(double) <= smem, "the sums");
-  auto kern = route_prefill_kernel<TG, TN, DEEP>;
+template <int TG, int TN, bool SEL>
+static hipError_t launch_prefill(RouteArgs a, const uint16_t* planes, int plane_rows, hipStream_t s) {
+  typedef PrefillShape<TG, TN, SEL> Shape;
+  static_assert(16 * TG * 16 * TN * sizeof(double) <= Shape::LDS, "the sums");
+  size_t smem = Shape::LDS;
+  if (SEL) {
+    static_assert(8 * 5 * 64 * sizeof(float) <= Shape::LDS, "the selection's rows: three tiles hold at most 47 experts");
+    a.region0 = (int)smem;
+    smem += (size_t)16 * TG * a.NOpad * sizeof(float);            // (79 KB at most)
+  }
+  auto kern = route_prefill_kernel<TG, TN, SEL>;
   static std::atomic<unsigned long long> allowed{0};
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), 160 * 1024, allowed);
   if (e != hipSuccess) return e;
   constexpr int BT = 16 * TG;
-  hipLaunchKernelGGL(kern, dim3((T + BT - 1) / BT), dim3(512), smem, s, a, planes, plane_rows);
+  hipLaunchKernelGGL(kern, dim3((a.T + BT - 1) / BT), dim3(512), smem, s, a, planes, plane_rows);
   return hipGetLastError();
 }
 
@@ -446,7 +470,7 @@ constexpr int kPrefillTokens = 8;
 template <int BT, bool SUMS>
 __global__ void __launch_bounds__(512) route_finish_kernel(const RouteArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int NW = blockDim.x >> 6;
+  constexpr int NW = 8;                    // (a constant: 41 registers instead of 98, the waves of four workgroups per compute unit)
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t0 = blockIdx.x * BT;
   float* lg = reinterpret_cast<float*>(smem + a.region0);         // [BT][NOpad]
@@ -534,6 +558,26 @@ static bool prefill_form(const LayerDesc& L, int dtype) {
   return L.T >= 8192 || tiles > 2 || (tiles == 2 && L.d >= 512);
 }
 
+// How the bf16 matrix-core form runs: token groups of 16 per workgroup, and whether it selects itself.  Whole call in us,
+// itself / with the second kernel, tokens per workgroup as chosen; 32 and 64 tokens per compute unit are whole rounds:
+//   more than 64 per unit: itself with 64 tokens where two workgroups share a unit, up to two tiles (32768 tokens: 10 rows,
+//     d = 128 20.5 / 24, d = 2048 38.6 / 44; 27 rows 24 / 30, 46 / 55), else the second kernel (68 rows, d = 1024 80 / 63)
+//   32 to 64: one tile itself, with 32 tokens (12000 tokens: d = 128 13.1 / 14.6, d = 2048 23.2 / 24.1), unless d is large (d = 4096
+//     39 / 35); two tiles in the last quarter, where the second kernel has the most to do (d = 1024: 12000 tokens 22.5 / 22.1, 16384
+//     22.9 / 24.6; d = 2048 30.9 / 30.9); three while the reduction is short (16384 tokens: d = 128 16.6 / 19.6, d = 512
+//     21.3 / 23.1, d = 1024 26.4 / 26.7, 12000 tokens 26 / 24); more: the second kernel (68 rows, 16384 tokens, d = 128 29 / 25)
+//   up to 32: one tile itself (8192 tokens, d = 128 11.5 / 13.2); two and three while the reduction is short (8192 tokens, 40 rows:
+//     d = 128 14.0 / 15.3, d = 512 17.1 / 17.6, d = 1024 20.6 / 20.2); more: the second kernel (68 rows, d = 128 18.4 / 18.8,
+//     d = 1024 28.4 / 26.0; 4097 tokens 18.3 / 15.8)
+struct PrefillPlan { int tg; bool sel; };
+static PrefillPlan prefill_plan(const LayerDesc& L, int cus) {
+  const int tn = pass_tiles(L);
+  if (L.T > 64ll * cus) return {4, tn <= 2};
+  if (L.T <= 32ll * cus) return {2, tn == 1 || (tn <= 3 && 16ll * L.d <= L.T)};
+  if (tn == 1 ? L.d < 4096 : tn == 2 ? L.T > 48ll * cus && L.d < 2048 : tn == 3 && 20ll * L.d <= L.T) return {2, true};
+  return {4, false};
+}
+
 static size_t plane_bytes(size_t rows, int d) { return (3 * rows * d * sizeof(uint16_t) + 255) / 256 * 256; }
 
 size_t route_workspace_bytes(const LayerDesc& L, int dtype) {
@@ -587,27 +631,31 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     a.glog = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + plane_bytes(plane_rows, L.d));
-    // 32 tokens per workgroup while every compute unit has at most one, else 64 (in two rounds: 68 rows, d = 4096, 11000
-    // tokens 91 us, in one 61)
-    const int TG = L.T <= 32 * tile_cus() ? 2 : 4;
+    const PrefillPlan plan = prefill_plan(L, tile_cus());
     auto logits = [&]() {
-      switch (TNp * 2 + (TG == 4)) {
-        case 2: return launch_prefill<2, 1>(a, L.T, planes, plane_rows, s);
-        case 3: return launch_prefill<4, 1>(a, L.T, planes, plane_rows, s);
-        case 4: return launch_prefill<2, 2>(a, L.T, planes, plane_rows, s);
-        case 5:
-          if (L.T > 64 * tile_cus()) return launch_prefill<4, 2, false>(a, L.T, planes, plane_rows, s);
-          return launch_prefill<4, 2>(a, L.T, planes, plane_rows, s);
-        case 6: return launch_prefill<2, 3>(a, L.T, planes, plane_rows, s);
-        case 7: return launch_prefill<4, 3>(a, L.T, planes, plane_rows, s);
-        case 8: return launch_prefill<2, 4>(a, L.T, planes, plane_rows, s);
-        case 9: return launch_prefill<4, 4>(a, L.T, planes, plane_rows, s);
-        case 10: return launch_prefill<2, 5>(a, L.T, planes, plane_rows, s);
-        default: return launch_prefill<4, 5>(a, L.T, planes, plane_rows, s);
+      if (plan.sel) {
+        switch (TNp * 2 + (plan.tg == 4)) {
+          case 2: return launch_prefill<2, 1, true>(a, planes, plane_rows, s);
+          case 3: return launch_prefill<4, 1, true>(a, planes, plane_rows, s);
+          case 4: return launch_prefill<2, 2, true>(a, planes, plane_rows, s);
+          case 5: return launch_prefill<4, 2, true>(a, planes, plane_rows, s);
+          default: return launch_prefill<2, 3, true>(a, planes, plane_rows, s);
+        }
+      }
+      switch (TNp * 2 + (plan.tg == 4)) {
+        case 3: return launch_prefill<4, 1, false>(a, planes, plane_rows, s);
+        case 4: return launch_prefill<2, 2, false>(a, planes, plane_rows, s);
+        case 5: return launch_prefill<4, 2, false>(a, planes, plane_rows, s);
+        case 6: return launch_prefill<2, 3, false>(a, planes, plane_rows, s);
+        case 7: return launch_prefill<4, 3, false>(a, planes, plane_rows, s);
+        case 8: return launch_prefill<2, 4, false>(a, planes, plane_rows, s);
+        case 9: return launch_prefill<4, 4, false>(a, planes, plane_rows, s);
+        case 10: return launch_prefill<2, 5, false>(a, planes, plane_rows, s);
+        default: return launch_prefill<4, 5, false>(a, planes, plane_rows, s);
       }
     };
     e = logits();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || plan.sel) return e;
     a.region0 = (int)((size_t)NW * 5 * a.Nepad * sizeof(float));
     const size_t smem_f = (size_t)a.region0 + (size_t)kPrefillTokens * a.NOpad * sizeof(float);
     hipLaunchKernelGGL((route_finish_kernel<kPrefillTokens, false>), dim3((L.T + kPrefillTokens - 1) / kPrefillTokens),

@@ -42,9 +42,15 @@ def test_route_uneven_slices(d, dtype):
     _check(d, dtype, 5, 5, (1, 17, 300, 2049, 4100))
 
 
-@pytest.mark.parametrize("ng,n", [(2, 4), (3, 8), (5, 7), (2, 32), (8, 16)])
+@pytest.mark.parametrize("ng,n", [(2, 4), (3, 8), (5, 7), (4, 12), (2, 32), (8, 16)])
 @pytest.mark.parametrize("d", [128, 384, 640, 1152])
 def test_route_many_tokens(d, ng, n):
     """One to five and more column tiles of router rows, one chunk of the hidden dimension to several groups of them, 32 and 64
-    tokens per workgroup, more workgroups than compute units."""
-    _check(d, "bf16", ng, n, (4097, 8192, 8193, 16400))
+    tokens per workgroup, more workgroups than compute units; selection inside the logits kernel and in a second one."""
+    _check(d, "bf16", ng, n, (4097, 8192, 8193, 12800, 16400))
+
+
+@pytest.mark.parametrize("ng,n", [(2, 4), (3, 8), (5, 7)])
+def test_route_many_tokens_deep(ng, n):
+    """Long reductions, where one to three column tiles go to a second kernel too."""
+    _check(4096, "bf16", ng, n, (4097, 8193, 16400))

@@ -41,3 +41,12 @@ def test_nothing_that_is_launched_spills(kernels):
             for tn in tns:
                 (_, spilled), = _of(kernels, rf"route_kernelILb{dtype}ELi{tm}ELi{tn}E")
                 assert spilled == 0, (dtype, tm, tn)
+
+
+def test_prefill_kernels_that_select_leave_room_for_a_second_workgroup(kernels):
+    selecting = _of(kernels, r"route_prefill_kernelILi[24]ELi[123]ELb1E")
+    assert len(selecting) == 5
+    for regs, spilled in selecting:
+        assert regs <= 128 and spilled == 0
+    for _, spilled in _of(kernels, r"route_prefill_kernel"):
+        assert spilled == 0
