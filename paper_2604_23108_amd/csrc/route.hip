@@ -266,6 +266,11 @@ __global__ void __launch_bounds__(256) route_split_kernel(const float* __restric
   uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if (!__builtin_isfinite(f[i])) {                         // as it is (the differences below would be NaN)
+      hi[i] = __builtin_isnan(f[i]) ? 0x7fc00000u : __float_as_uint(f[i]);
+      mid[i] = lo[i] = 0u;
+      continue;
+    }
     hi[i] = __float_as_uint(f[i]) & 0xffff0000u;
     const float r1 = f[i] - __uint_as_float(hi[i]);          // exact
     mid[i] = __float_as_uint(r1) & 0xffff0000u;

@@ -54,3 +54,38 @@ def test_route_many_tokens(d, ng, n):
 def test_route_many_tokens_deep(ng, n):
     """Long reductions, where one to three column tiles go to a second kernel too."""
     _check(4096, "bf16", ng, n, (4097, 8193, 16400))
+
+
+@pytest.mark.parametrize("T", [300, 4100, 8200])
+@pytest.mark.parametrize("sign", [-1, 1])
+def test_route_infinite_weight(T, sign):
+    """A router weight of -inf times positive elements is a logit of -inf, in every form: the expert is as if its bias were -inf.
+    (+inf: the group's softmax is NaN, as it is in the fp32 form, and every id is still one of an expert.)"""
+    import paper_2604_23108_amd as M
+    d, ng, n, kg, ke = 256, 8, 4, 3, 6
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    wg, we = (torch.randn((r, d), generator=gen, device="cuda") * 0.1 for r in (ng, ng * n))
+    x = torch.randn((T, d), generator=gen, device="cuda")
+    x[:, 5] = x[:, 5].abs() + 0.5
+    x = x.bfloat16()
+    cfg = M.Config(T=T, d=d, n_groups=ng, experts_per_group=n, d_ff=(64,) * ng, k_groups=kg, k_experts=ke,
+                   select_mode=M.SELECT_GLOBAL, dtype=M.BF16)
+    size = M.mohge_workspace_size(cfg, M.CALL_ROUTE)
+
+    def call(w, bias):
+        i32 = dict(dtype=torch.int32, device="cuda")
+        f32 = dict(dtype=torch.float32, device="cuda")
+        out = (torch.full((T, kg), -1, **i32), torch.full((T, ke), -1, **i32), torch.zeros((T, ke), **f32),
+               torch.zeros((T, ng), **f32), torch.zeros((T, ng * n), **f32))
+        M.mohge_route(cfg, x, wg, w, bias, *out, torch.empty(size, dtype=torch.uint8, device="cuda") if size else None)
+        return out
+
+    inf = float("inf") * sign
+    weight, bias = we.clone(), torch.zeros(ng * n, device="cuda")
+    weight[13, 5], bias[13] = inf, inf
+    got, want = call(weight, None), call(we, bias)
+    assert ((got[1] >= 0) & (got[1] < ng * n)).all() and ((got[0] >= 0) & (got[0] < ng)).all()
+    for a, b in zip(got, want):
+        assert torch.equal(torch.nan_to_num(a.float(), nan=-7.0), torch.nan_to_num(b.float(), nan=-7.0))
+    if sign < 0:
+        assert not (got[1] == 13).any() and all(torch.isfinite(t.float()).all() for t in got)
