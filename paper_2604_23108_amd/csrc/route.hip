@@ -513,12 +513,12 @@ static hipError_t launch_one(const RouteArgs& a, dim3 grid, dim3 block, size_t s
 template <bool BF16, int TM>
 static hipError_t launch_tn(const RouteArgs& a, int TN, dim3 grid, dim3 block, size_t smem,
                             hipStream_t s) {
-  switch (TN) {
-    case 1: return launch_one<BF16, TM, 1>(a, grid, block, smem, s);
-    case 2: return launch_one<BF16, TM, 2>(a, grid, block, smem, s);
-    case 3: return launch_one<BF16, TM, 3>(a, grid, block, smem, s);
-    default: return launch_one<BF16, TM, 5>(a, grid, block, smem, s);
+  if (TN == 1) return launch_one<BF16, TM, 1>(a, grid, block, smem, s);
+  if constexpr (TM == 1) {                       // (two token tiles take at most two of router rows)
+    if (TN == 3) return launch_one<BF16, TM, 3>(a, grid, block, smem, s);
+    if (TN == 5) return launch_one<BF16, TM, 5>(a, grid, block, smem, s);
   }
+  return launch_one<BF16, TM, 2>(a, grid, block, smem, s);
 }
 
 // Split form: used for at most kSplitMaxT tokens; the workspace holds split_most() (up to 256 tokens

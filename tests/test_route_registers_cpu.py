@@ -34,13 +34,11 @@ def test_fp32_two_token_tiles_leave_room_for_a_second_workgroup(kernels):
     assert regs <= 128 and spilled == 0
 
 
-def test_nothing_that_is_launched_spills(kernels):
-    """route_kernel takes two token tiles with at most two tiles of router rows."""
-    for dtype in "01":
-        for tm, tns in ((1, (1, 2, 3, 5)), (2, (1, 2))):
-            for tn in tns:
-                (_, spilled), = _of(kernels, rf"route_kernelILb{dtype}ELi{tm}ELi{tn}E")
-                assert spilled == 0, (dtype, tm, tn)
+def test_nothing_spills(kernels):
+    """route_kernel takes two token tiles with at most two tiles of router rows: wider ones would not fit, and are not built."""
+    assert len(_of(kernels, r"route_kernelILb")) == 2 * (4 + 2)
+    for name, (_, spilled) in kernels.items():
+        assert spilled == 0, name
 
 
 def test_prefill_kernels_that_select_leave_room_for_a_second_workgroup(kernels):
@@ -48,5 +46,3 @@ def test_prefill_kernels_that_select_leave_room_for_a_second_workgroup(kernels):
     assert len(selecting) == 5
     for regs, spilled in selecting:
         assert regs <= 128 and spilled == 0
-    for _, spilled in _of(kernels, r"route_prefill_kernel"):
-        assert spilled == 0
