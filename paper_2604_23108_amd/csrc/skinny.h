@@ -78,7 +78,7 @@ __device__ __forceinline__ void skinny_store(const SkinnyArgs& a, const int c0, 
 // the same weight rows and a quarter of the reduction indices each; their partial sums meet in LDS and are
 // added in wave order.  Bound by the weight stream, i.e. by the loads in flight: a wave has the weights
 // and token rows of 128 (64 with more than 16 rows) reduction indices on the way while it multiplies the
-// previous ones, and requests its first weights before it looks up the expert's rows.  The quarters
+// previous ones, and requests its first weights before it looks up the expert's tokens.  The quarters
 // also start a quarter of a row apart, which spreads the waves over the memory channels (rows begin at
 // multiples of the row size, a power of two at the usual hidden sizes).
 // Measured against a wave per 32 weight rows that walked the whole reduction, up + down of d = 4096, 64
@@ -118,25 +118,27 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
       constexpr int NTB = decltype(NTBC)::value;             // token blocks of 16
       constexpr int U = NTB == 1 ? 4 : 2;                    // 32-deep matrix-core steps per request
       constexpr int S = 32 * U;
-      // (the token numbers first: loads return in order)
-      const uint16_t* xp[NTB];
+      // The token numbers are requested before the first weights (loads return in order) and waited for behind them.  (Waited for
+      // in front: d = 1024, 128 experts 158.9 us at 32 tokens, 64 experts 54.9 instead of 53.5 at 8, longer than with the checks.)
+      int row[NTB];
 #pragma unroll
       for (int tb = 0; tb < NTB; ++tb) {
         const int tt = tb0 + 16 * tb + r;
-        const int pos = row0 + (tt < cnt ? tt : 0);          // columns past the count: any of its rows, never stored
-        xp[tb] = a.A + 8 * q;
-        if constexpr (UP) xp[tb] += (a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos) * a.lda;
-        else xp[tb] += (long long)pos * a.lda;
+        row[tb] = row0 + (tt < cnt ? tt : 0);                // columns past the count: any of its rows, never stored
+        if (UP && a.perm) row[tb] = a.perm[row[tb]];
       }
       struct Step { Frag w[2][U], x[NTB][U]; };
       // The first pieces of 32 indices from k on.  No branch between requests, so that the compiler's waits count: behind one
       // it waits for everything on its way, the step just requested included.  (It did, and no step was multiplied before the
-      // next had landed.  Layer calls, that -> this: d = 4096, 64 experts, one token 52 -> 47.5 us, 4 127 -> 117.5, 32 367 -> 351;
-      // d = 2560 32 tokens 280 -> 249; d = 2048 one token 35 -> 31; d = 1024 with two steps per wave 33 -> 28.6 and, 32
-      // tokens, 158 -> 160.)
+      // next had landed.  Layer calls, that -> this: d = 4096, 64 experts, one token 52.7 -> 47.3 us, 4 123.6 -> 112.9, 32 356 -> 341;
+      // d = 2560 32 tokens 273 -> 243; d = 2048 one token 35 -> 33; d = 1024, 128 experts, 32 tokens 157.6 -> 148.5.)
       const uint16_t* pw[2] = {wp[0] + kb, wp[1] + kb};
+      const uint16_t* xp[NTB];
+      auto find_rows = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int tb = 0; tb < NTB; ++tb) xp[tb] += kb;
+        for (int tb = 0; tb < NTB; ++tb) xp[tb] = a.A + 8 * q + kb + (long long)(UP && a.perm ? row[tb] / a.Ke : row[tb]) * a.lda;
+      };
       auto load_w = [&](Step& st, int k, auto NC) {
 #pragma unroll
         for (int u = 0; u < decltype(NC)::value; ++u)
@@ -178,6 +180,7 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
         // two sets of registers in turn: copied from one to the other, they would have to have landed
         Step s0, s1;
         load_w(s0, 0, All{});
+        find_rows();
         load_x(s0, 0, All{});
         for (; rem >= 3 * S; rem -= 2 * S) {
           load_w(s1, S, All{});
@@ -200,6 +203,8 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, const int g, co
           advance(S);
           rem -= S;
         }
+      } else {
+        find_rows();
       }
       if (U > 2 && rem > 0) {
         Step st;
