@@ -1312,34 +1312,71 @@ __device__ __forceinline__ int small_tile_index(int b) {
 }
 
 // Tall tiles.  An expert of 129 to 192 rows as two row tiles has every weight fetched twice, the second time for a few
-// rows.  Where at least three quarters of the experts are of that size they are one tile of 192 rows each (two stages of both
-// operands instead of two and three, the same 80 KB).  Layer calls, two tiles -> one, rows spread evenly: 64 experts x 139 rows, d = 1024
-// 136 -> 131.5 us, 32 x 169 67.5 -> 63.9, 25 x 160, d = 1344 79.2 -> 71.9; training step 64 x 141 500 -> 472, 24 x 167,
-// d = 2048 435 -> 410, 32 x 146 207.7 -> 205.5.  With few such experts, or a remainder of up to 64 rows joined to the last of
+// rows.  Where at least three quarters of the experts are of that size they can be one tile of 192 rows each (two stages of both
+// operands instead of two and three, the same 80 KB).  With few such experts, or a remainder of up to 64 rows joined to the last of
 // several tiles, the longer tiles end later than what they save: 64 x 112 121 -> 125, 24 x 183 skewed 140 -> 145.
 __device__ __forceinline__ bool small_tall(int cnt) { return cnt > SmallTile::BM && cnt <= TallTile::BM; }
 __device__ __forceinline__ int small_row_tiles(int cnt, bool tall) {
   return tall && small_tall(cnt) ? 1 : (cnt + SmallTile::BM - 1) / SmallTile::BM;
 }
 
+// Whether a launch takes them: n_tall experts of that size, n_past above it, `tiles` in the launch with tall ones.  A unit runs two workgroups
+// at a time, and a tall tile is about as long as two of the others, so what counts is how both lists fill whole rounds.  Time
+// of the launch tall / plain, 23 layers of d = 1024 to 4096 with 12 to 80 experts, 145 to 178 rows each (256 units):
+//   up: up to 512 tall tiles 0.73 to 1.03, mean 0.88 (saving the pre-activations 0.81 to 1.06, 0.94); 513 to 800 0.90 to 1.17, mean
+//     1.06 (1.00 to 1.27, 1.13): they begin a third tile per unit; from 832 on 0.88 to 1.09, mean 0.96 (0.97 to 1.06, 1.01), with a
+//     fifth of the experts past 192 rows 1.02 (call 145 -> 148 us)
+//   down, with nothing else in the launch to fill its units: from 512 on with at most a twentieth of the
+//     experts past 192 rows 0.79 to 0.99, mean 0.92, with more 0.84 to 1.09, 1.00; 448 to 511 0.80 to 1.00, 0.94, but
+//     1.01 to 1.14 where the last tile of every expert is half a one (d = 1344) and 0.87 to 1.10 with more past 192; below 0.84 to
+//     1.30, mean 1.08
+//   dH: below 180 0.95 to 1.34, mean 1.09; 180 to 512 0.69 to 0.97, mean 0.83
+//   dX (the weight gradients fill what it leaves idle): 0.90 to 1.03, mean 0.94
+// (The launch after one of the same form finds its operands nearer: down 44 us behind tall up tiles, 46 behind plain ones, tall itself.
+// Whole calls with these lines against no tall tiles: forward 0.81 to 1.01, mean 0.95 (56 sizes), training step 0.92 to 1.00, 0.96
+// (36); tall wherever three quarters of the experts are of their size 0.83 to 1.12, 0.97, and 0.92 to 1.01, 0.97.)
+template <int MODE>
+__device__ __forceinline__ bool tall_pays(const TileArgs& a, int n_tall, int n_past, int tiles) {
+  if (4 * n_tall < 3 * a.Ne) return false;
+  if constexpr (is_up(MODE)) return tiles <= 2 * a.ncu || (20 * n_past <= a.Ne && 4 * tiles >= 13 * a.ncu);
+  if constexpr (MODE == kDown)
+    return 20 * n_past <= a.Ne && (tiles >= 2 * a.ncu || (4 * tiles >= 7 * a.ncu && a.d % TallTile::BN == 0));
+  if constexpr (MODE == kDgradH) return 10 * tiles >= 7 * a.ncu && tiles <= 2 * a.ncu;
+  return true;
+}
+
 // tile t of the list of a token mode; false if there is none.  The same in every lane; called by whole waves.
 template <int MODE, bool TALL>
 __device__ __forceinline__ bool small_token_tile(const TileArgs& a, int t, int lane, TileRec& rec) {
   constexpr int NCPT = is_up(MODE) ? TallTile::BN / 2 : TallTile::BN;
-  int before = 0, n_tall = 0;
-  for (int v0 = TALL && a.Ne > 64 ? 0 : a.Ne; v0 < a.Ne; v0 += 64) {
-    const int v = min(v0 + lane, a.Ne - 1);
-    n_tall += __popcll(__ballot(v0 + lane < a.Ne && small_tall(a.offsets[v + 1] - a.offsets[v])));
+  auto columns = [&](int g) { return ((red_d(MODE) ? a.F[g] : a.d) + NCPT - 1) / NCPT; };
+  int before = 0;
+  bool tall = false;
+  if (TALL && a.Ne > 64) {                         // (up to 64 experts: in the only round below)
+    int n_tall = 0, n_past = 0, tiles = 0;
+    for (int v0 = 0; v0 < a.Ne; v0 += 64) {
+      const int v = min(v0 + lane, a.Ne - 1), cnt = v0 + lane < a.Ne ? a.offsets[v + 1] - a.offsets[v] : 0;
+      n_tall += __popcll(__ballot(small_tall(cnt)));
+      n_past += __popcll(__ballot(cnt > TallTile::BM));
+      tiles += small_row_tiles(cnt, true) * columns(v / a.N);
+    }
+    tall = tall_pays<MODE>(a, n_tall, n_past, __builtin_amdgcn_readlane(wave_incl_scan(tiles), 63));
   }
   for (int v0 = 0; v0 < a.Ne; v0 += 64) {
     const int v = v0 + lane;                       // groups by decreasing width: the longest tiles start first
     const int g = a.order[(v < a.Ne ? v : 0) / a.N], e = g * a.N + (v < a.Ne ? v : 0) % a.N;
     const int lo = a.offsets[e], cnt = v < a.Ne ? a.offsets[e + 1] - lo : 0;
-    const int nt = ((red_d(MODE) ? a.F[g] : a.d) + NCPT - 1) / NCPT;
-    if (TALL && a.Ne <= 64) n_tall = __popcll(__ballot(small_tall(cnt)));
-    const bool tall = TALL && 4 * n_tall >= 3 * a.Ne;
-    const int n = small_row_tiles(cnt, tall) * nt;
-    const int incl = wave_incl_scan(n);
+    const int nt = columns(g);
+    int n = small_row_tiles(cnt, TALL && (a.Ne <= 64 || tall)) * nt;
+    int incl = wave_incl_scan(n);
+    if (TALL && a.Ne <= 64) {
+      tall = tall_pays<MODE>(a, __popcll(__ballot(small_tall(cnt))), __popcll(__ballot(cnt > TallTile::BM)),
+                             __builtin_amdgcn_readlane(incl, 63));
+      if (!tall) {
+        n = small_row_tiles(cnt, false) * nt;
+        incl = wave_incl_scan(n);
+      }
+    }
     const int first = before + incl - n;
     const unsigned long long hit = __ballot(t >= first && t < first + n);
     if (hit) {
@@ -1451,11 +1488,15 @@ __global__ void __launch_bounds__(kSmallThreads, 2) ffn_small_bwd2_kernel(const 
 // ---------------------------------------------------------------------------------------
 // Workgroups of a small-tile list, a multiple of 64 (small_tile_index).  Token modes: the counts are not
 // known here; full row tiles of the widest group plus a partial one per expert that can have rows.
-static long long small_grid(const LayerDesc& L, int mode) {
+static long long small_column_tiles(const LayerDesc& L, int mode, int g) {
   const int cp = is_up(mode) ? SmallTile::BN / 2 : SmallTile::BN;
+  return ((red_d(mode) ? L.F[g] : L.d) + cp - 1) / cp;
+}
+
+static long long small_grid(const LayerDesc& L, int mode) {
   long long n = 0, widest = 0;
   for (int g = 0; g < L.Ng; ++g) {
-    const long long nt = ((red_d(mode) ? L.F[g] : L.d) + cp - 1) / cp;
+    const long long nt = small_column_tiles(L, mode, g);
     n += nt * L.N;
     widest = nt > widest ? nt : widest;
   }
@@ -1464,10 +1505,20 @@ static long long small_grid(const LayerDesc& L, int mode) {
   return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
-// Launches in which tall tiles are looked for: outside, an even spread leaves fewer than three quarters of the experts
-// with 129 to 192 rows (135 and 187 per expert: 1.01 to 1.02 of the time), and the instantiation without them is up to
-// 1 % faster where it finds none.
-static bool may_be_tall(const LayerDesc& L) { return L.P >= 140ll * L.Ne && L.P <= 184ll * L.Ne; }
+// Launches in which tall tiles are looked for.  Outside of these sizes an even spread leaves fewer than three quarters of the
+// experts with 129 to 192 rows (135 and 187 per expert: 1.01 to 1.02 of the time), or tall_pays says no with one tile per expert
+// already; the instantiation without them is up to 1 % faster where it finds none (3 % with more than 64 experts, whose lists take
+// two rounds of counting).
+static bool may_be_tall(const LayerDesc& L, int mode) {
+  if (L.P < 140ll * L.Ne || L.P > 184ll * L.Ne) return false;
+  const long long cus = tile_num_cus();
+  long long n = 0;                                        // tiles with one row tile per expert: the fewest
+  for (int g = 0; g < L.Ng; ++g) n += L.N * small_column_tiles(L, mode, g);
+  if (is_up(mode)) return n <= 2 * cus || n >= 3 * cus;
+  if (mode == kDown) return 4 * n >= 7 * cus;
+  if (mode == kDgradH) return 10 * n >= 6 * cus && n <= 2 * cus;
+  return true;
+}
 
 static long long small_wgrad_grid(const TileArgs& a) {
   long long n = 0;
@@ -1522,13 +1573,12 @@ hipError_t launch_small_bwd(const LayerDesc& L, const TileArgs& dh, const TileAr
   const long long n_dh = small_grid(L, kDgradH);
   // at least one gather workgroup: it writes the row of zeros (a call without tokens still clears the weight gradients)
   const int gather = ga.perm && ga.P > 0 ? (ga.P + kSmallGatherRows - 1) / kSmallGatherRows : 1;
-  const bool tall = may_be_tall(L);
-  hipError_t e = tall ? launch_small<ffn_small_bwd1_kernel<true>>(n_dh + gather, s, dh, ga, (int)n_dh)
-                      : launch_small<ffn_small_bwd1_kernel<false>>(n_dh + gather, s, dh, ga, (int)n_dh);
+  hipError_t e = may_be_tall(L, kDgradH) ? launch_small<ffn_small_bwd1_kernel<true>>(n_dh + gather, s, dh, ga, (int)n_dh)
+                                         : launch_small<ffn_small_bwd1_kernel<false>>(n_dh + gather, s, dh, ga, (int)n_dh);
   if (e != hipSuccess) return e;
   const long long n_dx = small_grid(L, kDgradX), n_w2 = small_wgrad_grid(w2), n_w13 = small_wgrad_grid(w13);
-  return tall ? launch_small<ffn_small_bwd2_kernel<true>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2)
-              : launch_small<ffn_small_bwd2_kernel<false>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
+  return may_be_tall(L, kDgradX) ? launch_small<ffn_small_bwd2_kernel<true>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2)
+                                 : launch_small<ffn_small_bwd2_kernel<false>>(n_dx + n_w2 + n_w13, s, dx, w2, w13, (int)n_dx, (int)n_w2);
 }
 
 void apply_options(TileArgs& t, const FfnOptions& o) {
@@ -1716,18 +1766,16 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
   if (parts == 3 && use_small_tiles(L, o, false)) {
-    // the down launch alone has nothing else to fill its units: 512 tiles of 128 rows, two per unit, take 16.3 us, 256 tall ones
-    // 20.7 (d = 1024, 32 experts x 146 rows); 1024 of 128 rows 38.8, 512 tall ones 37.1 (64 x 144)
-    const bool tall = may_be_tall(L), tall_dn = tall && (long long)L.Ne * ((L.d + 127) / 128) > up.ncu;
     hipError_t e = hipSuccess;
     if (stages & 1) {
       const long long n = small_grid(L, kUp);
+      const bool tall = may_be_tall(L, pre ? kUpSave : kUp);
       if (pre) e = tall ? launch_small<ffn_small_kernel<kUpSave, true>>(n, s, up) : launch_small<ffn_small_kernel<kUpSave, false>>(n, s, up);
       else e = tall ? launch_small<ffn_small_kernel<kUp, true>>(n, s, up) : launch_small<ffn_small_kernel<kUp, false>>(n, s, up);
     }
     if (e == hipSuccess && (stages & 2)) {
       const long long n = small_grid(L, kDown);
-      e = tall_dn ? launch_small<ffn_small_kernel<kDown, true>>(n, s, dn) : launch_small<ffn_small_kernel<kDown, false>>(n, s, dn);
+      e = may_be_tall(L, kDown) ? launch_small<ffn_small_kernel<kDown, true>>(n, s, dn) : launch_small<ffn_small_kernel<kDown, false>>(n, s, dn);
     }
     return e;
   }

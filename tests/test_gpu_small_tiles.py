@@ -65,31 +65,28 @@ TALL = [129, 192, 191, 160, 130, 161, 144, 180, 128, 193, 150, 190]
 FEW_TALL = [129, 192, 191, 64, 130, 161, 65, 257, 128, 193, 150, 320]
 
 
-@pytest.mark.parametrize("counts", [TALL, FEW_TALL], ids=["tall", "few"])
-@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448)), (2816, (128, 320))])
-def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
-    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage;
-    d = 2816: enough down tiles for that launch to take tall ones.)"""
+def _tall_equals_big(d, d_ff, per_group, counts, permuted=True):
     import paper_2604_23108_amd as M
     from paper_2604_23108_amd import bench_binding as BB
     from gpu_harness import DeviceLayer, to_dev
-    T = sum(counts)
-    assert 140 * 12 <= T <= 184 * 12
-    w = Workload("tall_tiles", T=T, d=d, n_groups=2, experts_per_group=6, d_ff=d_ff, k_groups=1, k_experts=1, seed=47,
+    T, ne = sum(counts), len(counts)
+    assert 140 * ne <= T <= 184 * ne
+    w = Workload("tall_tiles", T=T, d=d, n_groups=2, experts_per_group=per_group, d_ff=d_ff, k_groups=1, k_experts=1, seed=47,
                  training=True)
     inp = generate(w)
     dl = DeviceLayer(w, inp, backward=True, guard=True)
     L = dl.layer
-    eidx = np.random.default_rng(6).permutation(np.repeat(np.arange(12), counts)).astype(np.int32).reshape(T, 1)
+    eidx = np.random.default_rng(6).permutation(np.repeat(np.arange(ne), counts)).astype(np.int32).reshape(T, 1)
     M.mohge_permute(dl.cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None,
                     L.ws_permute)
     L.dy_perm.copy_(to_dev(inp.dy, True)[L.perm.long()])
+    x, perm = (dl.x, L.perm) if permuted else (dl.x[L.perm.long()].contiguous(), None)
     outs = []
     for small in (1, 0):
         for t in [L.y_perm, L.dx_perm, *L.dw13, *L.dw2]:
             t.fill_(float("nan"))
-        print(f"[tall tiles] d={d} d_ff={d_ff} small={small}", flush=True)
-        args, o = (dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2), BB.FfnOptions(small_tiles=small)
+        print(f"[tall tiles] d={d} d_ff={d_ff} experts={ne} permuted={permuted} small={small}", flush=True)
+        args, o = (dl.cfg, x, perm, L.offsets, L.w13, L.w2), BB.FfnOptions(small_tiles=small)
         BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn, o)
         y = L.y_perm.clone()
         BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved, o)
@@ -99,6 +96,34 @@ def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
         outs.append([t.clone() for t in [y, L.y_perm, L.dx_perm, *L.dw13, *L.dw2]])
     for a, b in zip(*outs):
         assert torch.isfinite(a.float()).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("counts", [TALL, FEW_TALL], ids=["tall", "few"])
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448)), (2816, (128, 320))])
+def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
+    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage.)  Of the
+    forward launches the up one takes tall tiles here, of the backward ones dX."""
+    _tall_equals_big(d, d_ff, 6, counts)
+
+
+def _tiles(counts, columns, tall):
+    """row tiles of 128, or one of 192 for 129 to 192 rows, times the column tiles of the expert's group"""
+    half = len(counts) // 2
+    return sum((1 if tall and 128 < c <= 192 else -(-c // 128)) * columns[i // half] for i, c in enumerate(counts))
+
+
+@pytest.mark.parametrize("permuted", [True, False])
+@pytest.mark.parametrize("per_group,d,d_ff", [(36, 1024, (384, 320)), (33, 1088, (384, 448)), (32, 1024, (320, 448))])
+def test_tall_tiles_in_every_launch(per_group, d, d_ff, permuted):
+    """Most of 64 to 72 experts tall, the others in the first and the last ones of the list: with more than 64 of them the list
+    has two rounds.  Sizes at which every launch takes tall tiles (256 compute units); rows given in expert order as well."""
+    rng = np.random.default_rng(per_group)
+    counts = [int(c) for c in rng.integers(129, 193, 2 * per_group)]
+    counts[0], counts[1], counts[per_group - 1], counts[-2], counts[-1] = 129, 0, 192, 257, 64
+    for columns, lo, hi in (([-(-f // 64) for f in d_ff], 0, 512), ([-(-d // 128)] * 2, 512, 1 << 30), ([-(-f // 128) for f in d_ff], 180, 512)):
+        assert lo <= _tiles(counts, columns, True) <= hi
+    assert 20 * sum(c > 192 for c in counts) <= len(counts)
+    _tall_equals_big(d, d_ff, per_group, counts, permuted)
 
 
 @pytest.mark.parametrize("forward,backward", [(1, 0), (0, 1)])
