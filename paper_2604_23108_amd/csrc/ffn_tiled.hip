@@ -1320,28 +1320,31 @@ __device__ __forceinline__ int small_row_tiles(int cnt, bool tall) {
   return tall && small_tall(cnt) ? 1 : (cnt + SmallTile::BM - 1) / SmallTile::BM;
 }
 
-// Whether a launch takes them: n_tall experts of that size, n_past above it, `tiles` in the launch with tall ones.  A unit runs two workgroups
-// at a time, and a tall tile is about as long as two of the others, so what counts is how both lists fill whole rounds.  Time
-// of the launch tall / plain, 23 layers of d = 1024 to 4096 with 12 to 80 experts, 145 to 178 rows each (256 units):
-//   up: up to 512 tall tiles 0.73 to 1.03, mean 0.88 (saving the pre-activations 0.81 to 1.06, 0.94); 513 to 800 0.90 to 1.17, mean
-//     1.06 (1.00 to 1.27, 1.13): they begin a third tile per unit; from 832 on 0.88 to 1.09, mean 0.96 (0.97 to 1.06, 1.01), with a
-//     fifth of the experts past 192 rows 1.02 (call 145 -> 148 us)
+// Whether a launch takes them.  A unit runs two workgroups at a time, and a tall tile is about as long as two of the others, so
+// what counts is how both lists fill whole rounds.  Time of the launch tall / plain, 23 layers of d = 1024 to 4096 with 12 to 80
+// experts, 145 to 178 rows each (256 units), by tall tiles:
+//   up: up to 512 0.73 to 1.03, mean 0.88 (saving the pre-activations 0.81 to 1.06, 0.94); 513 to 800 0.90 to 1.17, mean 1.06 (1.00
+//     to 1.27, 1.13): they begin a third tile per unit; from 832 on 0.88 to 1.09, mean 0.96 (0.97 to 1.06, 1.01), with a fifth of the
+//     experts past 192 rows 1.02 (call 145 -> 148 us)
 //   down, with nothing else in the launch to fill its units: from 512 on with at most a twentieth of the
 //     experts past 192 rows 0.79 to 0.99, mean 0.92, with more 0.84 to 1.09, 1.00; 448 to 511 0.80 to 1.00, 0.94, but
 //     1.01 to 1.14 where the last tile of every expert is half a one (d = 1344) and 0.87 to 1.10 with more past 192; below 0.84 to
 //     1.30, mean 1.08
 //   dH: below 180 0.95 to 1.34, mean 1.09; 180 to 512 0.69 to 0.97, mean 0.83
-//   dX (the weight gradients fill what it leaves idle): 0.90 to 1.03, mean 0.94
+//   dX (the weight gradients fill what it leaves idle): from 192 on 0.90 to 1.03, mean 0.94
+// With less than three quarters of a tile per unit a launch lasts as long as its longest tile: up and dX, 10 layers of two or three
+// experts per group and two shared experts of 145 to 180 rows, 16 to 168 up tiles, call 0.96 to 1.15, step 0.98 to 1.17.
 // (The launch after one of the same form finds its operands nearer: down 44 us behind tall up tiles, 46 behind plain ones, tall itself.
-// Whole calls with these lines against no tall tiles: forward 0.81 to 1.01, mean 0.95 (56 sizes), training step 0.92 to 1.00, 0.96
-// (36); tall wherever three quarters of the experts are of their size 0.83 to 1.12, 0.97, and 0.92 to 1.01, 0.97.)
+// Whole calls with these lines against no tall tiles: forward 0.81 to 1.02, mean 0.96 (98 sizes), training step 0.92 to 1.00, 0.97
+// (74); tall wherever three quarters of the experts are of their size 0.83 to 1.16, 1.01, and 0.92 to 1.14, 1.01.)
+// Here, what only the counts tell: n_tall experts of that size, n_past above it, `tiles` in the launch with tall ones; the rest is
+// in may_be_tall.
 template <int MODE>
 __device__ __forceinline__ bool tall_pays(const TileArgs& a, int n_tall, int n_past, int tiles) {
   if (4 * n_tall < 3 * a.Ne) return false;
   if constexpr (is_up(MODE)) return tiles <= 2 * a.ncu || (20 * n_past <= a.Ne && 4 * tiles >= 13 * a.ncu);
-  if constexpr (MODE == kDown)
-    return 20 * n_past <= a.Ne && (tiles >= 2 * a.ncu || (4 * tiles >= 7 * a.ncu && a.d % TallTile::BN == 0));
-  if constexpr (MODE == kDgradH) return 10 * tiles >= 7 * a.ncu && tiles <= 2 * a.ncu;
+  if constexpr (MODE == kDown) return 20 * n_past <= a.Ne;
+  if constexpr (MODE == kDgradH) return tiles <= 2 * a.ncu;
   return true;
 }
 
@@ -1505,19 +1508,19 @@ static long long small_grid(const LayerDesc& L, int mode) {
   return (n + kXcds * kSmallChunk - 1) / (kXcds * kSmallChunk) * (kXcds * kSmallChunk);
 }
 
-// Launches in which tall tiles are looked for.  Outside of these sizes an even spread leaves fewer than three quarters of the
-// experts with 129 to 192 rows (135 and 187 per expert: 1.01 to 1.02 of the time), or tall_pays says no with one tile per expert
-// already; the instantiation without them is up to 1 % faster where it finds none (3 % with more than 64 experts, whose lists take
-// two rounds of counting).
+// Launches in which tall tiles are looked for (tall_pays: why these lines).  Outside of 140 to 184 rows per expert an even spread
+// leaves fewer than three quarters of the experts with 129 to 192 rows (135 and 187: 1.01 to 1.02 of the time); the
+// instantiation without them is up to 1 % faster where it finds none (3 % with more than 64 experts, whose lists take two rounds of
+// counting, and 5 to 12 % of an up launch whose tiles turn out to begin a third one per unit).
 static bool may_be_tall(const LayerDesc& L, int mode) {
   if (L.P < 140ll * L.Ne || L.P > 184ll * L.Ne) return false;
   const long long cus = tile_num_cus();
-  long long n = 0;                                        // tiles with one row tile per expert: the fewest
+  long long n = 0;                                        // tiles with one row tile per expert
   for (int g = 0; g < L.Ng; ++g) n += L.N * small_column_tiles(L, mode, g);
-  if (is_up(mode)) return n <= 2 * cus || n >= 3 * cus;
-  if (mode == kDown) return 4 * n >= 7 * cus;
-  if (mode == kDgradH) return 10 * n >= 6 * cus && n <= 2 * cus;
-  return true;
+  if (is_up(mode)) return 4 * n >= 3 * cus && (n <= 2 * cus || n >= 3 * cus);
+  if (mode == kDown) return n >= 2 * cus || (4 * n >= 7 * cus && L.d % SmallTile::BN == 0);
+  if (mode == kDgradH) return 10 * n >= 7 * cus && n <= 2 * cus;
+  return 4 * n >= 3 * cus;
 }
 
 static long long small_wgrad_grid(const TileArgs& a) {

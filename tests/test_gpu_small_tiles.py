@@ -101,8 +101,8 @@ def _tall_equals_big(d, d_ff, per_group, counts, permuted=True):
 @pytest.mark.parametrize("counts", [TALL, FEW_TALL], ids=["tall", "few"])
 @pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448)), (2816, (128, 320))])
 def test_tall_tiles_equal_big_tiles(d, d_ff, counts):
-    """Bit by bit: every output adds its products in the same order in either form.  (d = 64: a reduction of one stage.)  Of the
-    forward launches the up one takes tall tiles here, of the backward ones dX."""
+    """Bit by bit: every output adds its products in the same order in either form.  (Few tiles: of the launches only dX takes tall
+    ones, at d = 2816.)"""
     _tall_equals_big(d, d_ff, 6, counts)
 
 
@@ -113,16 +113,27 @@ def _tiles(counts, columns, tall):
 
 
 @pytest.mark.parametrize("permuted", [True, False])
-@pytest.mark.parametrize("per_group,d,d_ff", [(36, 1024, (384, 320)), (33, 1088, (384, 448)), (32, 1024, (320, 448))])
-def test_tall_tiles_in_every_launch(per_group, d, d_ff, permuted):
-    """Most of 64 to 72 experts tall, the others in the first and the last ones of the list: with more than 64 of them the list
-    has two rounds.  Sizes at which every launch takes tall tiles (256 compute units); rows given in expert order as well."""
+@pytest.mark.parametrize("per_group,d,d_ff,launches", [(36, 1024, (384, 320), "up down dH dX"), (33, 1088, (384, 448), "up down dH dX"),
+                                                       (32, 1024, (320, 448), "up down dH dX"), (36, 64, (384, 320), "up dH"),
+                                                       (12, 2048, (960, 1024), "up dH dX"), (36, 1024, (384, 320), "")])
+def test_tall_tiles_by_launch(per_group, d, d_ff, launches, permuted):
+    """Most of 24 to 72 experts tall, the others in the first and the last ones of the list: with more than 64 of them the list
+    has two rounds.  Sizes at which the launches named take tall tiles (256 compute units); d = 64: a reduction of one stage.  Last:
+    too few experts of that size.  Rows given in expert order as well."""
     rng = np.random.default_rng(per_group)
     counts = [int(c) for c in rng.integers(129, 193, 2 * per_group)]
-    counts[0], counts[1], counts[per_group - 1], counts[-2], counts[-1] = 129, 0, 192, 257, 64
-    for columns, lo, hi in (([-(-f // 64) for f in d_ff], 0, 512), ([-(-d // 128)] * 2, 512, 1 << 30), ([-(-f // 128) for f in d_ff], 180, 512)):
-        assert lo <= _tiles(counts, columns, True) <= hi
-    assert 20 * sum(c > 192 for c in counts) <= len(counts)
+    counts[:9] = [129, 0, 192, 191, 130, 160, 161, 128, 129]
+    if per_group > 12:
+        counts[per_group - 1], counts[-2], counts[-1] = 192, 257, 64
+    if not launches:
+        counts[10:30] = [128, 200] * 10
+    few = 4 * sum(128 < c <= 192 for c in counts) < 3 * len(counts)
+    assert few == (not launches)
+    assert 20 * sum(c > 192 for c in counts) <= len(counts) or few
+    for name, columns, lo, hi in (("up", [-(-f // 64) for f in d_ff], 192, 512), ("down", [-(-d // 128)] * 2, 512, 1 << 30),
+                                  ("dH", [-(-f // 128) for f in d_ff], 180, 512), ("dX", [-(-d // 128)] * 2, 192, 1 << 30)):
+        takes = lo <= per_group * sum(columns) <= hi and _tiles(counts, columns, True) <= hi and not few
+        assert takes == (name in launches.split()), name
     _tall_equals_big(d, d_ff, per_group, counts, permuted)
 
 
