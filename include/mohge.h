@@ -89,15 +89,17 @@ typedef struct mohge_config {
  * Out: group_idx DEVICE [T,K_g] and expert_idx DEVICE [T,K_e], ascending ids;
  *      gates DEVICE [T,K_e] aligned with expert_idx; gs_out DEVICE [T,N_g] (GS) and
  *      es1_out DEVICE [T,N_e] (ES', zero outside kept groups), each may be NULL.
- * Logits are accumulated in fp32 over 64 hidden elements at a time and in fp64 across those
- * slices (error about 1e-7).
+ * Logits are accumulated in fp32 over at most 64 hidden elements at a time and in fp64 across those
+ * slices (2-norm error 1.5e-7 of the logits, 4e-8 from the bf16 matrix cores).
  * workspace DEVICE, optional (NULL / 0 allowed), mohge_workspace_size(cfg, MOHGE_CALL_ROUTE) bytes
  * (0 where it has no use).  Without it the logits come from the fp32 matrix cores, one workgroup
  * per 16 tokens.  With it, two other forms are chosen by size: up to 2048 tokens the
  * reduction over d is spread over several workgroups, which leave partial sums there; from 8192
- * bf16 tokens on, the router rows are first split there into three bf16 parts that add up to the
- * fp32 weight exactly, and the logits come from the bf16 matrix cores with exact products.  The
- * logits of the forms can differ in the last bit (the fp64 partial sums are grouped
+ * bf16 tokens on, and above 4096 with more than 16 router rows (d >= 512) or more than 32, where
+ * d is a multiple of 128, the router rows are first split there into three bf16 parts that add up
+ * to the fp32 weight exactly, and the logits come from the bf16 matrix cores with exact products
+ * (the workspace then holds the parts and T * (N_g + N_e) fp32 logits).  The
+ * logits of the forms can differ in the last bits (the sums are grouped
  * differently); each form is deterministic.
  */
 int mohge_route(const mohge_config* cfg, const void* x, const float* w_group,

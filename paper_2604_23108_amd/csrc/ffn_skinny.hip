@@ -6,7 +6,7 @@
 // v_mfma_f32_16x16x32_bf16, the weight rows as the first operand and up to 32 of the
 // expert's tokens as the second.  Lanes load 16 contiguous bytes of "their" weight row,
 // which is the operand layout, so weights go global -> registers -> matrix core with no
-// LDS traffic; token rows come through L1/L2 (lanes past the token count load nothing).
+// LDS traffic; token rows come through L1/L2 (lanes past the token count load the expert's first row again).
 // Experts without tokens get no workgroups.
 //
 // Quantised weights (ffn_skinny_q_kernel): FP8 E4M3 codes with one fp32 scale per weight row, or

@@ -219,9 +219,10 @@ __global__ void __launch_bounds__(512) route_kernel(const RouteArgs a) {
 // leading 8 bits, the next 8, the rest: each taken by truncation, the remainders are exact
 // in fp32), a token element is one bf16 number, and a product of two bf16 numbers is exact in
 // fp32.  So  x . w = x . w_hi + x . w_mid + x . w_lo  with v_mfma_f32_16x16x32_bf16, whose only
-// rounding is the fp32 accumulation; the large part (w_hi) of every 32 hidden elements is added
-// to an fp64 total, which keeps the logit error below that of the fp32 form above (2-norm against float64: 3.9e-8
-// against 1.07e-7 at d = 128, 1.5e-7 from d = 1024 on).  Sixteen times the fp32 matrix rate at three times the work.
+// rounding is that of its fp32 sums.  It cuts them off downwards, so few may follow each other: the large part (w_hi) of
+// every 32 hidden elements is added to an fp64 total.  That keeps the logit error below that of the fp32 form above (2-norm
+// against float64, d = 128 to 8192: 3.9e-8 against 1.07e-7 at d = 128 and 1.5e-7 from d = 384 on; mean error, of the logits'
+// rms, at most 2e-9, downwards).  Sixteen times the fp32 matrix rate at three times the work.
 //
 // A small kernel first splits the router rows into the three bf16 planes (workspace:
 // [3][rows padded to whole passes][d], padding rows zero).  In the main kernel a workgroup of 8
@@ -243,7 +244,7 @@ typedef __bf16 rbf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kPfDepth = 128;            // the hidden size is a multiple of it
 
 // Hidden elements per chunk and chunks in LDS: four where they fit, so that several are on their way while one is used.  (One
-// workgroup per compute unit has all of its LDS.  Two chunks: 68 router rows, d = 4096, 16384 tokens 80 us for the call, now 67.)
+// workgroup per compute unit has all of its LDS.  Two chunks: 68 router rows, d = 4096, 16384 tokens 80 us for the call, now 65.)
 // SEL (up to two column tiles, or three with 32 tokens): two chunks, registers and LDS for two workgroups per compute unit.
 template <int TG, int TN, bool SEL>
 struct PrefillShape {

@@ -926,7 +926,7 @@ def test_shared_routing_with_the_largest_expert_count():
 @pytest.mark.parametrize("Ng,N,mode", [(3, 3, SELECT_PER_GROUP), (4, 16, SELECT_PER_GROUP), (4, 16, SELECT_GLOBAL),
                                        (8, 16, SELECT_GLOBAL), (16, 16, SELECT_PER_GROUP)])
 def test_router_matrix_core_form_many_tokens(Ng, N, mode):
-    # from 8192 bf16 tokens on the logits come from the bf16 matrix cores (router rows split into
+    # these come from the bf16 matrix cores (from 8192 bf16 tokens on always; router rows split into
     # three bf16 parts): 12 router rows (one column tile), 68 (one pass of five), 136 and 272
     # (several passes), a token count that is not a multiple of the 32 / 64 a workgroup takes
     import paper_2604_23108_amd as M
