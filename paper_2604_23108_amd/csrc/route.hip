@@ -572,14 +572,14 @@ static bool prefill_form(const LayerDesc& L, int dtype) {
 //     39 / 35); two tiles in the last quarter, where the second kernel has the most to do (d = 1024: 12000 tokens 22.5 / 22.1, 16384
 //     22.9 / 24.6; d = 2048 30.9 / 30.9); three while the reduction is short (16384 tokens: d = 128 16.6 / 19.6, d = 512
 //     21.3 / 23.1, d = 1024 26.4 / 26.7, 12000 tokens 26 / 24); more: the second kernel (68 rows, 16384 tokens, d = 128 29 / 25)
-//   up to 32: one tile itself (8192 tokens, d = 128 11.5 / 13.2); two and three while the reduction is short (8192 tokens, 40 rows:
+//   up to 32: one tile itself unless d is large (8192 tokens, d = 128 11.5 / 13.2, d = 1024 15.2 / 15.8, d = 3072 24.5 / 22.9); two and three while the reduction is short (8192 tokens, 40 rows:
 //     d = 128 14.0 / 15.3, d = 512 17.1 / 17.6, d = 1024 20.6 / 20.2); more: the second kernel (68 rows, d = 128 18.4 / 18.8,
 //     d = 1024 28.4 / 26.0; 4097 tokens 18.3 / 15.8)
 struct PrefillPlan { int tg; bool sel; };
 static PrefillPlan prefill_plan(const LayerDesc& L, int cus) {
   const int tn = pass_tiles(L);
   if (L.T > 64ll * cus) return {4, tn <= 2};
-  if (L.T <= 32ll * cus) return {2, tn == 1 || (tn <= 3 && 16ll * L.d <= L.T)};
+  if (L.T <= 32ll * cus) return {2, tn == 1 ? L.d < 2048 : tn <= 3 && 16ll * L.d <= L.T};
   if (tn == 1 ? L.d < 4096 : tn == 2 ? L.T > 48ll * cus && L.d < 2048 : tn == 3 && 20ll * L.d <= L.T) return {2, true};
   return {4, false};
 }
@@ -649,6 +649,7 @@ hipError_t launch_route(const LayerDesc& L, int dtype, const void* x, const floa
         }
       }
       switch (TNp * 2 + (plan.tg == 4)) {
+        case 2: return launch_prefill<2, 1, false>(a, planes, plane_rows, s);
         case 3: return launch_prefill<4, 1, false>(a, planes, plane_rows, s);
         case 4: return launch_prefill<2, 2, false>(a, planes, plane_rows, s);
         case 5: return launch_prefill<4, 2, false>(a, planes, plane_rows, s);
