@@ -572,9 +572,9 @@ static bool prefill_form(const LayerDesc& L, int dtype) {
 //     39 / 35); two tiles in the last quarter, where the second kernel has the most to do (d = 1024: 12000 tokens 22.5 / 22.1, 16384
 //     22.9 / 24.6; d = 2048 30.9 / 30.9); three while the reduction is short (16384 tokens: d = 128 16.6 / 19.6, d = 512
 //     21.3 / 23.1, d = 1024 26.4 / 26.7, 12000 tokens 26 / 24); more: the second kernel (68 rows, 16384 tokens, d = 128 29 / 25)
-//   up to 32: one tile itself unless d is large (8192 tokens, d = 128 11.5 / 13.2, d = 1024 15.2 / 15.8, d = 3072 24.5 / 22.9); two and three while the reduction is short (8192 tokens, 40 rows:
-//     d = 128 14.0 / 15.3, d = 512 17.1 / 17.6, d = 1024 20.6 / 20.2); more: the second kernel (68 rows, d = 128 18.4 / 18.8,
-//     d = 1024 28.4 / 26.0; 4097 tokens 18.3 / 15.8)
+//   up to 32: one tile itself unless d is large (8192 tokens, d = 128 11.5 / 13.2, d = 1024 15.2 / 15.8, d = 3072 24.5 / 22.9); two
+//     and three while the reduction is short (8192 tokens, 40 rows: d = 128 14.0 / 15.3, d = 512 17.1 / 17.6, d = 1024 20.6 / 20.2);
+//     more: the second kernel (68 rows, d = 128 18.4 / 18.8, d = 1024 28.4 / 26.0; 4097 tokens 18.3 / 15.8)
 struct PrefillPlan { int tg; bool sel; };
 static PrefillPlan prefill_plan(const LayerDesc& L, int cus) {
   const int tn = pass_tiles(L);
