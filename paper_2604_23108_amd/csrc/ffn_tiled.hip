@@ -1,5 +1,5 @@
 // Expert feed-forward networks for prefill-sized token counts on gfx950: a ragged
-// grouped GEMM on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16, fp32 accumulate).
+// grouped GEMM on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulate).
 //
 // Two launches: "up" computes H = SiLU(X W_gate^T) * (X W_up^T) for every expert's
 // rows, "down" computes Y = H W_down^T.  Both have the form C[rows of expert e] =
@@ -28,11 +28,14 @@
 // tiles of an expert and mostly hit in L2) and three for the weight operand (streamed from
 // HBM), which therefore is requested two stages ahead.  The token gather is fused: a tile
 // row's global address is taken through `perm`.
-// The inner loop is ordered by hand (pinned with sched_barrier): operand fragments of the
-// next 16-deep k-step are read from LDS into a second register set and the global -> LDS
-// requests are issued between the MFMAs of the current one; one barrier per stage, placed
-// after the third of its four k-steps so that the first fragments of the next stage are
-// read under MFMAs as well.
+// Which instruction: power bounds these launches (the clock falls to 1.7 to 2.0 GHz), and on operands with full mantissas
+// 16x16x32 draws less of it than 32x32x16, whose accumulators are read and written twice as often per product: alone 2060
+// against 1750 TFLOP/s, with the operand reads from LDS 1870 against 1650.
+// The inner loop is ordered by hand (pinned with sched_barrier): between the MFMAs of a 32-deep k-step stand the LDS reads of
+// the fragments it will need next, a token fragment's register being refilled right after its last use, and the global -> LDS
+// requests, spread over the whole stage; one barrier per stage, placed three token fragments into its second k-step, so
+// that the first fragments of the next stage are read under MFMAs as well (run_tile has the figures).  16384 tokens, d = 4096,
+// skewed: launch 2029 -> 1820 us (1.07 -> 1.19 PFLOP/s), main loop 2400 -> 2260 clocks a stage at 1.72 -> 1.82 GHz.
 // The MFMA takes the weight fragment as first operand: a lane then holds 4 consecutive
 // output features of one token; the epilogue packs them to bf16 (hardware conversion),
 // transposes through a wave-private LDS patch and stores whole row segments.
@@ -45,10 +48,7 @@
 // chunks swizzled by the row), and its MFMA fragments are read with ds_read_b64_tr_b16, which
 // hands every lane four consecutive reduction indices of one feature.  No operand is
 // transposed in memory.  The ragged reduction of the weight gradients needs no padding
-// either: rows past the expert's last token are fetched from a row of zeros.  These modes
-// run within 10 % of the forward's rate (8192 tokens, 24 experts, 412 GFLOP each: forward 409 us,
-// input gradients 446, weight gradients 423; 533 and 481 while the compiler made every stage
-// wait for the copies just requested, see async_copy16_unmodelled).
+// either: rows past the expert's last token are fetched from a row of zeros.
 #include <type_traits>
 
 #include "common.h"
@@ -57,7 +57,7 @@
 namespace mohge {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 256, kBN = 256, kBK = 64;
 constexpr int kStagesA = 2, kStagesB = 3;   // 32 KB parts: 2 token + 3 weight = all 160 KB of LDS
@@ -452,29 +452,24 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-__device__ __forceinline__ void async_copy16(const void* gptr, void* lds_uniform_base) {
-  __builtin_amdgcn_global_load_lds(
-      (const __attribute__((address_space(1))) void*)gptr,
-      (__attribute__((address_space(3))) void*)lds_uniform_base, 16, 0, 0);
-}
-
-// The same copy for the modes with transposing LDS reads, as instructions the compiler does not model: in
-// front of a transposing read (an intrinsic) it waits for every modelled copy to LDS, whatever part that
-// copy fills, i.e. for all stages on their way, once per stage.  M0 holds the LDS destination; the compiler puts it
-// there (an operand bound to the register, so it knows what M0 holds before and after); five wait states cover any
-// way in which it or the base registers may have been written.  Both address forms write no register; completion
-// is awaited by the explicit vmcnt waits of the stages, as for the copies above.
+// Copy to LDS, 16 bytes per lane, as an instruction the compiler does not model.  The builtin counts as an access to both
+// memories: until a wait for every one of them, which this kernel never makes in its main loop, each wait for an LDS read is
+// for all of them, and in front of a transposing read (an intrinsic) it waits for every copy on its way.  M0 holds the LDS
+// destination; the compiler puts it there (an operand bound to the register, so it knows what M0 holds before and after).
+// One wait state, which the hardware asks for after a scalar write of M0; a vector instruction that wrote it or the base would
+// need five, and a test looks for one in the code the compiler made (with five everywhere: 602 -> 608 us for 8192 rows, d =
+// 4096).  Both address forms write no register; completion is awaited by the explicit vmcnt waits of the stages.
 // lds_addr: address in the workgroup's LDS (lds_address() of the buffer plus an offset), wave-uniform.
 __device__ __forceinline__ int lds_address(const unsigned char* lds) {
   return (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)lds;
 }
-__device__ __forceinline__ void async_copy16_unmodelled(const void* gptr, int lds_addr) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, off"
+__device__ __forceinline__ void async_copy16(const void* gptr, int lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                ::"v"(gptr), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 // wave-uniform base, 32-bit byte offset per lane (half the registers)
-__device__ __forceinline__ void async_copy16_unmodelled(const void* uniform_base, uint32_t offset, int lds_addr) {
-  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
+__device__ __forceinline__ void async_copy16(const void* uniform_base, uint32_t offset, int lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                ::"v"(offset), "s"(uniform_base), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 
@@ -542,17 +537,22 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr bool TRA = tr_a(MODE), TRB = tr_b(MODE);   // operand read by transposing LDS reads
   constexpr bool WG = MODE == kWgrad;
   constexpr bool DH = MODE == kDgradH;
-  constexpr bool DG = TRB && !WG;          // the input-gradient modes: both operands as a wave-uniform base and
-                                           // 32-bit offsets (with 64-bit pointers their main loops spilled)
+  constexpr bool DG = TRB && !WG;
+  // Operands as a wave-uniform base and 32-bit offsets per lane (64-bit pointers cost twice the registers): the weights of
+  // the token modes, and their tokens where they are neighbouring rows (the up modes gather theirs through perm)
+  constexpr bool OFFA = !WG && !UP, OFFB = !WG;
+  // (a value the compiler cannot trace, here and before the epilogue: what depends on the lane would be computed once before
+  // the first tile and kept through every main loop, in registers that those do not have)
+  asm volatile("" : "+v"(lane));
   long long ts[6] = {0, 0, 0, 0, 0, 0};
   PROBE_T(0);
   constexpr int BM = GEO::BM, BN = GEO::BN, BK = kBK;
   static_assert(BM == BN || !TRA, "one part size for both operands");
   constexpr int WGM = GEO::WGM, WGN = GEO::WGN, NWAVES = WGM * WGN, NT = 64 * NWAVES;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int MF = WTM / 32, NF = WTN / 32;
+  constexpr int MF = WTM / 32;             // 32-row token blocks of a wave
   constexpr int CH = BK / 8, ROWB = BK * 2, RPL = 64 / CH, SH = 1;   // 8 chunks, 128-byte rows
-  constexpr int KK = BK / 16;                                        // MFMA k-steps per stage
+  constexpr int KK = BK / 32;                                        // MFMA k-steps per stage
   constexpr int B_LOADS = BN * CH / NT;
   // wave-wide load j of the token part fills tile rows [64j, 64j+64): only NACT of them matter
   // (token-major operands: a part is 64 tokens x BM features, all of it is loaded)
@@ -560,10 +560,10 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr int A_LOADS = TRA ? BM * CH / NT : NACT * (32 * WGM / (NWAVES * RPL));
   static_assert((32 * WGM) % (NWAVES * RPL) == 0 && B_LOADS * NWAVES * RPL == BN, "whole wave-wide loads");
   constexpr int PART = BN * ROWB;                 // 32 (16) KB: one weight part, or a token part of as many rows
-  constexpr int NM = NACT * NF;     // MFMAs per k-step
-  constexpr int NR = NACT + NF;     // fragment reads per k-step
-  static_assert(NACT >= 1 && NACT <= MF, "active fragments");
-  static_assert(!UP || NF % 2 == 0, "gate and up halves per wave");
+  // 16-row fragments: MT of the tokens (two per active block), NW of the weights
+  constexpr int MT = 2 * NACT, NW = WTN / 16;
+  static_assert(NACT >= 1 && NACT <= MF, "active token blocks");
+  static_assert(KK == 2 && (!UP || NW % 2 == 0), "two k-steps a stage; gate and up halves per wave");
   // LDS map: token parts A0, A1 (two stages), then weight parts B0, B1, B2 (three stages).
   // Short tiles (see short_depth): DEPTH stages of both, the token parts only as long as the tile.
   constexpr int DEPTH = short_depth<GEO>(MODE, NACT);
@@ -593,29 +593,28 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // wave-wide load j fills tile rows (j*NWAVES + w)*RPL .. +RPL-1; lane l fills row l/CH,
   // physical chunk l%CH, which holds logical chunk (l%CH) ^ ((row >> SH) & (CH-1)).
   const int lrow = lane / CH, lpos = lane % CH;
-  const uint16_t* src_a[TRA || DG ? 1 : A_LOADS];
-  uint32_t off_a[DG ? A_LOADS : 1];
-  uint32_t off_b = 0;                             // DG
-  const uint16_t* base_b = nullptr;               // DG
-  // DG: first row of wave-wide load j, and from there the lane's row (at most 7 further: offsets stay small)
+  const uint16_t* src_a[TRA || OFFA ? 1 : A_LOADS];
+  uint32_t off_a[OFFA ? A_LOADS : 1];             // (WG: the lane's part, the same for every load; so off_b)
+  uint32_t off_b[TRB ? 1 : B_LOADS];
+  const uint16_t* base_b = nullptr;               // OFFB
+  // OFFA: first row of wave-wide load j, and from there the lane's row (at most 7 further: offsets stay small)
   auto first_row = [&](int j) { return min((j * NWAVES + w) * RPL, rec.rows - 1); };
-  const uint16_t* src_b[TRB ? 1 : B_LOADS];
   // Operands stored reduction-index major (rows = reduction index, features contiguous): a part
   // holds 64 reduction rows x BN features, TRB_ROW = 512 (256) bytes a row.  Wave-wide load j fills
   // the TPL = 2 (4) rows from TPL*(j*NWAVES + w); lane l fills physical chunk l%TCH of row t = that +
-  // l/TCH, which holds logical chunk (l%TCH) ^ (4*(t&3)): the four rows a transposing read touches
-  // at once then sit in different banks.
+  // l/TCH, which holds logical chunk (l%TCH) ^ (4*(t&3)) ^ (2*((t>>3)&1)): the eight rows that 32 lanes of a
+  // transposing read touch at once (k0..k0+3 and k0+8..k0+11) then sit in different banks.
   constexpr int TRB_ROW = BN * 2, TCH = BN / 8, TPL = 1024 / TRB_ROW;
-  static_assert(!(TRA || TRB) || (NWAVES * TPL % 4 == 0 && B_LOADS == BN * CH / NT), "part layout");
+  static_assert(!(TRA || TRB) || (NWAVES * TPL % 16 == 0 && B_LOADS == BN * CH / NT), "part layout");
   const int trow0 = TPL * w + lane / TCH;         // row of load 0; load j: + TPL*NWAVES*j
-  const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3));
+  const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3)) ^ (2 * ((trow0 >> 3) & 1));
   const uint16_t* zsrc = nullptr;
   unsigned tr_ldb = 0;                            // row pitch of the B operand in elements
   if constexpr (TRA) {
     int ma = rec.row_start + tr_lc * 8;
     // feature chunks past the matrix edge: any chunk inside the row (never stored)
     if (ma > a.Mrows[g] - 8) ma = a.Mrows[g] - 8;
-    src_a[0] = a.A + (long long)(tok0 + trow0) * a.lda + ma;      // load 0 of stage 0
+    off_a[0] = ((uint32_t)trow0 * (uint32_t)a.lda + (uint32_t)ma) * 2u;
   }
   if constexpr (TRB) {
     int nb = rec.n0 + tr_lc * 8;
@@ -623,17 +622,17 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       if (nb > a.Ncols[g] - 8) nb = a.Ncols[g] - 8;
       zsrc = a.zero_row + (lane % TCH) * 8;
       tr_ldb = a.ldb;
-      src_b[0] = a.B2 + (long long)(tok0 + trow0) * a.ldb + nb;
+      off_b[0] = ((uint32_t)trow0 * (uint32_t)a.ldb + (uint32_t)nb) * 2u;
     } else if constexpr (DH) {
       if (nb > F - 8) nb = F - 8;                 // W_down[e]: [d, F]
       tr_ldb = a.ldw[g];
       base_b = a.W[g] + (long long)e_i * a.d * a.ldw[g];
-      off_b = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
+      off_b[0] = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
     } else {
       if (nb > a.d - 8) nb = a.d - 8;             // W13[e]: [2F, d]; F holds 2 F_g here
       tr_ldb = a.ldw[g];
       base_b = a.W[g] + (long long)e_i * F * a.ldw[g];
-      off_b = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
+      off_b[0] = (uint32_t)(trow0 * a.ldw[g] + nb) * 2u;
     }
   }
 #pragma unroll
@@ -645,77 +644,72 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     if constexpr (UP) src_row = a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
     else src_row = pos;
     const int chunk = lpos ^ ((row >> SH) & (CH - 1));
-    if constexpr (DG) off_a[j] = ((uint32_t)(rr - first_row(j)) * (uint32_t)a.lda + chunk * 8) * 2u;
+    if constexpr (OFFA) off_a[j] = ((uint32_t)(rr - first_row(j)) * (uint32_t)a.lda + chunk * 8) * 2u;
     else src_a[j] = a.A + src_row * a.lda + chunk * 8;
   }
+  // plain weights: row n0 of the tile's matrix; up modes: W_up is F rows further, and a wave-wide load holds rows of one of them
+  static_assert(!UP || (BN / 2) % (NWAVES * RPL) == 0, "loads of one half");
+  const int ncols_b = UP ? F : a.d;
+  if constexpr (!TRB) base_b = a.W[g] + ((long long)e_i * (UP ? 2 : 1) * ncols_b + rec.n0) * a.ldw[g];
 #pragma unroll
   for (int j = 0; j < (TRB ? 0 : B_LOADS); ++j) {
     const int row = (j * NWAVES + w) * RPL + lrow;
     const int chunk = lpos ^ ((row >> SH) & (CH - 1));
-    long long wrow;
-    if constexpr (UP) {
-      // tile rows [0, BN/2): W_gate rows n0.., rows [BN/2, BN): W_up rows n0..
-      const int half = row >= BN / 2;
-      int f = rec.n0 + (row - half * (BN / 2));
-      if (f > F - 1) f = F - 1;
-      wrow = (long long)e_i * 2 * F + (long long)half * F + f;
-    } else {
-      int n = rec.n0 + row;
-      if (n > a.d - 1) n = a.d - 1;
-      wrow = (long long)e_i * a.d + n;
-    }
-    src_b[j] = a.W[g] + wrow * a.ldw[g] + chunk * 8;
+    // the row of the tile's weights, from the first one of its half (up modes: [0, BN/2) W_gate rows n0.., the rest W_up rows)
+    int r = UP ? row % (BN / 2) : row;
+    if (rec.n0 + r > ncols_b - 1) r = ncols_b - 1 - rec.n0;
+    off_b[j] = ((uint32_t)r * (uint32_t)a.ldw[g] + chunk * 8) * 2u;
   }
   const int ld_off = w * 1024;      // + j * NWAVES * 1024: wave-uniform destination inside a part
 
   // ---- LDS offsets of the MFMA operand fragments ---------------------------------------
-  // fragment row = base + lane%32, logical chunk = 2*kk + lane/32
-  // Token-major parts: the transposing read works on groups of 16 lanes.  Lane 4*a + b of a
-  // group passes the address of 4 features (8 bytes) of token k0 + a at feature m0 + 4*b and
-  // gets back tokens k0..k0+3 of feature m0 + (its index in the group).  Group q of the wave
-  // covers features 16*(q&1).. of the fragment and tokens 8*(q>>1).. of the k-step, so two
+  // fragment row = base + lane%16, logical chunk = 4*kk + lane/16
+  // Reduction-major parts: the transposing read works on groups of 16 lanes.  Lane 4*a + b of a
+  // group passes the address of 4 features (8 bytes) of row k0 + a at feature m0 + 4*b and
+  // gets back rows k0..k0+3 of feature m0 + (its index in the group).  Group q of the wave
+  // covers the fragment's 16 features and rows 8*q.. of the k-step, so two
   // reads (k0, k0 + 4) give a lane its 8 consecutive reduction indices of one fragment row.
-  const int frow = lane & 31, fh = lane >> 5;
-  const int tq = lane >> 4, ta = (lane & 15) >> 2, tb = lane & 3;
+  const int frow = lane & 15, fh = lane >> 4;
+  const int ta = (lane & 15) >> 2, tb = lane & 3;
   int foff[KK], foff_t[KK];       // plain parts / reduction-major parts (only one is live
                                   // unless the two operands differ)
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    foff_t[kk] = (16 * kk + 8 * (tq >> 1) + ta) * TRB_ROW + (2 * (tq & 1) + (tb >> 1)) * 16 + (tb & 1) * 8;
-    foff[kk] = frow * ROWB + (((2 * kk + fh) ^ ((frow >> SH) & (CH - 1))) << 4);
+    foff_t[kk] = (32 * kk + 8 * fh + ta) * TRB_ROW + (tb >> 1) * 16 + (tb & 1) * 8;
+    foff[kk] = frow * ROWB + (((4 * kk + fh) ^ ((frow >> SH) & (CH - 1))) << 4);
   }
   // first feature of a fragment -> its 16-byte chunk, swizzled like the loads wrote it
-  auto tr_base = [&](int feat) { return (((feat >> 3) ^ (4 * ta)) << 4); };
-  int fbase[NR];     // token fragments first (interleaved over the wave rows), then weights
+  auto tr_base = [&](int feat) { return (((feat >> 3) ^ (4 * ta) ^ (2 * (fh & 1))) << 4); };
+  int fbase_a[MT], fbase_b[NW];   // token fragments (32-row blocks interleaved over the wave rows), weight fragments
 #pragma unroll
-  for (int ti = 0; ti < NACT; ++ti)
-    fbase[ti] = TRA ? tr_base((ti * WGM + wm) * 32) : ((ti * WGM + wm) * 32) * ROWB;
+  for (int ti = 0; ti < MT; ++ti) {
+    const int row = ((ti >> 1) * WGM + wm) * 32 + (ti & 1) * 16;
+    fbase_a[ti] = TRA ? tr_base(row) : row * ROWB;
+  }
 #pragma unroll
-  for (int fi = 0; fi < NF; ++fi) {
+  for (int fi = 0; fi < NW; ++fi) {
     int row;
     if constexpr (UP) {
-      constexpr int NFh = NF / 2;
-      row = (fi < NFh) ? wn * (WTN / 2) + fi * 32 : BN / 2 + wn * (WTN / 2) + (fi - NFh) * 32;
+      constexpr int NWh = NW / 2;
+      row = (fi < NWh) ? wn * (WTN / 2) + fi * 16 : BN / 2 + wn * (WTN / 2) + (fi - NWh) * 16;
     } else {
-      row = wn * WTN + fi * 32;
+      row = wn * WTN + fi * 16;
     }
-    fbase[NACT + fi] = TRB ? tr_base(row) : row * ROWB;
+    fbase_b[fi] = TRB ? tr_base(row) : row * ROWB;
   }
 
-  f32x16 acc[NF][NACT];
+  f32x4 acc[NW][MT];
 #pragma unroll
-  for (int fi = 0; fi < NF; ++fi)
+  for (int fi = 0; fi < NW; ++fi)
 #pragma unroll
-    for (int ti = 0; ti < NACT; ++ti)
+    for (int ti = 0; ti < MT; ++ti)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[fi][ti][r] = 0.f;
+      for (int r = 0; r < 4; ++r) acc[fi][ti][r] = 0.f;
 
   const int KT = K / BK;
-  // fragment r of k-step kk of the stage whose parts are pa (tokens) / pb (weights)
-  auto read_frag = [&](const unsigned char* pa, const unsigned char* pb, int kk, int r) {
-    const bool tr = r < NACT ? TRA : TRB;
-    const unsigned char* p = (r < NACT ? pa : pb) + fbase[r] + (tr ? foff_t[kk] : foff[kk]);
-    if (tr) {
+  // a fragment at p: plain, or two transposing reads
+  auto read_frag = [&](const unsigned char* p, auto TR) {
+    if constexpr (decltype(TR)::value) {
       typedef short s16x4 __attribute__((ext_vector_type(4)));
       typedef short s16x8 __attribute__((ext_vector_type(8)));
       typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
@@ -727,79 +721,67 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       return *reinterpret_cast<const bf16x8*>(p);
     }
   };
-  // reduction-major operands: load j of a stage starts TPL*NWAVES*j rows further down; in
-  // kWgrad the rows are routed tokens, and those at or past the expert's count read the zero
-  // row instead
-  auto tr_src = [&](const uint16_t* base, unsigned ld, int stage, int j) {
+  auto read_a = [&](const unsigned char* pa, int kk, int ti) {
+    return read_frag(pa + fbase_a[ti] + (TRA ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRA>{});
+  };
+  auto read_b = [&](const unsigned char* pb, int kk, int fi) {
+    return read_frag(pb + fbase_b[fi] + (TRB ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRB>{});
+  };
+  // reduction-major operands: load j of a stage starts TPL*NWAVES*j rows further down.  In kWgrad the rows are routed tokens;
+  // in the expert's last stage those at or past its count read the zero row instead (ENDS: the stage may be that one; without,
+  // every lane's row is there, and what the choice costs per load, a branch among the MFMAs, is saved)
+  auto wg_copy = [&](const uint16_t* base, unsigned ld, uint32_t off, int stage, int j, int to, auto ENDS) {
     const int t = stage * BK + TPL * NWAVES * j;    // row of this load, less trow0
     // wave-uniform 32 x 32 -> 64 bit product: stays in scalar registers
-    const uint16_t* p = base + (unsigned long long)(unsigned)t * ld;
-    if constexpr (WG) return t + trow0 < ntok ? p : zsrc;
-    else return p;
+    const uint16_t* p = base + (unsigned long long)(unsigned)(tok0 + t) * ld;
+    if constexpr (decltype(ENDS)::value) {
+      const uint16_t* row = reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(p) + off);
+      async_copy16(t + trow0 < ntok ? row : zsrc, to);
+    } else {
+      async_copy16(p, off, to);
+    }
   };
   const int lds0 = lds_address(lds);
-  auto issue_a = [&](int stage, int slot, int j) {
-    if constexpr (DG) {
+  auto issue_a = [&](int stage, int slot, int j, auto ENDS) {
+    const int to = lds0 + (int)(a_part(stage, slot) - lds) + j * NWAVES * 1024 + ld_off;
+    if constexpr (OFFA) {
       const uint16_t* base = a.A + (unsigned long long)(unsigned)(rec.row_start + first_row(j)) * (unsigned)a.lda;
-      async_copy16_unmodelled(base + stage * BK, off_a[j], lds0 + (int)(a_part(stage, slot) - lds) + j * NWAVES * 1024 + ld_off);
-      return;
+      async_copy16(base + stage * BK, off_a[j], to);
+    } else if constexpr (TRA) {
+      wg_copy(a.A, a.lda, off_a[0], stage, j, to, ENDS);
+    } else {
+      async_copy16(src_a[j] + stage * BK, to);
     }
-    const uint16_t* src;
-    if constexpr (TRA) src = tr_src(src_a[0], a.lda, stage, j);
-    else src = src_a[j] + stage * BK;
-    if constexpr (TRA || TRB) async_copy16_unmodelled(src, lds0 + (int)(a_part(stage, slot) - lds) + j * NWAVES * 1024 + ld_off);
-    else async_copy16(src, a_part(stage, slot) + j * NWAVES * 1024 + ld_off);
   };
-  auto issue_b = [&](int stage, int slot, int j) {
-    if constexpr (DG) {
+  auto issue_b = [&](int stage, int slot, int j, auto ENDS) {
+    const int to = lds0 + (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off;
+    if constexpr (WG) {
+      wg_copy(a.B2, a.ldb, off_b[0], stage, j, to, ENDS);
+    } else if constexpr (TRB) {
       const unsigned t = stage * BK + TPL * NWAVES * j;           // row of this load, less trow0
-      async_copy16_unmodelled(base_b + (unsigned long long)t * tr_ldb, off_b,
-                              lds0 + (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
-      return;
+      async_copy16(base_b + (unsigned long long)t * tr_ldb, off_b[0], to);
+    } else {
+      const long long half = UP && j * NWAVES * RPL >= BN / 2 ? (long long)F * a.ldw[g] : 0;
+      async_copy16(base_b + half + stage * BK, off_b[j], to);
     }
-    const uint16_t* src;
-    if constexpr (TRB) src = tr_src(src_b[0], tr_ldb, stage, j);
-    else src = src_b[j] + stage * BK;
-    if constexpr (TRA || TRB) async_copy16_unmodelled(src, lds0 + (int)(b_part(slot) - lds) + j * NWAVES * 1024 + ld_off);
-    else async_copy16(src, b_part(slot) + j * NWAVES * 1024 + ld_off);
   };
 
-  // prologue: request B(0), A(0), B(1), A(1), B(2) (those that exist), wait for the first
-  // two, read the first fragments
+  // prologue: request the first two stages (DEEP: DEPTH of them, as far as they exist), wait for the first, read its first
+  // fragments
+  using Ends = std::true_type;
+  constexpr int AHEAD = DEEP ? DEPTH : 2;
   PROBE_T(1);
   __syncthreads();                  // the previous tile's epilogue has left the LDS
-  if constexpr (DEEP) {
 #pragma unroll
-    for (int st = 0; st < DEPTH; ++st)
-      if (st < KT) {
+  for (int st = 0; st < AHEAD; ++st)
+    if (st < KT) {
 #pragma unroll
-        for (int j = 0; j < B_LOADS; ++j) issue_b(st, st, j);
+      for (int j = 0; j < B_LOADS; ++j) issue_b(st, st, j, Ends{});
 #pragma unroll
-        for (int j = 0; j < A_LOADS; ++j) issue_a(st, st, j);
-      }
-    if (KT >= DEPTH) wait_vmcnt<(DEPTH - 1) * (A_LOADS + B_LOADS)>();
-    else wait_vmcnt<0>();
-  } else {
-#pragma unroll
-  for (int j = 0; j < B_LOADS; ++j) issue_b(0, 0, j);
-#pragma unroll
-  for (int j = 0; j < A_LOADS; ++j) issue_a(0, 0, j);
-  if (KT > 1) {
-#pragma unroll
-    for (int j = 0; j < B_LOADS; ++j) issue_b(1, 1, j);
-#pragma unroll
-    for (int j = 0; j < A_LOADS; ++j) issue_a(1, 1, j);
-    if (KT > 2) {
-#pragma unroll
-      for (int j = 0; j < B_LOADS; ++j) issue_b(2, 2, j);
-      wait_vmcnt<2 * B_LOADS + A_LOADS>();
-    } else {
-      wait_vmcnt<B_LOADS + A_LOADS>();
+      for (int j = 0; j < A_LOADS; ++j) issue_a(st, st, j, Ends{});
     }
-  } else {
-    wait_vmcnt<0>();
-  }
-  }
+  if (KT >= AHEAD) wait_vmcnt<(AHEAD - 1) * (A_LOADS + B_LOADS)>();
+  else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   MOHGE_PIN();
   // Fused launches: the counter of the row block that this workgroup's PREVIOUS tile completed.
@@ -810,78 +792,109 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   if (signal != nullptr && threadIdx.x == 0)
     __hip_atomic_fetch_add(signal, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   PROBE_T(2);
-  bf16x8 f0[NR], f1[NR];
+  // Registers of the main loop: the weight fragments of a k-step and those of the next one, and a ring of RA token
+  // fragments.  A group is one token fragment times all weight fragments, MT groups a k-step, 2 MT a stage; after
+  // group G its register takes the token fragment of group G + RA.
+  constexpr int RA = MT < 4 ? 4 : MT, NG = KK * MT;
+  static_assert(NG % RA == 0, "a ring position per group of a stage");
+  bf16x8 fa[RA], fb[KK][NW];
+  __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0): with scalar loads among the LDS reads they could not be counted below
 #pragma unroll
-  for (int r = 0; r < NR; ++r) f0[r] = read_frag(a_part(0, 0), b_part(0), 0, r);
+  for (int fi = 0; fi < NW; ++fi) fb[0][fi] = read_b(b_part(0), 0, fi);
+#pragma unroll
+  for (int i = 0; i < RA; ++i) fa[i] = read_a(a_part(0, 0), i / MT, i % MT);
 
-  // One k-step: NM MFMAs on `use`; after MFMA i the extra instructions of this k-step are
-  // placed round-robin: first the NR fragment reads of the next k-step into `nxt`, then the
-  // global -> LDS requests handed in as `nld` callables.
-  auto kstep = [&](bf16x8 (&use)[NR], bf16x8 (&nxt)[NR], auto READ_NEXT, const unsigned char* pa,
-                   const unsigned char* pb, int kk_next, auto NLD, auto&& issue_one) {
-    constexpr bool RN = decltype(READ_NEXT)::value;
-    constexpr int NL = decltype(NLD)::value;
-    constexpr int NX = (RN ? NR : 0) + NL;
-    constexpr int PER = (NX + NM - 1) / NM;
-#pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      const int fi = i / NACT, ti = i % NACT;
-      acc[fi][ti] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(use[NACT + fi], use[ti], acc[fi][ti], 0, 0, 0);
-      MOHGE_PIN();
-#pragma unroll
-      for (int q = 0; q < PER; ++q) {
-        const int x = i * PER + q;
-        if (RN && x < NR) {
-          // in order of first use by the next k-step's MFMAs: weight fragment 0, the token
-          // fragments, then the other weight fragments
-          const int fr = x == 0 ? NACT : (x <= NACT ? x - 1 : x);
-          nxt[fr] = read_frag(pa, pb, kk_next, fr);
-          MOHGE_PIN();
-        } else if (x < NX) {
-          issue_one(x - (RN ? NR : 0));
-          MOHGE_PIN();
-        }
-      }
-    }
-  };
-
-  // Stage kt: token part kt&1, weight slot `slot` = kt%3.  The one barrier of the stage comes
-  // after its third k-step, when every wave holds the fragments of the fourth in registers:
-  // from then on nobody reads the stage's LDS parts again, so the token part of stage kt+2 and
-  // the weight part of stage kt+3 are requested into them during the fourth k-step (tokens
-  // first, so that "all but the newest B_LOADS requests have landed" certifies stage kt+1 at
-  // the next barrier), and the first fragments of stage kt+1 are read under the fourth
-  // k-step's MFMAs instead of after a barrier.
+  // Stage kt: token part kt&1, weight slot `slot` = kt%3.  Its groups [0, GB) run before the one barrier of the stage,
+  // and under them everything that is still to be read of the stage: the second k-step's weight fragments and the token
+  // fragments of groups RA and up.  The reads end GB - (NG - RA) groups ahead of the barrier, which they need to arrive.
+  // From the barrier on nobody reads the stage's LDS parts again.  Stage kt requests stage kt+2: the weights under the groups
+  // before the barrier, into the slot that stage kt-1 left (so all but the newest B_LOADS requests having landed certifies
+  // stage kt+1 at the barrier), the tokens under the groups after it, into the stage's own part.  The requests are spread
+  // over the MFMAs: a compute unit takes about 57 bytes a clock of them, a stage's 64 KB in 1150 clocks, and a wave
+  // whose request finds the queue full issues nothing else (all of them behind the barrier, with the first fragments of stage
+  // kt+1, which are read there as well: 2520 clocks a stage of 256 x 256 at d = 4096, 2080 without LDS reads or
+  // requests, 2220 with the reads, 2400 with the requests alone).
+  constexpr int GB = NG - RA + (MT == 8 ? (WG ? 2 : 3) : MT == 6 ? 2 : MT == 4 ? 1 : 2);
+  static_assert(GB > NG - RA && 2 * GB >= NW, "a stage's reads are issued before its barrier");
   int slot = 0;
-  // DEEP: both parts of stage kt+DEPTH are requested in the fourth k-step, LATER stages past kt+1 may be in flight at the
+  // DEEP: both parts of stage kt+DEPTH are requested after the barrier, LATER stages past kt+1 may be in flight at the
   // barrier.
-  auto stage = [&](int kt, auto LA, auto LB, auto LAST, auto LATER) {
-    // la: stage kt+2 exists (so A(kt+2) is requested and B(kt+2) may be in flight at the
-    // barrier); lb: stage kt+3 exists; last: no stage kt+1
-    constexpr bool la = decltype(LA)::value, lb = decltype(LB)::value, last = decltype(LAST)::value;
+  auto stage = [&](int kt, auto REQ, auto LAST, auto LATER, auto ENDS) {
+    // req: stage kt+AHEAD exists and is requested (ENDS: it may be the last); last: no stage kt+1
+    constexpr bool req = decltype(REQ)::value, last = decltype(LAST)::value;
     const unsigned char* pa = a_part(kt, slot);
     const unsigned char* pb = b_part(slot);
     const int slot1 = slot == SLOTS - 1 ? 0 : slot + 1;        // stage kt+1
-    using c0 = std::integral_constant<int, 0>;
-    using cAB = std::integral_constant<int, (la ? A_LOADS : 0) + (lb ? B_LOADS : 0)>;
-    kstep(f0, f1, std::true_type{}, pa, pb, 1, c0{}, [&](int) {});
-    kstep(f1, f0, std::true_type{}, pa, pb, 2, c0{}, [&](int) {});
-    kstep(f0, f1, std::true_type{}, pa, pb, 3, c0{}, [&](int) {});
-    if constexpr (!last) {
-      // my reads of this stage are complete; my requests for stage kt+1 have landed
-      if constexpr (DEEP)
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(LATER)::value * (A_LOADS + B_LOADS)) : "memory");
-      else if constexpr (la) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(B_LOADS) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-      __builtin_amdgcn_s_barrier();
+    const int slot2 = slot1 == SLOTS - 1 ? 0 : slot1 + 1;      // stage kt+2
+    const unsigned char* pa1 = a_part(kt + 1, slot1);
+    const unsigned char* pb1 = b_part(slot1);
+    constexpr int NPRE = req && !DEEP ? B_LOADS : 0;                          // requests before the barrier
+    constexpr int NPOST = req ? (DEEP ? A_LOADS + B_LOADS : A_LOADS) : 0;     // and after it
+    constexpr int NP = (NG - GB) * NW;                 // MFMAs after the barrier
+    constexpr int NOLD = GB - (NG - RA);               // token fragments of stage kt+1 whose register is free at the barrier
+    static_assert(NW + NOLD <= NP, "a read per MFMA");
+    // x-th read after the barrier: weight fragment 0, those token fragments and the other weight fragments of stage kt+1
+    auto ahead = [&](int x) {
+      if (x == 0) fb[0][0] = read_b(pb1, 0, 0);
+      else if (x == 1) fa[(NG - RA) % RA] = read_a(pa1, 0, 0);
+      else if (x <= NW) fb[0][x - 1] = read_b(pb1, 0, x - 1);
+      else fa[(NG - RA + x - NW) % RA] = read_a(pa1, (x - NW) / MT, (x - NW) % MT);
+    };
+    // the register of group G takes the token fragment of group G + RA
+    auto refill = [&](int G) {
+      const int nx = G + RA;
+      if (nx < NG) fa[G % RA] = read_a(pa, nx / MT, nx % MT);
+      else if (!last && G >= GB) fa[G % RA] = read_a(pa1, (nx - NG) / MT, (nx - NG) % MT);
       MOHGE_PIN();
-      kstep(f1, f0, std::true_type{}, a_part(kt + 1, slot1), b_part(slot1), 0, cAB{}, [&](int j) {
-        if (la && j < A_LOADS) issue_a(kt + (DEEP ? DEPTH : 2), slot, j);
-        else issue_b(kt + SLOTS, slot, j - (la ? A_LOADS : 0));
-      });
-    } else {
-      kstep(f1, f0, std::false_type{}, pa, pb, 0, c0{}, [&](int) {});
+    };
+#pragma unroll
+    for (int G = 0; G < NG; ++G) {
+      const int kk = G / MT, ti = G % MT;
+      if (!last && G == GB) {
+        // my reads of this stage are complete; my requests for stage kt+1 have landed
+        if constexpr (DEEP)
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(LATER)::value * (A_LOADS + B_LOADS)) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NPRE) : "memory");
+        __builtin_amdgcn_s_barrier();
+        MOHGE_PIN();
+      }
+#pragma unroll
+      for (int fi = 0; fi < NW; ++fi) {
+        acc[fi][ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][fi], fa[G % RA], acc[fi][ti], 0, 0, 0);
+        MOHGE_PIN();
+        // (one MFMA later: the register is the third operand's of the last one as often as not, and that is still being read)
+        if (fi == 0 && G > 0) refill(G - 1);
+        // second k-step's weight fragments, two under each of the first groups
+        if (G < (NW + 1) / 2 && fi < 2 && 2 * G + fi < NW) {
+          fb[1][2 * G + fi] = read_b(pb, 1, 2 * G + fi);
+          MOHGE_PIN();
+        }
+        if (G < GB) {
+          const int m = G * NW + fi;                   // this MFMA among the GB * NW before the barrier
+#pragma unroll
+          for (int j = 0; j < NPRE; ++j)
+            if (m == (2 * j + 1) * GB * NW / (2 * (NPRE > 0 ? NPRE : 1))) {
+              issue_b(kt + 2, slot2, j, ENDS);
+              MOHGE_PIN();
+            }
+        } else if (!last) {
+          const int m = (G - GB) * NW + fi;
+          if (m < NW + NOLD) {
+            ahead(m);
+            MOHGE_PIN();
+          }
+#pragma unroll
+          for (int j = 0; j < NPOST; ++j)
+            if (m == (2 * j + 1) * NP / (2 * (NPOST > 0 ? NPOST : 1))) {
+              if (j < A_LOADS) issue_a(kt + AHEAD, slot, j, ENDS);
+              else issue_b(kt + AHEAD, slot, j - A_LOADS, ENDS);
+              MOHGE_PIN();
+            }
+        }
+      }
     }
+    refill(NG - 1);
     slot = slot1;
   };
 
@@ -891,22 +904,24 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     using I0 = std::integral_constant<int, 0>;
     int kt = 0;
     if constexpr (DEEP) {
-      for (; kt + DEPTH < KT; ++kt) stage(kt, T{}, T{}, Fa{}, std::integral_constant<int, DEPTH - 2>{});
+      for (; kt + DEPTH < KT; ++kt) stage(kt, T{}, Fa{}, std::integral_constant<int, DEPTH - 2>{}, Fa{});
       if constexpr (DEPTH == 4)
-        if (kt + 3 < KT) { stage(kt, Fa{}, Fa{}, Fa{}, std::integral_constant<int, 2>{}); ++kt; }
-      if (kt + 2 < KT) { stage(kt, Fa{}, Fa{}, Fa{}, std::integral_constant<int, 1>{}); ++kt; }
+        if (kt + 3 < KT) { stage(kt, Fa{}, Fa{}, std::integral_constant<int, 2>{}, Fa{}); ++kt; }
+      if constexpr (DEPTH >= 3)
+        if (kt + 2 < KT) { stage(kt, Fa{}, Fa{}, std::integral_constant<int, 1>{}, Fa{}); ++kt; }
     } else {
-      for (; kt + 3 < KT; ++kt) stage(kt, T{}, T{}, Fa{}, I0{});
-      if (kt + 2 < KT) { stage(kt, T{}, Fa{}, Fa{}, I0{}); ++kt; }
+      for (; kt + 2 + WG < KT; ++kt) stage(kt, T{}, Fa{}, I0{}, Fa{});
+      if constexpr (WG)
+        if (kt + 2 < KT) { stage(kt, T{}, Fa{}, I0{}, T{}); ++kt; }
     }
-    if (kt + 1 < KT) { stage(kt, Fa{}, Fa{}, Fa{}, I0{}); ++kt; }
-    stage(kt, Fa{}, Fa{}, T{}, I0{});
+    if (kt + 1 < KT) { stage(kt, Fa{}, Fa{}, I0{}, Fa{}); ++kt; }
+    stage(kt, Fa{}, T{}, I0{}, Fa{});
   }
   PROBE_T(3);
 
   // ---- epilogue: accumulators -> bf16 -> a wave-private LDS patch -> 16-byte stores ------
-  // A lane holds, per 32x32 block, token lane%32 and weight rows 8*(r/4) + 4*(lane/32) +
-  // r%4: runs of 4 consecutive output features.  Every wave transposes its part through
+  // A lane holds, per 16x16 block, token lane%16 and weight rows 4*(lane/16) + r:
+  // 4 consecutive output features.  Every wave transposes its part through
   // LDS (row stride padded by 16 bytes against bank conflicts) and stores row segments.
   __syncthreads();                     // all waves are done reading the stages
   {
@@ -914,11 +929,12 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     constexpr int RS = OC * 2 + 16;                  // LDS row stride in bytes
     constexpr int EPI_BYTES = 32 * RS;               // one 32-token fragment at a time
     constexpr int CPR = OC * 2 / 16;                 // 16-byte chunks per row
-    constexpr int NFo = UP ? NF / 2 : NF;
+    constexpr int NFo = UP ? NW / 2 : NW;
     static_assert(NWAVES * EPI_BYTES <= (kStagesA + kStagesB) * PART, "epilogue patch must fit the stage buffers");
     static_assert(32 * CPR % 64 == 0, "whole wave-wide copies");
     unsigned char* my = lds + w * EPI_BYTES;
-    const int tok_l = lane & 31, fsub = (lane >> 5) * 4;
+    asm volatile("" : "+v"(lane));
+    const int tok_l = lane & 15, fsub = (lane >> 4) * 4;
     const int ncols = red_d(MODE) ? F : (WG ? a.Ncols[g] : a.d);
     const int col0 = rec.n0 + wn * OC;
     // kUpSave makes three passes over the patch: h, then the backward factors p and q
@@ -944,40 +960,41 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       if constexpr (DH) load_pre(ti, pre_a, pre_b);
       // kUpSave: the two factors the backward pass multiplies dh with, computed along with h
       // (one sigmoid per element) and kept packed until their pass
-      uint2 keep_p[MODE == kUpSave ? NFo * 4 : 1], keep_q[MODE == kUpSave ? NFo * 4 : 1];
+      uint2 keep_p[MODE == kUpSave ? NFo * 2 : 1], keep_q[MODE == kUpSave ? NFo * 2 : 1];
 #pragma unroll
       for (int pass = 0; pass < NPASS; ++pass) {
 #pragma unroll
         for (int fi = 0; fi < NFo; ++fi)
 #pragma unroll
-          for (int blk = 0; blk < 4; ++blk) {
+          for (int hh = 0; hh < 2; ++hh) {
+            const int t16 = 2 * ti + hh;
             uint2 o;
             if (MODE == kUpSave && pass > 0) {
-              o = pass == 1 ? keep_p[fi * 4 + blk] : keep_q[fi * 4 + blk];
+              o = pass == 1 ? keep_p[fi * 2 + hh] : keep_q[fi * 2 + hh];
             } else {
               float v[4], vp[4], vq[4];
 #pragma unroll
               for (int b = 0; b < 4; ++b) {
                 if constexpr (MODE == kUpSave) {
-                  const float ga = acc[fi][ti][blk * 4 + b], ub = acc[fi + NF / 2][ti][blk * 4 + b];
+                  const float ga = acc[fi][t16][b], ub = acc[fi + NW / 2][t16][b];
                   const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-ga));
                   vq[b] = ga * sg;                                   // SiLU(a)
                   v[b] = ga * ub * sg;                               // h, rounded as in kUp
                   vp[b] = ub * sg * (1.f + ga * (1.f - sg));         // b * SiLU'(a)
                 } else if constexpr (UP) {
-                  v[b] = swiglu(acc[fi][ti][blk * 4 + b], acc[fi + NF / 2][ti][blk * 4 + b]);
+                  v[b] = swiglu(acc[fi][t16][b], acc[fi + NW / 2][t16][b]);
                 } else {
-                  v[b] = acc[fi][ti][blk * 4 + b];
+                  v[b] = acc[fi][t16][b];
                 }
               }
               o.x = pack_bf16x2(v[0], v[1]);
               o.y = pack_bf16x2(v[2], v[3]);
               if constexpr (MODE == kUpSave) {
-                keep_p[fi * 4 + blk] = make_uint2(pack_bf16x2(vp[0], vp[1]), pack_bf16x2(vp[2], vp[3]));
-                keep_q[fi * 4 + blk] = make_uint2(pack_bf16x2(vq[0], vq[1]), pack_bf16x2(vq[2], vq[3]));
+                keep_p[fi * 2 + hh] = make_uint2(pack_bf16x2(vp[0], vp[1]), pack_bf16x2(vp[2], vp[3]));
+                keep_q[fi * 2 + hh] = make_uint2(pack_bf16x2(vq[0], vq[1]), pack_bf16x2(vq[2], vq[3]));
               }
             }
-            *reinterpret_cast<uint2*>(my + tok_l * RS + (fi * 32 + blk * 8 + fsub) * 2) = o;
+            *reinterpret_cast<uint2*>(my + (hh * 16 + tok_l) * RS + (fi * 16 + fsub) * 2) = o;
           }
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
