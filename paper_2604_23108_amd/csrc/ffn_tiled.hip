@@ -861,7 +861,10 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       }
 #pragma unroll
       for (int fi = 0; fi < NW; ++fi) {
-        acc[fi][ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][fi], fa[G % RA], acc[fi][ti], 0, 0, 0);
+        // to and fro over the weight fragments: every MFMA shares an operand with the one before it, which saves power (all of
+        // them the same way 1860 TFLOP/s with the operand reads from LDS and nothing else, to and fro 1897)
+        const int fw = G & 1 ? NW - 1 - fi : fi;
+        acc[fw][ti] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[kk][fw], fa[G % RA], acc[fw][ti], 0, 0, 0);
         MOHGE_PIN();
         // (one MFMA later: the register is the third operand's of the last one as often as not, and that is still being read)
         if (fi == 0 && G > 0) refill(G - 1);
