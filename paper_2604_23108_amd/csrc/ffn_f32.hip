@@ -1,5 +1,5 @@
 // Expert feed-forward networks of a layer stored in fp32, on gfx950: a ragged grouped GEMM on the
-// fp32 matrix cores (v_mfma_f32_32x32x2_f32), one launch per projection.
+// fp32 matrix cores (v_mfma_f32_32x32x2_f32, v_mfma_f32_16x16x4_f32), one launch per projection.
 //
 // What bounds it: the fp32 matrix rate, 256 FLOP per clock and compute unit (a sixteenth of bf16),
 // and the vector instructions beside it, which the fp32 MFMA does not run in parallel with: eight of them take 522 clocks of a
@@ -7,7 +7,7 @@
 // nothing else); so every vector instruction in the main loop counts.
 // Down to a few rows per expert it is the weight stream.  An MFMA keeps a SIMD busy for 64
 // clocks on two operand registers, so operand delivery is never the limit and the tile is chosen for
-// balance: 32 token rows x 64 weight rows (up: 32 W_gate rows and the matching 32 W_up rows), so that
+// balance: 32 token rows (or 16, the last of an expert) x 64 weight rows (up: 32 W_gate rows and the matching 32 W_up rows), so that
 // partial row blocks cost little and a layer of 3072 routed rows gives every compute unit several
 // tiles.  Four waves: two weight fragments x two halves of every stage's reduction indices, which
 // meet in LDS at the end.
@@ -28,7 +28,8 @@
 // total that is rounded once: 6.5 roundings for any length of the reduction.  The conversions and fp64 additions of
 // a pair run under the MFMAs of the next one (every group folded by itself, behind its MFMAs: 144 us instead of 130 at
 // 300 tokens of the layer above).
-// Error of the two projections against float64 (2-norm): 1.21e-7 at 64 indices, 1.25e-7 at 4096; with fp32 chains of
+// Error of the two projections against float64 (2-norm): 1.21e-7 at 64 indices, 1.25e-7 at 4096 (tiles of at most 16 rows 1.17e-7 to
+// 1.25e-7); with fp32 chains of
 // 64 in a second fp32 set it was 2.1e-7 and 3.1e-7, with the dot products (a sum spread over 64 lanes, then a
 // butterfly) 1.26e-7 and 2.6e-7.
 //
@@ -66,7 +67,6 @@ constexpr int kFW = 4;                                 // waves: two weight frag
 constexpr int kFStage = (kFM + kFN) * kFK * 4;         // 24 KB
 constexpr int kFStages = 2;
 constexpr int kFChunks = kFK / 4;                      // 16-byte pieces of a stage row
-constexpr int kFLoads = (kFM + kFN) * kFChunks / (64 * kFW);   // loads per thread and stage
 constexpr int kFKW = 2 * kFK / kFW;                    // reduction indices of a stage per wave
 
 __device__ __forceinline__ void f32_copy16(const float* g, unsigned char* lds_uniform_base) {
@@ -100,24 +100,30 @@ __device__ __forceinline__ bool f32_row_tile(const F32Args& a, int m, int lane, 
   return false;
 }
 
-template <bool UP>
+// HALF: a tile of at most 16 rows.  32x32x2 would spend as long on 16 rows as on 32; 16x16x4 takes half the time for the same
+// products, at the same rate, in groups of the same eight.  (For 32 rows too it was 1.5 to 2.5 % slower: twice the MFMAs.)  Layer
+// call before / now: 9 tokens of 25 experts, d = 1344, 102 / 77 us, 60 tokens 105 / 85; 60 tokens of 32 experts, d = 1024, 94 / 76, 512 tokens 202 / 197.
+template <bool UP, bool HALF>
 __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, int e, int row, int rows, int n0,
                                          int w, int lane) {
   const int g = e / a.N, i = e % a.N, F = a.F[g], K = UP ? a.d : F;
   const int ncols = UP ? F : a.d;
   // wave-wide load j fills stage rows 4*(4j + w) .. +3: first the token rows, then the weight rows;
   // lane l fills row l/16, physical piece l%16, which holds logical piece (l%16) ^ (row & 15)
-  const float* src[kFLoads];
+  constexpr int TM = HALF ? 16 : kFM;                            // token rows in LDS
+  constexpr int RPL = 64 / kFChunks;                             // rows of a wave-wide load
+  constexpr int TLOADS = TM / (RPL * kFW), LOADS = TLOADS + kFN / (RPL * kFW);   // loads per thread and stage: tokens, all
+  const float* src[LOADS];
 #pragma unroll
-  for (int j = 0; j < kFLoads; ++j) {
-    const int r = (64 / kFChunks) * (kFW * j + w) + lane / kFChunks;
+  for (int j = 0; j < LOADS; ++j) {
+    const int r = RPL * (kFW * j + w) + lane / kFChunks;
     const int piece = (lane % kFChunks) ^ (r & 15);
-    if (j < kFM * kFChunks / (64 * kFW)) {
+    if (j < TLOADS) {
       const int pos = row + (r < rows ? r : rows - 1);         // rows past the end: any valid row
       const long long s = UP && a.perm ? (long long)(a.perm[pos] / a.Ke) : (long long)pos;
       src[j] = a.A + s * a.lda + piece * 4;
     } else {
-      const int b = r - kFM;
+      const int b = r - TM;
       long long wrow;
       if constexpr (UP) {
         // weight rows of a wave: 16 of W_gate, then the matching 16 of W_up
@@ -137,7 +143,7 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
   auto issue = [&](int kt) {
     unsigned char* dst = lds + (kt % kFStages) * kFStage + w * 1024;
 #pragma unroll
-    for (int j = 0; j < kFLoads; ++j) {
+    for (int j = 0; j < LOADS; ++j) {
       f32_copy16(src[j], dst + j * kFW * 1024);
       src[j] += kFK;
     }
@@ -148,28 +154,68 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
 
   // wave: weight fragment wn (32 rows), and of every stage the reduction indices [kFKW kq, kFKW kq + kFKW)
   const int wn = w & 1, kq = w >> 1;
-  const int fr = lane & 31, fh = lane >> 5, sw = fr & 15;
-  constexpr int NK = kFKW / 8;
-  struct Frags { f32v4 b[NK], x[NK]; };
+  // A lane's 128-bit read: piece fh of the PK pieces that a group of MFMAs takes, of fragment row fr
+  constexpr int FR = HALF ? 16 : 32, PK = 64 / FR;
+  const int fr = lane % FR, fh = lane / FR, sw = fr & 15;
+  constexpr int NK = kFKW / (4 * PK), NW = 32 / FR;              // groups of a stage; weight fragments of a wave
+  struct Frags { f32v4 b[NK][NW], x[NK]; };
   auto read = [&](int kt, Frags& f) {
     const unsigned char* st = lds + (kt % kFStages) * kFStage;
     const unsigned char* pa = st + fr * (kFK * 4);
-    const unsigned char* pb = st + (kFM + 32 * wn + fr) * (kFK * 4);
+    const unsigned char* pb = st + (TM + 32 * wn + fr) * (kFK * 4);
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
-      const int off = ((2 * (NK * kq + k) + fh) ^ sw) << 4;
-      f.b[k] = *reinterpret_cast<const f32v4*>(pb + off);
+      const int off = ((PK * (NK * kq + k) + fh) ^ sw) << 4;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) f.b[k][i] = *reinterpret_cast<const f32v4*>(pb + FR * i * (kFK * 4) + off);
       f.x[k] = *reinterpret_cast<const f32v4*>(pa + off);
     }
   };
   // total so far, and the sum of the last two groups of eight products, not in it yet
-  double tot[16];
-  float pair[16];
+  constexpr int NS = HALF ? 8 : 16;
+  double tot[NS];
+  float pair[NS];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { tot[r] = 0.0; pair[r] = 0.f; }
+  for (int r = 0; r < NS; ++r) { tot[r] = 0.0; pair[r] = 0.f; }
   auto fold = [&]() {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) tot[r] += (double)pair[r];
+    for (int r = 0; r < NS; ++r) tot[r] += (double)pair[r];
+  };
+  // the sums of two groups of eight products each, added: a group is four MFMAs, HALF two for each weight fragment (not in a
+  // row, they would wait for each other)
+  auto multiply = [&](const Frags& use, int k) {
+    if constexpr (HALF) {
+      f32v4 n[2][NW];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          const int e = c < 2 ? 2 * c : 2 * c - 3;               // elements 0 and 1 make the first group, 2 and 3 the second
+          n[c & 1][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(use.b[k][i][e], use.x[k][e], c < 2 ? f32v4{0.f, 0.f, 0.f, 0.f} : n[c & 1][i], 0, 0, 0);
+        }
+      fold();
+#pragma unroll
+      for (int r = 0; r < NS; ++r) pair[r] = n[0][r / 4][r % 4] + n[1][r / 4][r % 4];
+    } else {
+      f32x16 n0, n1;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { n0[r] = 0.f; n1[r] = 0.f; }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][0][c], use.x[k][c], n0, 0, 0, 0);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + 1][0][c], use.x[k + 1][c], n1, 0, 0, 0);
+      fold();
+#pragma unroll
+      for (int r = 0; r < NS; ++r) pair[r] = n0[r] + n1[r];
+    }
+    // the previous pair is folded under the MFMAs of this one
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);             // one MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, 2 * NS / 8, 0);    // its share of the conversions and additions
+    }
+    __builtin_amdgcn_sched_barrier(0);
   };
   // Stage kt, whose fragments are in `use`: once the loads of stage kt+1 have landed everywhere its
   // fragments are read into `nxt` (under the MFMAs of stage kt), and stage kt+2 is requested into the
@@ -177,7 +223,7 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
   auto stage = [&](int kt, Frags& use, Frags& nxt) {
     if (kt + 1 < KT) {
       // (a plain barrier: __syncthreads() would also wait for the loads of later stages)
-      if (kt + kFStages - 1 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kFStages - 2) * kFLoads) : "memory");
+      if (kt + kFStages - 1 < KT) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kFStages - 2) * LOADS) : "memory");
       else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -188,29 +234,10 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int k = 0; k < NK; k += 2) {
-      f32x16 n0, n1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { n0[r] = 0.f; n1[r] = 0.f; }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][c], use.x[k][c], n0, 0, 0, 0);
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + 1][c], use.x[k + 1][c], n1, 0, 0, 0);
-      fold();
-#pragma unroll
-      for (int r = 0; r < 16; ++r) pair[r] = n0[r] + n1[r];
-      // the previous pair is folded under the MFMAs of this one
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);       // four of the 32 conversions and additions
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int k = 0; k < NK; k += HALF ? 1 : 2) multiply(use, k);
   };
   Frags f0, f1;
-  if (KT >= kFStages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kFStages - 1) * kFLoads) : "memory");
+  if (KT >= kFStages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kFStages - 1) * LOADS) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
@@ -222,33 +249,34 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
   fold();
   // The two halves of the reduction meet in LDS and are added in order.
   __syncthreads();                                               // the stages have been read
-  double* ex = reinterpret_cast<double*>(lds) + wn * 1024;       // [wn][16][64]
+  double* ex = reinterpret_cast<double*>(lds) + wn * 1024;       // [wn][NS][64]
   if (kq == 1)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) ex[r * 64 + lane] = tot[r];
+    for (int r = 0; r < NS; ++r) ex[r * 64 + lane] = tot[r];
   __syncthreads();
-  // accumulator r of a lane: token lane%32, weight row 8*(r/4) + 4*(lane/32) + r%4 of the wave's 32
+  // accumulator r of a lane: token fr, weight row STEP*(r/4) + 4*fh + r%4 of the wave's 32
+  constexpr int NQ = NS / 4, STEP = 32 / NQ;
   if (kq == 1 || fr >= rows) return;
-  float sum[16];
+  float sum[NS];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) sum[r] = (float)(tot[r] + ex[r * 64 + lane]);
+  for (int r = 0; r < NS; ++r) sum[r] = (float)(tot[r] + ex[r * 64 + lane]);
   float* crow = a.C + (long long)(row + fr) * a.ldc;
   if constexpr (UP) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int col = n0 + 16 * wn + 8 * q + 4 * fh;
+    for (int q = 0; q < NQ / 2; ++q) {
+      const int col = n0 + 16 * wn + STEP * q + 4 * fh;
       float h[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float gt = sum[4 * q + j], up = sum[8 + 4 * q + j];
+        const float gt = sum[4 * q + j], up = sum[NS / 2 + 4 * q + j];
         h[j] = gt / (1.f + expf(-gt)) * up;
       }
       if (col < ncols) *reinterpret_cast<float4*>(crow + col) = make_float4(h[0], h[1], h[2], h[3]);
     }
   } else {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = n0 + 32 * wn + 8 * q + 4 * fh;
+    for (int q = 0; q < NQ; ++q) {
+      const int col = n0 + 32 * wn + STEP * q + 4 * fh;
       if (col < ncols)
         *reinterpret_cast<float4*>(crow + col) = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
     }
@@ -270,7 +298,8 @@ __global__ void __launch_bounds__(64 * kFW, 3) ffn_f32_kernel(const F32Args a) {
   if (!f32_row_tile(a, m, lane, e, row, rows)) return;
   const int n0 = n * (UP ? kFN / 2 : kFN);
   if (n0 >= (UP ? a.F[e / a.N] : a.d)) return;
-  f32_tile<UP>(a, lds, e, row, rows, n0, w, lane);
+  if (rows > 16) f32_tile<UP, false>(a, lds, e, row, rows, n0, w, lane);
+  else f32_tile<UP, true>(a, lds, e, row, rows, n0, w, lane);
 }
 
 // Workgroups in rows of at most kFGridX: a launch has fewer than 2^32 threads per grid dimension, which a call with

@@ -170,3 +170,38 @@ def test_ffn_f32_more_workgroups_than_one_grid_dimension():
     # the bound of the error test above
     assert float((y[0].double() - want).norm() / want.norm()) <= 1.5e-7
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448))])
+def test_ffn_f32_half_tiles(d, d_ff):
+    """Row tiles of at most 16 rows have MFMAs of their own: experts whose last tile is around that size, alone and behind whole
+    tiles.  The sums are in the same groups of eight products, so the bound of test_ffn_f32_rounding_error holds for them."""
+    import paper_2604_23108_amd as M
+    from gpu_harness import DeviceLayer
+    counts = [15, 16, 17, 47, 48, 49, 2, 0, 9, 80, 1, 31]
+    T, n = sum(counts), 6
+    w = Workload("f32_half", T=T, d=d, n_groups=2, experts_per_group=n, d_ff=d_ff, k_groups=1, k_experts=1, dtype="f32", seed=47)
+    dl = DeviceLayer(w, generate(w), training=False, guard=True)
+    L = dl.layer
+    eidx = np.random.default_rng(6).permutation(np.repeat(np.arange(2 * n), counts)).astype(np.int32).reshape(T, 1)
+    M.mohge_permute(dl.cfg, torch.from_numpy(eidx).cuda(), L.counts, L.offsets, L.perm, L.inv_perm, None, None,
+                    L.ws_permute)
+    L.y_perm.fill_(float("nan"))
+    print(f"[f32 half tiles] d={d} d_ff={d_ff}", flush=True)
+    M.mohge_expert_ffn(dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2, L.y_perm, L.ws_ffn)
+    dl.check_guards()
+    rows = dl.x[L.perm.long()].cpu().double()
+    y = L.y_perm.cpu().double()
+    at, off, norm = 0, 0.0, 0.0
+    for e, c in enumerate(counts):
+        g, i = divmod(e, n)
+        w13, w2 = L.w13[g][i].cpu().double(), L.w2[g][i].cpu().double()
+        a, b = (rows[at:at + c] @ w13.T).split(d_ff[g], dim=1)
+        want, got = (a * torch.sigmoid(a) * b) @ w2.T, y[at:at + c]
+        assert torch.isfinite(got).all()
+        if c:
+            assert float((got - want).abs().max()) <= 5e-6 * float(want.abs().max()), e      # as in the test of the tile edges
+            if 0 < c % 32 <= 16:
+                off, norm = off + float((got - want).square().sum()), norm + float(want.square().sum())
+        at += c
+    assert (off / norm) ** 0.5 <= 1.5e-7
