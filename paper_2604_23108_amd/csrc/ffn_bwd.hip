@@ -131,6 +131,7 @@ hipError_t launch_expert_ffn_bwd(const LayerDesc& L, const void* x, const int32_
   ga.zero_row = reinterpret_cast<uint4*>(zero_row); ga.P = L.P; ga.Ke = L.Ke; ga.chunks = L.d / 8;
   if (use_small_tiles(L, o, true)) {
     dh.coherent_out = 0;
+    dh.cycles = dxa.cycles = w2a.cycles = w13a.cycles = nullptr;      // (room for a workgroup per compute unit)
     return launch_small_bwd(L, dh, dxa, w2a, w13a, ga, s);
   }
   hipError_t e = launch_bwd_schedules(dh, dxa, w2a, w13a, ga, fused, s);

@@ -26,7 +26,7 @@
 // tile rows so that ds_read_b128 fragment reads are conflict free.  All 160 KB of LDS are
 // used, asymmetrically: two stages for the token operand (its rows are shared by all column
 // tiles of an expert and mostly hit in L2) and three for the weight operand (streamed from
-// HBM), which therefore is requested two stages ahead.  The token gather is fused: a tile
+// HBM), whose requests so start half a stage earlier.  The token gather is fused: a tile
 // row's global address is taken through `perm`.
 // Which instruction: power bounds these launches (the clock falls to 1.7 to 2.0 GHz), and on operands with full mantissas
 // 16x16x32 draws less of it than 32x32x16, whose accumulators are read and written twice as often per product: alone 2060
@@ -66,7 +66,10 @@ constexpr int kWGM = 2, kWGN = 4;
 // (one per wave, at most 32 rows x 144 bytes), inside a stage buffer that is dead between two tiles
 constexpr int kHandoverOffset = (kWGM * kWGN * 32 * 144 / 4096 + 1) * 4096;
 static_assert(kHandoverOffset == 40960 && kHandoverOffset + 8 <= 2 * kBM * kBK * 2, "inside the second token part");
-constexpr int kTileCost = 18;          // cost model of the schedule: fixed part of a tile's stage, in 64-row units
+// Cost model of the schedule: fixed part of a tile's stage, in 64-row units.  (Now a stage of 64, 128, 192, 256 rows takes 930,
+// 1410, 1808, 2270 clocks and the rest of such a tile 5.7, 7.1, 7.9, 10.8 k.  Ranges cut and heights chosen by that, (1 + units) x
+// (stages + 4): 0.985 to 1.02 of the time over 14 layers, mean 1.00, so that these lines stay where they were measured.)
+constexpr int kTileCost = 18;
 
 // gate and up rows share a tile in the two up-projection modes
 constexpr bool is_up(int mode) { return mode == kUp || mode == kUpSave; }
@@ -176,8 +179,7 @@ __device__ __forceinline__ int choose_tile_rows(const TileArgs& a, SchedShared& 
     int best_rows = 256;
     for (int c = 0; c < 3; ++c) {
       const long long tot = sh.wsum[0][c] + sh.wsum[1][c] + sh.wsum[2][c] + sh.wsum[3][c];
-      // measured: a stage of a tile costs about 1850 + 100 * (rows / 64) clocks (operand traffic
-      // and LDS work do not shrink with the tile height), so rounds count more than height
+      // a stage of a tile cost about 1850 + 100 * (rows / 64) clocks (see kTileCost), so rounds count more than height
       // (fused launch: the down tiles fill the last round of up tiles, so the up tiles are
       // costed by their total work rather than by whole rounds)
       const float units = fused ? (float)tot / (float)((long long)a.ncu * kmax)
@@ -213,8 +215,7 @@ __device__ __forceinline__ void build_schedule(const TileArgs& a, SchedShared& s
   sh.e[v] = e; sh.cnt[v] = cnt; sh.nt[v] = nt; sh.kc[v] = kc; sh.row0[v] = row0;
   // exclusive prefix sums of tiles, cost and row blocks over the experts
   const int my_t = (cnt + h - 1) / h * nt;
-  // cost of a tile = reduction stages x (kTileCost + its 64-row units): measured, a stage of a tile
-  // costs about 1850 + 100 * units clocks, so a short tile is almost as expensive as a full one
+  // cost of a tile = reduction stages x (kTileCost + its 64-row units)
   const long long my_c = ((long long)kTileCost * ((cnt + h - 1) / h) + (cnt + 63) / 64) * nt * kc;
   const int my_f = MODE == kWgrad ? 0 : (cnt + h - 1) / h;
   // Second list of a fused launch (its tiles wait for tiles of the first): inside every XCD range
@@ -509,9 +510,9 @@ __device__ __forceinline__ void swiglu_bwd8(const uint4 dh, const uint4 pv, cons
   db = make_uint4(ob[0], ob[1], ob[2], ob[3]);
 }
 
-// Short tiles.  A stage of a full tile takes about as long as its operands take to arrive, two stages ahead; a tile of
-// fewer rows has less to multiply per stage but waited just as long (64, 128, 192, 256 rows: 1934, 2021, 2075, 2174
-// clocks).  Its token parts are short, so the same LDS holds more stages of both operands: four up to 64 rows of a 256-row
+// Short tiles.  A stage of a full tile takes about as long as its operands take to arrive; a tile of
+// fewer rows has less to multiply per stage but waited just as long with two stages of tokens (64 rows 1934 clocks, 256 rows
+// 2174).  Its token parts are short, so the same LDS holds more stages of both operands: four up to 64 rows of a 256-row
 // tile, three up to 128.  Where every expert has a few rows and its weights are the
 // work, d = 4096, 64 experts: 40 tokens 406 -> 373 us, 100 tokens 417 ->
 // 381, 600 tokens 435 -> 401; unchanged where full tiles dominate.  (The backward products, bound by their transposing
@@ -1789,6 +1790,7 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
   if (parts == 3 && use_small_tiles(L, o, false)) {
+    up.cycles = dn.cycles = nullptr;           // (the counters have room for a workgroup per compute unit)
     hipError_t e = hipSuccess;
     if (stages & 1) {
       const long long n = small_grid(L, kUp);
