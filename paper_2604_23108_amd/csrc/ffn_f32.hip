@@ -21,7 +21,7 @@
 // the row) through two stages of 64 reduction indices (48 KB: three workgroups per compute unit), one
 // barrier per stage; the fragments of a stage are in registers while the next but one is on its way.
 // A lane's 128-bit fragment read holds four consecutive reduction indices of one row and feeds four
-// MFMAs; both operands use the same assignment.
+// MFMAs; both operands use the same assignment.  Sixteen indices make two groups: the first two of each four, then the last two.
 //
 // Every product of an MFMA rounds the running sum, so a chain of n products carries about n/2 roundings.  A chain
 // here is the eight products of one such group; the sums of two groups are added, and the pairs go into an fp64
@@ -101,7 +101,8 @@ __device__ __forceinline__ bool f32_row_tile(const F32Args& a, int m, int lane, 
 }
 
 // HALF: a tile of at most 16 rows.  32x32x2 would spend as long on 16 rows as on 32; 16x16x4 takes half the time for the same
-// products, at the same rate, in groups of the same eight.  (For 32 rows too it was 1.5 to 2.5 % slower: twice the MFMAs.)  Layer
+// products, at the same rate.  Both add up the same groups of eight in the same order, so that the bits of a row do not depend on
+// how full its tile is (a test compares them).  (For 32 rows too it was 1.5 to 2.5 % slower: twice the MFMAs.)  Layer
 // call before / now: 9 tokens of 25 experts, d = 1344, 102 / 77 us, 60 tokens 105 / 85; 60 tokens of 32 experts, d = 1024, 94 / 76, 512 tokens 202 / 197.
 template <bool UP, bool HALF>
 __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, int e, int row, int rows, int n0,
@@ -201,10 +202,11 @@ __device__ __forceinline__ void f32_tile(const F32Args& a, unsigned char* lds, i
 #pragma unroll
       for (int r = 0; r < 16; ++r) { n0[r] = 0.f; n1[r] = 0.f; }
 #pragma unroll
-      for (int c = 0; c < 4; ++c) n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k][0][c], use.x[k][c], n0, 0, 0, 0);
+      for (int c = 0; c < 4; ++c)
+        n0 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + c % 2][0][c / 2], use.x[k + c % 2][c / 2], n0, 0, 0, 0);
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + 1][0][c], use.x[k + 1][c], n1, 0, 0, 0);
+        n1 = __builtin_amdgcn_mfma_f32_32x32x2f32(use.b[k + c % 2][0][2 + c / 2], use.x[k + c % 2][2 + c / 2], n1, 0, 0, 0);
       fold();
 #pragma unroll
       for (int r = 0; r < NS; ++r) pair[r] = n0[r] + n1[r];

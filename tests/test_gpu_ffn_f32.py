@@ -175,7 +175,8 @@ def test_ffn_f32_more_workgroups_than_one_grid_dimension():
 @pytest.mark.parametrize("d,d_ff", [(64, (64, 128)), (192, (320, 64)), (1024, (192, 448))])
 def test_ffn_f32_half_tiles(d, d_ff):
     """Row tiles of at most 16 rows have MFMAs of their own: experts whose last tile is around that size, alone and behind whole
-    tiles.  The sums are in the same groups of eight products, so the bound of test_ffn_f32_rounding_error holds for them."""
+    tiles.  Their sums are in groups of eight products as well, so the bound of test_ffn_f32_rounding_error holds for them: here for
+    the rows of these tiles alone."""
     import paper_2604_23108_amd as M
     from gpu_harness import DeviceLayer
     counts = [15, 16, 17, 47, 48, 49, 2, 0, 9, 80, 1, 31]
@@ -202,6 +203,31 @@ def test_ffn_f32_half_tiles(d, d_ff):
         if c:
             assert float((got - want).abs().max()) <= 5e-6 * float(want.abs().max()), e      # as in the test of the tile edges
             if 0 < c % 32 <= 16:
-                off, norm = off + float((got - want).square().sum()), norm + float(want.square().sum())
+                last = slice(c - c % 32, c)
+                off, norm = off + float((got - want)[last].square().sum()), norm + float(want[last].square().sum())
         at += c
     assert (off / norm) ** 0.5 <= 1.5e-7
+
+
+@pytest.mark.parametrize("d,F", [(64, 64), (192, 320), (1024, 896)])
+def test_ffn_f32_a_row_does_not_depend_on_its_tile(d, F):
+    """The result of a row is the same, bit for bit, whether the rows around it fill a tile of 32 or leave it with 16 or fewer:
+    both kinds of tile add up the same groups of eight products in the same order."""
+    import paper_2604_23108_amd as M
+    gen = torch.Generator().manual_seed(d + F)
+    x = torch.randn((64, d), generator=gen).cuda()
+    w13, w2 = (torch.randn((1, 2 * F, d), generator=gen) * 0.1).cuda(), (torch.randn((1, d, F), generator=gen) * 0.1).cuda()
+
+    def layer(T):
+        cfg = M.Config(T=T, d=d, n_groups=1, experts_per_group=1, d_ff=(F,), k_groups=1, k_experts=1,
+                       select_mode=M.SELECT_PER_GROUP, dtype=M.F32)
+        y = torch.full((T, d), float("nan"), device="cuda")
+        ws = torch.empty(M.mohge_workspace_size(cfg, M.CALL_EXPERT_FFN), dtype=torch.uint8, device="cuda")
+        M.mohge_expert_ffn(cfg, x[:T].contiguous(), None, torch.tensor([0, T], dtype=torch.int32, device="cuda"), [w13], [w2], y, ws)
+        return y.cpu()
+
+    print(f"[f32 tile of a row] d={d} F={F}", flush=True)
+    want = layer(64)
+    assert torch.isfinite(want).all()
+    for T in (1, 7, 15, 16, 17, 32, 33, 47, 48, 49):
+        assert torch.equal(layer(T), want[:T]), T
