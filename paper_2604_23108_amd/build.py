@@ -8,6 +8,11 @@ import os
 import subprocess
 import sys
 
+try:
+    from .lds_hazards import hazards_of_file
+except ImportError:                      # run as a script
+    from lds_hazards import hazards_of_file
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
@@ -23,9 +28,18 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJDIR, src.replace(".hip", ".o"))
-    cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+# Sources whose copies to LDS are inline assembly: their code is looked through for copies that read a scalar register too early,
+# which this compiler's output is free of with the one wait state that a copy has.
+LDS_COPY_SOURCES = ["ffn_tiled.hip"]
+
+
+def device_assembly(obj: str) -> str:
+    """The assembly beside an object of LDS_COPY_SOURCES."""
+    return obj[:-2] + "-hip-amdgcn-amd-amdhsa-gfx950.s"
+
+
+def _hipcc(src: str, obj: str, extra) -> None:
+    cmd = ["hipcc", *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     p = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in p.stderr.splitlines() if noise not in l)
@@ -33,7 +47,19 @@ def _compile(src: str) -> str:
         raise RuntimeError(f"hipcc failed for {src}:\n{err}")
     if err.strip():
         sys.stderr.write(err + "\n")
-    return obj
+
+
+def _compile(src: str) -> str:
+    obj = os.path.join(OBJDIR, src.replace(".hip", ".o"))
+    if src not in LDS_COPY_SOURCES:
+        _hipcc(src, obj, [])
+        return obj
+    for nop in ([], ['-DMOHGE_LDS_COPY_NOP="4"']):       # one wait state in front of a copy, then the most that one may need
+        _hipcc(src, obj, ["--save-temps=obj", *nop])
+        bad = hazards_of_file(device_assembly(obj))[1]
+        if not bad:
+            return obj
+    raise RuntimeError(f"{src}: copies to LDS read a scalar register too early: {bad[:3]}")
 
 
 def _link(out: str, objs, extra=()) -> None:

@@ -458,19 +458,22 @@ __device__ __forceinline__ void wait_vmcnt() {
 // for all of them, and in front of a transposing read (an intrinsic) it waits for every copy on its way.  M0 holds the LDS
 // destination; the compiler puts it there (an operand bound to the register, so it knows what M0 holds before and after).
 // One wait state, which the hardware asks for after a scalar write of M0; a vector instruction that wrote it or the base would
-// need five, and a test looks for one in the code the compiler made (with five everywhere: 602 -> 608 us for 8192 rows, d =
-// 4096).  Both address forms write no register; completion is awaited by the explicit vmcnt waits of the stages.
+// need five: the build looks for one in the code the compiler made and takes five everywhere if it finds it (602 -> 608 us for
+// 8192 rows, d = 4096).  Both address forms write no register; completion is awaited by the explicit vmcnt waits of the stages.
+#ifndef MOHGE_LDS_COPY_NOP
+#define MOHGE_LDS_COPY_NOP "0"
+#endif
 // lds_addr: address in the workgroup's LDS (lds_address() of the buffer plus an offset), wave-uniform.
 __device__ __forceinline__ int lds_address(const unsigned char* lds) {
   return (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)lds;
 }
 __device__ __forceinline__ void async_copy16(const void* gptr, int lds_addr) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+  asm volatile("s_nop " MOHGE_LDS_COPY_NOP "\n\tglobal_load_lds_dwordx4 %0, off"
                ::"v"(gptr), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 // wave-uniform base, 32-bit byte offset per lane (half the registers)
 __device__ __forceinline__ void async_copy16(const void* uniform_base, uint32_t offset, int lds_addr) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_nop " MOHGE_LDS_COPY_NOP "\n\tglobal_load_lds_dwordx4 %0, %1"
                ::"v"(offset), "s"(uniform_base), "{m0}"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 

@@ -3,62 +3,10 @@ import os
 import re
 import subprocess
 
+import pytest
+
 from paper_2604_23108_amd import build
-
-WAIT_STATES = 5          # between a vector instruction that writes a scalar register and a memory access that reads it
-
-
-def _scalars(text):
-    found = {"m0"} if re.search(r"\bm0\b", text) else set()
-    for lo, hi, one in re.findall(r"\bs\[(\d+):(\d+)\]|\bs(\d+)\b", text):
-        found |= {f"s{one}"} if one else {f"s{i}" for i in range(int(lo), int(hi) + 1)}
-    return found
-
-
-def hazards(lines):
-    """The number of copies, and those whose M0 or base a vector instruction wrote less than WAIT_STATES before on some path,
-    or whose M0 the instruction right before them wrote."""
-    jumps = {}
-    for i, line in enumerate(lines):
-        if line.startswith(("s_cbranch", "s_branch")):
-            jumps.setdefault(line.split()[1], []).append(i)
-
-    def before(i):
-        """Indices of the instructions that may run right before line i."""
-        todo, seen, found = [i - 1], set(), []
-        while todo:
-            k = todo.pop()
-            if k < 0 or k in seen:
-                continue
-            seen.add(k)
-            if lines[k].endswith(":"):
-                todo += [k - 1]
-                found += jumps.get(lines[k][:-1], [])
-            elif not (lines[k].startswith(("s_branch", "s_endpgm", "s_setpc")) and k + 1 < len(lines) and lines[k + 1].endswith(":")):
-                found.append(k)
-        return found
-
-    bad, copies = [], 0
-    for i, line in enumerate(lines):
-        if not line.startswith("global_load_lds"):
-            continue
-        copies += 1
-        reads = _scalars(line.split(None, 1)[1]) | {"m0"}
-        todo, seen = [(k, 0) for k in before(i)], set()
-        while todo:
-            k, states = todo.pop()
-            if (k, states) in seen or states >= WAIT_STATES:
-                continue
-            seen.add((k, states))
-            op, _, rest = lines[k].replace("\t", " ").partition(" ")
-            if op == "s_nop":
-                todo += [(q, states + int(rest, 0) + 1) for q in before(k)]
-                continue
-            written = _scalars(rest.split(",")[0])
-            if written & reads and (op.startswith("v_") or (states == 0 and "m0" in written)):
-                bad.append((lines[k], line))
-            todo += [(q, states + 1) for q in before(k)]
-    return copies, bad
+from paper_2604_23108_amd.lds_hazards import hazards, hazards_of_file
 
 
 def test_the_look_back_finds_what_it_looks_for():
@@ -75,7 +23,37 @@ def test_no_copy_reads_a_scalar_register_too_early(tmp_path):
     out = tmp_path / "ffn_tiled.s"
     subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ffn_tiled.hip"), "-o", str(out)],
                    check=True, capture_output=True)
-    lines = [re.sub(r"[;/].*", "", l).strip() for l in out.read_text().split("\n")]
-    copies, bad = hazards([l for l in lines if l and (l.endswith(":") or not l.startswith((".", "#")))])
+    copies, bad = hazards_of_file(out)
     assert copies > 1000
     assert not bad, bad[:5]
+
+
+def test_every_source_with_such_copies_is_looked_through():
+    of = [f for f in os.listdir(build.CSRC) if re.search(r'"[^"\n]*global_load_lds[^"\n]*"', open(os.path.join(build.CSRC, f)).read())]
+    assert sorted(of) == sorted(build.LDS_COPY_SOURCES)
+
+
+PLANTED = """#include <hip/hip_runtime.h>
+#ifndef MOHGE_LDS_COPY_NOP
+#define MOHGE_LDS_COPY_NOP "0"
+#endif
+__global__ void k(const void* p, int i) {
+  asm volatile("v_readfirstlane_b32 s4, %0\\n\\ts_mov_b32 s5, 0\\n\\ts_nop " NOP "\\n\\tglobal_load_lds_dwordx4 %0, s[4:5]"
+               ::"v"(i), "{m0}"(0) : "memory", "s4", "s5");
+}
+"""
+
+
+@pytest.mark.parametrize("nop,ends_well", [("MOHGE_LDS_COPY_NOP", True), ('"0"', False)])
+def test_build_answers_a_copy_too_early_with_more_wait_states(tmp_path, monkeypatch, nop, ends_well):
+    """A planted one is compiled again with the wait states it needs; where that does not help the build fails."""
+    (tmp_path / "planted.hip").write_text(PLANTED.replace("NOP \"\\n", nop + " \"\\n", 1))
+    for name in ("CSRC", "OBJDIR"):
+        monkeypatch.setattr(build, name, str(tmp_path))
+    monkeypatch.setattr(build, "LDS_COPY_SOURCES", ["planted.hip"])
+    if ends_well:
+        copies, bad = hazards_of_file(build.device_assembly(build._compile("planted.hip")))
+        assert copies == 1 and not bad
+    else:
+        with pytest.raises(RuntimeError, match="too early"):
+            build._compile("planted.hip")
