@@ -546,8 +546,10 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // the token modes, and their tokens where they are neighbouring rows (the up modes gather theirs through perm)
   constexpr bool OFFA = !WG && !UP, OFFB = !WG;
   // (a value the compiler cannot trace, here and before the epilogue: what depends on the lane would be computed once before
-  // the first tile and kept through every main loop, in registers that those do not have)
+  // the first tile and kept through every main loop, in registers that those do not have.  Its range is told again: divisions of
+  // a number that may be negative are three times as long)
   asm volatile("" : "+v"(lane));
+  lane &= 63;
   long long ts[6] = {0, 0, 0, 0, 0, 0};
   PROBE_T(0);
   constexpr int BM = GEO::BM, BN = GEO::BN, BK = kBK;
@@ -670,42 +672,6 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   }
   const int ld_off = w * 1024;      // + j * NWAVES * 1024: wave-uniform destination inside a part
 
-  // ---- LDS offsets of the MFMA operand fragments ---------------------------------------
-  // fragment row = base + lane%16, logical chunk = 4*kk + lane/16
-  // Reduction-major parts: the transposing read works on groups of 16 lanes.  Lane 4*a + b of a
-  // group passes the address of 4 features (8 bytes) of row k0 + a at feature m0 + 4*b and
-  // gets back rows k0..k0+3 of feature m0 + (its index in the group).  Group q of the wave
-  // covers the fragment's 16 features and rows 8*q.. of the k-step, so two
-  // reads (k0, k0 + 4) give a lane its 8 consecutive reduction indices of one fragment row.
-  const int frow = lane & 15, fh = lane >> 4;
-  const int ta = (lane & 15) >> 2, tb = lane & 3;
-  int foff[KK], foff_t[KK];       // plain parts / reduction-major parts (only one is live
-                                  // unless the two operands differ)
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    foff_t[kk] = (32 * kk + 8 * fh + ta) * TRB_ROW + (tb >> 1) * 16 + (tb & 1) * 8;
-    foff[kk] = frow * ROWB + (((4 * kk + fh) ^ ((frow >> SH) & (CH - 1))) << 4);
-  }
-  // first feature of a fragment -> its 16-byte chunk, swizzled like the loads wrote it
-  auto tr_base = [&](int feat) { return (((feat >> 3) ^ (4 * ta) ^ (2 * (fh & 1))) << 4); };
-  int fbase_a[MT], fbase_b[NW];   // token fragments (32-row blocks interleaved over the wave rows), weight fragments
-#pragma unroll
-  for (int ti = 0; ti < MT; ++ti) {
-    const int row = ((ti >> 1) * WGM + wm) * 32 + (ti & 1) * 16;
-    fbase_a[ti] = TRA ? tr_base(row) : row * ROWB;
-  }
-#pragma unroll
-  for (int fi = 0; fi < NW; ++fi) {
-    int row;
-    if constexpr (UP) {
-      constexpr int NWh = NW / 2;
-      row = (fi < NWh) ? wn * (WTN / 2) + fi * 16 : BN / 2 + wn * (WTN / 2) + (fi - NWh) * 16;
-    } else {
-      row = wn * WTN + fi * 16;
-    }
-    fbase_b[fi] = TRB ? tr_base(row) : row * ROWB;
-  }
-
   f32x4 acc[NW][MT];
 #pragma unroll
   for (int fi = 0; fi < NW; ++fi)
@@ -715,26 +681,6 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       for (int r = 0; r < 4; ++r) acc[fi][ti][r] = 0.f;
 
   const int KT = K / BK;
-  // a fragment at p: plain, or two transposing reads
-  auto read_frag = [&](const unsigned char* p, auto TR) {
-    if constexpr (decltype(TR)::value) {
-      typedef short s16x4 __attribute__((ext_vector_type(4)));
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * TRB_ROW));
-      const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      return __builtin_bit_cast(bf16x8, v);
-    } else {
-      return *reinterpret_cast<const bf16x8*>(p);
-    }
-  };
-  auto read_a = [&](const unsigned char* pa, int kk, int ti) {
-    return read_frag(pa + fbase_a[ti] + (TRA ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRA>{});
-  };
-  auto read_b = [&](const unsigned char* pb, int kk, int fi) {
-    return read_frag(pb + fbase_b[fi] + (TRB ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRB>{});
-  };
   // reduction-major operands: load j of a stage starts TPL*NWAVES*j rows further down.  In kWgrad the rows are routed tokens;
   // in the expert's last stage those at or past its count read the zero row instead (ENDS: the stage may be that one; without,
   // every lane's row is there, and what the choice costs per load, a branch among the MFMAs, is saved)
@@ -791,8 +737,78 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   if (FAR && KT > 2) {
 #pragma unroll
     for (int j = 0; j < B_LOADS; ++j) issue_b(2, 2, j, Ends{});
-    wait_vmcnt<A_LOADS + 2 * B_LOADS>();
-  } else if (KT >= AHEAD) wait_vmcnt<(AHEAD - 1) * (A_LOADS + B_LOADS)>();
+  }
+
+  // ---- LDS offsets of the MFMA operand fragments ---------------------------------------
+  // fragment row = base + lane%16, logical chunk = 4*kk + lane/16
+  // Reduction-major parts: the transposing read works on groups of 16 lanes.  Lane 4*a + b of a
+  // group passes the address of 4 features (8 bytes) of row k0 + a at feature m0 + 4*b and
+  // gets back rows k0..k0+3 of feature m0 + (its index in the group).  Group q of the wave
+  // covers the fragment's 16 features and rows 8*q.. of the k-step, so two
+  // reads (k0, k0 + 4) give a lane its 8 consecutive reduction indices of one fragment row.
+  const int frow = lane & 15, fh = lane >> 4;
+  const int ta = (lane & 15) >> 2, tb = lane & 3;
+  int foff[KK], foff_t[KK];       // plain parts / reduction-major parts (only one is live
+                                  // unless the two operands differ)
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    foff_t[kk] = (32 * kk + 8 * fh + ta) * TRB_ROW + (tb >> 1) * 16 + (tb & 1) * 8;
+    foff[kk] = frow * ROWB + (((4 * kk + fh) ^ ((frow >> SH) & (CH - 1))) << 4);
+  }
+  // first feature of a fragment -> its 16-byte chunk, swizzled like the loads wrote it
+  auto tr_base = [&](int feat) { return (((feat >> 3) ^ (4 * ta) ^ (2 * (fh & 1))) << 4); };
+  int fbase_a[MT], fbase_b[NW];   // token fragments (32-row blocks interleaved over the wave rows), weight fragments
+#pragma unroll
+  for (int ti = 0; ti < MT; ++ti) {
+    const int row = ((ti >> 1) * WGM + wm) * 32 + (ti & 1) * 16;
+    fbase_a[ti] = TRA ? tr_base(row) : row * ROWB;
+  }
+#pragma unroll
+  for (int fi = 0; fi < NW; ++fi) {
+    int row;
+    if constexpr (UP) {
+      constexpr int NWh = NW / 2;
+      row = (fi < NWh) ? wn * (WTN / 2) + fi * 16 : BN / 2 + wn * (WTN / 2) + (fi - NWh) * 16;
+    } else {
+      row = wn * WTN + fi * 16;
+    }
+    fbase_b[fi] = TRB ? tr_base(row) : row * ROWB;
+  }
+  // (They are worked out here, under the wait for the first stage.  Placed by the compiler, they stood between its arrival and the
+  // first products: a weight-gradient tile of one stage took 2400 clocks for those, now 2130.)
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    if constexpr (TRA || TRB) asm volatile("" : "+v"(foff_t[kk]));
+    if constexpr (!TRA || !TRB) asm volatile("" : "+v"(foff[kk]));
+  }
+  if constexpr (TRA)
+#pragma unroll
+    for (int ti = 0; ti < MT; ++ti) asm volatile("" : "+v"(fbase_a[ti]));
+  if constexpr (TRB)
+#pragma unroll
+    for (int fi = 0; fi < NW; ++fi) asm volatile("" : "+v"(fbase_b[fi]));
+  // a fragment at p: plain, or two transposing reads
+  auto read_frag = [&](const unsigned char* p, auto TR) {
+    if constexpr (decltype(TR)::value) {
+      typedef short s16x4 __attribute__((ext_vector_type(4)));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * TRB_ROW));
+      const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_bit_cast(bf16x8, v);
+    } else {
+      return *reinterpret_cast<const bf16x8*>(p);
+    }
+  };
+  auto read_a = [&](const unsigned char* pa, int kk, int ti) {
+    return read_frag(pa + fbase_a[ti] + (TRA ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRA>{});
+  };
+  auto read_b = [&](const unsigned char* pb, int kk, int fi) {
+    return read_frag(pb + fbase_b[fi] + (TRB ? foff_t[kk] : foff[kk]), std::integral_constant<bool, TRB>{});
+  };
+  if (FAR && KT > 2) wait_vmcnt<A_LOADS + 2 * B_LOADS>();
+  else if (KT >= AHEAD) wait_vmcnt<(AHEAD - 1) * (A_LOADS + B_LOADS)>();
   else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   MOHGE_PIN();
@@ -955,6 +971,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     static_assert(32 * CPR % 64 == 0, "whole wave-wide copies");
     unsigned char* my = lds + w * EPI_BYTES;
     asm volatile("" : "+v"(lane));
+    lane &= 63;
     const int tok_l = lane & 15, fsub = (lane >> 4) * 4;
     const int ncols = red_d(MODE) ? F : (WG ? a.Ncols[g] : a.d);
     const int col0 = rec.n0 + wn * OC;
