@@ -690,6 +690,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     const uint16_t* p = base + (unsigned long long)(unsigned)(tok0 + t) * ld;
     if constexpr (decltype(ENDS)::value) {
       const uint16_t* row = reinterpret_cast<const uint16_t*>(reinterpret_cast<const unsigned char*>(p) + off);
+      asm("" : "+v"(row));          // (computed in every lane: as a branch per load it waits for its scalar operands each time)
       async_copy16(t + trow0 < ntok ? row : zsrc, to);
     } else {
       async_copy16(p, off, to);
@@ -975,6 +976,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     const int tok_l = lane & 15, fsub = (lane >> 4) * 4;
     const int ncols = red_d(MODE) ? F : (WG ? a.Ncols[g] : a.d);
     const int col0 = rec.n0 + wn * OC;
+    // kWgrad: first row of the tile in the expert's gradient
+    uint16_t* wout = nullptr;
+    if constexpr (WG) wout = a.Wout[g] + ((long long)e_i * a.Mrows[g] + rec.row_start) * ncols;
     // kUpSave makes three passes over the patch: h, then the backward factors p and q
     constexpr int NPASS = MODE == kUpSave ? 3 : 1;
     constexpr int NIT = 32 * CPR / 64;     // row-segment copies per lane and fragment
@@ -1043,8 +1047,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
           const int col = col0 + c * 8;
           if (trow < rec.rows && col < ncols) {
             if constexpr (WG) {
-              uint16_t* dst = a.Wout[g] + ((long long)e_i * a.Mrows[g] + rec.row_start + trow) * ncols + col;
-              *reinterpret_cast<uint4*>(dst) = v;
+              *reinterpret_cast<uint4*>(wout + (unsigned long long)(unsigned)trow * (unsigned)ncols + col) = v;
             } else if constexpr (DH) {
               // v holds dh; the stored factors turn it into the gradients of the pre-activations
               const long long at = (long long)(rec.row_start + trow) * a.ldpre + col;
