@@ -82,10 +82,14 @@ constexpr bool red_d(int mode) { return is_up(mode) || mode == kDgradH; }
 // Tile geometry.  Big: 256 x 256 tiles, 8 waves, all 160 KB of LDS, one persistent workgroup per
 // compute unit.  Small: 128 x 128 tiles, 4 waves, half the LDS, two workgroups per compute unit (the
 // launches that would leave compute units idle with big tiles, see use_small_tiles).
-struct BigTile { static constexpr int BM = kBM, BN = kBN, WGM = kWGM, WGN = kWGN; };
-struct SmallTile { static constexpr int BM = 128, BN = 128, WGM = 2, WGN = 2; };
+struct BigTile { static constexpr int BM = kBM, BN = kBN, WGM = kWGM, WGN = kWGN; static constexpr bool LONG = false; };
+// Long: big tiles of weights whose rows are so long (kLongRow) that a 32-bit offset does not reach from a tile's first row to its last.
+// With its addresses everywhere 16384 tokens of d = 4096 took 1.4 % longer (2031 -> 2062 us).
+struct LongTile : BigTile { static constexpr bool LONG = true; };
+constexpr int kLongRow = 1 << 23;       // 256 rows of 2 bytes times this: 2^32 bytes
+struct SmallTile { static constexpr int BM = 128, BN = 128, WGM = 2, WGN = 2; static constexpr bool LONG = false; };
 // Tall: the small form's token modes, up to 192 rows of one expert (see small_token_tile)
-struct TallTile { static constexpr int BM = 192, BN = 128, WGM = 2, WGN = 2; };
+struct TallTile : SmallTile { static constexpr int BM = 192; };
 
 template <int MODE>
 struct Shape {
@@ -616,6 +620,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // transposing read touch at once (k0..k0+3 and k0+8..k0+11) then sit in different banks.
   constexpr int TRB_ROW = BN * 2, TCH = BN / 8, TPL = 1024 / TRB_ROW;
   static_assert(!(TRA || TRB) || (NWAVES * TPL % 16 == 0 && B_LOADS == BN * CH / NT), "part layout");
+  // (trow0 <= 15: from there the offset of a row has 32 bits up to rows of 2^27 elements; the list of a backward call with rows of
+  // 2^24 would fill the memory of the GPU)
   const int trow0 = TPL * w + lane / TCH;         // row of load 0; load j: + TPL*NWAVES*j
   const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3)) ^ (2 * ((trow0 >> 3) & 1));
   const uint16_t* zsrc = nullptr;
@@ -660,6 +666,8 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   // plain weights: row n0 of the tile's matrix; up modes: W_up is F rows further, and a wave-wide load holds rows of one of them
   static_assert(!UP || (BN / 2) % (NWAVES * RPL) == 0, "loads of one half");
   const int ncols_b = UP ? F : a.d;
+  // LONG: first row of wave-wide load j in its half, and from there the lane's row (at most 7 further)
+  auto first_row_b = [&](int j) { return min((j * NWAVES + w) * RPL % (UP ? BN / 2 : BN), ncols_b - 1 - rec.n0); };
   if constexpr (!TRB) base_b = a.W[g] + ((long long)e_i * (UP ? 2 : 1) * ncols_b + rec.n0) * a.ldw[g];
 #pragma unroll
   for (int j = 0; j < (TRB ? 0 : B_LOADS); ++j) {
@@ -668,6 +676,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     // the row of the tile's weights, from the first one of its half (up modes: [0, BN/2) W_gate rows n0.., the rest W_up rows)
     int r = UP ? row % (BN / 2) : row;
     if (rec.n0 + r > ncols_b - 1) r = ncols_b - 1 - rec.n0;
+    if constexpr (GEO::LONG) r -= first_row_b(j);
     off_b[j] = ((uint32_t)r * (uint32_t)a.ldw[g] + chunk * 8) * 2u;
   }
   const int ld_off = w * 1024;      // + j * NWAVES * 1024: wave-uniform destination inside a part
@@ -716,8 +725,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
       const unsigned t = stage * BK + TPL * NWAVES * j;           // row of this load, less trow0
       async_copy16(base_b + (unsigned long long)t * tr_ldb, off_b[0], to);
     } else {
-      const long long half = UP && j * NWAVES * RPL >= BN / 2 ? (long long)F * a.ldw[g] : 0;
-      async_copy16(base_b + half + stage * BK, off_b[j], to);
+      long long first = UP && j * NWAVES * RPL >= BN / 2 ? (long long)F * a.ldw[g] : 0;
+      if constexpr (GEO::LONG) first += (long long)first_row_b(j) * a.ldw[g];
+      async_copy16(base_b + first + stage * BK, off_b[j], to);
     }
   };
 
@@ -1105,7 +1115,7 @@ __device__ __forceinline__ void run_tile_rows(const TileArgs& a, const TileRec& 
 // atomic's latency hides behind the tile) and the result is passed to the other waves
 // through one LDS word between the tiles.  Which workgroup computes a tile has no influence
 // on the tile's result, so the output stays bit-identical from run to run.
-template <int MODE>
+template <int MODE, typename GEO = BigTile>
 __global__ void __launch_bounds__(Shape<MODE>::THREADS) ffn_tile_kernel(const TileArgs a) {
   extern __shared__ __align__(1024) unsigned char lds[];
   // LDS word for the hand-over: beyond the epilogue patches, inside a stage buffer that is
@@ -1141,7 +1151,7 @@ __global__ void __launch_bounds__(Shape<MODE>::THREADS) ffn_tile_kernel(const Ti
       }
     }
     if (ok) {
-      run_tile_rows<MODE>(a, rec, lds, lane, w, nullptr);
+      run_tile_rows<MODE, GEO>(a, rec, lds, lane, w, nullptr);
     }
     __syncthreads();       // every wave is past its epilogue (and past reading the old word)
     if (threadIdx.x == 0) *reinterpret_cast<volatile int*>(lds + kBcastOffset) = t_next;
@@ -1698,10 +1708,10 @@ int tile_num_cus() {
   return n;
 }
 
-template <int MODE>
+template <int MODE, typename GEO = BigTile>
 static hipError_t launch_stage(const TileArgs& a, hipStream_t s) {
   constexpr size_t smem = (size_t)(kStagesA * kBM + kStagesB * kBN) * kBK * 2;
-  auto kern = ffn_tile_kernel<MODE>;
+  auto kern = ffn_tile_kernel<MODE, GEO>;
   static std::atomic<unsigned long long> allowed{0};
   const hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), (int)smem, allowed);
   if (e != hipSuccess) return e;
@@ -1826,6 +1836,19 @@ hipError_t launch_ffn_tiled(const LayerDesc& L, const void* x, const int32_t* pe
     t.force_rows = o.tile_rows[st];
   }
   up.fam_done = dn.fam_done = reinterpret_cast<int*>(p);
+  // weight rows of kLongRow elements: the two lists one after the other, in the form that has 64-bit addresses
+  if (L.d >= kLongRow || L.Fmax >= kLongRow) {
+    if (parts & 1) {
+      hipLaunchKernelGGL(ffn_schedule_kernel, dim3(stages == 3 ? 2 : 1), dim3(256), 0, s, up, dn, stages);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    if (!(parts & 2)) return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (stages & 1) e = pre ? launch_stage<kUpSave, LongTile>(up, s) : launch_stage<kUp, LongTile>(up, s);
+    if (e == hipSuccess && (stages & 2)) e = launch_stage<kDown, LongTile>(dn, s);
+    return e;
+  }
   if (parts == 3 && use_small_tiles(L, o, false)) {
     up.cycles = dn.cycles = nullptr;           // (the counters have room for a workgroup per compute unit)
     hipError_t e = hipSuccess;
