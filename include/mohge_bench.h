@@ -125,8 +125,8 @@ size_t mohge_bench_decode_trace_bytes(const mohge_config* cfg);
  * (a multiple of 512) with the access pattern of the decode kernels on rows of that size, the
  * waves walking their rows in step (staggered = 0) or each from a different start (1).  out:
  * DEVICE, at least 16 bytes, may receive a dummy value.  bytes_read: HOST.
- * mohge_probe_mfma enqueues 1024 workgroups that issue nothing but independent chains of
- * v_mfma_f32_32x32x16_bf16, `iters` per chain; *flops (HOST) receives the FLOPs of the launch;
+ * mohge_probe_mfma enqueues 1024 workgroups that issue nothing but eight independent chains of
+ * v_mfma_f32_16x16x32_bf16 per wave, the instruction of the large tiles, in their order, `iters` per chain; *flops (HOST) receives the FLOPs of the launch;
  * out: DEVICE, at least 1 MiB.  Time either with events on `stream`.
  */
 int mohge_probe_read(const void* buf, size_t bytes, int row_bytes, int staggered, void* out,

@@ -6,14 +6,15 @@
 //                - rows: the access pattern of the decode kernels (a wave owns 32 rows of
 //                  `row_bytes`; one wave instruction reads 16 rows x 64 bytes), the waves walking
 //                  along their rows in step, or each starting at a different step (staggered);
-//   MFMA probe   every wave issues independent chains of v_mfma_f32_32x32x16_bf16 and nothing
-//                else: the matrix-core rate the chip sustains under that load.
+//   MFMA probe   every wave issues independent chains of the instruction of the large tiles, v_mfma_f32_16x16x32_bf16, in their
+//                order (every one shares an operand with the one before it) and nothing else: the matrix-core rate the chip
+//                sustains under that load.
 #include "common.h"
 
 namespace mohge {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kProbeU = 8;                          // 16-byte loads in flight per lane and row set
 constexpr int kProbeChunk = 256 * kProbeU;          // uint4 per workgroup iteration (32 KB)
@@ -58,25 +59,36 @@ __global__ void __launch_bounds__(256) probe_read_rows(const unsigned char* __re
   if (acc == 0x12345678u) out[0] = acc;
 }
 
-constexpr int kMfmaChains = 4;
+constexpr int kMfmaA = 4, kMfmaB = 2;         // operands of a wave; a chain for each pair
 __global__ void __launch_bounds__(256) probe_mfma(float* out, int iters) {
-  bf16x8 a, b;
+  bf16x8 a[kMfmaA], b[kMfmaB];
   // operands with full mantissas, different in every lane (constant small integers would toggle
   // few bits and draw less power than real data)
-  for (int i = 0; i < 8; ++i) {
-    const unsigned h = (threadIdx.x * 8u + i + blockIdx.x * 2048u) * 2654435761u;
-    a[i] = (__bf16)((float)((h >> 9) & 1023u) / 512.f - 1.f);
-    b[i] = (__bf16)((float)((h >> 19) & 1023u) / 512.f - 1.f);
-  }
-  f32x16 acc[kMfmaChains];
-  for (int j = 0; j < kMfmaChains; ++j)
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  auto fill = [&](bf16x8& v, int f) {
+    for (int i = 0; i < 8; ++i) {
+      const unsigned h = ((threadIdx.x * 8u + i + blockIdx.x * 2048u) * 8u + f) * 2654435761u;
+      v[i] = (__bf16)((float)((h >> 14) & 1023u) / 512.f - 1.f);
+    }
+  };
+  for (int f = 0; f < kMfmaA; ++f) fill(a[f], f);
+  for (int f = 0; f < kMfmaB; ++f) fill(b[f], kMfmaA + f);
+  f32x4 acc[kMfmaB][kMfmaA];
+  for (int t = 0; t < kMfmaB; ++t)
+    for (int f = 0; f < kMfmaA; ++f)
+      for (int r = 0; r < 4; ++r) acc[t][f][r] = 0.f;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
-    for (int j = 0; j < kMfmaChains; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[j], 0, 0, 0);
+    for (int t = 0; t < kMfmaB; ++t)
+#pragma unroll
+      for (int i = 0; i < kMfmaA; ++i) {
+        const int f = t & 1 ? kMfmaA - 1 - i : i;      // to and fro
+        acc[t][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[f], b[t], acc[t][f], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
   }
   float s = 0.f;
-  for (int j = 0; j < kMfmaChains; ++j) s += acc[j][0];
+  for (int t = 0; t < kMfmaB; ++t)
+    for (int f = 0; f < kMfmaA; ++f) s += acc[t][f][0];
   out[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
@@ -104,7 +116,7 @@ hipError_t launch_probe_read(const void* buf, size_t bytes, int row_bytes, int s
 
 hipError_t launch_probe_mfma(void* out, int blocks, int iters, double* flops, hipStream_t s) {
   hipLaunchKernelGGL(probe_mfma, dim3(blocks), dim3(256), 0, s, static_cast<float*>(out), iters);
-  *flops = (double)blocks * 4 * kMfmaChains * (double)iters * 2.0 * 32 * 32 * 16;
+  *flops = (double)blocks * 4 * kMfmaA * kMfmaB * (double)iters * 2.0 * 16 * 16 * 32;
   return hipGetLastError();
 }
 
