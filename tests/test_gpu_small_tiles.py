@@ -187,3 +187,33 @@ def test_backward_of_a_call_without_tokens(with_perm):
     for t in dw13 + dw2:
         assert not t.any()
     assert torch.isnan(dx_perm.float()).all()
+
+
+def test_small_tiles_leave_the_clock_counters_alone():
+    """The counters have room for a workgroup per compute unit; the small form has more, and counts nothing: neither in the buffer
+    nor behind it."""
+    import paper_2604_23108_amd as M
+    from paper_2604_23108_amd import bench_binding as BB
+    from gpu_harness import DeviceLayer, to_dev
+    w = Workload("small_cycles", T=900, d=512, n_groups=2, experts_per_group=8, d_ff=(512, 1024), k_groups=1, k_experts=2,
+                 seed=48, training=True)
+    inp = generate(w)
+    dl = DeviceLayer(w, inp, backward=True)
+    dl.run()
+    L = dl.layer
+    L.dy_perm.copy_(to_dev(inp.dy, True)[(L.perm // 2).long()])
+    room = BB.cycles_buffer()
+    buf = torch.zeros((64,) + tuple(room.shape), dtype=torch.int64, device="cuda")      # (64 times the room for what came behind it)
+    print("[small tiles] clock counters", flush=True)
+    args = (dl.cfg, dl.x, L.perm, L.offsets, L.w13, L.w2)
+    for launch in (0, 1):
+        o = BB.FfnOptions(cycles=buf[0], cycles_launch=launch, small_tiles=1)
+        BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn, o)
+        BB.mohge_bench_expert_ffn_train(*args, L.y_perm, L.saved, o)
+        BB.mohge_bench_expert_ffn_bwd(*args, L.saved, L.dy_perm, L.dx_perm, L.dw13, L.dw2, L.ws_ffn_bwd, o)
+    torch.cuda.synchronize()
+    assert int(buf.abs().sum()) == 0
+    o = BB.FfnOptions(cycles=buf[0], small_tiles=0)
+    BB.mohge_bench_expert_ffn(*args, L.y_perm, L.ws_ffn, o)
+    torch.cuda.synchronize()
+    assert int(buf[0, 0, :, 4].sum()) > 0 and int(buf[1:].abs().sum()) == 0
