@@ -183,7 +183,8 @@ __device__ __forceinline__ int choose_tile_rows(const TileArgs& a, SchedShared& 
     int best_rows = 256;
     for (int c = 0; c < 3; ++c) {
       const long long tot = sh.wsum[0][c] + sh.wsum[1][c] + sh.wsum[2][c] + sh.wsum[3][c];
-      // a stage of a tile cost about 1850 + 100 * (rows / 64) clocks (see kTileCost), so rounds count more than height
+      // rounds count more than height (the constants are those of the loop before this one; heights chosen by the present
+      // clocks gain nothing, see kTileCost)
       // (fused launch: the down tiles fill the last round of up tiles, so the up tiles are
       // costed by their total work rather than by whole rounds)
       const float units = fused ? (float)tot / (float)((long long)a.ncu * kmax)
@@ -517,14 +518,12 @@ __device__ __forceinline__ void swiglu_bwd8(const uint4 dh, const uint4 pv, cons
   db = make_uint4(ob[0], ob[1], ob[2], ob[3]);
 }
 
-// Short tiles.  A stage of a full tile takes about as long as its operands take to arrive; a tile of
-// fewer rows has less to multiply per stage but waited just as long with two stages of tokens (64 rows 1934 clocks, 256 rows
-// 2174).  Its token parts are short, so the same LDS holds more stages of both operands: four up to 64 rows of a 256-row
-// tile, three up to 128.  Where every expert has a few rows and its weights are the
-// work, d = 4096, 64 experts: 40 tokens 406 -> 373 us, 100 tokens 417 ->
-// 381, 600 tokens 435 -> 401; unchanged where full tiles dominate.  (The backward products, bound by their transposing
-// reads, gain nothing: 0.99 to 1.04 of the time.  Three stages up to 64 rows of a 128-row tile, ten layers, 33 to 400 tokens:
-// 0.94 to 1.065 of the time, slower at d = 2048 with 24 experts and d = 4096 with 8.)
+// Short tiles.  A tile of fewer rows has less to multiply per stage and waits for its weights.  Its token parts are short, so the
+// same LDS holds more stages of both operands: four up to 64 rows of a 256-row tile, three up to 128.  Measured on the loop of
+// 32x32x16 MFMAs before this one, where every expert has a few rows and its weights are the work, d = 4096, 64 experts: 40 tokens
+// 406 -> 373 us, 100 tokens 417 -> 381, 600 tokens 435 -> 401; unchanged where full tiles dominate.  (The backward products, bound by
+// their transposing reads, gained nothing: 0.99 to 1.04 of the time.  Three stages up to 64 rows of a 128-row tile, ten layers, 33 to
+// 400 tokens: 0.94 to 1.065 of the time, slower at d = 2048 with 24 experts and d = 4096 with 8.)
 // Tall tiles of more than 128 rows: two stages of both operands (2 x 24 KB of tokens and 2 x 16 KB of weights).
 template <typename GEO>
 constexpr int short_depth(int mode, int nact) {
@@ -545,10 +544,9 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   constexpr bool TRA = tr_a(MODE), TRB = tr_b(MODE);   // operand read by transposing LDS reads
   constexpr bool WG = MODE == kWgrad;
   constexpr bool DH = MODE == kDgradH;
-  constexpr bool DG = TRB && !WG;
   // Operands as a wave-uniform base and 32-bit offsets per lane (64-bit pointers cost twice the registers): the weights of
   // the token modes, and their tokens where they are neighbouring rows (the up modes gather theirs through perm)
-  constexpr bool OFFA = !WG && !UP, OFFB = !WG;
+  constexpr bool OFFA = !WG && !UP;
   // (a value the compiler cannot trace, here and before the epilogue: what depends on the lane would be computed once before
   // the first tile and kept through every main loop, in registers that those do not have.  Its range is told again: divisions of
   // a number that may be negative are three times as long)
@@ -610,7 +608,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   const uint16_t* src_a[TRA || OFFA ? 1 : A_LOADS];
   uint32_t off_a[OFFA ? A_LOADS : 1];             // (WG: the lane's part, the same for every load; so off_b)
   uint32_t off_b[TRB ? 1 : B_LOADS];
-  const uint16_t* base_b = nullptr;               // OFFB
+  const uint16_t* base_b = nullptr;               // not WG
   // OFFA: first row of wave-wide load j, and from there the lane's row (at most 7 further: offsets stay small)
   auto first_row = [&](int j) { return min((j * NWAVES + w) * RPL, rec.rows - 1); };
   // Operands stored reduction-index major (rows = reduction index, features contiguous): a part
@@ -625,7 +623,7 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
   const int trow0 = TPL * w + lane / TCH;         // row of load 0; load j: + TPL*NWAVES*j
   const int tr_lc = (lane % TCH) ^ (4 * (trow0 & 3)) ^ (2 * ((trow0 >> 3) & 1));
   const uint16_t* zsrc = nullptr;
-  unsigned tr_ldb = 0;                            // row pitch of the B operand in elements
+  unsigned tr_ldb = 0;                            // row pitch of the transposed weights in elements (input gradients)
   if constexpr (TRA) {
     int ma = rec.row_start + tr_lc * 8;
     // feature chunks past the matrix edge: any chunk inside the row (never stored)
@@ -637,7 +635,6 @@ __device__ __forceinline__ void run_tile(const TileArgs& a, const TileRec rec, u
     if constexpr (WG) {
       if (nb > a.Ncols[g] - 8) nb = a.Ncols[g] - 8;
       zsrc = a.zero_row + (lane % TCH) * 8;
-      tr_ldb = a.ldb;
       off_b[0] = ((uint32_t)trow0 * (uint32_t)a.ldb + (uint32_t)nb) * 2u;
     } else if constexpr (DH) {
       if (nb > F - 8) nb = F - 8;                 // W_down[e]: [d, F]
@@ -1389,8 +1386,8 @@ __device__ __forceinline__ int small_row_tiles(int cnt, bool tall) {
 }
 
 // Whether a launch takes them.  A unit runs two workgroups at a time, and a tall tile is about as long as two of the others, so
-// what counts is how both lists fill whole rounds.  Time of the launch tall / plain, 23 layers of d = 1024 to 4096 with 12 to 80
-// experts, 145 to 178 rows each (256 units), by tall tiles:
+// what counts is how both lists fill whole rounds.  Time of the launch tall / plain (on the loop of 32x32x16 MFMAs before this one),
+// 23 layers of d = 1024 to 4096 with 12 to 80 experts, 145 to 178 rows each (256 units), by tall tiles:
 //   up: up to 512 0.73 to 1.03, mean 0.88 (saving the pre-activations 0.81 to 1.06, 0.94); 513 to 800 0.90 to 1.17, mean 1.06 (1.00
 //     to 1.27, 1.13): they begin a third tile per unit; from 832 on 0.88 to 1.09, mean 0.96 (0.97 to 1.06, 1.01), with a fifth of the
 //     experts past 192 rows 1.02 (call 145 -> 148 us)
@@ -1611,19 +1608,21 @@ static hipError_t launch_small(long long grid, hipStream_t s, const Args&... arg
 // Which geometry a bf16 call past decode size takes.  Small tiles fill the chip, need no schedule launch and overlap one
 // workgroup's ends with the other's stages; big ones move half the operand bytes per FLOP.  The measure is the work
 // per compute unit in stages of a big tile, both projections, for evenly spread rows.  Time small / big over 17 layer
-// shapes (d = 768 to 8192, 8 to 128 experts, 4 to 1024 rows per expert), even and skewed routing:
+// shapes (d = 768 to 8192, 8 to 128 experts, 4 to 1024 rows per expert), even and skewed routing, on the present loop:
 //   one row tile per expert in either form (up to 112 rows; at 128 half of the experts need two small ones), weights to
-//     move and little else:      forward up to 180 stages 0.50 to 1.01, mean 0.75, above 0.86 to 1.07, mean 1.00;
-//     backward up to 130 stages 0.41 to 1.08, mean 0.77, above 0.81 to 1.15, mean 1.00
-//   more rows, up to 80 stages:  forward 0.44 to 1.14, mean 0.77, backward 0.40 to 1.09, mean 0.78
-//              above:            forward 0.79 to 1.29, mean 1.07, backward 0.81 to 1.23, mean 1.08
-//     but above 48 where several big row tiles are nine tenths full (d = 2048, 24 experts x 500 rows: 188 -> 205 us)
-// The mean cost of a wrong choice is 0.9 % forward, 1.3 % backward (the largest, 1.14, where 576 up tiles start a second
-// round on 512 slots: d = 4096, 24 experts x 144 rows).  From 1.7 big up tiles per compute unit on the big form has no
-// idle units to lose to (d = 1024, 32 experts, 768 rows: 122 -> 127 us); that limit alone, whatever the length
-// of the reduction, cost 1.7 and 2.2 %, up to 1.29.  Forward, where the big row tiles are not nearly full, it lies at 2.0: 26 layers
-// and token counts with 1.69 to 1.76 tiles per unit 0.58 to 0.99, mean 0.87 (rows spread evenly 0.70 to 1.03, 0.92), 13 with 1.83 to
-// 2.0, d = 768 to 1856, 137 to 1375 rows, 0.77 to 1.05, mean 0.91 (0.75 to 1.07, 0.93).
+//     move and little else:      forward up to 180 stages 0.46 to 1.03, mean 0.76, above 1.06 to 1.13, mean 1.10;
+//     backward up to 130 stages 0.40 to 1.10, mean 0.73, above 1.00 to 1.15, mean 1.08
+//   more rows, up to 80 stages:  forward 0.46 to 1.21, mean 0.81, backward 0.41 to 1.19, mean 0.82
+//              above:            forward 0.81 to 1.37, mean 1.11, backward 0.82 to 1.28, mean 1.13
+//     but above 48 where several big row tiles are nine tenths full (d = 2048, 24 experts x 500 rows, on the loop before this one:
+//     188 -> 205 us)
+// The mean cost of a wrong choice is 0.8 % forward, 0.7 % backward (the largest 1.40 and 1.34: d = 2048, 8 experts x 500 rows, 1.5 big
+// up tiles per unit, where full row tiles take the big form).  From 1.7 big up tiles per compute unit on the big form has no
+// idle units to lose to; forward, where the big row tiles are not nearly full, from 2.0.  These two limits and the exception for full
+// row tiles were drawn on the loop before this one: d = 1024, 32 experts, 768 rows 122 -> 127 us; that limit alone, whatever the length
+// of the reduction, cost 1.7 and 2.2 %, up to 1.29; forward 26 layers and token counts with 1.69 to 1.76 tiles per unit 0.58 to 0.99,
+// mean 0.87 (rows spread evenly 0.70 to 1.03, 0.92), 13 with 1.83 to 2.0, d = 768 to 1856, 137 to 1375 rows, 0.77 to 1.05, mean 0.91
+// (0.75 to 1.07, 0.93).
 bool use_small_tiles(const LayerDesc& L, const FfnOptions& o, bool backward) {
   if (o.small >= 0) return o.small != 0;
   const long long rows = L.P > L.Ne ? L.P / L.Ne : 1;     // per expert if they were spread evenly
