@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d,F", [((1 << 24) + (1 << 20), 128), (256, (1 << 23) + (1 << 19))], ids=["first", "second"])
 def test_ffn_rows_of_a_tile_span_more_than_4_gib(d, F):
-    """One expert, weights that are zero but for 96 reduction indices spread over the rows."""
+    """One expert, weights that are zero but for 96 reduction indices spread over the rows; by itself, and captured and replayed."""
     import paper_2604_23108_amd as M
     T, K = 200, max(d, F)
     if torch.cuda.mem_get_info()[0] < 8 * (T + 3 * min(d, F)) * K:
@@ -30,7 +30,18 @@ def test_ffn_rows_of_a_tile_span_more_than_4_gib(d, F):
     ws = torch.empty(M.mohge_workspace_size(cfg, M.CALL_EXPERT_FFN), dtype=torch.uint8, device="cuda")
     print(f"[long rows] d={d} F={F}", flush=True)
     M.mohge_expert_ffn(cfg, x, None, offsets, [w13], [w2], y, ws)
-    torch.cuda.synchronize()
+    assert M.mohge_fused_status(cfg, M.CALL_EXPERT_FFN, ws) == 0
+    bits = y.clone()
+    y.fill_(float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        M.mohge_expert_ffn(cfg, x, None, offsets, [w13], [w2], y, ws)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), bits.view(torch.int16))
+    del graph, bits
     if d == K:
         a, b = (x[:, idx].float() @ w13[0][:, idx].float().T.contiguous()).split(F, dim=1)
         cols = idx
